@@ -851,23 +851,19 @@ __global__ __launch_bounds__(kFusedThreads) void bwd_fused_kernel(BwdFastArgs A)
     }
 }
 
-// out[q] = sum over slices of partial[s][q] (+ the upper-half share of the last layer where a slice has
-// one), in double, slice order; skipped for flagged plans
+// out[q] = sum over slices of partial[s][q] (+ the upper-half share of the last layer where a slice has one), in
+// double, in a fixed order; skipped for flagged plans.  n_angles and last_layer_at are multiples of kReduceAngles.
 template <typename Out>
-__global__ void bwd_reduce_kernel(const float *__restrict__ partial, Out *__restrict__ out, size_t n_angles,
-                                  size_t slice_floats, size_t last_layer_at, int n_parts, PlanRef plan)
+__global__ __launch_bounds__(kReduceThreads) void bwd_reduce_kernel(const float *__restrict__ partial, Out *__restrict__ out,
+                                                                    size_t n_angles, size_t slice_floats, size_t last_layer_at,
+                                                                    int n_parts, PlanRef plan)
 {
+    __shared__ double lds[kReduceThreads * 4];
     if (!plan_fast_both(plan)) return;
-    const size_t q = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (q >= n_angles) return;
-    const size_t extra = slice_floats - n_angles;  // 0, or the number of angles of the last layer
-    double acc = 0.0;
-    for (int w = 0; w < n_parts; ++w) {
-        const float *s = partial + (size_t)w * slice_floats;
-        acc += (double)s[q];
-        if (extra && q >= last_layer_at) acc += (double)s[q + extra];
-    }
-    out[q] = (Out)acc;
+    const size_t first = (size_t)blockIdx.x * kReduceAngles;
+    const size_t extra = first >= last_layer_at ? slice_floats - n_angles : 0;  // 0, or the number of angles of the last layer
+    const double t = sum_slices(partial, first, slice_floats, extra, n_parts, lds);
+    if (threadIdx.x < kReduceAngles) out[first + threadIdx.x] = (Out)t;
 }
 
 // n < 4096: the sums of a 4096-point block hold, per layer, the block's rows side by side, each with its `heads`
@@ -968,14 +964,14 @@ static hipError_t launch_bwd_fast_t(BwdFastArgs A, const Shape &s, float *dtheta
     }
     if (kVirt) {
         const size_t sums = (size_t)s.k * (G::n / 2);  // the layers the transform has
-        hipLaunchKernelGGL(bwd_reduce_kernel<double>, dim3((unsigned)((sums + 255) / 256)), dim3(256), 0, stream,
+        hipLaunchKernelGGL(bwd_reduce_kernel<double>, dim3((unsigned)(sums / kReduceAngles)), dim3(kReduceThreads), 0, stream,
                            (const float *)ws, fold, sums, (size_t)A.slice_floats, sums, slices, A.plan);
         const unsigned angles = (unsigned)(s.heads * s.k * (s.n / 2));
         hipLaunchKernelGGL(bwd_fold_kernel, dim3((angles + 255) / 256), dim3(256), 0, stream, (const double *)fold, dtheta, s.k,
                            s.heads, A.plan);
     } else {
         const size_t angles = (size_t)s.k * (s.n / 2);
-        hipLaunchKernelGGL(bwd_reduce_kernel<float>, dim3((unsigned)((angles + 255) / 256)), dim3(256), 0, stream,
+        hipLaunchKernelGGL(bwd_reduce_kernel<float>, dim3((unsigned)(angles / kReduceAngles)), dim3(kReduceThreads), 0, stream,
                            (const float *)ws, dtheta, angles, (size_t)A.slice_floats, (size_t)(s.k - 1) * (s.n / 2), slices,
                            A.plan);
     }
