@@ -101,7 +101,6 @@ struct BwdFastArgs {
     void *dx;
     float *partial;  // [slices][slice_floats]
     const float *fg_inv, *fd_inv, *fw_inv;  // plan tables of the transposed cascade
-    const int *bad_fwd, *bad_inv;
     PlanRef plan;
     int64_t row0, rows;  // this chunk: rows [row0, row0 + rows) of the batch
     int64_t ld_in, ld_out;
@@ -115,12 +114,6 @@ struct BwdFastArgs {
     int n, n_log, row_log, heads;
     int64_t sub_ld_in, sub_ld_out, total_rows;
 };
-
-// true: this kernel must not run (tables flagged unusable, or not a plan of this shape at all)
-__device__ __forceinline__ bool plan_is_bad(const BwdFastArgs &A)
-{
-    return !plan_matches(A.plan) || (*A.bad_fwd | *A.bad_inv) != 0;
-}
 
 constexpr int K = 12;  // layers inside one 4096-point block
 using G = Geo<K>;
@@ -507,7 +500,7 @@ template <typename T, bool kDx, bool kHalf, bool kVirt>
 __global__ __launch_bounds__(kFusedThreads) void bwd_fused_kernel(BwdFastArgs A)
 {
     extern __shared__ float lds[];
-    if (plan_is_bad(A)) return;
+    if (!plan_fast_both(A.plan)) return;
     using L = FusedLds<T, kHalf>;
     const Part<kHalf, kVirt> pt(A);
     const int ts = pt.ts;
@@ -998,8 +991,6 @@ hipError_t launch_bwd_fast(const void *x, const void *dy, const PlanView &pv, vo
     A.fg_inv = pv.fg_inv;
     A.fd_inv = pv.fd_inv;
     A.fw_inv = pv.fw_inv;
-    A.bad_fwd = &pv.hdr->fast_bad_fwd;
-    A.bad_inv = &pv.hdr->fast_bad_inv;
     A.plan = pv.ref;
     A.n = s.n;
     A.n_log = s.k;

@@ -28,7 +28,6 @@ struct SmallBwdArgs {
     void *dx;
     float *partial;  // [slots][n_angles]
     const float *fg_fwd, *fd_fwd, *fg_inv, *fd_inv, *fw_inv;
-    const int *bad_fwd, *bad_inv;
     PlanRef plan;
     int64_t rows, ld_in, ld_out;
     int heads, width;    // width = heads * n
@@ -44,7 +43,7 @@ template <typename T, int K, bool kDx>
 __global__ __launch_bounds__(kSbThreads) void small_bwd_kernel(SmallBwdArgs A)
 {
     constexpr int n = 1 << K;
-    if (!plan_matches(A.plan) || (*A.bad_fwd | *A.bad_inv) != 0) return;
+    if (!plan_fast_both(A.plan)) return;
     const int tid = threadIdx.x;
     const int chunk = (tid & ~15) | lane_chunk(tid & 15);  // chunk of 8 elements inside the workgroup's span
     const int e0 = chunk * 8;
@@ -257,8 +256,6 @@ hipError_t launch_small_bwd(const void *x, const void *dy, const PlanView &pv, v
     A.fg_inv = pv.fg_inv;
     A.fd_inv = pv.fd_inv;
     A.fw_inv = pv.fw_inv;
-    A.bad_fwd = &pv.hdr->fast_bad_fwd;
-    A.bad_inv = &pv.hdr->fast_bad_inv;
     A.plan = pv.ref;
     A.rows = s.rows;
     A.ld_in = s.ld_x;

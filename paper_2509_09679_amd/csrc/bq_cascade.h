@@ -103,6 +103,13 @@ __device__ __forceinline__ void reg_layer_first(float (&u)[8], const float (&c)[
     }
 }
 
+// 8 consecutive entries of a plan table (p: 32-byte aligned) in two 16-byte loads
+__device__ __forceinline__ void load_coef8(const float *p, float (&c)[8])
+{
+    const float4 a = *(const float4 *)p, b = *((const float4 *)p + 1);
+    c[0] = a.x; c[1] = a.y; c[2] = a.z; c[3] = a.w; c[4] = b.x; c[5] = b.y; c[6] = b.z; c[7] = b.w;
+}
+
 // ---- row I/O: 8 consecutive elements per thread ------------------------------------------------
 struct Raw8 {
     uint4 lo, hi;  // f16/bf16 use lo only

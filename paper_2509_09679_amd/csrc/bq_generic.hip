@@ -266,7 +266,8 @@ template <typename T>
 __global__ __launch_bounds__(kGenThreads) void generic_bwd_kernel(BwdArgs A)
 {
     extern __shared__ float lds[];
-    if (!plan_matches(A.plan) || (A.only_if_bad && plan_fast_both(A.plan))) return;
+    const PlanHead ph = plan_head(A.plan);
+    if (!ph.matches || (A.only_if_bad && (ph.bad_fwd | ph.bad_inv) == 0)) return;
     const int n = A.n, k = A.k, heads = A.heads, U = A.rows_per_tile;
     float *xb = lds;
     float *gb = lds + (size_t)U * n;
@@ -340,7 +341,8 @@ __global__ __launch_bounds__(kGenThreads) void generic_bwd_kernel(BwdArgs A)
 __global__ void reduce_partials_kernel(const float *__restrict__ partial, float *__restrict__ dtheta,
                                        size_t n_angles, int n_parts, PlanRef plan, int only_if_bad)
 {
-    if (!plan_matches(plan) || (only_if_bad && plan_fast_both(plan))) return;
+    const PlanHead ph = plan_head(plan);
+    if (!ph.matches || (only_if_bad && (ph.bad_fwd | ph.bad_inv) == 0)) return;
     size_t q = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (q >= n_angles) return;
     double acc = 0.0;

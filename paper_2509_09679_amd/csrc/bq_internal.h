@@ -86,15 +86,33 @@ struct PlanRef {
     int32_t n, heads;
 };
 
-__device__ __forceinline__ bool plan_matches(const PlanRef &p)
+struct PlanHead {
+    bool matches;           // the buffer is a plan of this shape
+    int bad_fwd, bad_inv;   // its scale-deferred tables (forward, transposed) are unusable
+};
+
+// The header in one 32-byte scalar load.  Field by field, with a branch after each, it was a chain of four dependent
+// round trips to the L2 at the front of every kernel.
+__device__ __forceinline__ PlanHead plan_head(const PlanRef &p)
 {
-    return p.hdr->magic == kPlanMagic && p.hdr->n == p.n && p.hdr->heads == p.heads;
+    typedef uint32_t u32x8 __attribute__((ext_vector_type(8)));
+    static_assert(offsetof(PlanHeader, n) == 4 && offsetof(PlanHeader, heads) == 8 && offsetof(PlanHeader, fast_bad_fwd) == 16 &&
+                  offsetof(PlanHeader, fast_bad_inv) == 20, "header words 0, 1, 2, 4, 5");
+    const u32x8 h = *(const u32x8 *)p.hdr;
+    PlanHead r;
+    r.matches = ((h[0] ^ kPlanMagic) | (h[1] ^ (uint32_t)p.n) | (h[2] ^ (uint32_t)p.heads)) == 0;
+    r.bad_fwd = (int)h[4];
+    r.bad_inv = (int)h[5];
+    return r;
 }
+
+__device__ __forceinline__ bool plan_matches(const PlanRef &p) { return plan_head(p).matches; }
 
 // the plan is of this shape and both of its scale-deferred table sets (forward, transposed) are usable
 __device__ __forceinline__ bool plan_fast_both(const PlanRef &p)
 {
-    return plan_matches(p) && (p.hdr->fast_bad_fwd | p.hdr->fast_bad_inv) == 0;
+    const PlanHead h = plan_head(p);
+    return h.matches && (h.bad_fwd | h.bad_inv) == 0;
 }
 
 struct PlanView {  // device pointers into a plan

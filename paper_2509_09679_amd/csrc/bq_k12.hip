@@ -37,6 +37,14 @@ bool hadamard_supported(const void *in, const void *out, const Shape &s)
     return true;
 }
 
+// per_head workgroups take the rows of every head in turn; returns the grid
+static unsigned split_rows(K12Args &A, int64_t per_head)
+{
+    A.rows_each = (int)(A.rows / per_head);
+    A.rows_extra = (int)(A.rows % per_head);
+    return (unsigned)(per_head * A.heads);
+}
+
 hipError_t launch_hadamard(const void *in, void *out, const Shape &s, hipStream_t stream)
 {
     K12Args A{};
@@ -53,7 +61,7 @@ hipError_t launch_hadamard(const void *in, void *out, const Shape &s, hipStream_
     const bool wide = s.n > kN;
     int64_t per_head = 256 / A.heads > 0 ? 256 / A.heads : 1;  // as for the forward transform: one workgroup per compute unit
     if (per_head > A.rows) per_head = A.rows;
-    const unsigned grid = (unsigned)(per_head * A.heads);
+    const unsigned grid = split_rows(A, per_head);
     if (wide) return launch_k13_dtype(kHadamard, A, 4, grid, s.dtype, stream);
     return launch_k12_dtype<false, false>(kHadamard, A, 4, grid, s.dtype, stream);
 }
@@ -73,7 +81,6 @@ hipError_t launch_k12(Mode mode, const void *in, void *out, const PlanView &pv, 
     A.fg = mode == kInv ? pv.fg_inv : pv.fg_fwd;
     A.fd = mode == kInv ? pv.fd_inv : pv.fd_fwd;
     A.cs = pv.cs;
-    A.fast_bad = mode == kInv ? &pv.hdr->fast_bad_inv : &pv.hdr->fast_bad_fwd;
     A.plan = pv.ref;
     const bool virt = s.n < kN, wide = s.n > kN;
     const int block_rows = k12_block_rows(s);  // rows of the caller per kernel row
@@ -106,7 +113,7 @@ hipError_t launch_k12(Mode mode, const void *in, void *out, const PlanView &pv, 
     // 0.79 ms for 2^30 16-bit elements at every n from 256 to 4096, float32 rows 0.793 -> 0.776 ms, small
     // batches too).  The three-phase inverse was not on 16-bit rows (0.88 against 0.855 ms), which now take the two-phase
     // kernel; on float32 rows, which it still serves, it is.
-    // n = 8192: one workgroup of 1024 threads per compute unit at a time.
+    // n = 8192: one workgroup (512 threads of up to 256 registers) per compute unit at a time.
     // The two-phase inverse of 16-bit rows (bq_k12_inv.h) also runs best with one workgroup per compute unit (256: 0.78 ms,
     // 512: 0.86, 768: 0.85, 1024: 0.99, 1280: 0.85, 2048: 0.95 ms for 2^30 fp16 elements).
     const bool inv_ring = mode == kInv && !wide && s.dtype != BQ_F32;
@@ -114,7 +121,7 @@ hipError_t launch_k12(Mode mode, const void *in, void *out, const PlanView &pv, 
     const int target = (mode == kFwdQuant || mode == kFwdFake) && !wide ? 1280 : 256;
     int64_t per_head = target / A.heads > 0 ? target / A.heads : 1;
     if (per_head > A.rows) per_head = A.rows;
-    unsigned grid = (unsigned)(per_head * A.heads);
+    const unsigned grid = split_rows(A, per_head);
     if ((mode == kFwdQuant || mode == kFwdFake) && q->group > 128)
         return launch_k12_big_dtype(mode, A, bits, grid, s.dtype, virt, wide, stream);
     if (wide) return launch_k13_dtype(mode, A, bits, grid, s.dtype, stream);

@@ -79,59 +79,56 @@ __global__ __launch_bounds__(kThreads, 4) void k12_inv_ring_kernel(K12Args A)
     const int head = blockIdx.x % A.heads;
     const int64_t row_first = blockIdx.x / A.heads;
     const int64_t row_step = gridDim.x / A.heads;
+    const int n_my = A.rows_each + ((int)row_first < A.rows_extra ? 1 : 0);  // rows of this workgroup
     const int tn = kVirt ? A.n : kN;
     const int nk = kVirt ? A.n_log : kK;
     const int tmask = tn - 1;
     const T *in = (const T *)A.in;
-    if (row_first >= A.rows) return;
-    if (!plan_matches(A.plan)) return;
+    if (n_my == 0) return;
+    const PlanHead ph = plan_head(A.plan);
+    if (!ph.matches) return;
+
+    if (ph.bad_inv != 0) {  // rare: plain rotations through LDS
+        const float2 *cs = A.cs + (kVirt ? 0 : (size_t)head * kK * (kN / 2));
+        const uint32_t off_n = elem_off<kVirt, false>(A, head, idx_n, A.sub_ld_in);
+        for (int64_t row = row_first; row < A.rows; row += row_step) {
+            float u[1][8];
+            unpack8(load8(in + row * A.ld_in + off_n), u[0], (const T *)nullptr);
+            slow_cascade<true, 1>(u, bufs, cs, idx_n, nk, kVirt ? (1 << A.row_log) - 1 : 0, kVirt ? head * kN : 0);
+            finish_row<T, kInv, 4, 0, 0, true, false, kVirt, 1, false>(A, u, row, head, chunk, bins, wg_bins, wg_max);
+        }
+        return;
+    }
 
     // coefficients: cn[j][r] for layer j+1 (layout N), cp[j][r'] for layer 8+j (layout P), d[r] (layout N)
     const int idx_p = base_p(wave, lane);
+    const int an = lds_addr(idx_n);
+    const int ap = lds_addr(idx_p);
     float cn[7][8], cp[5][8], d[8];
     {
-        const float *fg = A.fg + (kVirt ? 0 : (size_t)head * kK * kN);
-        const float *fg_n = fg + (kVirt ? (size_t)virt_head(A, head, idx_n) * nk * tn : 0);
+        const size_t th = kVirt ? (size_t)virt_head(A, head, idx_n) : (size_t)head;
+        const float *fg = A.fg + th * nk * tn + (idx_n & tmask);
+        float st[5][8];
 #pragma unroll
-        for (int j = 0; j < 7; ++j)
+        for (int j = 0; j < 5; ++j) {  // layers above log2 n do not exist: weight zero leaves the element as it is
 #pragma unroll
-            for (int r = 0; r < 8; ++r) cn[j][r] = fg_n[j * tn + (idx_n & tmask) + r];
+            for (int r = 0; r < 8; ++r) st[j][r] = 0.0f;
+            if (!kVirt || 8 + j <= nk) load_coef8(fg + (size_t)(7 + j) * tn, st[j]);
+        }
 #pragma unroll
-        for (int j = 0; j < 5; ++j)
-#pragma unroll
-            for (int r = 0; r < 8; ++r) {  // layers above log2 n do not exist: weight zero leaves the element as it is
-                const int e = idx_p + p_reg_idx(r);
-                const float *fg_p = fg + (kVirt ? (size_t)virt_head(A, head, e) * nk * tn : 0);
-                cp[j][r] = (!kVirt || 8 + j <= nk) ? fg_p[(7 + j) * tn + (e & tmask)] : 0.0f;
-            }
-        const float *fd = A.fd + (kVirt ? (size_t)virt_head(A, head, idx_n) * tn : (size_t)head * kN);
-#pragma unroll
-        for (int r = 0; r < 8; ++r) d[r] = fd[(idx_n & tmask) + r];
+        for (int j = 0; j < 7; ++j) load_coef8(fg + (size_t)j * tn, cn[j]);
+        load_coef8(A.fd + th * tn + (idx_n & tmask), d);
+        to_layout_p(bufs, bufs + kLdsRow, an, ap, st[0], st[1], cp[0], cp[1]);
+        to_layout_p(bufs, bufs + kLdsRow, an, ap, st[2], st[3], cp[2], cp[3]);
+        to_layout_p(bufs, an, ap, st[4], cp[4]);
         // the empty statements consume the loaded values: their waits then sit here and not inside the row loop
 #pragma unroll
         for (int r = 0; r < 8; ++r) {
 #pragma unroll
             for (int j = 0; j < 7; ++j) asm volatile("" ::"v"(cn[j][r]));
-#pragma unroll
-            for (int j = 0; j < 5; ++j) asm volatile("" ::"v"(cp[j][r]));
             asm volatile("" ::"v"(d[r]));
         }
     }
-    if (*A.fast_bad != 0) {  // rare: plain rotations through LDS
-        const float2 *cs = A.cs + (kVirt ? 0 : (size_t)head * kK * (kN / 2));
-        const uint32_t off_n = elem_off<kVirt, false>(A, head, idx_n, A.sub_ld_in);
-        for (int64_t row = row_first; row < A.rows; row += row_step) {
-            float u[8];
-            unpack8(load8(in + row * A.ld_in + off_n), u, (const T *)nullptr);
-            slow_cascade<true, false>(u, bufs, cs, idx_n, nk, kVirt ? (1 << A.row_log) - 1 : 0, kVirt ? head * kN : 0);
-            finish_row<T, kInv, 4, 0, 0, true, false, kVirt, false, false>(A, u, row, head, chunk, bins, wg_bins, wg_max);
-        }
-        return;
-    }
-
-    const int an = lds_addr(idx_n);
-    const int ap = lds_addr(idx_p);
-    const int n_my = (int)((A.rows - row_first + row_step - 1) / row_step);
 
     // ---- input ring ----------------------------------------------------------------------------------------
     const uint32_t ring0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)inv_lds;
@@ -161,7 +158,8 @@ __global__ __launch_bounds__(kThreads, 4) void k12_inv_ring_kernel(K12Args A)
         constexpr int sb = decltype(SB)::value, bb = decltype(BB)::value;  // ring slot and row buffer of row it
         ring_load(it + 3, (sb + 3) & 3);  // the slot of row it - 1, which every wave has finished reading
         if (it >= 1) {  // C(it - 1)
-            float u[8];
+            float y[1][8];
+            float(&u)[8] = y[0];
             lds_read_n(bufs + (bb ^ 1) * kLdsRow, an, u);
             dpp_layer_xor8(u, cn[6]);
             dpp_layer_xor7(u, cn[5]);
@@ -172,7 +170,7 @@ __global__ __launch_bounds__(kThreads, 4) void k12_inv_ring_kernel(K12Args A)
             reg_layer<0>(u, cn[0]);
 #pragma unroll
             for (int r = 0; r < 8; ++r) u[r] *= d[r];
-            finish_row<T, kInv, 4, 0, 0, true, false, kVirt, false, false, kNt>(A, u, row_first + (it - 1) * row_step, head, chunk,
+            finish_row<T, kInv, 4, 0, 0, true, false, kVirt, 1, false, kNt>(A, y, row_first + (it - 1) * row_step, head, chunk,
                                                                               bins, wg_bins, wg_max);
         }
         if (it < n_my) {  // B(it)

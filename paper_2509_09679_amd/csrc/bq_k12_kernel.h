@@ -30,11 +30,14 @@
 // bits move the address by 2, 4, 8 and 16 words modulo 32, so the 16 lanes hit 16 different bank
 // pairs (the padding terms supply what the plain index lacks).
 //
-// n = 8192 (kWide): layers 1..12 act inside each half of a row and only layer 13 couples element e with
-// e + 4096.  A workgroup of 1024 threads runs the scheme above on both halves side by side (threads 0..511
-// on the lower half, 512..1023 on the upper, each with its own row buffers, one barrier for all) and adds
-// layer 13 where both halves are in LDS anyway: forward in phase C (a thread reads its own 8 elements and
-// the 8 elements of the other half at the same position), inverse at the start of phase B.
+// n = 8192 (kWide): layers 1..12 act inside each half of a row and only layer 13 couples element e with e + 4096.  A
+// thread holds the same 8 positions of both halves (16 elements, up to 256 registers, one workgroup of 512 threads per
+// compute unit) and runs the scheme above on both, each half in row buffers of its own; layer 13 pairs registers, forward in
+// phase C (layout N), inverse at the start of phase B (layout P).  One workgroup of 1024 threads with a half each, which
+// this replaces, had 128 registers for the same 120 values per thread: 4 to 20 of them were reloaded from scratch memory in
+// every row (each reload waiting for everything in flight), layer 13 went through LDS and cost a second barrier.  32768 rows:
+// bf16 forward 209 -> 198 us, inverse 259 -> 218, INT4 271 -> 219, fake-quantised INT4 with counts 617 -> 385; float32 forward
+// 396 -> 381, inverse 400 -> 382, INT2 276 -> 238.
 //
 // If the plan flags the scale-deferred tables as unusable (a cosine too close to zero), the cascade
 // of a row runs through LDS with plain (cos, sin) rotations instead; everything else is unchanged.
@@ -48,11 +51,14 @@ namespace bq {
 
 constexpr int kN = 4096, kK = 12, kThreads = 512;
 constexpr int kLdsRow = 4368;  // floats: 4095 + 2*127 + 2*7 + 1, rounded up to a multiple of 4
-// per half of a row: the input ring (16-bit rows: 3 slots of 8 KB; 32-bit rows: 2 slots of 16 KB) and behind
-// it three row buffers (the variants that use two of them fit the same allocation)
-constexpr int kFrontFloats = 3 * kN * 2 / 4;  // 6144 floats = 24 KB in front of the row buffers
-constexpr size_t kLdsBytes = (kFrontFloats + 3 * kLdsRow) * sizeof(float);
-static_assert((2 * kN + 2 * kLdsRow) * sizeof(float) <= kLdsBytes, "32-bit rows: two slots and two buffers must fit");
+// Dynamic LDS of a workgroup, n <= 4096: the input ring (three slots of 8 KB or, two-buffer variants, two slots of a row) and
+// behind it as many row buffers; the two-buffer variants keep per-thread constants in the rest ("parked": float4 q of
+// thread t at park[512 q + t]).  Two workgroups fit on a compute unit.  The kernel asserts that its variant fits.
+constexpr size_t kParkQuadBytes = 16 * kThreads;
+constexpr size_t kLdsBytes = (3 * kN * 2 / 4 + 3 * kLdsRow) * sizeof(float);
+// n = 8192: one workgroup; largest with 32-bit rows, two slots and two buffers per half and three quads
+constexpr size_t kLdsBytesWide = 2 * (2 * kN + 2 * kLdsRow) * sizeof(float) + 3 * kParkQuadBytes;
+static_assert(kLdsBytes + 512 <= 80 * 1024 && kLdsBytesWide + 512 <= 160 * 1024, "LDS of a compute unit");
 
 struct K12Args {
     const void *in;
@@ -60,10 +66,12 @@ struct K12Args {
     const float *fg;   // [heads][k][n] coefficients of the direction
     const float *fd;   // [heads][n] output scales
     const float2 *cs;  // [heads][k][n/2]
-    const int *fast_bad;
     PlanRef plan;  // not read by the fixed transform (its coefficients come from the element index)
     int64_t rows, ld_in, ld_out;
     int heads;
+    // The workgroups of a head take its rows in turn: row_step of them, each rows / row_step rows (< 2^31), the first
+    // rows % row_step one more.  Divided on the host: a 64-bit division takes the kernel a hundred instructions.
+    int row_step, rows_each, rows_extra;
     // quantiser
     uint8_t *codes;
     void *scales;
@@ -135,39 +143,63 @@ __device__ __forceinline__ void lds_read_p(const float *buf, int ap, float (&u)[
     }
 }
 
-// Layer 13 of an 8192-point transform: u[r] += c[r] * (the other half's element at the same position), read
-// from the other half's row buffer.
-template <bool kLayoutP>
-__device__ __forceinline__ void cross_layer(const float *other, int addr, const float (&c)[8], float (&u)[8])
+// Two rows of a plan table in layout P.  They are read from memory in natural order (s0, s1: the thread's 8 consecutive
+// entries, its own place in layout N) and transposed through two row buffers in LDS.  Read straight from memory in layout P,
+// neighbouring lanes are 512 bytes apart and every lane becomes an access of its own: the 20 eight-byte loads of the five
+// rows took 13 000 cycles per workgroup, two thirds of a call with few rows and 5.5 us for every further workgroup of a
+// compute unit; this way all tables of a workgroup are there after 4 000.  Every thread of the workgroup must call it.
+__device__ __forceinline__ void to_layout_p(float *b0, float *b1, int an, int ap, const float (&s0)[8], const float (&s1)[8],
+                                            float (&c0)[8], float (&c1)[8])
+{
+    lds_write_n(b0, an, s0);
+    lds_write_n(b1, an, s1);
+    __syncthreads();
+    lds_read_p(b0, ap, c0);
+    lds_read_p(b1, ap, c1);
+    __syncthreads();
+}
+__device__ __forceinline__ void to_layout_p(float *b0, int an, int ap, const float (&s0)[8], float (&c0)[8])
+{
+    lds_write_n(b0, an, s0);
+    __syncthreads();
+    lds_read_p(b0, ap, c0);
+    __syncthreads();
+}
+
+// Layer 13 of an 8192-point transform on the two halves of a thread's elements.  kFirst: it opens the cascade, every scale
+// is still 1 and the lower element's coefficient is minus the upper one's.
+template <bool kFirst>
+__device__ __forceinline__ void half_layer(float (&u)[2][8], const float (&lo)[8], const float (&up)[8])
 {
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const int a = kLayoutP ? addr + (j & 1) * kPStepR1 + (j >> 1) * kPStepR2 : addr + 2 * j;
-        const float2 v = *(const float2 *)&other[a];
-        u[2 * j] = __builtin_fmaf(c[2 * j], v.x, u[2 * j]);
-        u[2 * j + 1] = __builtin_fmaf(c[2 * j + 1], v.y, u[2 * j + 1]);
+    for (int r = 0; r < 8; ++r) {
+        const float ua = u[0][r], ub = u[1][r];
+        u[0][r] = __builtin_fmaf(kFirst ? -up[r] : lo[r], ub, ua);
+        u[1][r] = __builtin_fmaf(up[r], ua, ub);
     }
 }
 
 // slow cascade through LDS with (cos, sin); in: u[] in layout N, out: y[] in layout N (true values)
 // n_log < 12: the block holds 4096 >> n_log independent transforms of 2^n_log points (same angles).
-// kWide: 1024 threads on one 8192-point transform (idx_n counts inside the whole row).
+// kHalves = 2: one 8192-point transform, u[h] the thread's elements of half h.
 // row_mask, head0: several transforms with their own angles side by side in the block (see K12Args): element a
 // belongs to transform (head0 + (a & row_mask)) >> n_log.
-template <bool kInverse, bool kWide = false>
-__device__ __forceinline__ void slow_cascade(float (&u)[8], float *buf, const float2 *__restrict__ cs, int idx_n,
-                                             int n_log = kWide ? kK + 1 : kK, int row_mask = 0, int head0 = 0)
+template <bool kInverse, int kHalves>
+__device__ __forceinline__ void slow_cascade(float (&u)[kHalves][8], float *buf, const float2 *__restrict__ cs, int idx_n,
+                                             int n_log, int row_mask = 0, int head0 = 0)
 {
-    constexpr int kPoints = kWide ? 2 * kN : kN, kWorkers = kWide ? 2 * kThreads : kThreads;
+    constexpr int kPoints = kHalves * kN;
     __syncthreads();
 #pragma unroll
-    for (int r = 0; r < 8; ++r) buf[idx_n + r] = u[r];
+    for (int h = 0; h < kHalves; ++h)
+#pragma unroll
+        for (int r = 0; r < 8; ++r) buf[h * kN + idx_n + r] = u[h][r];
     __syncthreads();
     const int half_n = 1 << (n_log - 1);
     for (int step = 0; step < n_log; ++step) {
         const int i = kInverse ? (n_log - step) : (step + 1);
         const int h = 1 << (i - 1);
-        for (int p = threadIdx.x; p < kPoints / 2; p += kWorkers) {
+        for (int p = threadIdx.x; p < kPoints / 2; p += kThreads) {
             const int a = ((p >> (i - 1)) << i) | (p & (h - 1));
             const int hd = (head0 + (a & row_mask)) >> n_log;
             const float2 w = cs[((size_t)hd * n_log + (i - 1)) * half_n + (p & (half_n - 1))];
@@ -183,7 +215,9 @@ __device__ __forceinline__ void slow_cascade(float (&u)[8], float *buf, const fl
         __syncthreads();
     }
 #pragma unroll
-    for (int r = 0; r < 8; ++r) u[r] = buf[idx_n + r];
+    for (int h = 0; h < kHalves; ++h)
+#pragma unroll
+        for (int r = 0; r < 8; ++r) u[h][r] = buf[h * kN + idx_n + r];
     __syncthreads();
 }
 
@@ -191,20 +225,29 @@ __device__ __forceinline__ void slow_cascade(float (&u)[8], float *buf, const fl
 // wave by two lane shuffles, several waves through `wg_max` (one float per wave) and one workgroup barrier.
 // Every thread of the workgroup must call it; successive calls must be separated by a barrier of their own
 // (the row loop's is).
-__device__ __forceinline__ float big_group_max(const float (&y)[8], int group, int wave_row, float *wg_max)
+template <int kHalves>
+__device__ __forceinline__ void big_group_max(const float (&y)[kHalves][8], int group, int wave, float *wg_max, float (&m)[kHalves])
 {
-    float m = row16_max(amax8(y));
-    m = fmaxf(m, __shfl_xor(m, 16));
-    if (group >= 512) m = fmaxf(m, __shfl_xor(m, 32));
-    if (group > 512) {
-        if ((threadIdx.x & 63) == 0) wg_max[wave_row] = m;
-        __syncthreads();
-        const int waves = group >> 9, first = wave_row & ~(waves - 1);
-        float g = wg_max[first];
-        for (int w = 1; w < waves; ++w) g = fmaxf(g, wg_max[first + w]);
-        m = g;
+#pragma unroll
+    for (int h = 0; h < kHalves; ++h) {
+        m[h] = row16_max(amax8(y[h]));
+        m[h] = fmaxf(m[h], __shfl_xor(m[h], 16));
+        if (group >= 512) m[h] = fmaxf(m[h], __shfl_xor(m[h], 32));
     }
-    return m;
+    if (group > 512) {
+        if ((threadIdx.x & 63) == 0)
+#pragma unroll
+            for (int h = 0; h < kHalves; ++h) wg_max[h * 8 + wave] = m[h];
+        __syncthreads();
+        const int waves = group >> 9;
+#pragma unroll
+        for (int h = 0; h < kHalves; ++h) {
+            const int first = (h * 8 + wave) & ~(waves - 1);
+            float g = wg_max[first];
+            for (int w = 1; w < waves; ++w) g = fmaxf(g, wg_max[first + w]);
+            m[h] = g;
+        }
+    }
 }
 
 // Epilogue shared by the fast and the slow loop: y[] holds the rotated values in layout N.
@@ -222,75 +265,74 @@ struct CountOf<kFwdFake, kBits> {
 };
 
 // kFwdFake only: kYq = the dequantised row is stored, kHist = the bins are counted.
-// chunk: the thread's group of 8 elements, counted inside the whole row.
+// y[h]: half h of the row (n = 8192), else the row; chunk: the thread's group of 8 elements inside its half.
 // kBig: quantiser groups of more than 128 channels (the maximum then comes from big_group_max()).
-template <typename T, int kMode, int kBits, int kLanes, int kScale, bool kYq, bool kHist, bool kVirt, bool kWide, bool kBig,
+template <typename T, int kMode, int kBits, int kLanes, int kScale, bool kYq, bool kHist, bool kVirt, int kHalves, bool kBig,
           bool kNt = false>
-__device__ __forceinline__ void finish_row(const K12Args &A, const float (&y)[8], int64_t row, int head, int chunk,
+__device__ __forceinline__ void finish_row(const K12Args &A, const float (&y)[kHalves][8], int64_t row, int head, int chunk,
                                            typename CountOf<kMode, kBits>::type &bins, unsigned long long *wg_bins,
                                            float *wg_max)
 {
-    constexpr bool big = kBig;
-    if (kMode == kFwdFake) {
-        const int lanes = A.group >> 3;  // lanes per group
-        float f[8], s;
-        bool ordinary;
-        if (big)
-            rounded8<kBits, true>(y, lanes, A.scale_f16 != 0, f, &s, &ordinary, big_group_max(y, A.group, chunk >> 6, wg_max));
-        else
-            rounded8<kBits>(y, lanes, A.scale_f16 != 0, f, &s, &ordinary);
-        if (kHist) {
-            auto &bc = (BinCount<kBits> &)bins;
-            count8<kBits>(bc, f, ordinary);
-            if (bc.full()) bc.drain(wg_bins);
-        }
-        if (kYq) {
-            float yq[8];
-            dequant8(f, s, yq);
-            T *out_row = (T *)A.out + row * A.ld_out;
+    constexpr bool kWide = kHalves == 2;
+    float group_max[kHalves] = {};
+    if (kBig) big_group_max<kHalves>(y, A.group, chunk >> 6, wg_max, group_max);
+#pragma unroll
+    for (int h = 0; h < kHalves; ++h) {
+        const int chunk_row = h * (kN / 8) + chunk;
+        if (kMode == kFwdFake) {
+            const int lanes = A.group >> 3;  // lanes per group
+            float f[8], s;
+            bool ordinary;
+            rounded8<kBits, kBig>(y[h], lanes, A.scale_f16 != 0, f, &s, &ordinary, group_max[h]);
+            if (kHist) {
+                auto &bc = (BinCount<kBits> &)bins;
+                count8<kBits>(bc, f, ordinary);
+                if (bc.full()) bc.drain(wg_bins);
+            }
+            if (kYq) {
+                float yq[8];
+                dequant8(f, s, yq);
+                T *out_row = (T *)A.out + row * A.ld_out + h * kN;
+                uint32_t off = elem_off<kVirt, kWide>(A, head, chunk * 8, A.sub_ld_out) * (uint32_t)sizeof(T);
+                asm volatile("" : "+v"(off));
+                store8((T *)((char *)out_row + off), yq);
+            }
+        } else if (kMode != kFwdQuant) {
+            T *out_row = (T *)A.out + row * A.ld_out + h * kN;
             uint32_t off = elem_off<kVirt, kWide>(A, head, chunk * 8, A.sub_ld_out) * (uint32_t)sizeof(T);
             asm volatile("" : "+v"(off));
-            store8((T *)((char *)out_row + off), yq);
+            if (kNt)
+                store8_nt((T *)((char *)out_row + off), y[h]);
+            else
+                store8((T *)((char *)out_row + off), y[h]);
+        } else {
+            const int lanes = kLanes > 0 ? kLanes : (A.group >> 3);  // lanes per group
+            const bool f16 = kLanes > 0 ? (kScale != 0) : (A.scale_f16 != 0);
+            float s;
+            const uint32_t packed = quant8<kBits, kBig>(y[h], lanes, f16, &s, group_max[h]);
+            const int64_t unit = row * A.heads + head;
+            uint8_t *codes_row = A.codes + unit * (kHalves * kN * kBits / 8) + h * (kN * kBits / 8);
+            uint32_t coff = (uint32_t)(chunk * kBits);
+            asm volatile("" : "+v"(coff));
+            if (kBits == 2)
+                *(uint16_t *)(codes_row + coff) = (uint16_t)packed;
+            else
+                *(uint32_t *)(codes_row + coff) = packed;
+            // every lane of a group stores the group's scale (same value, same address): no divergence
+            const int groups = (kHalves * kN / 8) / lanes;
+            uint32_t goff = ((uint32_t)chunk_row / (uint32_t)lanes) * (f16 ? 2u : 4u);
+            asm volatile("" : "+v"(goff));
+            if (f16)
+                *(__half *)((char *)((__half *)A.scales + unit * groups) + goff) = __float2half_rn(s);
+            else
+                *(float *)((char *)((float *)A.scales + unit * groups) + goff) = s;
         }
-    } else if (kMode != kFwdQuant) {
-        T *out_row = (T *)A.out + row * A.ld_out;
-        uint32_t off = elem_off<kVirt, kWide>(A, head, chunk * 8, A.sub_ld_out) * (uint32_t)sizeof(T);
-        asm volatile("" : "+v"(off));
-        if (kNt)
-            store8_nt((T *)((char *)out_row + off), y);
-        else
-            store8((T *)((char *)out_row + off), y);
-    } else {
-        const int lanes = kLanes > 0 ? kLanes : (A.group >> 3);  // lanes per group
-        const bool f16 = kLanes > 0 ? (kScale != 0) : (A.scale_f16 != 0);
-        float s;
-        uint32_t packed;
-        if (big)
-            packed = quant8<kBits, true>(y, lanes, f16, &s, big_group_max(y, A.group, chunk >> 6, wg_max));
-        else
-            packed = quant8<kBits>(y, lanes, f16, &s);
-        const int64_t unit = row * A.heads + head;
-        uint8_t *codes_row = A.codes + unit * ((kWide ? 2 * kN : kN) * kBits / 8);
-        uint32_t coff = (uint32_t)(chunk * kBits);
-        asm volatile("" : "+v"(coff));
-        if (kBits == 2)
-            *(uint16_t *)(codes_row + coff) = (uint16_t)packed;
-        else
-            *(uint32_t *)(codes_row + coff) = packed;
-        // every lane of a group stores the group's scale (same value, same address): no divergence
-        const int groups = ((kWide ? 2 * kN : kN) / 8) / lanes;
-        uint32_t goff = ((uint32_t)chunk / (uint32_t)lanes) * (f16 ? 2u : 4u);
-        asm volatile("" : "+v"(goff));
-        if (f16)
-            *(__half *)((char *)((__half *)A.scales + unit * groups) + goff) = __float2half_rn(s);
-        else
-            *(float *)((char *)((float *)A.scales + unit * groups) + goff) = s;
     }
 }
 
 template <typename T, int kMode, int kBits, int kLanes, int kScale, bool kYq = true, bool kHist = false, bool kVirt = false,
           bool kWide = false, bool kBig = false, bool kNt = false>
-__global__ __launch_bounds__(kWide ? 2 * kThreads : kThreads, 4) void k12_kernel(K12Args A)
+__global__ __launch_bounds__(kThreads, kWide ? 2 : 4) void k12_kernel(K12Args A)
 {
     static_assert(!(kWide && kVirt), "blocks of small transforms are a 4096-point scheme");
     // kNt: rows are loaded and stored with the non-temporal hint.  262144 fp16 rows of n = 4096: forward 0.796 ->
@@ -318,154 +360,164 @@ __global__ __launch_bounds__(kWide ? 2 * kThreads : kThreads, 4) void k12_kernel
             if (threadIdx.x < (1 << kBits) && wg_bins[threadIdx.x]) atomicAdd(&A.hist[threadIdx.x], wg_bins[threadIdx.x]);
         }
     };
-    // LDS: [input ring 3 x 8 KB | output-scale table] first (low addresses), then the row buffers L[0..2]
-    extern __shared__ float lds_raw[];
-    // (32-bit rows: two ring slots of 16 KB per half in front, two row buffers behind them)
     constexpr bool kRing32 = sizeof(T) == 4;
-    float *lds = lds_raw + kHalves * (kRing32 ? 2 * kN : kFrontFloats);
+    // kTwoBuf: two row buffers and two ring slots instead of three.  Phase A of row `it` writes the buffer that
+    // phase C of row it-2 has just read (there each thread reads and writes the same addresses, and C comes
+    // first), and the load of row it+2 refills the slot that A has just read.  What is saved holds per-thread constants
+    // (kPark*, below).  Used
+    //  - for 32-bit rows (slots twice as large: three of them plus three buffers would not leave room for two
+    //    workgroups per compute unit; before, such rows were prefetched in registers, at the price of a dozen
+    //    spilled ones: 131072 rows of n = 4096 went from 1.20 / 0.92 / 0.84 ms to 0.81 / 0.80 / 0.53 ms);
+    //  - for n = 8192, which needs the registers;
+    //  - for the fake-quantising variants that count bins, where they are short as well: INT4 with both outputs (65536 fp16
+    //    rows of n = 4096: 1.14 -> 1.00 ms for four times as many), INT2 that only counts (0.82 -> 0.77 ms), and blocks of
+    //    smaller transforms (65536 fp16 rows of n = 1024: INT2 109 -> 84 us, INT4 100 -> 75).  On the other 16-bit variants
+    //    of n <= 4096 it measured equal or slower.
+    constexpr bool kTwoBuf = kRing32 || kWide || (kMode == kFwdFake && kHist && (kVirt || (kYq && kBits == 4) || (!kYq && kBits == 2)));
+    // What the two-buffer variants park in the LDS that is left, in quads of four floats per thread: output scales (all of
+    // them for 16-bit rows; for 32-bit rows, in the modes that are short of registers, what fits) and, where the bins are
+    // counted, the first layer's four coefficients per half.
+    constexpr bool kShort = kMode == kFwdQuant || kMode == kFwdFake;
+    constexpr int kParkScales = !kTwoBuf ? 0 : !kRing32 ? 2 * kHalves : !kShort ? 0 : kWide ? 3 : 1;
+    constexpr bool kParkFirst = kTwoBuf && !kRing32 && kMode == kFwdFake;
+    // LDS: the input ring first (low addresses), then the row buffers, then what is parked
+    constexpr int kSlots = kTwoBuf ? 2 : 3;
+    constexpr int kRingFloats = kSlots * kPoints * (int)sizeof(T) / 4;
+    static_assert((kRingFloats + kSlots * kHalves * kLdsRow) * sizeof(float) + (kParkScales + (kParkFirst ? kHalves : 0)) * kParkQuadBytes <=
+                      (kWide ? kLdsBytesWide : kLdsBytes), "dynamic LDS of the launch");
+    extern __shared__ float lds_raw[];
+    float *lds = lds_raw + kRingFloats;
     constexpr bool kInverse = (kMode == kInv);
     // kHadamard: the same cascade with every coefficient +1 (lower element of a pair) or -1 (upper element), i.e.
     // additions and subtractions; nothing is read from a plan.  A layer then maps (a, b) to (a + b, b - a), which
     // is the Sylvester butterfly (a + b, a - b) up to the sign of its second output; over all layers the signs
     // collect to (-1)^popcount(index) per output element, which the single scale 1 / sqrt(n) takes along.
     constexpr bool kHad = (kMode == kHadamard);
-    // kWide: `half` selects the half of the row; tid, wave, chunk and idx_n count inside the half
-    const int half = kWide ? (int)(threadIdx.x >> 9) : 0;
-    const int tid = threadIdx.x & (kThreads - 1), wave = tid >> 6, lane = tid & 63;
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;  // kWide: chunk and idx_n count inside a half
     const int chunk = wave * 64 + lane_chunk(lane);
     const int idx_n = chunk * 8;
-    const int col0 = half * kN;                 // first column of the half
-    const int chunk_row = half * (kN / 8) + chunk;  // the thread's chunk counted inside the whole row
     const int head = blockIdx.x % A.heads;
     const int64_t row_first = blockIdx.x / A.heads;
     const int64_t row_step = gridDim.x / A.heads;
-    const uint32_t off_n = elem_off<kVirt, kWide>(A, head, col0 + idx_n, A.sub_ld_in);  // element offset of the thread inside a row
+    const uint32_t off_n = elem_off<kVirt, kWide>(A, head, idx_n, A.sub_ld_in);  // element offset of the thread inside a row
     // tables: rows of n entries, indexed inside the transform the element belongs to
     const int tn = kVirt ? A.n : kPoints;
     const int nk = kVirt ? A.n_log : kLayers;
     const int tmask = tn - 1;
     const T *in = (const T *)A.in;
     if (row_first >= A.rows) return;
-    if (!kHad && !plan_matches(A.plan)) return;
+    PlanHead ph = {true, 0, 0};
+    if (!kHad) ph = plan_head(A.plan);
+    if (!ph.matches) return;
 
-    // coefficients: cn[j][r] for layer j+1 (layout N), cp[j][r'] for layer 8+j (layout P), d[r] (layout N)
-    const int idx_p = base_p(wave, lane);
-    float cn[7][8], cp[5][8];
-    float cw[8];  // kWide: layer 13, in layout N (forward, phase C) or layout P (inverse, phase B)
-    auto load_coefficients = [&]() {
-        if (kHad) {
-#pragma unroll
-            for (int r = 0; r < 8; ++r) {
-#pragma unroll
-                for (int j = 0; j < 7; ++j) cn[j][r] = (((idx_n + r) >> j) & 1) ? -1.0f : 1.0f;
-#pragma unroll
-                for (int j = 0; j < 5; ++j) cp[j][r] = (((idx_p + p_reg_idx(r)) >> (7 + j)) & 1) ? -1.0f : 1.0f;
-                cw[r] = half ? -1.0f : 1.0f;
-            }
-            return;
-        }
-        // tables are [head][layer][n]; kVirt: the head is the element's own (virt_head)
-        const float *fg = A.fg + (kVirt ? 0 : (size_t)head * kLayers * kPoints);
-        const float *fg_n = fg + (kVirt ? (size_t)virt_head(A, head, idx_n) * nk * tn : 0);
-#pragma unroll
-        for (int j = 0; j < 7; ++j)
-#pragma unroll
-            for (int r = 0; r < 8; ++r) cn[j][r] = fg_n[j * tn + ((col0 + idx_n) & tmask) + r];
-#pragma unroll
-        for (int j = 0; j < 5; ++j)
-#pragma unroll
-            for (int r = 0; r < 8; ++r) {  // layers above log2 n do not exist: weight zero leaves the element as it is
-                const int e = col0 + idx_p + p_reg_idx(r);
-                const float *fg_p = fg + (kVirt ? (size_t)virt_head(A, head, e) * nk * tn : 0);
-                cp[j][r] = (!kVirt || 8 + j <= nk) ? fg_p[(7 + j) * tn + (e & tmask)] : 0.0f;
-            }
-#pragma unroll
-        for (int r = 0; r < 8; ++r)
-            cw[r] = !kWide ? 0.0f : kInverse ? fg[kK * tn + col0 + idx_p + p_reg_idx(r)] : fg[kK * tn + col0 + idx_n + r];
-    };
-    // Transforms and the fused quantiser are also called with a handful of rows (decoding), where the call's
-    // latency is a chain of memory round trips: there the coefficient loads are issued in front of the branch
-    // on the plan's flag (the empty statements consume their results, which pins them there), so that the two
-    // round trips overlap.
-    constexpr bool kEarlyLoads = (kMode != kFwdFake) && !kWide;  // (not where registers are short anyway)
-    if (kEarlyLoads) {
-        load_coefficients();
-#pragma unroll
-        for (int r = 0; r < 8; ++r) {
-#pragma unroll
-            for (int j = 0; j < 7; ++j) asm volatile("" ::"v"(cn[j][r]));
-#pragma unroll
-            for (int j = 0; j < 5; ++j) asm volatile("" ::"v"(cp[j][r]));
-            if (kWide) asm volatile("" ::"v"(cw[r]));
-        }
-    }
-    if (!kHad && *A.fast_bad != 0) {  // rare: plain rotations through LDS
+    if ((kInverse ? ph.bad_inv : ph.bad_fwd) != 0) {  // rare: plain rotations through LDS
         const float2 *cs = A.cs + (kVirt ? 0 : (size_t)head * kLayers * (kPoints / 2));
         for (int64_t row = row_first; row < A.rows; row += row_step) {
-            float u[8];
-            unpack8(load8(in + row * A.ld_in + off_n), u, (const T *)nullptr);
-            slow_cascade<kInverse, kWide>(u, lds, cs, col0 + idx_n, nk, kVirt ? (1 << A.row_log) - 1 : 0, kVirt ? head * kN : 0);
-            finish_row<T, kMode, kBits, kLanes, kScale, kYq, kHist, kVirt, kWide, kBig, kNt>(A, u, row, head, chunk_row, bins, wg_bins, wg_max);
+            float u[kHalves][8];
+#pragma unroll
+            for (int h = 0; h < kHalves; ++h) unpack8(load8(in + row * A.ld_in + off_n + h * kN), u[h], (const T *)nullptr);
+            slow_cascade<kInverse, kHalves>(u, lds, cs, idx_n, nk, kVirt ? (1 << A.row_log) - 1 : 0, kVirt ? head * kN : 0);
+            finish_row<T, kMode, kBits, kLanes, kScale, kYq, kHist, kVirt, kHalves, kBig, kNt>(A, u, row, head, chunk, bins, wg_bins, wg_max);
         }
         flush_bins();
         return;
     }
-    if (!kEarlyLoads) load_coefficients();
-
+    // coefficients: cn[h][j][r] for layer j+1 (layout N), cp[h][j][r'] for layer 8+j (layout P), d[h][r] (layout N)
+    const int idx_p = base_p(wave, lane);
     const int an = lds_addr(idx_n);
     const int ap = lds_addr(idx_p);
+    float cn[kHalves][7][8], cp[kHalves][5][8];
+    float cw[2][8];  // kWide: layer 13, in layout N (forward, phase C) or layout P (inverse, phase B; the upper half's only)
+    if (kHad) {
+#pragma unroll
+        for (int h = 0; h < kHalves; ++h)
+#pragma unroll
+            for (int r = 0; r < 8; ++r) {
+#pragma unroll
+                for (int j = 0; j < 7; ++j) cn[h][j][r] = (((idx_n + r) >> j) & 1) ? -1.0f : 1.0f;
+#pragma unroll
+                for (int j = 0; j < 5; ++j) cp[h][j][r] = (((idx_p + p_reg_idx(r)) >> (7 + j)) & 1) ? -1.0f : 1.0f;
+                cw[h][r] = h ? -1.0f : 1.0f;
+            }
+    } else {
+        // tables are [head][layer][n]; kVirt: the head is the element's own (virt_head)
+        const float *fg0 = A.fg + (kVirt ? (size_t)virt_head(A, head, idx_n) * nk * tn : (size_t)head * kLayers * kPoints) + (idx_n & tmask);
+#pragma unroll
+        for (int h = 0; h < kHalves; ++h) {
+            const float *fg = fg0 + h * kN;
+            float st[5][8], sw[8];
+#pragma unroll
+            for (int j = 0; j < 5; ++j) {  // layers above log2 n do not exist: weight zero leaves the element as it is
+#pragma unroll
+                for (int r = 0; r < 8; ++r) st[j][r] = 0.0f;
+                if (!kVirt || 8 + j <= nk) load_coef8(fg + (size_t)(7 + j) * tn, st[j]);
+            }
+#pragma unroll
+            for (int j = 0; j < 7; ++j) load_coef8(fg + (size_t)j * tn, cn[h][j]);
+            if (kWide && !kInverse) load_coef8(fg + (size_t)kK * tn, cw[h]);
+            float *b0 = lds + h * kLdsRow, *b1 = lds + (kHalves + h) * kLdsRow;
+            to_layout_p(b0, b1, an, ap, st[0], st[1], cp[h][0], cp[h][1]);
+            to_layout_p(b0, b1, an, ap, st[2], st[3], cp[h][2], cp[h][3]);
+            if (kWide && kInverse && h == 1) {
+                load_coef8(fg + (size_t)kK * tn, sw);
+                to_layout_p(b0, b1, an, ap, st[4], sw, cp[h][4], cw[1]);
+            } else {
+                to_layout_p(b0, an, ap, st[4], cp[h][4]);
+            }
+        }
+    }
+
     // rows of this workgroup: below 2^28 for every batch the library accepts, so the loop counters are 32-bit
     // (64-bit comparisons of uniform values would be done on the vector unit)
     const int n_my = (int)((A.rows - row_first + row_step - 1) / row_step);
 
-    // Phase B of one row: layers 8..12 (or 12..8) on layout P, in place in its LDS buffer.
-    // kWide: lb is the buffer of the thread's own half, lo the other half's; the inverse starts with layer 13.
-    auto phase_b = [&](float *lb, const float *lo) {
-        float u[8];
-        lds_read_p(lb, ap, u);
-        if (kWide && kInverse) {
-            cross_layer<true>(lo, ap, cw, u);
-            // both halves must have read the other's values before either overwrites its own
-            __syncthreads();
+    // Phase B of one row: layers 8..12 (or 12..8) on layout P, in place in its LDS buffer (one per half).
+    auto phase_b = [&](float *lb) {
+        float u[kHalves][8];
+#pragma unroll
+        for (int h = 0; h < kHalves; ++h) lds_read_p(lb + h * kLdsRow, ap, u[h]);
+        if constexpr (kWide && kInverse) half_layer<true>(u, cw[0], cw[1]);
+#pragma unroll
+        for (int h = 0; h < kHalves; ++h) {
+            if (!kInverse) {
+                dpp_layer_xor1(u[h], cp[h][0]);
+                dpp_layer_xor2(u[h], cp[h][1]);
+                dpp_layer_xor7(u[h], cp[h][2]);
+                reg_layer<1>(u[h], cp[h][3]);
+                reg_layer<2>(u[h], cp[h][4]);
+            } else {
+                if (kWide)
+                    reg_layer<2>(u[h], cp[h][4]);
+                else
+                    reg_layer_first<2>(u[h], cp[h][4]);
+                reg_layer<1>(u[h], cp[h][3]);
+                dpp_layer_xor7(u[h], cp[h][2]);
+                dpp_layer_xor2(u[h], cp[h][1]);
+                dpp_layer_xor1(u[h], cp[h][0]);
+            }
+            lds_write_p(lb + h * kLdsRow, ap, u[h]);
         }
-        if (!kInverse) {
-            dpp_layer_xor1(u, cp[0]);
-            dpp_layer_xor2(u, cp[1]);
-            dpp_layer_xor7(u, cp[2]);
-            reg_layer<1>(u, cp[3]);
-            reg_layer<2>(u, cp[4]);
-        } else {
-            if (kWide)
-                reg_layer<2>(u, cp[4]);
-            else
-                reg_layer_first<2>(u, cp[4]);
-            reg_layer<1>(u, cp[3]);
-            dpp_layer_xor7(u, cp[2]);
-            dpp_layer_xor2(u, cp[1]);
-            dpp_layer_xor1(u, cp[0]);
-        }
-        lds_write_p(lb, ap, u);
     };
     // Layers of phase A after the first one / layers of phase C before the output scale.
-    auto layers_a = [&](float (&u)[8]) {
+    auto layers_a = [&](float (&u)[8], const float (&c)[7][8]) {
         if (!kInverse) {
-            reg_layer<1>(u, cn[1]);
-            reg_layer<2>(u, cn[2]);
-            dpp_layer_xor1(u, cn[3]);
-            dpp_layer_xor2(u, cn[4]);
-            dpp_layer_xor7(u, cn[5]);
-            dpp_layer_xor8(u, cn[6]);
+            reg_layer<1>(u, c[1]);
+            reg_layer<2>(u, c[2]);
+            dpp_layer_xor1(u, c[3]);
+            dpp_layer_xor2(u, c[4]);
+            dpp_layer_xor7(u, c[5]);
+            dpp_layer_xor8(u, c[6]);
         }
     };
-    auto layers_c = [&](float (&u)[8]) {
+    auto layers_c = [&](float (&u)[8], const float (&c)[7][8]) {
         if (kInverse) {
-            dpp_layer_xor8(u, cn[6]);
-            dpp_layer_xor7(u, cn[5]);
-            dpp_layer_xor2(u, cn[4]);
-            dpp_layer_xor1(u, cn[3]);
-            reg_layer<2>(u, cn[2]);
-            reg_layer<1>(u, cn[1]);
-            reg_layer<0>(u, cn[0]);
+            dpp_layer_xor8(u, c[6]);
+            dpp_layer_xor7(u, c[5]);
+            dpp_layer_xor2(u, c[4]);
+            dpp_layer_xor1(u, c[3]);
+            reg_layer<2>(u, c[2]);
+            reg_layer<1>(u, c[1]);
+            reg_layer<0>(u, c[0]);
         }
     };
     // ---- input staged through an LDS ring filled by direct global->LDS loads -------------------
@@ -480,72 +532,51 @@ __global__ __launch_bounds__(kWide ? 2 * kThreads : kThreads, 4) void k12_kernel
     // earlier, followed by stores, the load of row it+1 and stores again, so at most
     // 2 kStores + 1 younger operations may still be pending when row `it` is consumed.  The
     // first four iterations (pipeline fill, fewer stores issued) wait for everything.
-    // 32-bit rows: two such loads per lane and row (kLoads), two stores per lane for a row of output.
-    constexpr int kLoads = (int)sizeof(T) / 2;
-    constexpr int kStores = (kMode == kFwdQuant) ? 2 : (kMode == kFwdFake && !kYq) ? 0 : kLoads;
+    // 32-bit rows: two such loads per lane and row (kHalfLoads), two stores per lane for a row of output; n = 8192: as many
+    // for each half.
+    constexpr int kHalfLoads = (int)sizeof(T) / 2, kLoads = kHalves * kHalfLoads;
+    constexpr int kStores = (kMode == kFwdQuant) ? 2 * kHalves : (kMode == kFwdFake && !kYq) ? 0 : kLoads;
     constexpr int kPending = 2 * kStores + kLoads;  // operations younger than the last load of the awaited row
     constexpr uint32_t kSlotBytes = kPoints * sizeof(T);
-    // kTwoBuf: two row buffers and two ring slots instead of three.  Phase A of row `it` writes the buffer that
-    // phase C of row it-2 has just read (there each thread reads and writes the same addresses, and C comes
-    // first), and the load of row it+2 refills the slot that A has just read.  Where the rows are 16-bit the
-    // third buffer then holds the output scales, which leave the registers.  Used
-    //  - for 32-bit rows (slots twice as large: three of them plus three buffers would not leave room for two
-    //    workgroups per compute unit; before, such rows were prefetched in registers, at the price of a dozen
-    //    spilled ones: 131072 rows of n = 4096 went from 1.20 / 0.92 / 0.84 ms to 0.81 / 0.80 / 0.53 ms);
-    //  - for n = 8192, whose kernels are short of registers (65536 fp16 rows: 0.67 / 0.78 / 0.62 ms ->
-    //    0.63 / 0.60 / 0.47 ms forward / inverse / fused quantiser, despite the barrier it adds, see below);
-    //  - for two fake-quantising variants of n <= 4096, where it measured faster: the one that stores the row
-    //    and counts INT4 codes as well (1.14 -> 1.00 ms for 262144 fp16 rows) and the INT2 one that only counts
-    //    (0.82 -> 0.77 ms).  On the other 16-bit variants of n <= 4096 it measured equal or slower.
-    constexpr bool kTwoBuf = kRing32 || kWide || (kMode == kFwdFake && kHist && ((kYq && kBits == 4) || (!kYq && kBits == 2)));
-    constexpr bool kScaleLds = kTwoBuf && !kRing32;
-    float d[8];
-    float *dtab = lds + (2 * kHalves + half) * kLdsRow;  // kScaleLds: the third buffer
-    {
+    float d[kHalves][8];
+    float4 *park = (float4 *)(lds + 2 * kHalves * kLdsRow) + tid;  // quad q: park[q * kThreads], read back by the same thread only
+#pragma unroll
+    for (int h = 0; h < kHalves; ++h) {
         if (kHad) {
             const float scale = kWide ? 0.011048543456039806f : 0.015625f;  // 1 / sqrt(8192), 1 / sqrt(4096)
 #pragma unroll
-            for (int r = 0; r < 8; ++r) d[r] = (__builtin_popcount(col0 + idx_n + r) & 1) ? -scale : scale;
+            for (int r = 0; r < 8; ++r) d[h][r] = (__builtin_popcount(h * kN + idx_n + r) & 1) ? -scale : scale;
         } else {
-            const float *fd = A.fd + (kVirt ? (size_t)virt_head(A, head, idx_n) * tn : (size_t)head * kPoints);
-#pragma unroll
-            for (int r = 0; r < 8; ++r) d[r] = fd[((col0 + idx_n) & tmask) + r];
+            const float *fd = A.fd + (kVirt ? (size_t)virt_head(A, head, idx_n) * tn : (size_t)head * kPoints) + h * kN;
+            load_coef8(fd + (idx_n & tmask), d[h]);
         }
-        if (kScaleLds) lds_write_n(dtab, an, d);  // read back by the same thread only
+#pragma unroll
+        for (int q = 0; q < 2; ++q)
+            if (2 * h + q < kParkScales) park[(2 * h + q) * kThreads] = make_float4(d[h][4 * q], d[h][4 * q + 1], d[h][4 * q + 2], d[h][4 * q + 3]);
+        if (kParkFirst) park[(kParkScales + h) * kThreads] = make_float4(cn[h][0][1], cn[h][0][3], cn[h][0][5], cn[h][0][7]);
     }
-    const int wave_row = half * 8 + wave;  // the wave's piece of a row: 512 elements, 1 KB per load
     constexpr int kPer = 16 / (int)sizeof(T);  // elements per lane and load
+    constexpr uint32_t kHalfSlot = kN * sizeof(T);  // bytes of a half in a slot
     const uint32_t ring0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)lds_raw;
-    const uint32_t slice = ring0 + (uint32_t)wave_row * (1024u * kLoads);             // this wave's piece of a slot
-    const uint32_t rd_addr = slice + (uint32_t)lane_chunk(lane) * (16u * kLoads);      // this thread's chunk
+    const uint32_t slice = ring0 + (uint32_t)wave * (1024u * kHalfLoads);             // this wave's piece of a slot's first half
+    const uint32_t rd_addr = slice + (uint32_t)lane_chunk(lane) * (16u * kHalfLoads);  // this thread's chunk
     // lane's bytes in a row, first and (32-bit rows) second load
-    const uint32_t voff = elem_off<kVirt, kWide>(A, head, wave_row * 512 + lane * kPer, A.sub_ld_in) * (uint32_t)sizeof(T);
-    const uint32_t voff1 = kLoads == 2 ? elem_off<kVirt, kWide>(A, head, wave_row * 512 + (64 + lane) * kPer, A.sub_ld_in) * (uint32_t)sizeof(T) : 0u;
+    const uint32_t voff = elem_off<kVirt, kWide>(A, head, wave * 512 + lane * kPer, A.sub_ld_in) * (uint32_t)sizeof(T);
+    const uint32_t voff1 = kHalfLoads == 2 ? elem_off<kVirt, kWide>(A, head, wave * 512 + (64 + lane) * kPer, A.sub_ld_in) * (uint32_t)sizeof(T) : 0u;
     const uint32_t slice_s = __builtin_amdgcn_readfirstlane(slice);  // uniform over the wave
     auto ring_load = [&](int j, int slot) {
         const int jj = j < n_my ? j : n_my - 1;  // past the end: re-read the last row (unused)
-        const char *rowp = (const char *)(in + (row_first + jj * row_step) * A.ld_in);
-        const uint32_t m0v = slice_s + (uint32_t)slot * kSlotBytes;
-        if (kNt) {
-            asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %2 nt"
-                         :
-                         : "v"(voff), "s"(m0v), "s"(rowp)
-                         : "memory");
-            if (kLoads == 2)
-                asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %2 nt"
-                             :
-                             : "v"(voff1), "s"(m0v + 1024u), "s"(rowp)
-                             : "memory");
-        } else {
-            asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %2"
-                         :
-                         : "v"(voff), "s"(m0v), "s"(rowp)
-                         : "memory");
-            if (kLoads == 2)
-                asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %2"
-                             :
-                             : "v"(voff1), "s"(m0v + 1024u), "s"(rowp)
-                             : "memory");
+#pragma unroll
+        for (int h = 0; h < kHalves; ++h) {
+            const char *rowp = (const char *)(in + (row_first + jj * row_step) * A.ld_in + h * kN);
+            const uint32_t m0v = slice_s + (uint32_t)slot * kSlotBytes + (uint32_t)h * kHalfSlot;
+            if (kNt) {
+                asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %2 nt" : : "v"(voff), "s"(m0v), "s"(rowp) : "memory");
+            } else {
+                asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %2" : : "v"(voff), "s"(m0v), "s"(rowp) : "memory");
+                if (kHalfLoads == 2)
+                    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %2" : : "v"(voff1), "s"(m0v + 1024u), "s"(rowp) : "memory");
+            }
         }
     };
     ring_load(0, 0);
@@ -553,76 +584,78 @@ __global__ __launch_bounds__(kWide ? 2 * kThreads : kThreads, 4) void k12_kernel
     // One pipeline step with the roles of the three buffers fixed at compile time (BA: phase A of row it,
     // BB: phase B of row it-1, BC: phase C of row it-2), so that buffer offsets become immediates of the
     // LDS instructions instead of per-lane address arithmetic.  Three such steps make one turn.
-    // n = 8192: whether phase B runs before phase C (see below)
-    constexpr bool kBFirst = kWide && (sizeof(T) == 2 ? (kMode == kFwd || kMode == kInv || kHad) : kMode == kFwdFake);
     auto step = [&](auto BA, auto BB, auto BC, int it) {
         constexpr int ba = decltype(BA)::value, bb = decltype(BB)::value, bc = decltype(BC)::value;
-        float *la = lds + (ba * kHalves + half) * kLdsRow, *lb = lds + (bb * kHalves + half) * kLdsRow;
-        float *lc = lds + (bc * kHalves + half) * kLdsRow;
-        const float *lb_other = lds + (bb * kHalves + (half ^ 1)) * kLdsRow;  // kWide only
-        const float *lc_other = lds + (bc * kHalves + (half ^ 1)) * kLdsRow;
+        float *la = lds + ba * kHalves * kLdsRow, *lb = lds + bb * kHalves * kLdsRow;  // (n = 8192: one buffer per half)
+        float *lc = lds + bc * kHalves * kLdsRow;
         auto phase_a = [&]() {  // A(it)
             typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-            u32x4 v, v1;
+            u32x4 v[4];  // 16 bytes of half h at h * kHalfLoads (32-bit rows: and the next)
             constexpr int ro = ba * (int)kSlotBytes;
-            if (kLoads == 1) {
-                if (it >= 4)
-                    asm volatile("s_waitcnt vmcnt(%3)\n\tds_read_b128 %0, %1 offset:%2\n\ts_waitcnt lgkmcnt(0)"
-                                 : "=v"(v) : "v"(rd_addr), "n"(ro), "n"(kPending) : "memory");
-                else
-                    asm volatile("s_waitcnt vmcnt(0)\n\tds_read_b128 %0, %1 offset:%2\n\ts_waitcnt lgkmcnt(0)"
-                                 : "=v"(v) : "v"(rd_addr), "n"(ro) : "memory");
-            } else {
-                if (it >= 4)
-                    asm volatile("s_waitcnt vmcnt(%5)\n\tds_read_b128 %0, %2 offset:%3\n\tds_read_b128 %1, %2 offset:%4\n\ts_waitcnt lgkmcnt(0)"
-                                 : "=&v"(v), "=&v"(v1) : "v"(rd_addr), "n"(ro), "n"(ro + 16), "n"(kPending) : "memory");
-                else
-                    asm volatile("s_waitcnt vmcnt(0)\n\tds_read_b128 %0, %2 offset:%3\n\tds_read_b128 %1, %2 offset:%4\n\ts_waitcnt lgkmcnt(0)"
-                                 : "=&v"(v), "=&v"(v1) : "v"(rd_addr), "n"(ro), "n"(ro + 16) : "memory");
-            }
+            constexpr int o1 = ro + (kHalfLoads == 2 ? 16 : (int)kHalfSlot), o2 = ro + (int)kHalfSlot, o3 = o2 + 16;
+            if (it >= 4)
+                asm volatile("s_waitcnt vmcnt(%0)" ::"n"(kPending) : "memory");
+            else
+                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            if (kLoads == 1)
+                asm volatile("ds_read_b128 %0, %1 offset:%2\n\ts_waitcnt lgkmcnt(0)" : "=v"(v[0]) : "v"(rd_addr), "n"(ro) : "memory");
+            else if (kLoads == 2)
+                asm volatile("ds_read_b128 %0, %2 offset:%3\n\tds_read_b128 %1, %2 offset:%4\n\ts_waitcnt lgkmcnt(0)"
+                             : "=&v"(v[0]), "=&v"(v[1]) : "v"(rd_addr), "n"(ro), "n"(o1) : "memory");
+            else
+                asm volatile("ds_read_b128 %0, %4 offset:%5\n\tds_read_b128 %1, %4 offset:%6\n\tds_read_b128 %2, %4 offset:%7\n\t"
+                             "ds_read_b128 %3, %4 offset:%8\n\ts_waitcnt lgkmcnt(0)"
+                             : "=&v"(v[0]), "=&v"(v[1]), "=&v"(v[2]), "=&v"(v[3])
+                             : "v"(rd_addr), "n"(ro), "n"(o1), "n"(o2), "n"(o3) : "memory");
             // refills the slot of row it-1, consumed in the previous iteration (kTwoBuf: the slot just read)
             ring_load(it + 2, kTwoBuf ? ba : bb);
-            Raw8 raw;
-            raw.lo = make_uint4(v.x, v.y, v.z, v.w);
-            if (kLoads == 2) raw.hi = make_uint4(v1.x, v1.y, v1.z, v1.w);
-            float u[8];
-            unpack8(raw, u, (const T *)nullptr);
-            if (!kInverse) reg_layer_first<0>(u, cn[0]);
-            layers_a(u);
-            lds_write_n(la, an, u);
+#pragma unroll
+            for (int h = 0; h < kHalves; ++h) {
+                Raw8 raw;
+                const u32x4 v0 = v[h * kHalfLoads], v1 = v[h * kHalfLoads + (kHalfLoads - 1)];
+                raw.lo = make_uint4(v0.x, v0.y, v0.z, v0.w);
+                if (kHalfLoads == 2) raw.hi = make_uint4(v1.x, v1.y, v1.z, v1.w);
+                float u[8];
+                unpack8(raw, u, (const T *)nullptr);
+                if (kParkFirst) {
+                    const float4 c = park[(kParkScales + h) * kThreads];
+                    const float c0[8] = {0.0f, c.x, 0.0f, c.y, 0.0f, c.z, 0.0f, c.w};
+                    reg_layer_first<0>(u, c0);
+                } else if (!kInverse) {
+                    reg_layer_first<0>(u, cn[h][0]);
+                }
+                layers_a(u, cn[h]);
+                lds_write_n(la + h * kLdsRow, an, u);
+            }
         };
         auto phase_c = [&]() {  // C(it-2)
-            float u[8];
-            lds_read_n(lc, an, u);
-            if (kWide && !kInverse) cross_layer<false>(lc_other, an, cw, u);  // layer 13
-            layers_c(u);
-            if (kScaleLds) {
-                float dl[8];
-                lds_read_n(dtab, an, dl);
+            float u[kHalves][8];
 #pragma unroll
-                for (int r = 0; r < 8; ++r) u[r] *= dl[r];
-            } else {
+            for (int h = 0; h < kHalves; ++h) lds_read_n(lc + h * kLdsRow, an, u[h]);
+            if constexpr (kWide && !kInverse) half_layer<false>(u, cw[0], cw[1]);  // layer 13
 #pragma unroll
-                for (int r = 0; r < 8; ++r) u[r] *= d[r];
+            for (int h = 0; h < kHalves; ++h) {
+                layers_c(u[h], cn[h]);
+#pragma unroll
+                for (int q = 0; q < 2; ++q) {
+                    if (2 * h + q < kParkScales) {
+                        const float4 p = park[(2 * h + q) * kThreads];
+                        u[h][4 * q] *= p.x;
+                        u[h][4 * q + 1] *= p.y;
+                        u[h][4 * q + 2] *= p.z;
+                        u[h][4 * q + 3] *= p.w;
+                    } else {
+#pragma unroll
+                        for (int r = 4 * q; r < 4 * q + 4; ++r) u[h][r] *= d[h][r];
+                    }
+                }
             }
-            finish_row<T, kMode, kBits, kLanes, kScale, kYq, kHist, kVirt, kWide, kBig, kNt>(A, u, row_first + (it - 2) * row_step, head, chunk_row, bins, wg_bins, wg_max);
+            finish_row<T, kMode, kBits, kLanes, kScale, kYq, kHist, kVirt, kHalves, kBig, kNt>(A, u, row_first + (it - 2) * row_step, head, chunk, bins, wg_bins, wg_max);
         };
         // The phases touch different buffers, so any order is correct as long as C precedes A where the two
         // share a buffer.  n = 4096: C, B, A measured 1-2 % faster than the other orders on all modes.
-        // n = 8192 (always two buffers): layer 13 makes phase C of the forward modes read the other half's
-        // buffer, which that half's phase A is about to overwrite, hence the extra barrier.  These kernels also
-        // spill a few coefficients, and the compiler waits for their reloads with vmcnt(0), which waits for every
-        // load and store the wave issued before; which order keeps those waits away from fresh loads depends on
-        // where the reloads fall, and was measured per mode (65536 rows: fp16 forward 0.66 -> 0.63 ms and
-        // inverse 0.69 -> 0.60 ms with B first, fused quantiser 0.52 -> 0.47 ms with C first).
-        if (!kBFirst) {
-            if (it >= 2) phase_c();
-            if (it >= 1 && it <= n_my) phase_b(lb, lb_other);  // B(it-1)
-        } else {
-            if (it >= 1 && it <= n_my) phase_b(lb, lb_other);
-            if (it >= 2) phase_c();
-        }
-        if (kWide && !kInverse) __syncthreads();  // the other half's reads in phase C are complete
+        if (it >= 2) phase_c();
+        if (it >= 1 && it <= n_my) phase_b(lb);  // B(it-1)
         if (it < n_my) phase_a();
         __syncthreads();
     };
@@ -679,14 +712,14 @@ static hipError_t launch_k12_t(Mode mode, const K12Args &A, int bits, unsigned g
         }
     }
     if (!kern) return hipErrorInvalidValue;
-    constexpr size_t lds_bytes = (kWide ? 2 : 1) * kLdsBytes;
+    constexpr size_t lds_bytes = kWide ? kLdsBytesWide : kLdsBytes;
     // one record per kernel of this instantiation of the launcher (the modes, bit widths and output choices)
     static LdsLimitOnce once[5][2][3][2];
     const int variant = mode != kFwdFake ? 0 : (A.out && A.hist) ? 0 : A.out ? 1 : 2;
     const int general = (mode == kFwdQuant && (kBig || kVirt || A.group != 128 || !A.scale_f16)) ? 1 : 0;
     hipError_t e = once[mode][bits == 2 ? 0 : 1][mode == kFwdQuant ? general : variant][(A.streaming && sizeof(T) == 2 && (mode == kFwd || mode == kHadamard)) ? 1 : 0].set((const void *)kern, lds_bytes);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(kWide ? 2 * kThreads : kThreads), lds_bytes, stream, A);
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(kThreads), lds_bytes, stream, A);
     return hipGetLastError();
 }
 

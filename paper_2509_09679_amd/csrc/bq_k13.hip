@@ -1,4 +1,4 @@
-// n = 8192 instantiations of the specialised transform kernels (1024 threads, both halves of a row side by side).
+// n = 8192 instantiations of the specialised transform kernels (a thread holds both halves of a row).
 #include "bq_k12_kernel.h"
 
 namespace bq {

@@ -25,7 +25,6 @@ struct SmallArgs {
     void *out;
     const float *fg, *fd;
     const float2 *cs;
-    const int *fast_bad;
     PlanRef plan;
     int64_t rows, ld_in, ld_out;
     int heads, width;    // width = heads * n
@@ -45,7 +44,8 @@ __global__ __launch_bounds__(kSmallThreads) void small_kernel(SmallArgs A)
 {
     constexpr int n = 1 << K;
     constexpr bool kInverse = (kMode == kInv);
-    if (!plan_matches(A.plan)) return;
+    const PlanHead ph = plan_head(A.plan);
+    if (!ph.matches) return;
     const int tid = threadIdx.x;
     __shared__ unsigned long long wg_bins[16];  // kFwdFake: this workgroup's bin counts
     BinCount<kBits> bins;
@@ -78,7 +78,7 @@ __global__ __launch_bounds__(kSmallThreads) void small_kernel(SmallArgs A)
     }
     const int head = col >> K;
     const int idx = col & (n - 1);
-    const bool fast = (*A.fast_bad == 0);
+    const bool fast = (kInverse ? ph.bad_inv : ph.bad_fwd) == 0;
 
     const float2 *cs_head = A.cs + (size_t)head * K * (n >> 1);
     const T *in = (const T *)A.in;
@@ -231,7 +231,6 @@ hipError_t launch_small(Mode mode, const void *in, void *out, const PlanView &pv
     A.fg = mode == kInv ? pv.fg_inv : pv.fg_fwd;
     A.fd = mode == kInv ? pv.fd_inv : pv.fd_fwd;
     A.cs = pv.cs;
-    A.fast_bad = mode == kInv ? &pv.hdr->fast_bad_inv : &pv.hdr->fast_bad_fwd;
     A.plan = pv.ref;
     A.rows = s.rows;
     A.ld_in = s.ld_x;

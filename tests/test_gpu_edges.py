@@ -25,3 +25,28 @@ def test_plan_tables_at_the_group_sizes(n, heads):
     # seeded sweep states why)
     floor = np.median(ab, axis=2, keepdims=True)
     gu.check_dtheta(dth, rdth, np.maximum(ab, floor), what=f"dtheta n={n}")
+
+
+@pytest.mark.parametrize("n,heads,rows,dtype", [(4096, 1, 1, "f16"), (4096, 2, 3, "f32"), (8192, 1, 1, "bf16"), (8192, 1, 2, "f32"),
+                                                (8192, 2, 5, "f16"), (256, 16, 2, "f16"), (1024, 4, 3, "f32"), (2048, 1, 2, "bf16")])
+@pytest.mark.parametrize("bits,group,sd", [(4, 128, "f16"), (2, 64, "f32"), (4, 256, "f16")])
+def test_few_rows_through_every_transform_kernel(n, heads, rows, dtype, bits, group, sd):
+    # the pipelines' fill and drain without a steady state in between, tables transposed through the row buffers that the
+    # first rows then use, constants parked in LDS
+    x, th, _ = synth.small_case(n, rows, dtype, heads=heads, seed=400 + n + rows)
+    x64 = synth.to_f64(x, dtype)
+    ref = oracle.forward(x64, th, n, heads)
+    tag = f"n={n} H={heads} T={rows} {dtype}"
+    gu.check_rotated(gu.run_transform(x, th, n, heads, dtype), ref, dtype, tag + " fwd")
+    gu.check_rotated(gu.run_transform(x, th, n, heads, dtype, inverse=True), oracle.inverse(x64, th, n, heads), dtype, tag + " inv")
+    codes, scales = gu.run_fwd_quant(x, th, n, heads, dtype, bits, group, sd)
+    gu.check_fused_codes(codes, scales, ref, bits, group, sd, dtype, tag)
+    c = oracle.unpack_codes(codes, bits)
+    want = synth.cast_storage(oracle.dequantize(c, scales.astype(np.float32), group).astype(np.float64), dtype)
+    u = np.uint16 if dtype != "f32" else np.uint32
+    for want_y, want_hist in ((True, True), (True, False), (False, True)):
+        yq, hist = gu.run_fwd_fakequant(x, th, n, heads, dtype, bits, group, sd, want_y=want_y, want_hist=want_hist)
+        if want_y:
+            np.testing.assert_array_equal(yq.view(u), want.view(u), err_msg=tag)
+        if want_hist:
+            np.testing.assert_array_equal(hist, oracle.bin_histogram(c, bits), err_msg=tag)
