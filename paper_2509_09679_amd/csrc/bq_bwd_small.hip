@@ -1,9 +1,8 @@
-// Backward pass for small transforms, n = 8 .. 128 (k = 3 .. 7), for the row widths the small forward kernels
-// take: dx = B^T dy and dtheta (paper, "Gradient Flow Through Butterfly Layers").
+// Backward pass for small transforms, n = 8 .. 128 (k = 3 .. 7), for any number of heads: dx = B^T dy and dtheta (paper, "Gradient Flow Through Butterfly Layers").
 //
 // Geometry of the small forward kernels (bq_small.hip): a transform occupies n/8 consecutive lanes, 8
-// consecutive elements per lane, no LDS and no barrier; a workgroup of 256 threads covers 2048 consecutive
-// elements (a slice of a wide row or several narrow rows) and loops over the batch.  Per row a thread
+// consecutive elements per lane, no LDS and no barrier; a workgroup of up to 256 threads covers up to 2048 consecutive
+// elements (a slice of a wide row or several narrow rows, small_tiling) and loops over the batch.  Per row a thread
 // recomputes the forward state of its 8 elements (layers 1..k), then runs the transposed cascade on the
 // state and the gradient together with the deferred sums of bq_bwd_blocks.h.  Everything a thread needs
 // for that (both directions' coefficients, 44 sums) stays in registers: about 230 of them, so two waves
@@ -23,6 +22,10 @@ namespace bq {
 constexpr int kSbThreads = 256;
 constexpr int kSbMaxSlots = 4096;  // (8192 measured no faster for narrow rows and slower where the reduction grows)
 
+// With no more slices than this a launch has at most 2048 waves, so the slots hold at most 2048 x 512 elements' angles
+// (14 MiB at n = 128): below the 32 MiB of the entry point that brings its own workspace.
+constexpr int kSbMaxSlices = 512;
+
 struct SmallBwdArgs {
     const void *x, *dy;
     void *dx;
@@ -31,10 +34,7 @@ struct SmallBwdArgs {
     PlanRef plan;
     int64_t rows, ld_in, ld_out;
     int heads, width;    // width = heads * n
-    int span;            // elements covered by a workgroup: 2048, or the largest power of two below it that
-                         // divides a wider row (the workgroup then has span / 8 threads)
-    int rows_per_block;  // span / width if width < span, else 1
-    int slices;          // width / span if width >= span, else 1
+    int span, rows_per_block, slices;  // SmallTiling
     int64_t n_groups;    // row groups = ceil(rows / rows_per_block)
     int64_t n_angles;    // heads * k * n / 2
 };
@@ -47,8 +47,8 @@ __global__ __launch_bounds__(kSbThreads) void small_bwd_kernel(SmallBwdArgs A)
     const int tid = threadIdx.x;
     const int chunk = (tid & ~15) | lane_chunk(tid & 15);  // chunk of 8 elements inside the workgroup's span
     const int e0 = chunk * 8;
-    int row_in_block, col;
-    int64_t grp_first, grp_step, slot;
+    int col;
+    int64_t row_in_block, grp_first, grp_step, slot;
     if (A.slices > 1) {
         row_in_block = 0;
         col = (int)(blockIdx.x % A.slices) * A.span + e0;
@@ -57,10 +57,15 @@ __global__ __launch_bounds__(kSbThreads) void small_bwd_kernel(SmallBwdArgs A)
         slot = grp_first;
     } else {
         row_in_block = e0 / A.width;
-        col = e0 - row_in_block * A.width;
+        col = e0 - (int)row_in_block * A.width;
         grp_first = blockIdx.x;
         grp_step = gridDim.x;
         slot = (int64_t)blockIdx.x * A.rows_per_block + row_in_block;
+    }
+    const bool idle = e0 >= A.span || col >= A.width;  // no row of the batch and no slot is this lane's own
+    if (idle) {
+        row_in_block = (int64_t)1 << 60;
+        col = 0;
     }
     const int head = col >> K;
     const int idx = col & (n - 1);
@@ -121,6 +126,7 @@ __global__ __launch_bounds__(kSbThreads) void small_bwd_kernel(SmallBwdArgs A)
         }
     }
     // deferred sums -> this slot's entries (workgroups without rows write zeros)
+    if (idle) return;  // (whole transforms are idle, so no partner is missing below)
     float *part = A.partial + slot * A.n_angles + (size_t)head * K * (n / 2);
     const float *fw_head = A.fw_inv + (size_t)head * K * n;
 #pragma unroll
@@ -179,7 +185,7 @@ __global__ __launch_bounds__(256) void small_bwd_reduce_kernel(const float *__re
 
 // ---- host side -----------------------------------------------------------------------------------
 struct SmallBwdGrid {
-    int span, rows_per_block, slices;
+    SmallTiling t;
     int64_t n_groups, slots;
     unsigned grid;
 };
@@ -187,27 +193,23 @@ struct SmallBwdGrid {
 static SmallBwdGrid small_bwd_grid(const Shape &s)
 {
     SmallBwdGrid g;
-    const int64_t width = (int64_t)s.n * s.heads;
-    g.span = small_span(width);
-    g.rows_per_block = width < g.span ? (int)(g.span / width) : 1;
-    g.slices = width >= g.span ? (int)(width / g.span) : 1;
-    g.n_groups = (s.rows + g.rows_per_block - 1) / g.rows_per_block;
+    g.t = small_tiling(s.n, s.heads, true);
+    g.n_groups = (s.rows + g.t.rows_per_block - 1) / g.t.rows_per_block;
     // 2048 waves, eight per compute unit (all that fit with these kernels' registers), whatever the workgroup width;
     // the slot count (partial sums to write and to add) stays bounded
-    const int64_t wgs = 2048 / (g.span / 512);
-    int64_t per_slice = wgs / g.slices > 0 ? wgs / g.slices : 1;
-    if (per_slice * g.rows_per_block > kSbMaxSlots) per_slice = kSbMaxSlots / g.rows_per_block;
+    const int64_t wgs = 2048 / (g.t.threads / 64);
+    int64_t per_slice = wgs / g.t.slices > 0 ? wgs / g.t.slices : 1;
+    if (per_slice * g.t.rows_per_block > kSbMaxSlots) per_slice = kSbMaxSlots / g.t.rows_per_block;
     if (per_slice > g.n_groups) per_slice = g.n_groups;
-    g.grid = (unsigned)(per_slice * g.slices);
-    g.slots = per_slice * g.rows_per_block;
+    g.grid = (unsigned)(per_slice * g.t.slices);
+    g.slots = per_slice * g.t.rows_per_block;
     return g;
 }
 
 bool small_bwd_supported(const void *x, const void *dy, const void *dx, const float *dtheta, const Shape &s)
 {
     if (s.k < 3 || s.k > 7 || dtheta == nullptr || s.rows == 0) return false;
-    const int64_t width = (int64_t)s.n * s.heads;
-    if (small_span(width) == 0 || width / small_span(width) > 512) return false;
+    if (small_tiling(s.n, s.heads, true).slices > kSbMaxSlices) return false;
     const int vec = s.dtype == BQ_F32 ? 4 : 8;
     if (((uintptr_t)x & 15) || ((uintptr_t)dy & 15) || (dx && ((uintptr_t)dx & 15))) return false;
     if ((s.ld_x % vec) || (s.ld_y % vec)) return false;
@@ -216,29 +218,29 @@ bool small_bwd_supported(const void *x, const void *dy, const void *dx, const fl
 
 size_t small_bwd_workspace_bytes(const Shape &s)
 {
-    if (small_span((int64_t)s.n * s.heads) == 0) return 0;  // not a shape of these kernels
     const SmallBwdGrid g = small_bwd_grid(s);
+    if (g.t.slices > kSbMaxSlices) return 0;  // not a shape of these kernels
     return align256((size_t)g.slots * s.heads * s.k * (s.n / 2) * sizeof(float));
 }
 
 template <typename T, int K>
-static void launch_small_bwd_k(const SmallBwdArgs &A, unsigned grid, hipStream_t stream)
+static void launch_small_bwd_k(const SmallBwdArgs &A, const SmallBwdGrid &g, hipStream_t stream)
 {
     if (A.dx)
-        hipLaunchKernelGGL((small_bwd_kernel<T, K, true>), dim3(grid), dim3(A.span / 8), 0, stream, A);
+        hipLaunchKernelGGL((small_bwd_kernel<T, K, true>), dim3(g.grid), dim3(g.t.threads), 0, stream, A);
     else
-        hipLaunchKernelGGL((small_bwd_kernel<T, K, false>), dim3(grid), dim3(A.span / 8), 0, stream, A);
+        hipLaunchKernelGGL((small_bwd_kernel<T, K, false>), dim3(g.grid), dim3(g.t.threads), 0, stream, A);
 }
 
 template <typename T>
-static void launch_small_bwd_t(const SmallBwdArgs &A, int k, unsigned grid, hipStream_t stream)
+static void launch_small_bwd_t(const SmallBwdArgs &A, int k, const SmallBwdGrid &g, hipStream_t stream)
 {
     switch (k) {
-        case 3: return launch_small_bwd_k<T, 3>(A, grid, stream);
-        case 4: return launch_small_bwd_k<T, 4>(A, grid, stream);
-        case 5: return launch_small_bwd_k<T, 5>(A, grid, stream);
-        case 6: return launch_small_bwd_k<T, 6>(A, grid, stream);
-        default: return launch_small_bwd_k<T, 7>(A, grid, stream);
+        case 3: return launch_small_bwd_k<T, 3>(A, g, stream);
+        case 4: return launch_small_bwd_k<T, 4>(A, g, stream);
+        case 5: return launch_small_bwd_k<T, 5>(A, g, stream);
+        case 6: return launch_small_bwd_k<T, 6>(A, g, stream);
+        default: return launch_small_bwd_k<T, 7>(A, g, stream);
     }
 }
 
@@ -262,15 +264,15 @@ hipError_t launch_small_bwd(const void *x, const void *dy, const PlanView &pv, v
     A.ld_out = s.ld_y;
     A.heads = s.heads;
     A.width = s.n * s.heads;
-    A.span = g.span;
-    A.rows_per_block = g.rows_per_block;
-    A.slices = g.slices;
+    A.span = g.t.span;
+    A.rows_per_block = g.t.rows_per_block;
+    A.slices = g.t.slices;
     A.n_groups = g.n_groups;
     A.n_angles = (int64_t)s.heads * s.k * (s.n / 2);
     switch (s.dtype) {
-        case BQ_F32: launch_small_bwd_t<float>(A, s.k, g.grid, stream); break;
-        case BQ_F16: launch_small_bwd_t<__half>(A, s.k, g.grid, stream); break;
-        default: launch_small_bwd_t<bf16_t>(A, s.k, g.grid, stream); break;
+        case BQ_F32: launch_small_bwd_t<float>(A, s.k, g, stream); break;
+        case BQ_F16: launch_small_bwd_t<__half>(A, s.k, g, stream); break;
+        default: launch_small_bwd_t<bf16_t>(A, s.k, g, stream); break;
     }
     const unsigned blocks = (unsigned)((A.n_angles + 31) / 32);
     hipLaunchKernelGGL(small_bwd_reduce_kernel, dim3(blocks), dim3(256), 0, stream, (const float *)ws, dtheta, A.n_angles,

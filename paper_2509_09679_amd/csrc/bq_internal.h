@@ -169,7 +169,15 @@ size_t bwd_workspace_bytes_generic(const Shape &s);
 hipError_t launch_generic_bwd(const void *x, const void *dy, const PlanView &pv, void *dx, float *dtheta,
                               void *ws, const Shape &s, hipStream_t stream, bool only_if_bad = false);
 
-int small_span(int64_t width);  // bq_small.hip: elements per workgroup of the small-transform kernels, 0 = unsupported
+// How the kernels for n = 8 .. 128 cover a batch (bq_small.hip: small_tiling).  Lanes of a workgroup beyond `span` elements,
+// or beyond the last head of a row, are idle: they load a clamped row and store nothing.
+struct SmallTiling {
+    int threads;         // of a workgroup, whole waves
+    int span;            // elements a workgroup covers, at most threads * 8
+    int rows_per_block;  // whole rows of a workgroup, 1 if slices > 1
+    int slices;          // workgroups that share a row
+};
+SmallTiling small_tiling(int n, int heads, bool backward);
 // backward for n = 8 .. 128 (bq_bwd_small.hip)
 bool small_bwd_supported(const void *x, const void *dy, const void *dx, const float *dtheta, const Shape &s);
 size_t small_bwd_workspace_bytes(const Shape &s);

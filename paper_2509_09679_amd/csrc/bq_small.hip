@@ -1,14 +1,12 @@
 // Specialised kernels for small transforms, n = 8 .. 128 (k = 3 .. 7): forward, inverse and fused forward +
-// quantisation, for any number of heads whose row width divides 2048 or is a multiple of 512 (rows that are
-// not a multiple of 2048 elements wide are covered by narrower workgroups: 1024 or 512 elements, 128 or 64
-// threads).
+// quantisation, for any number of heads.
 //
 // A transform of n elements occupies n/8 consecutive lanes (at most one 16-lane row), 8 consecutive
 // elements per lane, and never touches LDS: layers 1-3 pair registers, layers 4..k pair lanes through
 // DPP (bq_cascade.h).  All k*8 scale-deferred coefficients and the 8 output scales of a thread stay
-// in registers; a workgroup of 256 threads covers 2048 consecutive elements — a slice of a wide row
-// (e.g. 32 heads x 128) or several narrow rows (e.g. 16 rows of 128) — and loops over the batch with
-// the same coefficients.  Two independent row groups are processed per iteration and the next two are
+// in registers; a workgroup of up to 256 threads covers up to 2048 consecutive elements: a slice of a wide row
+// (e.g. 32 heads x 128) or several narrow rows (e.g. 16 rows of 128, 2 rows of 12 x 64), see small_tiling, and loops
+// over the batch with the same coefficients.  Two independent row groups are processed per iteration and the next two are
 // prefetched meanwhile, so that four 16-byte loads per lane are in flight.
 //
 // If the plan flags the scale-deferred tables as unusable, rows go through plain (cos, sin) rotations
@@ -18,7 +16,6 @@
 namespace bq {
 
 constexpr int kSmallThreads = 256;
-constexpr int kSmallSpan = kSmallThreads * 8;  // elements covered by a workgroup
 
 struct SmallArgs {
     const void *in;
@@ -28,10 +25,7 @@ struct SmallArgs {
     PlanRef plan;
     int64_t rows, ld_in, ld_out;
     int heads, width;    // width = heads * n
-    int span;            // elements covered by a workgroup: kSmallSpan, or the largest power of two below it that
-                         // divides a wider row (the workgroup then has span / 8 threads)
-    int rows_per_block;  // span / width if width < span, else 1
-    int slices;          // width / span if width >= span, else 1
+    int span, rows_per_block, slices;  // SmallTiling
     int64_t n_groups;    // row groups = ceil(rows / rows_per_block)
     uint8_t *codes;
     void *scales;
@@ -39,7 +33,80 @@ struct SmallArgs {
     int group, scale_f16;
 };
 
-template <typename T, int K, int kMode, int kBits>
+// The forward cascade in plain (cos, sin) rotations held in registers, rounded as the kernel for any n rounds them:
+//   y_a = fma(c, x_a, -(s x_b)),  y_b = fma(s, x_a, c x_b)
+// i.e. fma(w1, x_a, w2 x_b) in either lane of a pair, with the lane's own (w1, w2).
+template <int K>
+struct PlainCascade {
+    float rc[3][4], rs[3][4];        // layers 1..3: (cos, sin) of the thread's four pairs
+    float w1[4][8], w2[4][8];        // layers 4..K
+    bool upper[4];                   // this lane holds the upper elements of the layer's pairs
+    __device__ __forceinline__ void load(const float2 *cs_head, int idx)
+    {
+        constexpr int half = 1 << (K - 1);
+        auto entry = [&](int e, int i) {  // of the pair that element e belongs to in layer i
+            const int h = 1 << (i - 1);
+            return cs_head[(size_t)(i - 1) * half + (((e >> i) << (i - 1)) | (e & (h - 1)))];
+        };
+#pragma unroll
+        for (int j = 0; j < 3; ++j) {
+            int q = 0;
+#pragma unroll
+            for (int r = 0; r < 8; ++r)
+                if (!(r & (1 << j))) {
+                    const float2 w = entry(idx + r, j + 1);
+                    rc[j][q] = w.x;
+                    rs[j][q] = w.y;
+                    ++q;
+                }
+        }
+#pragma unroll
+        for (int j = 0; j < K - 3; ++j) {
+            upper[j] = ((idx >> (3 + j)) & 1) != 0;
+#pragma unroll
+            for (int r = 0; r < 8; ++r) {
+                const float2 w = entry(idx + r, 4 + j);
+                w1[j][r] = upper[j] ? w.y : w.x;
+                w2[j][r] = upper[j] ? w.x : -w.y;
+            }
+        }
+    }
+    template <int J>
+    __device__ __forceinline__ void pairs(float (&u)[8]) const
+    {
+        int q = 0;
+#pragma unroll
+        for (int r = 0; r < 8; ++r)
+            if (!(r & (1 << J))) {
+                const float xa = u[r], xb = u[r | (1 << J)];
+                u[r] = __builtin_fmaf(rc[J][q], xa, -(rs[J][q] * xb));
+                u[r | (1 << J)] = __builtin_fmaf(rs[J][q], xa, rc[J][q] * xb);
+                ++q;
+            }
+    }
+    template <int J, int CTRL>
+    __device__ __forceinline__ void lanes(float (&u)[8]) const
+    {
+#pragma unroll
+        for (int r = 0; r < 8; ++r) {
+            const float p = dpp_read<CTRL>(u[r]);
+            const float xa = upper[J] ? p : u[r], xb = upper[J] ? u[r] : p;
+            u[r] = __builtin_fmaf(w1[J][r], xa, w2[J][r] * xb);
+        }
+    }
+    __device__ __forceinline__ void run(float (&u)[8]) const
+    {
+        pairs<0>(u);
+        pairs<1>(u);
+        pairs<2>(u);
+        if (K >= 4) lanes<0, 0xB1>(u);   // quad_perm [1,0,3,2]
+        if (K >= 5) lanes<1, 0x4E>(u);   // quad_perm [2,3,0,1]
+        if (K >= 6) lanes<2, 0x141>(u);  // row_half_mirror
+        if (K >= 7) lanes<3, 0x128>(u);  // row_ror:8
+    }
+};
+
+template <typename T, int K, int kMode, int kBits, bool kPlain = false>
 __global__ __launch_bounds__(kSmallThreads) void small_kernel(SmallArgs A)
 {
     constexpr int n = 1 << K;
@@ -63,8 +130,8 @@ __global__ __launch_bounds__(kSmallThreads) void small_kernel(SmallArgs A)
     };
     const int chunk = (tid & ~15) | lane_chunk(tid & 15);  // chunk of 8 elements inside the workgroup's span
     const int e0 = chunk * 8;
-    int row_in_block, col;
-    int64_t grp_first, grp_step;
+    int col;
+    int64_t row_in_block, grp_first, grp_step;
     if (A.slices > 1) {
         row_in_block = 0;
         col = (int)(blockIdx.x % A.slices) * A.span + e0;
@@ -72,9 +139,13 @@ __global__ __launch_bounds__(kSmallThreads) void small_kernel(SmallArgs A)
         grp_step = gridDim.x / A.slices;
     } else {
         row_in_block = e0 / A.width;
-        col = e0 - row_in_block * A.width;
+        col = e0 - (int)row_in_block * A.width;
         grp_first = blockIdx.x;
         grp_step = gridDim.x;
+    }
+    if (e0 >= A.span || col >= A.width) {  // idle lane (whole transforms are): no row of the batch is its own
+        row_in_block = (int64_t)1 << 60;
+        col = 0;
     }
     const int head = col >> K;
     const int idx = col & (n - 1);
@@ -139,6 +210,22 @@ __global__ __launch_bounds__(kSmallThreads) void small_kernel(SmallArgs A)
     };
 
     if (grp_first >= A.n_groups) return;
+    if constexpr (kPlain) {
+        PlainCascade<K> pc;
+        pc.load(cs_head, idx);
+        Raw8 raw0 = load_row(grp_first);
+        Raw8 raw1 = load_row(grp_first + grp_step);
+        for (int64_t g = grp_first; g < A.n_groups; g += grp_step) {
+            float u[8];
+            unpack8(raw0, u, (const T *)nullptr);
+            raw0 = raw1;
+            raw1 = load_row(g + 2 * grp_step);
+            pc.run(u);
+            finish(u, g);
+        }
+        flush_bins();
+        return;
+    }
     if (!fast) {  // rare
         for (int64_t g = grp_first; g < A.n_groups; g += grp_step) {
             float u[8];
@@ -176,41 +263,73 @@ __global__ __launch_bounds__(kSmallThreads) void small_kernel(SmallArgs A)
 }
 
 template <typename T, int K>
-static void (*pick_small(Mode mode, int bits))(SmallArgs)
+static void (*pick_small(Mode mode, int bits, bool plain))(SmallArgs)
 {
     if (mode == kFwd) return small_kernel<T, K, kFwd, 4>;
     if (mode == kInv) return small_kernel<T, K, kInv, 4>;
+    if (plain) {
+        if (mode == kFwdFake) return bits == 2 ? small_kernel<T, K, kFwdFake, 2, true> : small_kernel<T, K, kFwdFake, 4, true>;
+        return bits == 2 ? small_kernel<T, K, kFwdQuant, 2, true> : small_kernel<T, K, kFwdQuant, 4, true>;
+    }
     if (mode == kFwdFake) return bits == 2 ? small_kernel<T, K, kFwdFake, 2> : small_kernel<T, K, kFwdFake, 4>;
     return bits == 2 ? small_kernel<T, K, kFwdQuant, 2> : small_kernel<T, K, kFwdQuant, 4>;
 }
 
 template <typename T>
-static void (*pick_small_k(int k, Mode mode, int bits))(SmallArgs)
+static void (*pick_small_k(int k, Mode mode, int bits, bool plain))(SmallArgs)
 {
     switch (k) {
-        case 3: return pick_small<T, 3>(mode, bits);
-        case 4: return pick_small<T, 4>(mode, bits);
-        case 5: return pick_small<T, 5>(mode, bits);
-        case 6: return pick_small<T, 6>(mode, bits);
-        default: return pick_small<T, 7>(mode, bits);
+        case 3: return pick_small<T, 3>(mode, bits, plain);
+        case 4: return pick_small<T, 4>(mode, bits, plain);
+        case 5: return pick_small<T, 5>(mode, bits, plain);
+        case 6: return pick_small<T, 6>(mode, bits, plain);
+        default: return pick_small<T, 7>(mode, bits, plain);
     }
 }
 
-// Elements per workgroup for rows of `width` elements: 2048 where rows tile it or it tiles rows, else the
-// largest power of two that divides the row, down to one wave (512); 0 if there is none.
-int small_span(int64_t width)
+// Workgroups of one to four waves.  Rows of up to 2048 elements: as many whole rows as fit; wider rows: slices of whole
+// heads.  The number of waves is the one that leaves the fewest lanes idle (none for widths that divide 2048, for multiples
+// of 512, and for 2 rows of 768 or 16 rows of 96 elements; 6 % for 3 rows of 640), the larger at equal shares.  Widths with
+// idle lanes went to the LDS kernel for any n before: 20011 fp16 rows of 12 x 64, forward, 81 -> 13 us, and
+// 574 -> 75 us backward.  The backward kernel holds eight waves per compute unit, of which three-wave workgroups fill six:
+// they count as four there (10000 rows of 12 x 128: 80 us in three-wave workgroups, 62 us in single-wave ones).
+SmallTiling small_tiling(int n, int heads, bool backward)
 {
-    if (width < kSmallSpan && kSmallSpan % width == 0) return kSmallSpan;  // several whole rows per workgroup
-    const int64_t low = width & -width;
-    const int span = (int)(low < kSmallSpan ? low : kSmallSpan);
-    return span >= 512 ? span : 0;
+    const int64_t width = (int64_t)n * heads;
+    SmallTiling best{};
+    int64_t best_lanes = 0, best_used = 0;  // lanes spent on so many elements
+    for (int waves = 4; waves >= 1; --waves) {
+        SmallTiling t{};
+        t.threads = waves * 64;
+        const int room = t.threads * 8;
+        const int cost = backward && waves == 3 ? 256 : t.threads;
+        int64_t used, lanes;
+        if (width <= room) {
+            t.rows_per_block = (int)(room / width);
+            t.slices = 1;
+            t.span = (int)(t.rows_per_block * width);
+            used = t.span;
+            lanes = cost;
+        } else {
+            const int most = room / n;  // heads per slice
+            t.rows_per_block = 1;
+            t.slices = (heads + most - 1) / most;
+            t.span = (heads + t.slices - 1) / t.slices * n;
+            used = width;
+            lanes = (int64_t)t.slices * cost;
+        }
+        if (best_lanes == 0 || used * best_lanes > best_used * lanes) {
+            best = t;
+            best_lanes = lanes;
+            best_used = used;
+        }
+    }
+    return best;
 }
 
 bool small_supported(Mode mode, const void *in, const void *out, const Shape &s, const QuantArgs *q)
 {
     if (s.k < 3 || s.k > 7) return false;
-    const int64_t width = (int64_t)s.n * s.heads;
-    if (small_span(width) == 0) return false;
     const int isz = s.dtype == BQ_F32 ? 4 : 2;
     const int vec = 16 / isz;
     if (((uintptr_t)in & 15) || (s.ld_x % vec)) return false;
@@ -237,12 +356,14 @@ hipError_t launch_small(Mode mode, const void *in, void *out, const PlanView &pv
     A.ld_out = s.ld_y;
     A.heads = s.heads;
     A.width = s.n * s.heads;
-    A.span = small_span(A.width);
+    SmallTiling t = small_tiling(s.n, s.heads, false);
     // the plain transforms of 16-bit rows stream fastest from single-wave workgroups (measured: up to 20 % over
     // four-wave ones at the same number of waves; float32 rows and the quantisers prefer the wider ones)
-    if ((mode == kFwd || mode == kInv) && s.dtype != BQ_F32 && (A.width % 512 == 0 || 512 % A.width == 0)) A.span = 512;
-    A.rows_per_block = A.width < A.span ? A.span / A.width : 1;
-    A.slices = A.width >= A.span ? A.width / A.span : 1;
+    if ((mode == kFwd || mode == kInv) && s.dtype != BQ_F32 && (A.width % 512 == 0 || 512 % A.width == 0))
+        t = SmallTiling{64, 512, A.width < 512 ? 512 / A.width : 1, A.width < 512 ? 1 : A.width / 512};
+    A.span = t.span;
+    A.rows_per_block = t.rows_per_block;
+    A.slices = t.slices;
     A.n_groups = (s.rows + A.rows_per_block - 1) / A.rows_per_block;
     int bits = 4;
     if (q) {
@@ -258,14 +379,19 @@ hipError_t launch_small(Mode mode, const void *in, void *out, const PlanView &pv
     // compute unit: 5.5 TB/s against 4.4 TB/s with four times as many), the 16-bit quantisers, which need the
     // occupancy to hide their arithmetic, with 8192.
     const bool few = mode == kFwd || mode == kInv || s.dtype == BQ_F32;
-    const int64_t wgs = (few ? 2048 : 8192) / (A.span / 512);
+    const int64_t wgs = (few ? 2048 : 8192) / (t.threads / 64);
     int64_t per_slice = wgs / A.slices > 0 ? wgs / A.slices : 1;
     if (per_slice > A.n_groups) per_slice = A.n_groups;
     const unsigned grid = (unsigned)(per_slice * A.slices);
-    void (*kern)(SmallArgs) = s.dtype == BQ_F32   ? pick_small_k<float>(s.k, mode, bits)
-                              : s.dtype == BQ_F16 ? pick_small_k<__half>(s.k, mode, bits)
-                                                  : pick_small_k<bf16_t>(s.k, mode, bits);
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(A.span / 8), 0, stream, A);
+    // The quantisers of widths that went to the LDS kernel before (all but divisors of 2048 and multiples of 512) keep its plain
+    // rotations, bit for bit: the deferred form's last bit would move a few codes in 10^6 across a rounding boundary, each of
+    // them by a whole step.  20011 fp16 rows of 12 x 64, INT4: 96 us there, 24 us here (14.5 in the
+    // deferred form: the plain one takes two operations per element and layer, five where a pair sits in two lanes).
+    const bool plain = 2048 % A.width != 0 && A.width % 512 != 0;
+    void (*kern)(SmallArgs) = s.dtype == BQ_F32   ? pick_small_k<float>(s.k, mode, bits, plain)
+                              : s.dtype == BQ_F16 ? pick_small_k<__half>(s.k, mode, bits, plain)
+                                                  : pick_small_k<bf16_t>(s.k, mode, bits, plain);
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(t.threads), 0, stream, A);
     return hipGetLastError();
 }
 

@@ -50,3 +50,34 @@ def test_few_rows_through_every_transform_kernel(n, heads, rows, dtype, bits, gr
             np.testing.assert_array_equal(yq.view(u), want.view(u), err_msg=tag)
         if want_hist:
             np.testing.assert_array_equal(hist, oracle.bin_histogram(c, bits), err_msg=tag)
+
+
+@pytest.mark.parametrize("n,heads,rows", [(64, 12, 5), (32, 3, 33), (128, 5, 7), (128, 33, 3), (8, 3, 200), (8, 257, 2), (16, 127, 3),
+                                          (128, 9, 4), (128, 65, 1), (64, 1, 1), (8, 67, 40)])
+@pytest.mark.parametrize("dtype", ["f16", "f32"])
+def test_small_transforms_of_any_row_width(n, heads, rows, dtype):
+    # small_tiling: idle lanes behind the last whole row of a workgroup, slices whose last one is short, one to four waves;
+    # strided rows and every mode through the same tiling
+    x, th, dy = synth.small_case(n, rows, dtype, heads=heads, seed=500 + n * heads + rows, with_dy=True, outliers=0)
+    x64, dy64 = synth.to_f64(x, dtype), synth.to_f64(dy, dtype)
+    ref = oracle.forward(x64, th, n, heads)
+    tag = f"n={n} H={heads} T={rows} {dtype}"
+    for pad in (0, 8):
+        gu.check_rotated(gu.run_transform(x, th, n, heads, dtype, pad=pad), ref, dtype, tag + " fwd")
+        gu.check_rotated(gu.run_transform(x, th, n, heads, dtype, inverse=True, pad=pad), oracle.inverse(x64, th, n, heads), dtype,
+                         tag + " inv")
+    for bits, group, sd in ((4, n, "f16"), (2, 8, "f32")):
+        codes, scales = gu.run_fwd_quant(x, th, n, heads, dtype, bits, group, sd)
+        gu.check_fused_codes(codes, scales, ref, bits, group, sd, dtype, tag)
+        c = oracle.unpack_codes(codes, bits)
+        want = synth.cast_storage(oracle.dequantize(c, scales.astype(np.float32), group).astype(np.float64), dtype)
+        yq, hist = gu.run_fwd_fakequant(x, th, n, heads, dtype, bits, group, sd)
+        u = np.uint16 if dtype != "f32" else np.uint32
+        np.testing.assert_array_equal(yq.view(u), want.view(u), err_msg=tag)
+        np.testing.assert_array_equal(hist, oracle.bin_histogram(c, bits), err_msg=tag)
+    rdx, rdth, ab = oracle.backward(x64, dy64, th, n, heads)
+    floor = np.median(ab, axis=2, keepdims=True)  # (few rows: as in the seeded sweep)
+    for pad in (0, 8):
+        dx, dth = gu.run_bwd(x, dy, th, n, heads, dtype, pad=pad)
+        gu.check_rotated(dx, rdx, dtype, tag + " dx")
+        gu.check_dtheta(dth, rdth, np.maximum(ab, floor), what=tag + " dtheta")
