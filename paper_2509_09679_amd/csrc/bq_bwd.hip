@@ -389,34 +389,58 @@ struct FinArgs {
     __device__ __forceinline__ float *at(int a, int i) const { return part + (size_t)(i - 1) * pairs + pair_index(c0 + a, i); }
 };
 
-// lane layer i whose pairs sit in lanes `mask_j` apart (0..3: masks 1, 2, 7, 8); e[r]: the thread's elements
-template <class Idx>
-__device__ __forceinline__ void finalize_lane_layer(const FinArgs &F, const float (&acc)[8], int i, int mask_j, Idx elem)
-{
-    if (i > F.n_log) return;  // a layer the transform does not have: no table row, nothing to write
+// Prologue and epilogue go through LDS because layout Q has neighbouring lanes 128 elements apart: read or written from
+// there directly, every instruction touches one cache line per lane.  At 2048 fp16 rows of n = 4096 (8 rows per workgroup)
+// the pass took 58 us with 48 such table loads, 88 loads of the sums' scales and 44 stores per thread of group Q; in natural
+// order, with 16-byte table loads and one trip each through the row buffers, it takes 36 us.
+//
+// Tables of layers 7..12 (kHalf: 13 as well) in natural order: thread t of 1024 holds elements 4 t .. 4 t + 3 of each.
+template <int kTables>
+struct TableStage {
+    float4 v[kTables];
+    template <class P>
+    __device__ __forceinline__ void load(const float *fg, const P &pt, int n_log)
+    {
+        const int e = threadIdx.x * 4;
 #pragma unroll
-    for (int r = 0; r < 8; ++r) {
-        const float mine = acc[r];
-        const float other = lane_partner(mine, mask_j);
-        const int e = elem(r);
-        if (!(e & (1 << (i - 1)))) {  // the lane holding the lower element writes
-            const int b = e | (1 << (i - 1));
-            put_partial(F.at(e, i), (mine - other) * F.scale(e, b, i), F.first);
+        for (int j = 0; j < kTables; ++j)  // layers above log2 n do not exist: weight zero leaves the element as it is
+            v[j] = 7 + j <= n_log ? *(const float4 *)(fg + pt.trow(e, 6 + j) + pt.col(e)) : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    }
+    __device__ __forceinline__ void put(float *lds) const  // table j -> row buffer j
+    {
+        const int at = lds_addr2(threadIdx.x * 4);
+#pragma unroll
+        for (int j = 0; j < kTables; ++j) {
+            float2 *d = (float2 *)&lds[j * G::kRowFloats + at];
+            d[0] = make_float2(v[j].x, v[j].y);
+            d[1] = make_float2(v[j].z, v[j].w);
         }
     }
-}
-// register layer i pairing register bit J
-template <int J, class Idx>
-__device__ __forceinline__ void finalize_reg_layer(const FinArgs &F, const float (&acc)[4], int i, Idx elem)
+};
+// the sums of a register layer (pairs of register bit J), each at its lower element
+template <int J>
+__device__ __forceinline__ void spread_pairs(const float (&acc)[4], float (&o)[8])
 {
-    if (i > F.n_log) return;
     int q = 0;
 #pragma unroll
-    for (int r = 0; r < 8; ++r) {
-        if (!(r & (1 << J))) {
-            const int a = elem(r), b = elem(r | (1 << J));
-            put_partial(F.at(a, i), acc[q] * F.scale(a, b, i), F.first);
-            ++q;
+    for (int r = 0; r < 8; ++r) o[r] = (r & (1 << J)) ? 0.0f : acc[q++];
+}
+// Row buffer j holds the sums of layer kFirst + j by element; all 1024 threads scale and store them in pair order.
+template <int kFirst>
+__device__ __forceinline__ void write_partials(const FinArgs &F, const float *lds)
+{
+#pragma unroll
+    for (int j = 0; j < 6; ++j) {
+        const int i = kFirst + j;
+        if (i > F.n_log) continue;  // a layer the transform does not have: no table row, nothing to write
+        const float *buf = lds + j * G::kRowFloats;
+#pragma unroll
+        for (int m = 0; m < 2; ++m) {
+            const int p = (int)threadIdx.x + 1024 * m;
+            const int a = ((p >> (i - 1)) << i) | (p & ((1 << (i - 1)) - 1)), b = a | (1 << (i - 1));
+            float v = buf[lds_addr2(a)];
+            if (i >= 4 && i <= 10) v -= buf[lds_addr2(b)];  // lane layers: each lane kept its own element's products
+            put_partial(F.at(a, i), v * F.scale(a, b, i), F.first);
         }
     }
 }
@@ -494,6 +518,8 @@ struct FusedLds {
     static_assert(kRingBytes <= 65536, "ring addresses must fit 16 bits");
     static constexpr size_t kBytes = kRingBytes + (3 * (size_t)G::kRowFloats + kTabFloats) * sizeof(float);
     static_assert(kBytes <= 160 * 1024, "LDS of a compute unit");
+    static constexpr int kTables = kHalf ? 7 : 6;  // staged by prologue and epilogue in row buffers from the start of LDS
+    static_assert(kTables * G::kRowFloats * sizeof(float) <= kBytes, "the staged tables fit");
 };
 
 template <typename T, bool kDx, bool kHalf, bool kVirt>
@@ -522,20 +548,22 @@ __global__ __launch_bounds__(kFusedThreads) void bwd_fused_kernel(BwdFastArgs A)
     F.n_log = pt.n_log;
     F.rmask = kVirt ? pt.rmask : 0;
     F.first = A.first_chunk;
+    TableStage<L::kTables> st;
+    st.load(fg, pt, kVirt ? pt.n_log : K + 1);
     if (role == 0) {
         // ---- group N ----
         const int idx_n = (wave * 64 + lane_chunk(lane)) * 8;
         const int an = lds_addr2(idx_n);
         float cn[6][8];
 #pragma unroll
-        for (int j = 0; j < 6; ++j)
-#pragma unroll
-            for (int r = 0; r < 8; ++r) cn[j][r] = fg[pt.trow(idx_n, j) + pt.col(idx_n) + r];
-        {
-            const float *e0 = A.fd_inv + (size_t)pt.head(idx_n) * ts + pt.col(idx_n);
-            tab[tid] = *(const float4 *)e0;
-            tab[512 + tid] = *(const float4 *)(e0 + 4);
-        }
+        for (int j = 0; j < 6; ++j) load_coef8(fg + pt.trow(idx_n, j) + pt.col(idx_n), cn[j]);
+        const float *e0_row = A.fd_inv + (size_t)pt.head(idx_n) * ts + pt.col(idx_n);
+        const float4 e0_lo = *(const float4 *)e0_row, e0_hi = *(const float4 *)(e0_row + 4);
+        st.put(lds);
+        wg_barrier();  // tables staged
+        wg_barrier();  // ... and read by group Q
+        tab[tid] = e0_lo;
+        tab[512 + tid] = e0_hi;
         if (L::kParkFwd) {
 #pragma unroll
             for (int j = 0; j < 3; ++j) {
@@ -664,39 +692,38 @@ __global__ __launch_bounds__(kFusedThreads) void bwd_fused_kernel(BwdFastArgs A)
             wg_barrier();  // E
         }
         if (kXRing) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        const auto elem = [&](int r) { return idx_n + r; };
-        finalize_reg_layer<0>(F, acc.r[0], 1, elem);
-        finalize_reg_layer<1>(F, acc.r[1], 2, elem);
-        finalize_reg_layer<2>(F, acc.r[2], 3, elem);
-        finalize_lane_layer(F, acc.d[0], 4, 0, elem);
-        finalize_lane_layer(F, acc.d[1], 5, 1, elem);
-        finalize_lane_layer(F, acc.d[2], 6, 2, elem);
+        wg_barrier();  // row buffers, rings and tables are free
+        float o[8];
+        spread_pairs<0>(acc.r[0], o);
+        lds_write_n2(lds, an, o);
+        spread_pairs<1>(acc.r[1], o);
+        lds_write_n2(lds + G::kRowFloats, an, o);
+        spread_pairs<2>(acc.r[2], o);
+        lds_write_n2(lds + 2 * G::kRowFloats, an, o);
+#pragma unroll
+        for (int j = 0; j < 3; ++j) lds_write_n2(lds + (3 + j) * G::kRowFloats, an, acc.d[j]);
+        wg_barrier();
+        write_partials<1>(F, lds);
+        wg_barrier();
+        wg_barrier();  // group Q's sums are there
     } else {
         // ---- group Q ----
         const int idx_q = base_q(wave, lane);
         const int aq = lds_addr2(idx_q);
-        float cq[5][8];
+        st.put(lds);
+        wg_barrier();  // tables staged
+        float cq[5][8], c7v[8], c13[8];
+        lds_read_p2<K>(lds, aq, c7v);
 #pragma unroll
-        for (int j = 0; j < 5; ++j)
-#pragma unroll
-            for (int r = 0; r < 8; ++r)  // layers above log2 n do not exist: weight zero leaves the element as it is
-                cq[j][r] = (!kVirt || 8 + j <= pt.n_log)
-                               ? fg[pt.trow(idx_q + p_reg_idx2<K>(r), 7 + j) + pt.col(idx_q + p_reg_idx2<K>(r))]
-                               : 0.0f;
+        for (int j = 0; j < 5; ++j) lds_read_p2<K>(lds + (1 + j) * G::kRowFloats, aq, cq[j]);
+        if (kHalf) lds_read_p2<K>(lds + (L::kTables - 1) * G::kRowFloats, aq, c13);
+        wg_barrier();  // ... and read
         Coef7<L::kPark7> c7;
-        {
-            float v[8];
-#pragma unroll
-            for (int r = 0; r < 8; ++r) v[r] = fg[pt.trow(idx_q + p_reg_idx2<K>(r), 6) + pt.col(idx_q + p_reg_idx2<K>(r))];
-            c7.init(v, tab, 2048 + tid);
-        }
+        c7.init(c7v, tab, 2048 + tid);
         float acc13[8];  // kHalf only: layer 13 pairs column e with e + 4096
 #pragma unroll
         for (int r = 0; r < 8; ++r) acc13[r] = 0.0f;
         if (kHalf) {
-            float c13[8];
-#pragma unroll
-            for (int r = 0; r < 8; ++r) c13[r] = fg[12 * ts + pt.col(idx_q + p_reg_idx2<K>(r))];
             tab[1024 + tid] = make_float4(c13[0], c13[1], c13[2], c13[3]);
             tab[1536 + tid] = make_float4(c13[4], c13[5], c13[6], c13[7]);
         }
@@ -822,24 +849,31 @@ __global__ __launch_bounds__(kFusedThreads) void bwd_fused_kernel(BwdFastArgs A)
             wg_barrier();  // E
         }
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        const auto elem = [&](int r) { return idx_q + p_reg_idx2<K>(r); };
-        finalize_reg_layer<2>(F, acc.r2, K, elem);
-        finalize_reg_layer<1>(F, acc.r1, K - 1, elem);
-        finalize_lane_layer(F, acc.d[3], 10, 2, elem);
-        finalize_lane_layer(F, acc.d[2], 9, 1, elem);
-        finalize_lane_layer(F, acc.d[1], 8, 0, elem);
-        finalize_lane_layer(F, acc.d[0], 7, 3, elem);
-        if (kHalf) {
-            // sum of layer 13 = (scale after the layer)^2 * deferred sum; the lower half's share goes to the
-            // layer's place in the slice, the upper half's, negated, behind the slice's regular part
-            float *dst = F.part + (size_t)(pt.half ? 13 : 12) * G::n;
+        wg_barrier();  // row buffers, rings and tables are free
+        wg_barrier();  // group N's sums are there
+        write_partials<1>(F, lds);
+        wg_barrier();
+        float o[8];
 #pragma unroll
-            for (int r = 0; r < 8; ++r) {
-                const int e = idx_q + p_reg_idx2<K>(r);
-                const float d = A.fw_inv[11 * ts + pt.col(e)];
-                const float v = acc13[r] * (d * d);
-                put_partial(dst + e, pt.half ? -v : v, A.first_chunk);
-            }
+        for (int j = 0; j < 4; ++j) lds_write_p2<K>(lds + j * G::kRowFloats, aq, acc.d[j]);  // layers 7..10
+        spread_pairs<1>(acc.r1, o);
+        lds_write_p2<K>(lds + 4 * G::kRowFloats, aq, o);
+        spread_pairs<2>(acc.r2, o);
+        lds_write_p2<K>(lds + 5 * G::kRowFloats, aq, o);
+        if (kHalf) lds_write_p2<K>(lds + (L::kTables - 1) * G::kRowFloats, aq, acc13);
+        wg_barrier();
+    }
+    write_partials<7>(F, lds);
+    if (kHalf) {
+        // sum of layer 13 = (scale after the layer)^2 * deferred sum; the lower half's share goes to the
+        // layer's place in the slice, the upper half's, negated, behind the slice's regular part
+        float *dst = F.part + (size_t)(pt.half ? 13 : 12) * G::n;
+#pragma unroll
+        for (int m = 0; m < 4; ++m) {
+            const int e = (int)threadIdx.x + 1024 * m;
+            const float d = A.fw_inv[11 * ts + pt.col(e)];
+            const float v = lds[(L::kTables - 1) * G::kRowFloats + lds_addr2(e)] * (d * d);
+            put_partial(dst + e, pt.half ? -v : v, A.first_chunk);
         }
     }
 }
