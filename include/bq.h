@@ -195,6 +195,26 @@ bq_status bq_kron_fwd(const void *x, void *y, const float *q1, int32_t d1, const
 bq_status bq_kron_inv(const void *y, void *x, const float *q1, int32_t d1, const void *plan,
                       const bq_rows *rows, void *stream);
 
+/* ---- calibration of a linear layer on 16-bit rows -------------------------------------------- */
+
+/* e: float32 [rows][cols], dense, 16-byte aligned.  Writes e as a sum of 16-bit matrices of type dtype
+ * (BQ_F16: 2 pieces of e times a power of two, BQ_BF16: 3 pieces of e) to pieces: [2 or 3][rows][ld], 16-byte
+ * aligned, ld >= cols a multiple of 8 (zeros behind the columns), and to result[0] the sum of squares of e (summed
+ * in double) and to result[1] the factor that turns a product with the sum of the pieces into one with 2 e.
+ * scratch: bq_residual_scratch_bytes() bytes, 8-byte aligned.  The sum of the pieces is within 2^-23 |e| of e,
+ * binary16 pieces of entries below 2^-17 of the largest within 2^-40 of the largest. */
+size_t bq_residual_scratch_bytes(void);
+bq_status bq_residual_split(const float *e, int64_t rows, int32_t cols, void *pieces, int32_t ld, int32_t dtype,
+                            float *result, void *scratch, void *stream);
+
+/* The gradient through vq = s * round(v / s), s = max |v| / (2^(bits-1) - 1) over groups of quant->group channels,
+ * with a straight-through round, in place: g becomes factor[0] * g, plus, on the entry of each group with the largest
+ * |v| (the first of equals), sign(v) / qmax * sum over the group of factor[0] g (vq - v) / s.  v, vq: dense rows
+ * (rows->ld_x = rows->ld_y = heads * n) of rows->dtype, BQ_F16 or BQ_BF16; g: float32 of the same shape; all 16-byte
+ * aligned.  quant->group: 8 .. 8192; quant->scale_dtype is not used (the scale's own rounding counts as the identity). */
+bq_status bq_quantiser_grad(const void *v, const void *vq, float *g, const float *factor, const bq_quant *quant,
+                            const bq_rows *rows, void *stream);
+
 /* ---- measurement helpers (not part of the method) ------------------------------------------- */
 
 /* dst[0, bytes) = src[0, bytes): a plain streaming copy (16 bytes per lane), the reference for what the memory

@@ -22,7 +22,8 @@ DTYPE_CODES = {"f32": BQ_F32, "f16": BQ_F16, "bf16": BQ_BF16}
 EXPORTS = ["bq_plan_bytes", "bq_plan_build", "bq_butterfly_fwd", "bq_butterfly_inv", "bq_butterfly_fwd_quant",
            "bq_butterfly_fwd_fakequant", "bq_hadamard_fwd", "bq_cayley_build", "bq_kron_fwd", "bq_kron_inv",
            "bq_butterfly_bwd_workspace_bytes", "bq_butterfly_bwd", "bq_butterfly_bwd_static",
-           "bq_butterfly_bwd_static_max_bytes", "bq_probe_copy", "bq_probe_read", "bq_probe_read_sink_bytes",
+           "bq_butterfly_bwd_static_max_bytes", "bq_residual_scratch_bytes", "bq_residual_split", "bq_quantiser_grad",
+           "bq_probe_copy", "bq_probe_read", "bq_probe_read_sink_bytes",
            "bq_probe_fma", "bq_probe_fma_out_floats",
            "bq_status_string", "bq_last_error",
            "bq_version"]
@@ -75,6 +76,12 @@ def lib() -> ctypes.CDLL:
             f.argtypes = [vp, vp, vp, ctypes.c_int32, vp, ctypes.POINTER(bq_rows), vp]
             f.restype = ctypes.c_int
         L.bq_butterfly_fwd_quant.restype = ctypes.c_int
+        L.bq_residual_scratch_bytes.argtypes = []
+        L.bq_residual_scratch_bytes.restype = sz
+        L.bq_residual_split.argtypes = [vp, ctypes.c_int64, ctypes.c_int32, vp, ctypes.c_int32, ctypes.c_int32, vp, vp, vp]
+        L.bq_residual_split.restype = ctypes.c_int
+        L.bq_quantiser_grad.argtypes = [vp, vp, vp, vp, ctypes.POINTER(bq_quant), ctypes.POINTER(bq_rows), vp]
+        L.bq_quantiser_grad.restype = ctypes.c_int
         L.bq_butterfly_bwd_workspace_bytes.argtypes = [ctypes.POINTER(bq_rows)]
         L.bq_butterfly_bwd_workspace_bytes.restype = sz
         L.bq_butterfly_bwd.argtypes = [vp, vp, vp, vp, vp, vp, sz, ctypes.POINTER(bq_rows), vp]
@@ -190,6 +197,25 @@ def bq_kron_fwd(x, y, q1, d1: int, plan, rows: bq_rows, stream=None) -> None:
 
 def bq_kron_inv(y, x, q1, d1: int, plan, rows: bq_rows, stream=None) -> None:
     _check(lib().bq_kron_inv(_ptr(y), _ptr(x), _ptr(q1), d1, _ptr(plan), ctypes.byref(rows), _stream_ptr(stream)))
+
+
+def bq_residual_scratch_bytes() -> int:
+    return int(lib().bq_residual_scratch_bytes())
+
+
+def bq_residual_split(e, pieces, result, scratch, stream=None) -> None:
+    """e: dense float32 [rows, cols]; pieces: [2 (float16) or 3 (bfloat16), rows, ld]; result: float32 [2]; scratch: uint8."""
+    rows, cols = e.shape
+    assert e.is_contiguous() and pieces.is_contiguous() and pieces.shape[0] == (2 if _dtype_code(pieces) == BQ_F16 else 3)
+    assert pieces.shape[1] == rows and result.numel() >= 2 and scratch.numel() >= bq_residual_scratch_bytes()
+    _check(lib().bq_residual_split(_ptr(e), rows, cols, _ptr(pieces), pieces.shape[2], _dtype_code(pieces), _ptr(result),
+                                   _ptr(scratch), _stream_ptr(stream)))
+
+
+def bq_quantiser_grad(v, vq, g, factor, quant: bq_quant, rows: bq_rows, stream=None) -> None:
+    """In place on g (float32); factor: float32 device tensor of one element."""
+    _check(lib().bq_quantiser_grad(_ptr(v), _ptr(vq), _ptr(g), _ptr(factor), ctypes.byref(quant), ctypes.byref(rows),
+                                   _stream_ptr(stream)))
 
 
 def bq_butterfly_bwd_workspace_bytes(rows: bq_rows) -> int:

@@ -258,6 +258,47 @@ bq_status bq_cayley_build(const float *params, int32_t d1, float *q1, void *stre
     return ok();
 }
 
+size_t bq_residual_scratch_bytes(void) { return bq::residual_scratch_bytes(); }
+
+bq_status bq_residual_split(const float *e, int64_t rows, int32_t cols, void *pieces, int32_t ld, int32_t dtype,
+                            float *result, void *scratch, void *stream)
+{
+    const char *who = "bq_residual_split";
+    if (dtype != BQ_F16 && dtype != BQ_BF16) return fail(BQ_ERR_DTYPE, "%s: dtype %d is not a 16-bit type", who, (int)dtype);
+    if (rows < 1 || cols < 1 || ld < cols || ld % 8 || rows > ((int64_t)1 << 40) / ld)
+        return fail(BQ_ERR_SHAPE, "%s: rows=%lld cols=%d ld=%d", who, (long long)rows, (int)cols, (int)ld);
+    if (!e || !pieces || !result || !scratch) return fail(BQ_ERR_NULL, "%s: pointer is NULL", who);
+    if (misaligned(e, 16) || misaligned(pieces, 16) || misaligned(result, 4) || misaligned(scratch, 8))
+        return fail(BQ_ERR_ALIGN, "%s: misaligned pointer", who);
+    hipError_t err = bq::launch_residual_split(e, rows, cols, pieces, ld, dtype, result, scratch, (hipStream_t)stream);
+    if (err != hipSuccess) return hip_fail(err, who);
+    return ok();
+}
+
+bq_status bq_quantiser_grad(const void *v, const void *vq, float *g, const float *factor, const bq_quant *quant,
+                            const bq_rows *rows, void *stream)
+{
+    const char *who = "bq_quantiser_grad";
+    bq::Shape s;
+    bq_status st = check_rows(rows, &s, who);
+    if (st != BQ_OK) return st;
+    if (!quant) return fail(BQ_ERR_NULL, "%s: quantiser descriptor is NULL", who);
+    if (s.dtype == BQ_F32) return fail(BQ_ERR_DTYPE, "%s: rows must be of a 16-bit type", who);
+    const int64_t width = (int64_t)s.n * s.heads;
+    if (s.ld_x != width || s.ld_y != width) return fail(BQ_ERR_SHAPE, "%s: rows must be dense", who);
+    if (quant->bits != 2 && quant->bits != 4) return fail(BQ_ERR_SHAPE, "%s: bits=%d", who, (int)quant->bits);
+    if (quant->group < 8 || quant->group > 8192 || s.n % quant->group)
+        return fail(BQ_ERR_SHAPE, "%s: group=%d must divide n=%d and lie in [8, 8192]", who, (int)quant->group, s.n);
+    if (s.rows > ((int64_t)1 << 34) / width) return fail(BQ_ERR_SHAPE, "%s: more than 2^34 elements", who);
+    if (s.rows == 0) return ok();
+    if (!v || !vq || !g || !factor) return fail(BQ_ERR_NULL, "%s: pointer is NULL", who);
+    if (misaligned(v, 16) || misaligned(vq, 16) || misaligned(g, 16) || misaligned(factor, 4))
+        return fail(BQ_ERR_ALIGN, "%s: misaligned pointer", who);
+    hipError_t err = bq::launch_quant_grad(v, vq, g, factor, s, quant->bits, quant->group, (hipStream_t)stream);
+    if (err != hipSuccess) return hip_fail(err, who);
+    return ok();
+}
+
 static bq_status kron(bool inverse, const void *in, void *out, const float *q1, int32_t d1, const void *plan,
                       const bq_rows *rows, void *stream, const char *who)
 {

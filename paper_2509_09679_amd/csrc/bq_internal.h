@@ -238,6 +238,13 @@ bool kron_fused_supported(const void *in, const void *out, int d1, int d2);
 hipError_t launch_kron_fused(bool inverse, const void *in, void *out, const float *q, int d1, const PlanView &pv,
                              int64_t rows, int dtype, hipStream_t stream);
 
+// calibration: the error matrix in 16-bit pieces, the gradient through the fake quantiser (bq_calib.hip)
+size_t residual_scratch_bytes();
+hipError_t launch_residual_split(const float *e, int64_t rows, int cols, void *pieces, int ld, int dtype, float *result,
+                                 void *scratch, hipStream_t stream);
+hipError_t launch_quant_grad(const void *v, const void *vq, float *g, const float *factor, const Shape &s, int bits, int group,
+                             hipStream_t stream);
+
 // plan build: bq_plan.hip
 hipError_t launch_plan_build(const float *theta, int n, int heads, int k, void *plan, hipStream_t stream);
 

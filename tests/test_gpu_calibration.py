@@ -132,3 +132,41 @@ def test_sgd_from_identity_lowers_the_reconstruction_loss():
     torch.cuda.synchronize()
     nx, ny = Xd.float().norm(dim=1), Y.float().norm(dim=1)
     assert float(((nx - ny).abs() / nx).max()) < 2e-3
+
+
+@gpu
+@pytest.mark.parametrize("n,m,T,dtype,act,wgt", [(256, 97, 131, "f16", (4, 64, "f16"), (2, 8, "f16")),
+                                                 (1024, 40, 33, "bf16", (4, 1024, "f16"), (4, 128, "f32")),
+                                                 (8192, 17, 9, "f16", (2, 8192, "f32"), (4, 2048, "f16"))])
+def test_half_step_matches_double(n, m, T, dtype, act, wgt):
+    # 16-bit rows: everything between the fake quantisations and the backward passes (dense products on 16-bit pieces,
+    # loss, gradient through the quantisers) against the same rule in double on the values the GPU quantised.  Odd m and T:
+    # padded pieces, short last workgroups; groups within a wave, across waves, of a whole row.  E is the difference of two
+    # products that nearly cancel: float32 sums of n terms leave about sqrt(n) 2^-24 |X| |W| on it, and as much of 2^-24 on
+    # the gradients' own sums; the bounds allow four times that.
+    import torch
+    from paper_2509_09679_amd import binding as B
+    from paper_2509_09679_amd.calibration import ButterflyCalibrator, QuantSpec
+
+    dev = "cuda:0"
+    X = synth.storage_to_torch(synth.small_case(n, T, dtype, seed=61)[0], dtype, dev)
+    W = synth.storage_to_torch(synth.small_case(n, m, dtype, seed=62, outliers=0, dist="normal")[0], dtype, dev)
+    theta = torch.from_numpy((0.3 * synth.small_case(n, 1, dtype, seed=63)[1]).astype(np.float32)).to(dev)
+    cal = ButterflyCalibrator(W, QuantSpec(*act), QuantSpec(*wgt), theta=theta)
+    cal.loss_and_grad(X)
+    rx, rw = B.make_rows(X, n, 1), B.make_rows(W, n, 1)
+    V, Wr = torch.empty_like(X), torch.empty_like(W)
+    B.bq_butterfly_fwd(X, V, cal.plan, rx)
+    B.bq_butterfly_fwd(W, Wr, cal.plan, rw)
+    loss, dV, dWr = cal._half_step(X, cal.Xq, V, Wr)
+    d = lambda t: t.double().cpu().numpy()
+    E = d(cal.Xq) @ d(cal.Wq).T - d(X) @ d(W).T
+    noise = 4 * np.sqrt(n) * 2.0 ** -24 * np.linalg.norm(d(X)) * np.linalg.norm(d(W)) / np.linalg.norm(E)  # |dE| / |E|
+    assert abs(float(loss) - (E ** 2).sum()) <= (2 * noise + 1e-6) * (E ** 2).sum()
+    for got, R, Q, G, spec in ((dV, V, cal.Xq, 2.0 * E @ d(cal.Wq), act), (dWr, Wr, cal.Wq, 2.0 * E.T @ d(cal.Xq), wgt)):
+        want = _through_quantiser(d(R), d(Q), G, spec[0], spec[1])
+        A = d(cal.Wq if R is V else cal.Xq)
+        room = (noise + 4 * np.sqrt(A.shape[0]) * 2.0 ** -24) * 2.0 * np.linalg.norm(E) * np.linalg.norm(A)
+        # the scale's own path sums a group's errors onto one entry: at most sqrt(group) / qmax times as much again
+        qmax = (1 << (spec[0] - 1)) - 1
+        assert np.linalg.norm(d(got) - want) <= room * (1 + np.sqrt(spec[1]) / qmax), np.linalg.norm(d(got) - want) / np.linalg.norm(want)
