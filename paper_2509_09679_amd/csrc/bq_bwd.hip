@@ -33,7 +33,8 @@
 // atomics, the result does not depend on scheduling.
 //
 // The kernel exits at once when the plan flags the scale-deferred tables as unusable; the generic
-// backward kernel, launched behind it with the opposite condition, then does the work.
+// backward kernel, launched behind it with the opposite condition, then does the work, and the last kernel adds that
+// kernel's partial sums.
 #include "bq_bwd_blocks.h"
 
 namespace bq {
@@ -879,14 +880,21 @@ __global__ __launch_bounds__(kFusedThreads) void bwd_fused_kernel(BwdFastArgs A)
 }
 
 // out[q] = sum over slices of partial[s][q] (+ the upper-half share of the last layer where a slice has one), in
-// double, in a fixed order; skipped for flagged plans.  n_angles and last_layer_at are multiples of kReduceAngles.
+// double, in a fixed order.  n_angles and last_layer_at are multiples of kReduceAngles.  Flagged plans: the sums of the
+// generic kernel's plain_parts slices (0: left to a later kernel).
 template <typename Out>
 __global__ __launch_bounds__(kReduceThreads) void bwd_reduce_kernel(const float *__restrict__ partial, Out *__restrict__ out,
                                                                     size_t n_angles, size_t slice_floats, size_t last_layer_at,
-                                                                    int n_parts, PlanRef plan)
+                                                                    int n_parts, PlanRef plan, int plain_parts)
 {
     __shared__ double lds[kReduceThreads * 4];
-    if (!plan_fast_both(plan)) return;
+    const PlanUse use = plan_use(plan);
+    if (use == kPlanForeign) return;
+    if (use == kPlanPlain) {
+        if (plain_parts == 0) return;
+        last_layer_at = slice_floats = n_angles;
+        n_parts = plain_parts;
+    }
     const size_t first = (size_t)blockIdx.x * kReduceAngles;
     const size_t extra = first >= last_layer_at ? slice_floats - n_angles : 0;  // 0, or the number of angles of the last layer
     const double t = sum_slices(partial, first, slice_floats, extra, n_parts, lds);
@@ -894,11 +902,12 @@ __global__ __launch_bounds__(kReduceThreads) void bwd_reduce_kernel(const float 
 }
 
 // n < 4096: the sums of a 4096-point block hold, per layer, the block's rows side by side, each with its `heads`
-// transforms; dtheta[h][i][p] = sum over the rows, in row order
+// transforms; dtheta[h][i][p] = sum over the rows, in row order (flagged plans: over the generic kernel's slices)
 __global__ void bwd_fold_kernel(const double *__restrict__ sums, float *__restrict__ dtheta, int n_log, int heads,
-                                PlanRef plan)
+                                PlanRef plan, const float *__restrict__ plain, int plain_parts)
 {
-    if (!plan_fast_both(plan)) return;
+    const PlanUse use = plan_use(plan);
+    if (use == kPlanForeign) return;
     const int half = 1 << (n_log - 1);
     const int q = blockIdx.x * blockDim.x + threadIdx.x;
     if (q >= heads * n_log * half) return;
@@ -906,6 +915,11 @@ __global__ void bwd_fold_kernel(const double *__restrict__ sums, float *__restri
     const int layer = hl % n_log, h = hl / n_log;
     const int block_rows = (G::n >> n_log) / heads;
     double acc = 0.0;
+    if (use == kPlanPlain) {
+        for (int w = 0; w < plain_parts; ++w) acc += (double)plain[(size_t)w * heads * n_log * half + q];
+        dtheta[q] = (float)acc;
+        return;
+    }
     for (int row = 0; row < block_rows; ++row) acc += sums[layer * (G::n / 2) + (row * heads + h) * half + p];
     dtheta[q] = (float)acc;
 }
@@ -967,7 +981,8 @@ static hipError_t fused_kernel_ready()
 }
 
 template <typename T, bool kHalf, bool kVirt>
-static hipError_t launch_bwd_fast_t(BwdFastArgs A, const Shape &s, float *dtheta, char *ws, hipStream_t stream)
+static hipError_t launch_bwd_fast_t(BwdFastArgs A, const PlanView &pv, const Shape &s, float *dtheta, char *ws,
+                                    hipStream_t stream)
 {
     const int slices = bwd_fast_slices(s.k);
     const int64_t kernel_rows = bwd_fast_kernel_rows(s);
@@ -989,29 +1004,33 @@ static hipError_t launch_bwd_fast_t(BwdFastArgs A, const Shape &s, float *dtheta
         else
             hipLaunchKernelGGL((bwd_fused_kernel<T, false, kHalf, kVirt>), dim3(grid), dim3(kFusedThreads), lds_bytes, stream, A);
     }
+    int plain_parts;
+    e = launch_generic_bwd_if_bad(A.x, A.dy, pv, A.dx, ws, s, stream, &plain_parts);
+    if (e != hipSuccess) return e;
     if (kVirt) {
         const size_t sums = (size_t)s.k * (G::n / 2);  // the layers the transform has
         hipLaunchKernelGGL(bwd_reduce_kernel<double>, dim3((unsigned)(sums / kReduceAngles)), dim3(kReduceThreads), 0, stream,
-                           (const float *)ws, fold, sums, (size_t)A.slice_floats, sums, slices, A.plan);
+                           (const float *)ws, fold, sums, (size_t)A.slice_floats, sums, slices, A.plan, 0);
         const unsigned angles = (unsigned)(s.heads * s.k * (s.n / 2));
         hipLaunchKernelGGL(bwd_fold_kernel, dim3((angles + 255) / 256), dim3(256), 0, stream, (const double *)fold, dtheta, s.k,
-                           s.heads, A.plan);
+                           s.heads, A.plan, (const float *)ws, plain_parts);
     } else {
         const size_t angles = (size_t)s.k * (s.n / 2);
         hipLaunchKernelGGL(bwd_reduce_kernel<float>, dim3((unsigned)(angles / kReduceAngles)), dim3(kReduceThreads), 0, stream,
                            (const float *)ws, dtheta, angles, (size_t)A.slice_floats, (size_t)(s.k - 1) * (s.n / 2), slices,
-                           A.plan);
+                           A.plan, plain_parts);
     }
     return hipGetLastError();
 }
 
 template <bool kHalf, bool kVirt>
-static hipError_t launch_bwd_fast_d(const BwdFastArgs &A, const Shape &s, float *dtheta, char *ws, hipStream_t stream)
+static hipError_t launch_bwd_fast_d(const BwdFastArgs &A, const PlanView &pv, const Shape &s, float *dtheta, char *ws,
+                                    hipStream_t stream)
 {
     switch (s.dtype) {
-        case BQ_F32: return launch_bwd_fast_t<float, kHalf, kVirt>(A, s, dtheta, ws, stream);
-        case BQ_F16: return launch_bwd_fast_t<__half, kHalf, kVirt>(A, s, dtheta, ws, stream);
-        default: return launch_bwd_fast_t<bf16_t, kHalf, kVirt>(A, s, dtheta, ws, stream);
+        case BQ_F32: return launch_bwd_fast_t<float, kHalf, kVirt>(A, pv, s, dtheta, ws, stream);
+        case BQ_F16: return launch_bwd_fast_t<__half, kHalf, kVirt>(A, pv, s, dtheta, ws, stream);
+        default: return launch_bwd_fast_t<bf16_t, kHalf, kVirt>(A, pv, s, dtheta, ws, stream);
     }
 }
 
@@ -1037,9 +1056,9 @@ hipError_t launch_bwd_fast(const void *x, const void *dy, const PlanView &pv, vo
     A.ld_in = s.ld_x * block_rows;
     A.ld_out = s.ld_y * block_rows;
     char *w = (char *)ws;
-    if (s.k < K) return launch_bwd_fast_d<false, true>(A, s, dtheta, w, stream);
-    if (s.k == K) return launch_bwd_fast_d<false, false>(A, s, dtheta, w, stream);
-    return launch_bwd_fast_d<true, false>(A, s, dtheta, w, stream);
+    if (s.k < K) return launch_bwd_fast_d<false, true>(A, pv, s, dtheta, w, stream);
+    if (s.k == K) return launch_bwd_fast_d<false, false>(A, pv, s, dtheta, w, stream);
+    return launch_bwd_fast_d<true, false>(A, pv, s, dtheta, w, stream);
 }
 
 }  // namespace bq

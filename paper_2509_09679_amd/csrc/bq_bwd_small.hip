@@ -13,14 +13,14 @@
 // order: no atomics, the result does not depend on scheduling.
 //
 // The kernels exit at once when the plan flags the scale-deferred tables as unusable; the generic backward
-// kernel, launched behind them with the opposite condition, then does the work.
+// kernel, launched between the two with the opposite condition, then does the work, and the second kernel adds its sums.
 #include "bq_bwd_blocks.h"
 #include "bq_internal.h"
 
 namespace bq {
 
 constexpr int kSbThreads = 256;
-constexpr int kSbMaxSlots = 4096;  // (8192 measured no faster for narrow rows and slower where the reduction grows)
+constexpr int kSbMaxSlots = 4096;  // (8192: 200000 rows of 128 unchanged at 60 us, 8192 rows 26 -> 39 us)
 
 // With no more slices than this a launch has at most 2048 waves, so the slots hold at most 2048 x 512 elements' angles
 // (14 MiB at n = 128): below the 32 MiB of the entry point that brings its own workspace.
@@ -161,24 +161,31 @@ __global__ __launch_bounds__(kSbThreads) void small_bwd_kernel(SmallBwdArgs A)
     }
 }
 
-// dtheta[q] = sum over slots of partial[slot][q], in double: a workgroup takes 32 angles, its 8 groups of 32
-// threads take every eighth slot each and their sums are added in group order.
-__global__ __launch_bounds__(256) void small_bwd_reduce_kernel(const float *__restrict__ partial, float *__restrict__ dtheta,
-                                                               int64_t n_angles, int64_t slots, PlanRef plan)
+// dtheta[q] = sum over slots of partial[slot][q], in double: a workgroup takes 16 angles (64 bytes of a slot), its 64 groups
+// of 16 threads take every 64th slot each and their sums are added in group order.  A serial chain of loads per thread: with
+// 32 angles and 8 groups of 256 threads, 4096 slots of n = 128 ran 14 workgroups of 512
+// loads each (whole backward pass of 8192 fp16 rows of 128: 156 -> 26 us).  Flagged
+// plans: the same over the generic kernel's plain_slots slices.
+constexpr int kSbReduceAngles = 16, kSbReduceGroups = 64;
+__global__ __launch_bounds__(kSbReduceAngles * kSbReduceGroups) void small_bwd_reduce_kernel(
+    const float *__restrict__ partial, float *__restrict__ dtheta, int64_t n_angles, int64_t slots, PlanRef plan, int64_t plain_slots)
 {
-    if (!plan_fast_both(plan)) return;
-    __shared__ double sums[8][32];
-    const int lane = threadIdx.x & 31, grp = threadIdx.x >> 5;
-    const int64_t q = (int64_t)blockIdx.x * 32 + lane;
+    const PlanUse use = plan_use(plan);
+    if (use == kPlanForeign) return;
+    if (use == kPlanPlain) slots = plain_slots;
+    __shared__ double sums[kSbReduceGroups][kSbReduceAngles];
+    const int lane = threadIdx.x % kSbReduceAngles, grp = threadIdx.x / kSbReduceAngles;
+    const int64_t q = (int64_t)blockIdx.x * kSbReduceAngles + lane;
     double acc = 0.0;
-    if (q < n_angles)
-        for (int64_t s = grp; s < slots; s += 8) acc += (double)partial[s * n_angles + q];
+    if (q < n_angles) {
+#pragma unroll 8
+        for (int64_t s = grp; s < slots; s += kSbReduceGroups) acc += (double)partial[s * n_angles + q];
+    }
     sums[grp][lane] = acc;
     __syncthreads();
     if (grp == 0 && q < n_angles) {
         double t = sums[0][lane];
-#pragma unroll
-        for (int g = 1; g < 8; ++g) t += sums[g][lane];
+        for (int g = 1; g < kSbReduceGroups; ++g) t += sums[g][lane];
         dtheta[q] = (float)t;
     }
 }
@@ -274,9 +281,12 @@ hipError_t launch_small_bwd(const void *x, const void *dy, const PlanView &pv, v
         case BQ_F16: launch_small_bwd_t<__half>(A, s.k, g, stream); break;
         default: launch_small_bwd_t<bf16_t>(A, s.k, g, stream); break;
     }
-    const unsigned blocks = (unsigned)((A.n_angles + 31) / 32);
-    hipLaunchKernelGGL(small_bwd_reduce_kernel, dim3(blocks), dim3(256), 0, stream, (const float *)ws, dtheta, A.n_angles,
-                       g.slots, A.plan);
+    int plain_parts;
+    const hipError_t e = launch_generic_bwd_if_bad(x, dy, pv, dx, ws, s, stream, &plain_parts);
+    if (e != hipSuccess) return e;
+    const unsigned blocks = (unsigned)((A.n_angles + kSbReduceAngles - 1) / kSbReduceAngles);
+    hipLaunchKernelGGL(small_bwd_reduce_kernel, dim3(blocks), dim3(kSbReduceAngles * kSbReduceGroups), 0, stream, (const float *)ws,
+                       dtheta, A.n_angles, g.slots, A.plan, (int64_t)plain_parts);
     return hipGetLastError();
 }
 

@@ -49,16 +49,8 @@ hipError_t launch_bwd(const void *x, const void *dy, const PlanView &pv, void *d
         Shape t = s;
         return launch_transform(kInv, dy, dx, pv, t, nullptr, stream);
     }
-    if (bwd_fast_supported(x, dy, dx, dtheta, s)) {
-        hipError_t e = launch_bwd_fast(x, dy, pv, dx, dtheta, ws, s, stream);
-        if (e != hipSuccess) return e;
-        return launch_generic_bwd(x, dy, pv, dx, dtheta, ws, s, stream, /*only_if_bad=*/true);
-    }
-    if (small_bwd_supported(x, dy, dx, dtheta, s)) {
-        hipError_t e = launch_small_bwd(x, dy, pv, dx, dtheta, ws, s, stream);
-        if (e != hipSuccess) return e;
-        return launch_generic_bwd(x, dy, pv, dx, dtheta, ws, s, stream, /*only_if_bad=*/true);
-    }
+    if (bwd_fast_supported(x, dy, dx, dtheta, s)) return launch_bwd_fast(x, dy, pv, dx, dtheta, ws, s, stream);
+    if (small_bwd_supported(x, dy, dx, dtheta, s)) return launch_small_bwd(x, dy, pv, dx, dtheta, ws, s, stream);
     return launch_generic_bwd(x, dy, pv, dx, dtheta, ws, s, stream);
 }
 

@@ -339,10 +339,9 @@ __global__ __launch_bounds__(kGenThreads) void generic_bwd_kernel(BwdArgs A)
 
 // dtheta[q] = sum over workgroups of partial[w][q], accumulated in double in workgroup order.
 __global__ void reduce_partials_kernel(const float *__restrict__ partial, float *__restrict__ dtheta,
-                                       size_t n_angles, int n_parts, PlanRef plan, int only_if_bad)
+                                       size_t n_angles, int n_parts, PlanRef plan)
 {
-    const PlanHead ph = plan_head(plan);
-    if (!ph.matches || (only_if_bad && (ph.bad_fwd | ph.bad_inv) == 0)) return;
+    if (!plan_matches(plan)) return;
     size_t q = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (q >= n_angles) return;
     double acc = 0.0;
@@ -380,12 +379,13 @@ size_t bwd_workspace_bytes_generic(const Shape &s)
     return align256((size_t)grid * n_angles * sizeof(float));
 }
 
-hipError_t launch_generic_bwd(const void *x, const void *dy, const PlanView &pv, void *dx, float *dtheta,
-                              void *ws, const Shape &s, hipStream_t stream, bool only_if_bad)
+static hipError_t launch_generic_bwd_main(const void *x, const void *dy, const PlanView &pv, void *dx, void *ws, const Shape &s,
+                                          hipStream_t stream, bool only_if_bad, int *parts)
 {
     BwdArgs A{};
     unsigned grid;
     bwd_geometry(s, &A.rows_per_tile, &A.n_tiles, &grid);
+    *parts = (int)grid;
     A.x = x;
     A.dy = dy;
     A.dx = dx;
@@ -409,16 +409,25 @@ hipError_t launch_generic_bwd(const void *x, const void *dy, const PlanView &pv,
         if (e != hipSuccess) return e;
     }
     hipLaunchKernelGGL(kern, dim3(grid), dim3(kGenThreads), lds_bytes, stream, A);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    if (dtheta) {
-        size_t n_angles = (size_t)s.heads * s.k * (s.n / 2);
-        unsigned blocks = (unsigned)((n_angles + 255) / 256);
-        hipLaunchKernelGGL(reduce_partials_kernel, dim3(blocks), dim3(256), 0, stream, (const float *)ws, dtheta,
-                           n_angles, (int)grid, A.plan, A.only_if_bad);
-        e = hipGetLastError();
-    }
-    return e;
+    return hipGetLastError();
+}
+
+hipError_t launch_generic_bwd_if_bad(const void *x, const void *dy, const PlanView &pv, void *dx, void *ws, const Shape &s,
+                                     hipStream_t stream, int *parts)
+{
+    return launch_generic_bwd_main(x, dy, pv, dx, ws, s, stream, true, parts);
+}
+
+hipError_t launch_generic_bwd(const void *x, const void *dy, const PlanView &pv, void *dx, float *dtheta,
+                              void *ws, const Shape &s, hipStream_t stream)
+{
+    int parts;
+    hipError_t e = launch_generic_bwd_main(x, dy, pv, dx, ws, s, stream, false, &parts);
+    if (e != hipSuccess || !dtheta) return e;
+    const size_t n_angles = (size_t)s.heads * s.k * (s.n / 2);
+    hipLaunchKernelGGL(reduce_partials_kernel, dim3((unsigned)((n_angles + 255) / 256)), dim3(256), 0, stream, (const float *)ws,
+                       dtheta, n_angles, parts, pv.ref);
+    return hipGetLastError();
 }
 
 }  // namespace bq

@@ -106,6 +106,13 @@ __device__ __forceinline__ PlanHead plan_head(const PlanRef &p)
     return r;
 }
 
+enum PlanUse { kPlanForeign, kPlanFast, kPlanPlain };  // not of this shape; tables usable; (cos, sin) only
+__device__ __forceinline__ PlanUse plan_use(const PlanRef &p)
+{
+    const PlanHead h = plan_head(p);
+    return !h.matches ? kPlanForeign : (h.bad_fwd | h.bad_inv) == 0 ? kPlanFast : kPlanPlain;
+}
+
 __device__ __forceinline__ bool plan_matches(const PlanRef &p) { return plan_head(p).matches; }
 
 // the plan is of this shape and both of its scale-deferred table sets (forward, transposed) are usable
@@ -164,10 +171,13 @@ enum Mode { kFwd = 0, kInv = 1, kFwdQuant = 2, kFwdFake = 3, kHadamard = 4 };
 hipError_t launch_generic(Mode mode, const void *in, void *out, const PlanView &pv, const Shape &s,
                           const QuantArgs *q, hipStream_t stream);
 size_t bwd_workspace_bytes_generic(const Shape &s);
-// only_if_bad: run only when the plan flags its scale-deferred tables as unusable (the specialised
-// backward kernels, launched before, then did nothing)
 hipError_t launch_generic_bwd(const void *x, const void *dy, const PlanView &pv, void *dx, float *dtheta,
-                              void *ws, const Shape &s, hipStream_t stream, bool only_if_bad = false);
+                              void *ws, const Shape &s, hipStream_t stream);
+// The same pass without its last kernel, for plans that flag their scale-deferred tables as unusable (else it does nothing):
+// the specialised backward passes, whose kernels exit at once on such a plan, launch it behind them, and their own last
+// kernel then adds its *parts partial sums ([part][head][layer][pair], from ws on) instead of theirs.
+hipError_t launch_generic_bwd_if_bad(const void *x, const void *dy, const PlanView &pv, void *dx, void *ws, const Shape &s,
+                                     hipStream_t stream, int *parts);
 
 // How the kernels for n = 8 .. 128 cover a batch (bq_small.hip: small_tiling).  Lanes of a workgroup beyond `span` elements,
 // or beyond the last head of a row, are idle: they load a clamped row and store nothing.

@@ -291,7 +291,7 @@ static void (*pick_small_k(int k, Mode mode, int bits, bool plain))(SmallArgs)
 // heads.  The number of waves is the one that leaves the fewest lanes idle (none for widths that divide 2048, for multiples
 // of 512, and for 2 rows of 768 or 16 rows of 96 elements; 6 % for 3 rows of 640), the larger at equal shares.  Widths with
 // idle lanes went to the LDS kernel for any n before: 20011 fp16 rows of 12 x 64, forward, 81 -> 13 us, and
-// 574 -> 75 us backward.  The backward kernel holds eight waves per compute unit, of which three-wave workgroups fill six:
+// 574 -> 40 us backward.  The backward kernel holds eight waves per compute unit, of which three-wave workgroups fill six:
 // they count as four there (10000 rows of 12 x 128: 80 us in three-wave workgroups, 62 us in single-wave ones).
 SmallTiling small_tiling(int n, int heads, bool backward)
 {

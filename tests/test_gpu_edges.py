@@ -81,3 +81,21 @@ def test_small_transforms_of_any_row_width(n, heads, rows, dtype):
         dx, dth = gu.run_bwd(x, dy, th, n, heads, dtype, pad=pad)
         gu.check_rotated(dx, rdx, dtype, tag + " dx")
         gu.check_dtheta(dth, rdth, np.maximum(ab, floor), what=tag + " dtheta")
+
+
+@pytest.mark.parametrize("n,heads,rows", [(4096, 1, 9), (8192, 1, 5), (1024, 2, 7), (2048, 1, 3), (128, 3, 33), (64, 12, 40), (8, 1, 600),
+                                          (16384, 1, 2)])
+@pytest.mark.parametrize("dtype", ["f16", "f32"])
+def test_backward_of_flagged_plans_through_every_route(n, heads, rows, dtype):
+    # angles of pi/2 in three layers drive the deferred scales out of range: the specialised kernels leave the batch to the
+    # generic one and their second pass adds that kernel's partial sums (n < 4096: the fold kernel does)
+    x, th, dy = synth.small_case(n, rows, dtype, heads=heads, seed=600 + n * heads, with_dy=True, outliers=0)
+    th = th.copy()
+    th[:, :3] = np.float32(np.pi / 2)
+    x64, dy64 = synth.to_f64(x, dtype), synth.to_f64(dy, dtype)
+    rdx, rdth, ab = oracle.backward(x64, dy64, th, n, heads)
+    floor = np.median(ab, axis=2, keepdims=True)  # (few rows: as in the seeded sweep)
+    dx, dth = gu.run_bwd(x, dy, th, n, heads, dtype)
+    tag = f"n={n} H={heads} T={rows} {dtype}"
+    gu.check_rotated(dx, rdx, dtype, tag + " dx")
+    gu.check_dtheta(dth, rdth, np.maximum(ab, floor), what=tag + " dtheta")
