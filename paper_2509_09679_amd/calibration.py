@@ -79,7 +79,7 @@ class ButterflyCalibrator:
         T, m, dev = X.shape[0], self.m, X.device
         f32 = torch.float32
         E = torch.mm(X, self.W.t(), out_dtype=f32)
-        E = torch.addmm(E, Xq, self.Wq.t(), beta=-1.0, out_dtype=f32)
+        E = torch.addmm(E, Xq, self.Wq.t(), beta=-1.0, out_dtype=f32, out=E)
         ld = (m + 7) // 8 * 8
         P = torch.empty((2 if X.dtype == torch.float16 else 3, T, ld), dtype=X.dtype, device=dev)
         res = torch.empty(2, dtype=f32, device=dev)
@@ -91,7 +91,7 @@ class ButterflyCalibrator:
             G = None
             for piece in P[:, :, :m]:
                 piece = piece.t() if transposed else piece
-                G = (torch.mm(piece, A, out_dtype=f32) if G is None else torch.addmm(G, piece, A, out_dtype=f32))
+                G = torch.mm(piece, A, out_dtype=f32) if G is None else torch.addmm(G, piece, A, out_dtype=f32, out=G)
             if 8 <= spec.group <= 8192:
                 B.bq_quantiser_grad(R, Q, G, res[1:], B.make_quant(spec.bits, spec.group, spec.scale_dtype),
                                     B.make_rows(R, self.n, 1))
