@@ -201,7 +201,7 @@ hipError_t launch_bwd_fast(const void *x, const void *dy, const PlanView &pv, vo
 
 // n = 4096 specialised kernels (also blocks of 4096 / n rows for n = 256 .. 2048): bq_k12.hip
 bool k12_supported(Mode mode, const void *in, const void *out, const Shape &s, const QuantArgs *q);
-int k12_block_rows(const Shape &s);  // launch_k12 processes floor(rows / this) * this rows, from the first
+int k12_block_rows(const Shape &s);  // rows of the caller that form a row of the kernel
 hipError_t launch_k12(Mode mode, const void *in, void *out, const PlanView &pv, const Shape &s,
                       const QuantArgs *q, hipStream_t stream);
 

@@ -5,14 +5,14 @@
 namespace bq {
 
 // n = 4096 or 8192 with any number of heads, or n = 256 .. 2048 where 4096 consecutive elements of the
-// [rows][heads * n] array form one block of the kernel: several whole rows (k12_block_rows of them; rows that do
-// not fill a block are the caller's to handle) or a 4096-element piece of a wider row.
+// [rows][heads * n] array form one block of the kernel: several whole rows (k12_block_rows of them; the last block may have
+// fewer) or a 4096-element piece of a wider row.
 bool k12_supported(Mode mode, const void *in, const void *out, const Shape &s, const QuantArgs *q)
 {
     if (s.n > 2 * kN || s.n < 256) return false;
     const int64_t width = (int64_t)s.n * s.heads;
     if (s.n < kN) {
-        const bool rows_per_block = width <= kN && kN % width == 0 && s.rows >= kN / width;
+        const bool rows_per_block = width <= kN && kN % width == 0;
         const bool blocks_per_row = width % kN == 0 && width / kN <= 512;
         if (!rows_per_block && !blocks_per_row) return false;
     }
@@ -84,7 +84,8 @@ hipError_t launch_k12(Mode mode, const void *in, void *out, const PlanView &pv, 
     A.plan = pv.ref;
     const bool virt = s.n < kN, wide = s.n > kN;
     const int block_rows = k12_block_rows(s);  // rows of the caller per kernel row
-    A.rows = s.rows / block_rows;     // whole blocks only (the caller handles the remainder)
+    A.rows = (s.rows + block_rows - 1) / block_rows;
+    A.tail_rows = (int)(s.rows % block_rows);
     A.ld_in = s.ld_x * block_rows;
     A.ld_out = s.ld_y * block_rows;
     A.sub_ld_in = s.ld_x;
@@ -122,7 +123,9 @@ hipError_t launch_k12(Mode mode, const void *in, void *out, const PlanView &pv, 
     int64_t per_head = target / A.heads > 0 ? target / A.heads : 1;
     if (per_head > A.rows) per_head = A.rows;
     const unsigned grid = split_rows(A, per_head);
-    if ((mode == kFwdQuant || mode == kFwdFake) && q->group > 128)
+    const bool big = (mode == kFwdQuant || mode == kFwdFake) && q->group > 128;
+    if (A.tail_rows) return launch_k12_tail_dtype(mode, A, bits, grid, s.dtype, big, stream);
+    if (big)
         return launch_k12_big_dtype(mode, A, bits, grid, s.dtype, virt, wide, stream);
     if (wide) return launch_k13_dtype(mode, A, bits, grid, s.dtype, stream);
     if (inv_ring)  // 16-bit rows: the two-phase inverse

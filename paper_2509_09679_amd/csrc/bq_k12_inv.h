@@ -64,7 +64,7 @@ __device__ __forceinline__ void unpack2<bf16_t>(uint32_t w, float &a, float &b)
 
 // kNt: the batch is larger than the caches; rows are loaded and stored with the non-temporal hint (0.780 -> 0.766 ms
 // for 2^30 fp16 elements)
-template <typename T, bool kVirt, bool kNt>
+template <typename T, bool kVirt, bool kNt, bool kTail>
 __global__ __launch_bounds__(kThreads, 4) void k12_inv_ring_kernel(K12Args A)
 {
     static_assert(sizeof(T) == 2, "16-bit rows");
@@ -93,9 +93,12 @@ __global__ __launch_bounds__(kThreads, 4) void k12_inv_ring_kernel(K12Args A)
         const uint32_t off_n = elem_off<kVirt, false>(A, head, idx_n, A.sub_ld_in);
         for (int64_t row = row_first; row < A.rows; row += row_step) {
             float u[1][8];
-            unpack8(load8(in + row * A.ld_in + off_n), u[0], (const T *)nullptr);
+            const bool short_block = kTail && row == A.rows - 1;
+            const uint32_t off = kTail ? tail_off<kTail, T>(A, off_n * (uint32_t)sizeof(T), idx_n, short_block) / (uint32_t)sizeof(T) : off_n;
+            unpack8(load8(in + row * A.ld_in + off), u[0], (const T *)nullptr);
             slow_cascade<true, 1>(u, bufs, cs, idx_n, nk, kVirt ? (1 << A.row_log) - 1 : 0, kVirt ? head * kN : 0);
-            finish_row<T, kInv, 4, 0, 0, true, false, kVirt, 1, false>(A, u, row, head, chunk, bins, wg_bins, wg_max);
+            finish_row<T, kInv, 4, 0, 0, true, false, kVirt, 1, false>(A, u, row, head, chunk, bins, wg_bins, wg_max,
+                                                                             !(short_block && in_tail_gap(A, idx_n)));
         }
         return;
     }
@@ -136,14 +139,17 @@ __global__ __launch_bounds__(kThreads, 4) void k12_inv_ring_kernel(K12Args A)
     const int jl = ((lane & 3) << 4) | (lane >> 2);  // the chunk this lane loads
     const uint32_t voff = elem_off<kVirt, false>(A, head, wave * 512 + jl * 8, A.sub_ld_in) * (uint32_t)sizeof(T);
     const uint32_t rd_p = ring0 + (uint32_t)inv_ring_addr(idx_p);  // + 2 r1 + 4 r2 pieces for the other register pairs
+    // the short last block, if it is this workgroup's, is the last of its rows
+    const int tail_j = kTail && row_first + (n_my - 1) * row_step == A.rows - 1 ? n_my - 1 : -1;
     auto ring_load = [&](int j, int slot) {
         const int jj = j < n_my ? j : n_my - 1;  // past the end: the last row again (unused)
+        const uint32_t vo = tail_off<kTail, T>(A, voff, wave * 512 + jl * 8, jj == tail_j);
         const char *rowp = (const char *)(in + (row_first + jj * row_step) * A.ld_in);
         const uint32_t m0v = piece_s + (uint32_t)slot * (uint32_t)kInvSlotBytes;
         if (kNt)
-            asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %2 nt" : : "v"(voff), "s"(m0v), "s"(rowp) : "memory");
+            asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %2 nt" : : "v"(vo), "s"(m0v), "s"(rowp) : "memory");
         else
-            asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %2" : : "v"(voff), "s"(m0v), "s"(rowp) : "memory");
+            asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %2" : : "v"(vo), "s"(m0v), "s"(rowp) : "memory");
     };
     // Memory operations of a wave complete in issue order.  Per iteration a wave issues one ring load (first) and
     // one store (in C).  Row it + 1 was requested at the start of iteration it - 2; younger than that load are the
@@ -171,7 +177,8 @@ __global__ __launch_bounds__(kThreads, 4) void k12_inv_ring_kernel(K12Args A)
 #pragma unroll
             for (int r = 0; r < 8; ++r) u[r] *= d[r];
             finish_row<T, kInv, 4, 0, 0, true, false, kVirt, 1, false, kNt>(A, y, row_first + (it - 1) * row_step, head, chunk,
-                                                                              bins, wg_bins, wg_max);
+                                                                              bins, wg_bins, wg_max,
+                                                                              !(kTail && it - 1 == tail_j && in_tail_gap(A, idx_n)));
         }
         if (it < n_my) {  // B(it)
             uint32_t w0, w1, w2, w3;
@@ -213,14 +220,14 @@ __global__ __launch_bounds__(kThreads, 4) void k12_inv_ring_kernel(K12Args A)
     }
 }
 
-template <bool kVirt>
+template <bool kVirt, bool kTail = false>
 static hipError_t launch_k12_inv_ring(const K12Args &A, unsigned grid, int dtype, hipStream_t stream)
 {
     void (*kern)(K12Args);
     if (A.streaming)
-        kern = dtype == BQ_F16 ? k12_inv_ring_kernel<__half, kVirt, true> : k12_inv_ring_kernel<bf16_t, kVirt, true>;
+        kern = dtype == BQ_F16 ? k12_inv_ring_kernel<__half, kVirt, true, kTail> : k12_inv_ring_kernel<bf16_t, kVirt, true, kTail>;
     else
-        kern = dtype == BQ_F16 ? k12_inv_ring_kernel<__half, kVirt, false> : k12_inv_ring_kernel<bf16_t, kVirt, false>;
+        kern = dtype == BQ_F16 ? k12_inv_ring_kernel<__half, kVirt, false, kTail> : k12_inv_ring_kernel<bf16_t, kVirt, false, kTail>;
     static LdsLimitOnce once[2][2];
     hipError_t e = once[dtype == BQ_F16 ? 0 : 1][A.streaming ? 1 : 0].set((const void *)kern, kInvLdsBytes);
     if (e != hipSuccess) return e;

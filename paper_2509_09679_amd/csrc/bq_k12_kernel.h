@@ -84,7 +84,12 @@ struct K12Args {
     // elements of the caller's [rows][heads * n] array.  Rows of up to 4096 elements: 2^(12 - row_log) whole rows
     // (row_log = log2 of the row width; ld_in / ld_out are the strides between blocks, sub_ld_* the caller's
     // strides, heads = 1).  Wider rows: block `head` of the heads = width / 4096 blocks of a row (row_log = 12).
-    int n, n_log, row_log;
+    // tail_rows != 0: the last of the `rows` blocks has only so many of the caller's rows.  Its missing rows are read as
+    // copies of its first one and not stored.  (kTail variants: in the kernels for whole
+    // blocks the check cost 1 to 5 %, and 14 % in one.  As rows of their own they went through the kernel for any n, a launch of
+    // 10 to 95 us behind this one: 2001 rows of 2048, float32 inverse 34 -> 11 us, fp16 INT4
+    // 36 -> 14 us.)
+    int n, n_log, row_log, tail_rows;
     int64_t sub_ld_in, sub_ld_out;
 };
 
@@ -94,6 +99,19 @@ __device__ __forceinline__ uint32_t elem_off(const K12Args &A, int head, int e, 
 {
     if (!kVirt) return (uint32_t)(head * (kWide ? 2 * kN : kN) + e);
     return (uint32_t)((e >> A.row_log) * (int)sub_ld + head * kN + (e & ((1 << A.row_log) - 1)));
+}
+// kVirt: element e of the short last block lies in a row that the block does not have
+__device__ __forceinline__ bool in_tail_gap(const K12Args &A, int e) { return (e >> A.row_log) >= A.tail_rows; }
+// Byte offset, inside a kernel row, of the 16 bytes at element e: `off` (elem_off of e) except in the short block
+// (a uniform branch, so that the offsets of the short block occupy no registers in the row loop).
+template <bool kTail, typename T>
+__device__ __forceinline__ uint32_t tail_off(const K12Args &A, uint32_t off, int e, bool short_block)
+{
+    if (kTail && short_block) {
+        asm volatile("" : "+v"(e));
+        if (in_tail_gap(A, e)) off = (uint32_t)(e & ((1 << A.row_log) - 1)) * (uint32_t)sizeof(T);
+    }
+    return off;
 }
 // kVirt: the transform (head of the caller's row) that element e of block `head` belongs to
 __device__ __forceinline__ int virt_head(const K12Args &A, int head, int e)
@@ -267,11 +285,12 @@ struct CountOf<kFwdFake, kBits> {
 // kFwdFake only: kYq = the dequantised row is stored, kHist = the bins are counted.
 // y[h]: half h of the row (n = 8192), else the row; chunk: the thread's group of 8 elements inside its half.
 // kBig: quantiser groups of more than 128 channels (the maximum then comes from big_group_max()).
+// live (kVirt): the thread's row exists; else nothing is stored or counted.
 template <typename T, int kMode, int kBits, int kLanes, int kScale, bool kYq, bool kHist, bool kVirt, int kHalves, bool kBig,
           bool kNt = false>
 __device__ __forceinline__ void finish_row(const K12Args &A, const float (&y)[kHalves][8], int64_t row, int head, int chunk,
                                            typename CountOf<kMode, kBits>::type &bins, unsigned long long *wg_bins,
-                                           float *wg_max)
+                                           float *wg_max, bool live = true)
 {
     constexpr bool kWide = kHalves == 2;
     float group_max[kHalves] = {};
@@ -286,10 +305,13 @@ __device__ __forceinline__ void finish_row(const K12Args &A, const float (&y)[kH
             rounded8<kBits, kBig>(y[h], lanes, A.scale_f16 != 0, f, &s, &ordinary, group_max[h]);
             if (kHist) {
                 auto &bc = (BinCount<kBits> &)bins;
-                count8<kBits>(bc, f, ordinary);
+                if (!kVirt || live)
+                    count8<kBits>(bc, f, ordinary);
+                else
+                    bc.skip();
                 if (bc.full()) bc.drain(wg_bins);
             }
-            if (kYq) {
+            if (kYq && (!kVirt || live)) {
                 float yq[8];
                 dequant8(f, s, yq);
                 T *out_row = (T *)A.out + row * A.ld_out + h * kN;
@@ -298,6 +320,7 @@ __device__ __forceinline__ void finish_row(const K12Args &A, const float (&y)[kH
                 store8((T *)((char *)out_row + off), yq);
             }
         } else if (kMode != kFwdQuant) {
+            if (kVirt && !live) continue;
             T *out_row = (T *)A.out + row * A.ld_out + h * kN;
             uint32_t off = elem_off<kVirt, kWide>(A, head, chunk * 8, A.sub_ld_out) * (uint32_t)sizeof(T);
             asm volatile("" : "+v"(off));
@@ -310,6 +333,7 @@ __device__ __forceinline__ void finish_row(const K12Args &A, const float (&y)[kH
             const bool f16 = kLanes > 0 ? (kScale != 0) : (A.scale_f16 != 0);
             float s;
             const uint32_t packed = quant8<kBits, kBig>(y[h], lanes, f16, &s, group_max[h]);
+            if (kVirt && !live) continue;
             const int64_t unit = row * A.heads + head;
             uint8_t *codes_row = A.codes + unit * (kHalves * kN * kBits / 8) + h * (kN * kBits / 8);
             uint32_t coff = (uint32_t)(chunk * kBits);
@@ -331,9 +355,10 @@ __device__ __forceinline__ void finish_row(const K12Args &A, const float (&y)[kH
 }
 
 template <typename T, int kMode, int kBits, int kLanes, int kScale, bool kYq = true, bool kHist = false, bool kVirt = false,
-          bool kWide = false, bool kBig = false, bool kNt = false>
+          bool kWide = false, bool kBig = false, bool kNt = false, bool kTail = false>
 __global__ __launch_bounds__(kThreads, kWide ? 2 : 4) void k12_kernel(K12Args A)
 {
+    static_assert(!kTail || kVirt, "short blocks of several rows");
     static_assert(!(kWide && kVirt), "blocks of small transforms are a 4096-point scheme");
     // kNt: rows are loaded and stored with the non-temporal hint.  262144 fp16 rows of n = 4096: forward 0.796 ->
     // 0.778 ms on every box tried.  Not used where it did not hold up: the inverse gained 3.5 % on some boxes and
@@ -414,10 +439,13 @@ __global__ __launch_bounds__(kThreads, kWide ? 2 : 4) void k12_kernel(K12Args A)
         const float2 *cs = A.cs + (kVirt ? 0 : (size_t)head * kLayers * (kPoints / 2));
         for (int64_t row = row_first; row < A.rows; row += row_step) {
             float u[kHalves][8];
+            const bool short_block = kTail && row == A.rows - 1;
+            const uint32_t off = kTail ? tail_off<kTail, T>(A, off_n * (uint32_t)sizeof(T), idx_n, short_block) / (uint32_t)sizeof(T) : off_n;
 #pragma unroll
-            for (int h = 0; h < kHalves; ++h) unpack8(load8(in + row * A.ld_in + off_n + h * kN), u[h], (const T *)nullptr);
+            for (int h = 0; h < kHalves; ++h) unpack8(load8(in + row * A.ld_in + off + h * kN), u[h], (const T *)nullptr);
             slow_cascade<kInverse, kHalves>(u, lds, cs, idx_n, nk, kVirt ? (1 << A.row_log) - 1 : 0, kVirt ? head * kN : 0);
-            finish_row<T, kMode, kBits, kLanes, kScale, kYq, kHist, kVirt, kHalves, kBig, kNt>(A, u, row, head, chunk, bins, wg_bins, wg_max);
+            finish_row<T, kMode, kBits, kLanes, kScale, kYq, kHist, kVirt, kHalves, kBig, kNt>(A, u, row, head, chunk, bins, wg_bins, wg_max,
+                                                                                                       !(short_block && in_tail_gap(A, idx_n)));
         }
         flush_bins();
         return;
@@ -469,7 +497,12 @@ __global__ __launch_bounds__(kThreads, kWide ? 2 : 4) void k12_kernel(K12Args A)
 
     // rows of this workgroup: below 2^28 for every batch the library accepts, so the loop counters are 32-bit
     // (64-bit comparisons of uniform values would be done on the vector unit)
-    const int n_my = (int)((A.rows - row_first + row_step - 1) / row_step);
+    // (The fake quantisers divide here: with the host's figures the compiler keeps other values in registers and the float32
+    // variants spill in the row loop, 40000 rows of 2048 with one group per row 193 -> 273 us.)
+    const int n_my = kMode == kFwdFake ? (int)((A.rows - row_first + row_step - 1) / row_step)
+                                       : A.rows_each + ((int)row_first < A.rows_extra ? 1 : 0);
+    // the short last block, if it is this workgroup's, is the last of its rows
+    const int tail_j = kTail && row_first + (n_my - 1) * row_step == A.rows - 1 ? n_my - 1 : -1;
 
     // Phase B of one row: layers 8..12 (or 12..8) on layout P, in place in its LDS buffer (one per half).
     auto phase_b = [&](float *lb) {
@@ -566,16 +599,18 @@ __global__ __launch_bounds__(kThreads, kWide ? 2 : 4) void k12_kernel(K12Args A)
     const uint32_t slice_s = __builtin_amdgcn_readfirstlane(slice);  // uniform over the wave
     auto ring_load = [&](int j, int slot) {
         const int jj = j < n_my ? j : n_my - 1;  // past the end: re-read the last row (unused)
+        const uint32_t vo = tail_off<kTail, T>(A, voff, wave * 512 + lane * kPer, jj == tail_j);
+        const uint32_t vo1 = kHalfLoads == 2 ? tail_off<kTail, T>(A, voff1, wave * 512 + (64 + lane) * kPer, jj == tail_j) : 0u;
 #pragma unroll
         for (int h = 0; h < kHalves; ++h) {
             const char *rowp = (const char *)(in + (row_first + jj * row_step) * A.ld_in + h * kN);
             const uint32_t m0v = slice_s + (uint32_t)slot * kSlotBytes + (uint32_t)h * kHalfSlot;
             if (kNt) {
-                asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %2 nt" : : "v"(voff), "s"(m0v), "s"(rowp) : "memory");
+                asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %2 nt" : : "v"(vo), "s"(m0v), "s"(rowp) : "memory");
             } else {
-                asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %2" : : "v"(voff), "s"(m0v), "s"(rowp) : "memory");
+                asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %2" : : "v"(vo), "s"(m0v), "s"(rowp) : "memory");
                 if (kHalfLoads == 2)
-                    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %2" : : "v"(voff1), "s"(m0v + 1024u), "s"(rowp) : "memory");
+                    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %2" : : "v"(vo1), "s"(m0v + 1024u), "s"(rowp) : "memory");
             }
         }
     };
@@ -650,7 +685,8 @@ __global__ __launch_bounds__(kThreads, kWide ? 2 : 4) void k12_kernel(K12Args A)
                     }
                 }
             }
-            finish_row<T, kMode, kBits, kLanes, kScale, kYq, kHist, kVirt, kHalves, kBig, kNt>(A, u, row_first + (it - 2) * row_step, head, chunk, bins, wg_bins, wg_max);
+            finish_row<T, kMode, kBits, kLanes, kScale, kYq, kHist, kVirt, kHalves, kBig, kNt>(A, u, row_first + (it - 2) * row_step, head, chunk, bins, wg_bins, wg_max,
+                                                                                               !(kTail && it - 2 == tail_j && in_tail_gap(A, idx_n)));
         };
         // The phases touch different buffers, so any order is correct as long as C precedes A where the two
         // share a buffer.  n = 4096: C, B, A measured 1-2 % faster than the other orders on all modes.
@@ -678,20 +714,20 @@ __global__ __launch_bounds__(kThreads, kWide ? 2 : 4) void k12_kernel(K12Args A)
     flush_bins();
 }
 
-template <typename T, bool kVirt, bool kWide, bool kBig>
+template <typename T, bool kVirt, bool kWide, bool kBig, bool kTail>
 static hipError_t launch_k12_t(Mode mode, const K12Args &A, int bits, unsigned grid, hipStream_t stream)
 {
     constexpr bool V = kVirt, W = kWide, G = kBig;
     void (*kern)(K12Args) = nullptr;
     if (mode == kFwdFake) {
         if (A.out && A.hist)
-            kern = bits == 2 ? k12_kernel<T, kFwdFake, 2, 0, 0, true, true, V, W, G> : k12_kernel<T, kFwdFake, 4, 0, 0, true, true, V, W, G>;
+            kern = bits == 2 ? k12_kernel<T, kFwdFake, 2, 0, 0, true, true, V, W, G, false, kTail> : k12_kernel<T, kFwdFake, 4, 0, 0, true, true, V, W, G, false, kTail>;
         else if (A.out)
-            kern = bits == 2 ? k12_kernel<T, kFwdFake, 2, 0, 0, true, false, V, W, G> : k12_kernel<T, kFwdFake, 4, 0, 0, true, false, V, W, G>;
+            kern = bits == 2 ? k12_kernel<T, kFwdFake, 2, 0, 0, true, false, V, W, G, false, kTail> : k12_kernel<T, kFwdFake, 4, 0, 0, true, false, V, W, G, false, kTail>;
         else
-            kern = bits == 2 ? k12_kernel<T, kFwdFake, 2, 0, 0, false, true, V, W, G> : k12_kernel<T, kFwdFake, 4, 0, 0, false, true, V, W, G>;
+            kern = bits == 2 ? k12_kernel<T, kFwdFake, 2, 0, 0, false, true, V, W, G, false, kTail> : k12_kernel<T, kFwdFake, 4, 0, 0, false, true, V, W, G, false, kTail>;
     } else if (mode == kFwdQuant && (kBig || kVirt || A.group != 128 || !A.scale_f16)) {
-        kern = bits == 2 ? k12_kernel<T, kFwdQuant, 2, 0, 0, true, false, V, W, G> : k12_kernel<T, kFwdQuant, 4, 0, 0, true, false, V, W, G>;
+        kern = bits == 2 ? k12_kernel<T, kFwdQuant, 2, 0, 0, true, false, V, W, G, false, kTail> : k12_kernel<T, kFwdQuant, 4, 0, 0, true, false, V, W, G, false, kTail>;
     } else if constexpr (!kBig) {
         if constexpr (!kVirt) {
             if (mode == kHadamard)
@@ -699,14 +735,14 @@ static hipError_t launch_k12_t(Mode mode, const K12Args &A, int bits, unsigned g
         }
         if (kern) {
         } else if (mode == kFwd)
-            kern = k12_kernel<T, kFwd, 4, 0, 0, true, false, V, W>;
+            kern = k12_kernel<T, kFwd, 4, 0, 0, true, false, V, W, false, false, kTail>;
         else if (mode == kInv)
-            kern = k12_kernel<T, kInv, 4, 0, 0, true, false, V, W>;
+            kern = k12_kernel<T, kInv, 4, 0, 0, true, false, V, W, false, false, kTail>;
         else  // the common activation format: group 128, binary16 scales
             kern = bits == 2 ? k12_kernel<T, kFwdQuant, 2, 16, 1, true, false, false, W> : k12_kernel<T, kFwdQuant, 4, 16, 1, true, false, false, W>;
     }
     if constexpr (!kBig && sizeof(T) == 2) {  // large batches of 16-bit rows: the non-temporal variants
-        if (A.streaming && mode == kFwd) kern = k12_kernel<T, kFwd, 4, 0, 0, true, false, V, W, false, true>;
+        if (A.streaming && mode == kFwd) kern = k12_kernel<T, kFwd, 4, 0, 0, true, false, V, W, false, true, kTail>;
         if constexpr (!kVirt) {
             if (A.streaming && mode == kHadamard) kern = k12_kernel<T, kHadamard, 4, 0, 0, true, false, false, W, false, true>;
         }
@@ -723,13 +759,13 @@ static hipError_t launch_k12_t(Mode mode, const K12Args &A, int bits, unsigned g
     return hipGetLastError();
 }
 
-template <bool kVirt, bool kWide, bool kBig = false>
+template <bool kVirt, bool kWide, bool kBig = false, bool kTail = false>
 static hipError_t launch_k12_dtype(Mode mode, const K12Args &A, int bits, unsigned grid, int dtype, hipStream_t stream)
 {
     switch (dtype) {
-        case BQ_F32: return launch_k12_t<float, kVirt, kWide, kBig>(mode, A, bits, grid, stream);
-        case BQ_F16: return launch_k12_t<__half, kVirt, kWide, kBig>(mode, A, bits, grid, stream);
-        default: return launch_k12_t<bf16_t, kVirt, kWide, kBig>(mode, A, bits, grid, stream);
+        case BQ_F32: return launch_k12_t<float, kVirt, kWide, kBig, kTail>(mode, A, bits, grid, stream);
+        case BQ_F16: return launch_k12_t<__half, kVirt, kWide, kBig, kTail>(mode, A, bits, grid, stream);
+        default: return launch_k12_t<bf16_t, kVirt, kWide, kBig, kTail>(mode, A, bits, grid, stream);
     }
 }
 
@@ -738,5 +774,7 @@ hipError_t launch_k13_dtype(Mode mode, const K12Args &A, int bits, unsigned grid
 // ... and so do those for quantiser groups of more than 128 channels (virt: n < 4096, wide: n = 8192)
 hipError_t launch_k12_big_dtype(Mode mode, const K12Args &A, int bits, unsigned grid, int dtype, bool virt, bool wide,
                                 hipStream_t stream);
+// ... and the variants for a short last block (n < 4096)
+hipError_t launch_k12_tail_dtype(Mode mode, const K12Args &A, int bits, unsigned grid, int dtype, bool big, hipStream_t stream);
 
 }  // namespace bq

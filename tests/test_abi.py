@@ -252,3 +252,26 @@ def test_hadamard_validation():
     assert call(_rows(rows=3, n=4096, dtype=B.BQ_F16, ld=4100)) == 6  # rows not 16-byte aligned
     assert call(_rows(rows=3, n=4096, dtype=B.BQ_F32), y=FAKE + 2) == 4
     assert call(_rows(rows=3, n=48)) == 2
+
+
+def test_calibration_entries_validation():
+    L = B.lib()
+
+    def split(e=FAKE, rows=3, cols=5, p=FAKE, ld=8, dtype=B.BQ_F16, res=FAKE, scratch=FAKE):
+        return L.bq_residual_split(e, rows, cols, p, ld, dtype, res, scratch, None)
+
+    assert split(dtype=B.BQ_F32) == 3
+    assert split(rows=0) == split(cols=0) == split(ld=9) == split(cols=9) == 2
+    assert split(e=None) == split(p=None) == split(res=None) == split(scratch=None) == 1
+    assert split(e=FAKE + 4) == split(p=FAKE + 8) == split(res=FAKE + 2) == split(scratch=FAKE + 4) == 4
+    assert B.bq_residual_scratch_bytes() > 0
+
+    def grad(v=FAKE, vq=FAKE, g=FAKE, f=FAKE, q=B.make_quant(4, 64, "f16"), r=_rows(dtype=B.BQ_F16)):
+        return L.bq_quantiser_grad(v, vq, g, f, ctypes.byref(q), ctypes.byref(r), None)
+
+    assert grad(r=_rows()) == 3
+    assert grad(r=_rows(dtype=B.BQ_F16, ld=136)) == 2
+    assert grad(q=B.make_quant(3, 64, "f16")) == grad(q=B.make_quant(4, 4, "f16")) == grad(q=B.make_quant(4, 256, "f16")) == 2
+    assert grad(v=None) == grad(vq=None) == grad(g=None) == grad(f=None) == 1
+    assert grad(v=FAKE + 8) == grad(vq=FAKE + 8) == grad(g=FAKE + 8) == grad(f=FAKE + 2) == 4
+    assert grad(r=_rows(rows=0, dtype=B.BQ_F16), v=None) == 0

@@ -99,3 +99,32 @@ def test_backward_of_flagged_plans_through_every_route(n, heads, rows, dtype):
     tag = f"n={n} H={heads} T={rows} {dtype}"
     gu.check_rotated(dx, rdx, dtype, tag + " dx")
     gu.check_dtheta(dth, rdth, np.maximum(ab, floor), what=tag + " dtheta")
+
+
+@pytest.mark.parametrize("n,heads,rows", [(256, 1, 1), (256, 1, 17), (256, 1, 15 + 16 * 300), (256, 4, 5), (512, 1, 7), (512, 8, 3), (1024, 2, 3),
+                                          (1024, 1, 1025), (2048, 1, 1), (2048, 1, 2563), (2048, 2, 3)])
+@pytest.mark.parametrize("dtype", ["f16", "f32"])
+def test_short_last_block_of_narrow_transforms(n, heads, rows, dtype):
+    # a block of 4096 elements whose rows are not all there: their lanes read copies and store, count and pack nothing; every
+    # mode, strided rows, in place, flagged plans, groups within a wave and across waves
+    x, th, _ = synth.small_case(n, rows, dtype, heads=heads, seed=700 + n * heads + rows)
+    x64 = synth.to_f64(x, dtype)
+    flagged = th.copy()
+    flagged[:, :3] = np.float32(np.pi / 2)
+    for angles, tag in ((th, ""), (flagged, " flagged")):
+        tag = f"n={n} H={heads} T={rows} {dtype}" + tag
+        ref, back = oracle.forward(x64, angles, n, heads), oracle.inverse(x64, angles, n, heads)
+        for pad, inplace in ((0, False), (8, False), (0, True)):
+            gu.check_rotated(gu.run_transform(x, angles, n, heads, dtype, pad=pad, inplace=inplace), ref, dtype, tag + " fwd")
+            gu.check_rotated(gu.run_transform(x, angles, n, heads, dtype, inverse=True, pad=pad, inplace=inplace), back, dtype, tag + " inv")
+        for bits, group, sd in ((4, 128, "f16"), (2, n, "f32")):
+            codes, scales = gu.run_fwd_quant(x, angles, n, heads, dtype, bits, group, sd)
+            gu.check_fused_codes(codes, scales, ref, bits, group, sd, dtype, tag)
+            c = oracle.unpack_codes(codes, bits)
+            want = synth.cast_storage(oracle.dequantize(c, scales.astype(np.float32), group).astype(np.float64), dtype)
+            u = np.uint16 if dtype != "f32" else np.uint32
+            yq, hist = gu.run_fwd_fakequant(x, angles, n, heads, dtype, bits, group, sd)
+            np.testing.assert_array_equal(yq.view(u), want.view(u), err_msg=tag)
+            np.testing.assert_array_equal(hist, oracle.bin_histogram(c, bits), err_msg=tag)
+            _, hist = gu.run_fwd_fakequant(x, angles, n, heads, dtype, bits, group, sd, want_y=False)
+            np.testing.assert_array_equal(hist, oracle.bin_histogram(c, bits), err_msg=tag)
