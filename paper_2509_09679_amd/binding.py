@@ -119,11 +119,22 @@ def _dtype_code(t) -> int:
     return {torch.float32: BQ_F32, torch.float16: BQ_F16, torch.bfloat16: BQ_BF16}[t.dtype]
 
 
-def _stream_ptr(stream=None) -> int:
-    import torch
+_current_raw_stream = None
 
-    s = torch.cuda.current_stream() if stream is None else stream
-    return int(s.cuda_stream)
+
+def _stream_ptr(stream=None) -> int:
+    """The stream's handle; the current stream's of the current device by default.  torch.cuda.current_stream() builds a Stream
+    object for it, 2.8 us of the 7.7 us of host time of a call; asked for the bare handle torch takes 0.15 us."""
+    global _current_raw_stream
+    if stream is not None:
+        return int(stream.cuda_stream)
+    if _current_raw_stream is None:
+        import torch
+
+        torch.cuda.init()
+        device, raw = torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream
+        _current_raw_stream = lambda: raw(device())  # noqa: E731
+    return _current_raw_stream()
 
 
 def _ptr(t) -> Optional[int]:
