@@ -197,12 +197,14 @@ bq_status bq_kron_inv(const void *y, void *x, const float *q1, int32_t d1, const
 
 /* ---- calibration of a linear layer on 16-bit rows -------------------------------------------- */
 
-/* e: float32 [rows][cols], dense, 16-byte aligned.  Writes e as a sum of 16-bit matrices of type dtype
- * (BQ_F16: 2 pieces of e times a power of two, BQ_BF16: 3 pieces of e) to pieces: [2 or 3][rows][ld], 16-byte
- * aligned, ld >= cols a multiple of 8 (zeros behind the columns), and to result[0] the sum of squares of e (summed
- * in double) and to result[1] the factor that turns a product with the sum of the pieces into one with 2 e.
- * scratch: bq_residual_scratch_bytes() bytes, 8-byte aligned.  The sum of the pieces is within 2^-23 |e| of e,
- * binary16 pieces of entries below 2^-17 of the largest within 2^-40 of the largest. */
+/* e: float32 [rows][cols], dense, 16-byte aligned.  Writes e as a sum of 16-bit matrices of type dtype to pieces:
+ * [2 or 3][rows][ld], 16-byte aligned, ld >= cols a multiple of 8 (zeros behind the columns), and to result[0] the sum of
+ * squares of e (summed in double) and to result[1] the factor that turns a product with the sum into one with 2 e.
+ * scratch: bq_residual_scratch_bytes() bytes, 8-byte aligned.
+ *   BQ_F16:  2 pieces, the sum is piece 0 + 2^-12 piece 1; 0.5 result[1] times it is within 2^-23 |e| of e, for entries below
+ *            2^-28 of the largest within 2^-51 of the largest, and within 2^-151 if the largest is below 2^-100
+ *   BQ_BF16: 3 pieces, the sum is piece 0 + piece 1 + piece 2 = e (|e| between 2^-100 and 2^127, or 0); result[1] is 2
+ * (finite e). */
 size_t bq_residual_scratch_bytes(void);
 bq_status bq_residual_split(const float *e, int64_t rows, int32_t cols, void *pieces, int32_t ld, int32_t dtype,
                             float *result, void *scratch, void *stream);

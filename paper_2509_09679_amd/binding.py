@@ -18,6 +18,7 @@ BQ_F32, BQ_F16, BQ_BF16 = 0, 1, 2
 STATUS_NAMES = {0: "BQ_OK", 1: "BQ_ERR_NULL", 2: "BQ_ERR_SHAPE", 3: "BQ_ERR_DTYPE", 4: "BQ_ERR_ALIGN",
                 5: "BQ_ERR_WORKSPACE", 6: "BQ_ERR_UNSUPPORTED", 7: "BQ_ERR_HIP"}
 DTYPE_CODES = {"f32": BQ_F32, "f16": BQ_F16, "bf16": BQ_BF16}
+RESIDUAL_STEP = {"f16": 2.0 ** -12, "bf16": 1.0}  # bq_residual_split: weight of a piece over the weight of the one before it
 
 EXPORTS = ["bq_plan_bytes", "bq_plan_build", "bq_butterfly_fwd", "bq_butterfly_inv", "bq_butterfly_fwd_quant",
            "bq_butterfly_fwd_fakequant", "bq_hadamard_fwd", "bq_cayley_build", "bq_kron_fwd", "bq_kron_inv",
@@ -215,7 +216,8 @@ def bq_residual_scratch_bytes() -> int:
 
 
 def bq_residual_split(e, pieces, result, scratch, stream=None) -> None:
-    """e: dense float32 [rows, cols]; pieces: [2 (float16) or 3 (bfloat16), rows, ld]; result: float32 [2]; scratch: uint8."""
+    """e: dense float32 [rows, cols]; pieces: [2 (float16) or 3 (bfloat16), rows, ld], piece p with weight
+    RESIDUAL_STEP ** p; result: float32 [2]; scratch: uint8."""
     rows, cols = e.shape
     assert e.is_contiguous() and pieces.is_contiguous() and pieces.shape[0] == (2 if _dtype_code(pieces) == BQ_F16 else 3)
     assert pieces.shape[1] == rows and result.numel() >= 2 and scratch.numel() >= bq_residual_scratch_bytes()

@@ -84,14 +84,16 @@ class ButterflyCalibrator:
         P = torch.empty((2 if X.dtype == torch.float16 else 3, T, ld), dtype=X.dtype, device=dev)
         res = torch.empty(2, dtype=f32, device=dev)
         scratch = torch.empty(B.bq_residual_scratch_bytes(), dtype=torch.uint8, device=dev)
+        step = B.RESIDUAL_STEP["f16" if X.dtype == torch.float16 else "bf16"]
         B.bq_residual_split(E, P, res, scratch)
         del E
         grads = []
         for A, Q, R, spec, transposed in ((self.Wq, Xq, V, self.act, False), (Xq, self.Wq, Wr, self.wgt, True)):
             G = None
-            for piece in P[:, :, :m]:
+            for piece in reversed(P[:, :, :m].unbind(0)):  # the smallest piece first
                 piece = piece.t() if transposed else piece
-                G = torch.mm(piece, A, out_dtype=f32) if G is None else torch.addmm(G, piece, A, out_dtype=f32, out=G)
+                G = torch.mm(piece, A, out_dtype=f32) if G is None else torch.addmm(G, piece, A, beta=step, out_dtype=f32,
+                                                                                     out=G)
             if 8 <= spec.group <= 8192:
                 B.bq_quantiser_grad(R, Q, G, res[1:], B.make_quant(spec.bits, spec.group, spec.scale_dtype),
                                     B.make_rows(R, self.n, 1))

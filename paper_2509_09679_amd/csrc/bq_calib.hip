@@ -4,9 +4,15 @@
 // The gradients multiply the float32 error matrix E with 16-bit operands.  As float32 products they ran at 0.15 PFLOP/s and
 // were 7.4 of the 16.8 ms of a step (16384 rows, n = m = 4096); with E as a sum of 16-bit pieces the same sums run on the
 // 16-bit matrix instructions, which accumulate in float32.  binary16 rows: E times a power of two that puts its largest
-// entry into [2^14, 2^15), in two pieces of 11 bits each (the remainder has a sign of its own, so the sum is within
-// 2^-23 |E| for entries down to 2^-17 of the largest and within 2^-40 of the largest below).  bfloat16 rows: three pieces of
-// 8 bits, no scale, within 2^-25 |E|.
+// entry into [2^14, 2^15), in two pieces of 11 bits each, the second of them 2^12 times the remainder (exact, with a sign of
+// its own, at most 2^15): E is piece 0 + 2^-12 piece 1 within 2^-23 |E| for entries down to 2^-28 of the largest and within
+// 2^-51 of the largest below.  Unscaled, the remainder of a small entry fell on binary16's subnormal grid: tokens at 2^-20 of
+// an outlier token had their gradient off by 2.1e-6, at 2^-24 by 3.3e-5.  Scaled it is 3.5e-7 for every token (median over
+// tokens against 64 bits, 768 rows, n = 1024, m = 512), where float32 products leave 7.5e-7; a third piece changes nothing.
+// bfloat16 rows: three pieces of 8 bits, no scales, their sum is E.
+//
+// The matrix instructions' products of binary16 operands below 2^-14 keep fewer bits: on a layer whose weights all lie there
+// but for one output channel, those channels' gradients are off by 4e-6 (float32 products: 4e-7).
 #include <cmath>
 
 #include "bq_cascade.h"
@@ -91,6 +97,8 @@ __device__ __forceinline__ void unpack4<bf16_t>(uint2 w, float (&v)[4])
     v[2] = __uint_as_float(w.y << 16); v[3] = __uint_as_float(w.y & 0xFFFF0000u);
 }
 
+constexpr float kPieceStep = 4096.0f;  // binary16: every piece is this times what the pieces before it leave
+
 // One read of E, one write of the pieces: bound by HBM.  Workgroups take whole rows; ld is a multiple of 8, so the pieces'
 // rows are 16-byte aligned whatever the number of columns (the products' loads want that), with zeros behind the columns.
 template <typename T>
@@ -153,7 +161,10 @@ __global__ __launch_bounds__(256) void residual_split_kernel(SplitArgs A)
                 float back[4];
                 unpack4<T>(w, back);
 #pragma unroll
-                for (int r = 0; r < 4; ++r) v[r] -= back[r];
+                for (int r = 0; r < 4; ++r) {
+                    v[r] -= back[r];
+                    if (kPieces == 2) v[r] *= kPieceStep;
+                }
             }
         }
     }

@@ -170,3 +170,77 @@ def test_half_step_matches_double(n, m, T, dtype, act, wgt):
         # the scale's own path sums a group's errors onto one entry: at most sqrt(group) / qmax times as much again
         qmax = (1 << (spec[0] - 1)) - 1
         assert np.linalg.norm(d(got) - want) <= room * (1 + np.sqrt(spec[1]) / qmax), np.linalg.norm(d(got) - want) / np.linalg.norm(want)
+
+
+def _spread(rng, shape, decades, largest):
+    """Values of both signs whose magnitudes spread evenly over the logarithm down to 2^-decades of the largest, some zero."""
+    e = np.exp2(-rng.uniform(0.0, decades, shape)) * np.where(rng.random(shape) < 0.5, -1.0, 1.0)
+    e[rng.random(shape) < 0.05] = 0.0
+    e.flat[0] = 1.0
+    return (e * largest).astype(np.float32)
+
+
+@gpu
+@pytest.mark.parametrize("rows,cols,ld", [(1, 1, 8), (3, 97, 104), (33, 96, 96), (33, 96, 112), (2101, 5, 8), (7, 1030, 1032)])
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("largest", [1.0, np.float32(2.0) - np.float32(2.0 ** -23), 3e13, 2.0 ** -60, 2.0 ** -110, 0.0])
+def test_residual_split_against_its_stated_bound(rows, cols, ld, dtype, largest):
+    # every entry of E against the weighted sum of its pieces; odd sizes: quads that straddle rows, zeros behind the columns,
+    # more rows than workgroups, entries down to 2^-60 of the largest, a largest below the scale's clamp, a matrix of zeros
+    import torch
+    from paper_2509_09679_amd import binding as B
+
+    if dtype == "bf16" and 0.0 < largest < 2.0 ** -40:
+        pytest.skip("bfloat16 pieces may be subnormal")
+    dev = "cuda:0"
+    e = _spread(np.random.default_rng(rows * 1000 + cols), (rows, cols), 60.0, np.float64(largest))
+    E = torch.from_numpy(e).to(dev)
+    P = torch.full((2 if dtype == "f16" else 3, rows, ld), 7.0, dtype=torch.float16 if dtype == "f16" else torch.bfloat16, device=dev)
+    res = torch.full((2,), -1.0, dtype=torch.float32, device=dev)
+    B.bq_residual_split(E, P, res, torch.empty(B.bq_residual_scratch_bytes(), dtype=torch.uint8, device=dev))
+    p, (total, factor) = P.double().cpu().numpy(), res.double().cpu().numpy()
+    assert np.all(p[:, :, cols:] == 0.0)
+    got = sum(p[i, :, :cols] * B.RESIDUAL_STEP[dtype] ** i for i in range(len(p))) * (0.5 * factor)
+    want = e.astype(np.float64)
+    top = np.abs(want).max()
+    bound = np.maximum(2.0 ** -23 * np.abs(want), 2.0 ** -51 * top if top >= 2.0 ** -100 else 2.0 ** -151) if dtype == "f16" else 0.0
+    assert np.all(np.abs(got - want) <= bound), np.max(np.abs(got - want) / np.maximum(np.abs(want), 1e-300))
+    # a double sum of exact squares, rounded once
+    assert abs(total - (want ** 2).sum()) <= 2.0 ** -23 * (want ** 2).sum() + 2.0 ** -149
+
+
+@gpu
+@pytest.mark.parametrize("tokens,channels", [(24, 0), (0, 6)])
+def test_small_rows_beside_a_large_one_keep_their_gradient(tokens, channels):
+    # one token 2^24 times as large as the others, or one output channel 2^6 times (2^-6 of it is where binary16 weights become
+    # subnormal): the products with the error matrix must leave the other tokens' and channels' gradients at least as close to
+    # double as float32 products do
+    import torch
+    from paper_2509_09679_amd import binding as B
+    from paper_2509_09679_amd.calibration import ButterflyCalibrator, QuantSpec
+
+    dev, n, m, T = "cuda:0", 1024, 256, 200
+    gen = torch.Generator().manual_seed(5)
+    X, W = torch.randn((T, n), generator=gen), 0.02 * torch.randn((m, n), generator=gen)
+    X[0] *= 2.0 ** 11
+    X[1:] *= 2.0 ** (11 - tokens)
+    W[1:] *= 2.0 ** -channels
+    X, W = X.half().to(dev), W.half().to(dev)
+    theta = 0.3 * (torch.rand((1, 10, n // 2), generator=gen) * 2 - 1).to(dev)
+    act, wgt = (4, 128, "f32"), (2, 128, "f32")
+    cal = ButterflyCalibrator(W, QuantSpec(*act), QuantSpec(*wgt), theta=theta)
+    cal.loss_and_grad(X)
+    V, Wr = torch.empty_like(X), torch.empty_like(W)
+    B.bq_butterfly_fwd(X, V, cal.plan, B.make_rows(X, n, 1))
+    B.bq_butterfly_fwd(W, Wr, cal.plan, B.make_rows(W, n, 1))
+    _, dV, dWr = cal._half_step(X, cal.Xq, V, Wr)
+    Xq, Wq = cal.Xq, cal.Wq
+    E32 = (Xq.float() @ Wq.float().t()) - (X.float() @ W.float().t())
+    d = lambda t: t.double().cpu().numpy()
+    E = d(Xq) @ d(Wq).T - d(X) @ d(W).T
+    for got, R, Q, G32, G, spec in ((dV, V, Xq, 2.0 * (E32 @ Wq.float()), 2.0 * E @ d(Wq), act),
+                                    (dWr, Wr, Wq, 2.0 * (E32.t() @ Xq.float()), 2.0 * E.T @ d(Xq), wgt)):
+        want = _through_quantiser(d(R), d(Q), G, spec[0], spec[1])
+        plain = cal._through_quantiser(R.float(), Q.float(), G32, QuantSpec(*spec))
+        err = [float(np.linalg.norm((d(t) - want)[1:]) / np.linalg.norm(want[1:])) for t in (got, plain)]
+        assert err[0] <= err[1], err
