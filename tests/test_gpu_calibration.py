@@ -182,18 +182,16 @@ def _spread(rng, shape, decades, largest):
 
 @gpu
 @pytest.mark.parametrize("rows,cols,ld", [(1, 1, 8), (3, 97, 104), (33, 96, 96), (33, 96, 112), (2101, 5, 8), (7, 1030, 1032)])
-@pytest.mark.parametrize("dtype", ["f16", "bf16"])
-@pytest.mark.parametrize("largest", [1.0, np.float32(2.0) - np.float32(2.0 ** -23), 3e13, 2.0 ** -60, 2.0 ** -110, 0.0])
+@pytest.mark.parametrize("dtype,largest", [(t, v) for t in ("f16", "bf16") for v in (1.0, 2.0 - 2.0 ** -23, 3e13, 0.0)] +
+                         [("f16", 2.0 ** -60), ("f16", 2.0 ** -110)])  # (bfloat16: no subnormal pieces)
 def test_residual_split_against_its_stated_bound(rows, cols, ld, dtype, largest):
     # every entry of E against the weighted sum of its pieces; odd sizes: quads that straddle rows, zeros behind the columns,
     # more rows than workgroups, entries down to 2^-60 of the largest, a largest below the scale's clamp, a matrix of zeros
     import torch
     from paper_2509_09679_amd import binding as B
 
-    if dtype == "bf16" and 0.0 < largest < 2.0 ** -40:
-        pytest.skip("bfloat16 pieces may be subnormal")
     dev = "cuda:0"
-    e = _spread(np.random.default_rng(rows * 1000 + cols), (rows, cols), 60.0, np.float64(largest))
+    e = _spread(np.random.default_rng(rows * 1000 + cols), (rows, cols), 60.0, largest)
     E = torch.from_numpy(e).to(dev)
     P = torch.full((2 if dtype == "f16" else 3, rows, ld), 7.0, dtype=torch.float16 if dtype == "f16" else torch.bfloat16, device=dev)
     res = torch.full((2,), -1.0, dtype=torch.float32, device=dev)
@@ -207,6 +205,47 @@ def test_residual_split_against_its_stated_bound(rows, cols, ld, dtype, largest)
     assert np.all(np.abs(got - want) <= bound), np.max(np.abs(got - want) / np.maximum(np.abs(want), 1e-300))
     # a double sum of exact squares, rounded once
     assert abs(total - (want ** 2).sum()) <= 2.0 ** -23 * (want ** 2).sum() + 2.0 ** -149
+
+
+@gpu
+@pytest.mark.parametrize("n,rows,group", [(8, 37, 8), (64, 33, 64), (512, 5, 512), (1024, 3, 16), (1024, 7, 1024), (2048, 3, 2048),
+                                          (4096, 5, 4096), (8192, 3, 128), (8192, 3, 8192), (8192, 2, 2048), (16384, 2, 8192)])
+@pytest.mark.parametrize("dtype,bits", [("f16", 4), ("bf16", 2)])
+def test_quantiser_grad_entry_by_entry(n, rows, group, dtype, bits):
+    # groups of one thread, within a wave, across 2 .. 16 waves; short last workgroups; the first of equal maxima (in one thread,
+    # in neighbouring lanes, in different waves, of either sign); a group of zeros
+    import torch
+    from paper_2509_09679_amd import binding as B
+
+    dev = "cuda:0"
+    rng = np.random.default_rng(n + rows + group)
+    qmax = (1 << (bits - 1)) - 1
+    t = torch.float16 if dtype == "f16" else torch.bfloat16
+    v = rng.standard_normal((rows, n))
+    first = v[:, :group]  # a view: the first group of each row
+    first[0, rng.integers(group)] = 6.0
+    for at, sign in ((group // 2, 1.0), (group // 2 + 1, -1.0), (group - 1, 1.0)):  # equal maxima, the lowest position counts
+        first[1, at] = 6.0 * sign
+    v[-1, n - group:] = 0.0
+    V = torch.from_numpy(v).to(t)
+    v = V.double().numpy()
+    s = np.abs(v).reshape(rows, n // group, group).max(axis=2, keepdims=True) / qmax
+    with np.errstate(invalid="ignore", divide="ignore"):
+        q = np.where(s > 0, s * np.rint(v.reshape(rows, n // group, group) / s), 0.0).reshape(rows, n)
+    Q = torch.from_numpy(q).to(t)
+    q = Q.double().numpy()
+    g = rng.standard_normal((rows, n)).astype(np.float32)
+    G, factor = torch.from_numpy(g).to(dev), torch.tensor([0.375], dtype=torch.float32, device=dev)
+    B.bq_quantiser_grad(V.to(dev), Q.to(dev), G, factor, B.make_quant(bits, group, "f16"), B.make_rows(V, n, 1))
+    g = 0.375 * g.astype(np.float64)
+    want = _through_quantiser(v, q, g, bits, group)
+    # float32 sums of the group's terms: eight in a thread, then pairwise over lanes and in turn over up to 16 waves; the scale,
+    # its reciprocal and the difference are rounded once each
+    with np.errstate(invalid="ignore", divide="ignore"):
+        terms = np.where(s > 0, np.abs((g * (q - v)).reshape(rows, n // group, group)) / s, 0.0).sum(axis=2, keepdims=True)
+    room = 40 * 2.0 ** -24 * np.broadcast_to(terms, (rows, n // group, group)).reshape(rows, n) / qmax + 2.0 ** -23 * np.abs(want)
+    got = G.double().cpu().numpy()
+    assert np.all(np.abs(got - want) <= room), np.max(np.abs(got - want) / room)
 
 
 @gpu
