@@ -28,8 +28,12 @@ __global__ void plan_header_kernel(PlanHeader *hdr, int n, int heads, int k)
 // forward cascade in threads 0 .. 127 and the transposed one in threads 128 .. 255, partners' scales exchanged through
 // LDS.  At n = 4096 that is 128 workgroups of 576 evaluations each (1.5 times the angles there are).  Bound by the
 // latency of the double-precision sine and cosine, three rounds of them.  One workgroup per head and direction walking
-// all layers with a barrier each, which this replaces, evaluated every angle four times on two compute units.  Plan of
-// one head, both launches, back to back: n = 4096 80 -> 7.7 us, n = 8192 165 -> 9.9, n = 16384 345 -> 12.4.
+// all layers with a barrier each, which this replaces, evaluated every angle four times on two compute units.
+// A high group's elements are 2^kl apart, so neighbouring groups share the cache lines they read and write: workgroups
+// (dealt to the eight dies in turn) are numbered so that neighbouring groups are on the same die, whose L2 then puts the lines
+// together.  In launch order many heads were slower than the kernel this replaces: 512 heads of 4096 396 us before, 606
+// in launch order, 319 this way; 512 heads of 8192 897, 1209, 669.  One head, both launches, back to back: n = 4096
+// 80 -> 7.1 us, n = 8192 163 -> 8.9, n = 16384 342 -> 10.9.
 constexpr int kPlanThreads = 256;
 constexpr int kPlanMaxGroup = 128;  // elements of a group: k <= 7 has one group per head, k <= 14 groups of <= 2^7
 
@@ -50,8 +54,10 @@ __global__ __launch_bounds__(kPlanThreads) void plan_table_kernel(PlanTableArgs 
     __shared__ double D[2][kPlanMaxGroup];
     const int n = A.n, k = A.k, kl = A.kl, kh = k - kl;
     const int groups = A.low_groups + A.high_groups;
-    const int head = blockIdx.x / groups;
-    int g = blockIdx.x % groups;
+    const int die = blockIdx.x & 7, each = gridDim.x >> 3, extra = gridDim.x & 7;
+    const int place = die * each + (die < extra ? die : extra) + (int)(blockIdx.x >> 3);
+    const int head = place / groups;
+    int g = place % groups;
     const bool low = g < A.low_groups;
     if (!low) g -= A.low_groups;
     const int own = low ? kl : kh, first = low ? 0 : kl;     // own layers first + 1 .. first + own
