@@ -117,6 +117,7 @@ __global__ __launch_bounds__(kGenThreads) void generic_kernel(GenArgs A)
             for (int g = threadIdx.x; g < n_groups; g += kGenThreads) {
                 const float *v = buf + (size_t)g * group;
                 float amax = 0.0f;
+#pragma unroll 8
                 for (int j = 0; j < group; ++j) amax = fmaxf(amax, fabsf(v[j]));
                 float inv;
                 const float s = group_scale(amax, qmax, A.scale_f16 != 0, &inv);
