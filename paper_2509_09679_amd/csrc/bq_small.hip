@@ -9,8 +9,8 @@
 // over the batch with the same coefficients.  Two independent row groups are processed per iteration and the next two are
 // prefetched meanwhile, so that four 16-byte loads per lane are in flight.
 //
-// If the plan flags the scale-deferred tables as unusable, rows go through plain (cos, sin) rotations
-// with the twiddles re-read from the plan (slow, rare).
+// If the plan flags the scale-deferred tables as unusable, rows go through plain (cos, sin) rotations (rare): the transforms
+// hold them in registers, the quantisers, which are short of those, re-read them from the plan for every row.
 #include "bq_cascade.h"
 
 namespace bq {
@@ -33,12 +33,16 @@ struct SmallArgs {
     int group, scale_f16;
 };
 
-// The forward cascade in plain (cos, sin) rotations held in registers, rounded as the kernel for any n rounds them:
+// The cascade in plain (cos, sin) rotations held in registers.
+// kOwn: rounded as slow_small() rounds them, an element's own product inside the fused operation:
+//   y_a = fma(c, x_a, -(s x_b)),  y_b = fma(c, x_b, s x_a)   (transposed: the signs of s swap)
+// i.e. fma(w1, own, w2 partner) in either lane of a pair.  Else (forward only) as the kernel for any n rounds them:
 //   y_a = fma(c, x_a, -(s x_b)),  y_b = fma(s, x_a, c x_b)
-// i.e. fma(w1, x_a, w2 x_b) in either lane of a pair, with the lane's own (w1, w2).
-template <int K>
+// i.e. fma(w1, x_a, w2 x_b), with the lane's own (w1, w2).
+template <int K, bool kInverse, bool kOwn>
 struct PlainCascade {
-    float rc[3][4], rs[3][4];        // layers 1..3: (cos, sin) of the thread's four pairs
+    static_assert(kOwn || !kInverse, "");
+    float rc[3][4], rs[3][4];        // layers 1..3: cos and (transposed: minus) sin of the thread's four pairs
     float w1[4][8], w2[4][8];        // layers 4..K
     bool upper[4];                   // this lane holds the upper elements of the layer's pairs
     __device__ __forceinline__ void load(const float2 *cs_head, int idx)
@@ -56,7 +60,7 @@ struct PlainCascade {
                 if (!(r & (1 << j))) {
                     const float2 w = entry(idx + r, j + 1);
                     rc[j][q] = w.x;
-                    rs[j][q] = w.y;
+                    rs[j][q] = kInverse ? -w.y : w.y;
                     ++q;
                 }
         }
@@ -66,8 +70,8 @@ struct PlainCascade {
 #pragma unroll
             for (int r = 0; r < 8; ++r) {
                 const float2 w = entry(idx + r, 4 + j);
-                w1[j][r] = upper[j] ? w.y : w.x;
-                w2[j][r] = upper[j] ? w.x : -w.y;
+                w1[j][r] = !kOwn && upper[j] ? w.y : w.x;
+                w2[j][r] = kOwn ? (upper[j] != kInverse ? w.y : -w.y) : (upper[j] ? w.x : -w.y);
             }
         }
     }
@@ -80,7 +84,7 @@ struct PlainCascade {
             if (!(r & (1 << J))) {
                 const float xa = u[r], xb = u[r | (1 << J)];
                 u[r] = __builtin_fmaf(rc[J][q], xa, -(rs[J][q] * xb));
-                u[r | (1 << J)] = __builtin_fmaf(rs[J][q], xa, rc[J][q] * xb);
+                u[r | (1 << J)] = kOwn ? __builtin_fmaf(rc[J][q], xb, rs[J][q] * xa) : __builtin_fmaf(rs[J][q], xa, rc[J][q] * xb);
                 ++q;
             }
     }
@@ -90,19 +94,29 @@ struct PlainCascade {
 #pragma unroll
         for (int r = 0; r < 8; ++r) {
             const float p = dpp_read<CTRL>(u[r]);
-            const float xa = upper[J] ? p : u[r], xb = upper[J] ? u[r] : p;
+            const float xa = !kOwn && upper[J] ? p : u[r], xb = !kOwn && upper[J] ? u[r] : p;
             u[r] = __builtin_fmaf(w1[J][r], xa, w2[J][r] * xb);
         }
     }
     __device__ __forceinline__ void run(float (&u)[8]) const
     {
-        pairs<0>(u);
-        pairs<1>(u);
-        pairs<2>(u);
-        if (K >= 4) lanes<0, 0xB1>(u);   // quad_perm [1,0,3,2]
-        if (K >= 5) lanes<1, 0x4E>(u);   // quad_perm [2,3,0,1]
-        if (K >= 6) lanes<2, 0x141>(u);  // row_half_mirror
-        if (K >= 7) lanes<3, 0x128>(u);  // row_ror:8
+        if (!kInverse) {
+            pairs<0>(u);
+            pairs<1>(u);
+            pairs<2>(u);
+            if (K >= 4) lanes<0, 0xB1>(u);   // quad_perm [1,0,3,2]
+            if (K >= 5) lanes<1, 0x4E>(u);   // quad_perm [2,3,0,1]
+            if (K >= 6) lanes<2, 0x141>(u);  // row_half_mirror
+            if (K >= 7) lanes<3, 0x128>(u);  // row_ror:8
+        } else {
+            if (K >= 7) lanes<3, 0x128>(u);
+            if (K >= 6) lanes<2, 0x141>(u);
+            if (K >= 5) lanes<1, 0x4E>(u);
+            if (K >= 4) lanes<0, 0xB1>(u);
+            pairs<2>(u);
+            pairs<1>(u);
+            pairs<0>(u);
+        }
     }
 };
 
@@ -210,9 +224,9 @@ __global__ __launch_bounds__(kSmallThreads) void small_kernel(SmallArgs A)
     };
 
     if (grp_first >= A.n_groups) return;
-    if constexpr (kPlain) {
-        PlainCascade<K> pc;
-        pc.load(cs_head, idx);
+    constexpr bool kTransform = kMode == kFwd || kMode == kInv;
+    auto plain_rows = [&](auto cascade) {
+        cascade.load(cs_head, idx);
         Raw8 raw0 = load_row(grp_first);
         Raw8 raw1 = load_row(grp_first + grp_step);
         for (int64_t g = grp_first; g < A.n_groups; g += grp_step) {
@@ -220,13 +234,20 @@ __global__ __launch_bounds__(kSmallThreads) void small_kernel(SmallArgs A)
             unpack8(raw0, u, (const T *)nullptr);
             raw0 = raw1;
             raw1 = load_row(g + 2 * grp_step);
-            pc.run(u);
+            cascade.run(u);
             finish(u, g);
         }
+    };
+    if constexpr (kPlain) {
+        plain_rows(PlainCascade<K, false, false>());
         flush_bins();
         return;
     }
-    if (!fast) {  // rare
+    if constexpr (kTransform) {
+        // (re-read for every row, 20011 rows of 12 x 64 took 213 us, 2.5 times as long as in the LDS kernel these widths had)
+        if (!fast) return plain_rows(PlainCascade<K, kInverse, true>());
+    }
+    if (!kTransform && !fast) {  // rare
         for (int64_t g = grp_first; g < A.n_groups; g += grp_step) {
             float u[8];
             unpack8(load_row(g), u, (const T *)nullptr);

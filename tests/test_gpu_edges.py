@@ -128,3 +128,21 @@ def test_short_last_block_of_narrow_transforms(n, heads, rows, dtype):
             np.testing.assert_array_equal(hist, oracle.bin_histogram(c, bits), err_msg=tag)
             _, hist = gu.run_fwd_fakequant(x, angles, n, heads, dtype, bits, group, sd, want_y=False)
             np.testing.assert_array_equal(hist, oracle.bin_histogram(c, bits), err_msg=tag)
+
+
+@pytest.mark.parametrize("n,heads,rows", [(8, 1, 300), (8, 3, 77), (16, 5, 40), (32, 3, 33), (64, 12, 700), (128, 1, 200), (128, 20, 60),
+                                          (128, 32, 40), (8192, 1, 3), (8192, 2, 2)])
+@pytest.mark.parametrize("dtype", ["f16", "bf16", "f32"])
+def test_transforms_of_flagged_plans(n, heads, rows, dtype):
+    # n = 8 .. 128: rotations held in registers, with idle lanes and several row groups per workgroup; n = 8192: the layers
+    # through LDS, several pairs per thread at a time
+    x, th, _ = synth.small_case(n, rows, dtype, heads=heads, seed=1000 + n * heads)
+    th = th.copy()
+    th[:, :3] = np.float32(np.pi / 2)
+    x64 = synth.to_f64(x, dtype)
+    tag = f"n={n} H={heads} T={rows} {dtype}"
+    for pad in (0, 8):
+        gu.check_rotated(gu.run_transform(x, th, n, heads, dtype, pad=pad), oracle.forward(x64, th, n, heads), dtype, tag + " fwd")
+        gu.check_rotated(gu.run_transform(x, th, n, heads, dtype, inverse=True, pad=pad), oracle.inverse(x64, th, n, heads), dtype, tag + " inv")
+    codes, scales = gu.run_fwd_quant(x, th, n, heads, dtype, 4, min(n, 128), "f16")
+    gu.check_fused_codes(codes, scales, oracle.forward(x64, th, n, heads), 4, min(n, 128), "f16", dtype, tag)
