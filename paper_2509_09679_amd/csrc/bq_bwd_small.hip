@@ -200,7 +200,7 @@ struct SmallBwdGrid {
 static SmallBwdGrid small_bwd_grid(const Shape &s)
 {
     SmallBwdGrid g;
-    g.t = small_tiling(s.n, s.heads, true);
+    g.t = small_tiling(s.n, s.heads, true, true);
     g.n_groups = (s.rows + g.t.rows_per_block - 1) / g.t.rows_per_block;
     // 2048 waves, eight per compute unit (all that fit with these kernels' registers), whatever the workgroup width;
     // the slot count (partial sums to write and to add) stays bounded
@@ -216,7 +216,7 @@ static SmallBwdGrid small_bwd_grid(const Shape &s)
 bool small_bwd_supported(const void *x, const void *dy, const void *dx, const float *dtheta, const Shape &s)
 {
     if (s.k < 3 || s.k > 7 || dtheta == nullptr || s.rows == 0) return false;
-    if (small_tiling(s.n, s.heads, true).slices > kSbMaxSlices) return false;
+    if (small_tiling(s.n, s.heads, true, true).slices > kSbMaxSlices) return false;
     const int vec = s.dtype == BQ_F32 ? 4 : 8;
     if (((uintptr_t)x & 15) || ((uintptr_t)dy & 15) || (dx && ((uintptr_t)dx & 15))) return false;
     if ((s.ld_x % vec) || (s.ld_y % vec)) return false;

@@ -187,7 +187,7 @@ struct SmallTiling {
     int rows_per_block;  // whole rows of a workgroup, 1 if slices > 1
     int slices;          // workgroups that share a row
 };
-SmallTiling small_tiling(int n, int heads, bool backward);
+SmallTiling small_tiling(int n, int heads, bool backward, bool few_workgroups);
 // backward for n = 8 .. 128 (bq_bwd_small.hip)
 bool small_bwd_supported(const void *x, const void *dy, const void *dx, const float *dtheta, const Shape &s);
 size_t small_bwd_workspace_bytes(const Shape &s);

@@ -314,12 +314,17 @@ static void (*pick_small_k(int k, Mode mode, int bits, bool plain))(SmallArgs)
 // idle lanes went to the LDS kernel for any n before: 20011 fp16 rows of 12 x 64, forward, 81 -> 13 us, and
 // 574 -> 40 us backward.  The backward kernel holds eight waves per compute unit, of which three-wave workgroups fill six:
 // they count as four there (10000 rows of 12 x 128: 80 us in three-wave workgroups, 62 us in single-wave ones).
-SmallTiling small_tiling(int n, int heads, bool backward)
+//
+// At equal shares three waves come last unless few_workgroups: 2048 waves are 682 workgroups of three, of which a compute unit
+// gets two or three (87382 rows of 12 x 128: float32 forward 226 us in workgroups of three waves, 211 us in slices of one;
+// fp16 INT4 83 and 75).  A call that counts bins ends with one atomic per bin and workgroup and wants few of them (2731
+// rows, fp16 INT4 43 and 108 us, float32 19 and 35), float32 rows up to 2^26 elements (87382 rows 239 and 225).
+SmallTiling small_tiling(int n, int heads, bool backward, bool few_workgroups)
 {
     const int64_t width = (int64_t)n * heads;
     SmallTiling best{};
     int64_t best_lanes = 0, best_used = 0;  // lanes spent on so many elements
-    for (int waves = 4; waves >= 1; --waves) {
+    for (const int waves : {4, few_workgroups ? 3 : 2, few_workgroups ? 2 : 1, few_workgroups ? 1 : 3}) {
         SmallTiling t{};
         t.threads = waves * 64;
         const int room = t.threads * 8;
@@ -377,7 +382,8 @@ hipError_t launch_small(Mode mode, const void *in, void *out, const PlanView &pv
     A.ld_out = s.ld_y;
     A.heads = s.heads;
     A.width = s.n * s.heads;
-    SmallTiling t = small_tiling(s.n, s.heads, false);
+    const bool counts = mode == kFwdFake && q->hist != nullptr;
+    SmallTiling t = small_tiling(s.n, s.heads, false, counts && (s.dtype != BQ_F32 || s.rows * A.width < (int64_t)1 << 26));
     // the plain transforms of 16-bit rows stream fastest from single-wave workgroups (measured: up to 20 % over
     // four-wave ones at the same number of waves; float32 rows and the quantisers prefer the wider ones)
     if ((mode == kFwd || mode == kInv) && s.dtype != BQ_F32 && (A.width % 512 == 0 || 512 % A.width == 0))
