@@ -207,6 +207,10 @@ __device__ __forceinline__ void slow_cascade(float (&u)[kHalves][8], float *buf,
                                              int n_log, int row_mask = 0, int head0 = 0)
 {
     constexpr int kPoints = kHalves * kN;
+    // n = 8192: the loads of four pairs in front of the first store.  Pair by pair a flagged plan's call took 40 % longer than
+    // with the 1024 threads this width had before (one row 17.2 us, 512 rows 34.8), this way 12.9 and 26.0.  All eight pairs
+    // at once 13.8 and 27.1; at n <= 4096 two pairs already cost 38 spilled registers.
+    constexpr int kBatch = kHalves == 2 ? 4 : 1;
     __syncthreads();
 #pragma unroll
     for (int h = 0; h < kHalves; ++h)
@@ -217,17 +221,29 @@ __device__ __forceinline__ void slow_cascade(float (&u)[kHalves][8], float *buf,
     for (int step = 0; step < n_log; ++step) {
         const int i = kInverse ? (n_log - step) : (step + 1);
         const int h = 1 << (i - 1);
-        for (int p = threadIdx.x; p < kPoints / 2; p += kThreads) {
-            const int a = ((p >> (i - 1)) << i) | (p & (h - 1));
-            const int hd = (head0 + (a & row_mask)) >> n_log;
-            const float2 w = cs[((size_t)hd * n_log + (i - 1)) * half_n + (p & (half_n - 1))];
-            const float xa = buf[a], xb = buf[a + h];
-            if (!kInverse) {
-                buf[a] = __builtin_fmaf(w.x, xa, -(w.y * xb));
-                buf[a + h] = __builtin_fmaf(w.y, xa, w.x * xb);
-            } else {
-                buf[a] = __builtin_fmaf(w.x, xa, w.y * xb);
-                buf[a + h] = __builtin_fmaf(w.x, xb, -(w.y * xa));
+        for (int p0 = threadIdx.x; p0 < kPoints / 2; p0 += kBatch * kThreads) {
+            float2 w[kBatch];
+            float xa[kBatch], xb[kBatch];
+#pragma unroll
+            for (int j = 0; j < kBatch; ++j) {
+                const int p = p0 + j * kThreads;
+                const int a = ((p >> (i - 1)) << i) | (p & (h - 1));
+                const int hd = (head0 + (a & row_mask)) >> n_log;
+                w[j] = cs[((size_t)hd * n_log + (i - 1)) * half_n + (p & (half_n - 1))];
+                xa[j] = buf[a];
+                xb[j] = buf[a + h];
+            }
+#pragma unroll
+            for (int j = 0; j < kBatch; ++j) {
+                const int p = p0 + j * kThreads;
+                const int a = ((p >> (i - 1)) << i) | (p & (h - 1));
+                if (!kInverse) {
+                    buf[a] = __builtin_fmaf(w[j].x, xa[j], -(w[j].y * xb[j]));
+                    buf[a + h] = __builtin_fmaf(w[j].y, xa[j], w[j].x * xb[j]);
+                } else {
+                    buf[a] = __builtin_fmaf(w[j].x, xa[j], w[j].y * xb[j]);
+                    buf[a + h] = __builtin_fmaf(w[j].x, xb[j], -(w[j].y * xa[j]));
+                }
             }
         }
         __syncthreads();
