@@ -72,9 +72,41 @@ int k12_block_rows(const Shape &s)
     return s.n < kN && width < kN ? (int)(kN / width) : 1;
 }
 
+// Elements of a batch from which its short last block is a launch of its own behind the whole blocks, which then run in the
+// kernels without the check: the second launch costs 5 to 6 us, the check a share of the batch.  Measured at n = 256, 1024 and
+// 2048, 2^18 to 2^30 elements, as one launch / as two:
+//   codes of float32 rows, groups of up to 128    2^25 43 / 43 us, 2^26 75 / 68, 2^28 285 / 238
+//   transforms of 16-bit rows                     2^26 52 / 56, 2^28 202 / 194 (forward), 191 / 190 (inverse), 2^30 789 / 752, 752 / 740
+//   quantisers of 16-bit rows, groups above 128   2^26 65 / 67, 2^28 242 / 220, 2^30 939 / 820
+//   everything else                               2^28 -2 to +6 %, 2^30 -4 to +1 %
+static int64_t short_block_apart(Mode mode, int dtype, bool big)
+{
+    if (dtype == BQ_F32) return mode == kFwdQuant && !big ? (int64_t)1 << 26 : (int64_t)1 << 29;
+    return mode == kFwd || mode == kInv || big ? (int64_t)1 << 28 : (int64_t)1 << 29;
+}
+
 hipError_t launch_k12(Mode mode, const void *in, void *out, const PlanView &pv, const Shape &s,
                       const QuantArgs *q, hipStream_t stream)
 {
+    const bool virt = s.n < kN, wide = s.n > kN;
+    const bool big = (mode == kFwdQuant || mode == kFwdFake) && q->group > 128;
+    const int64_t width = (int64_t)s.n * s.heads;
+    const int block_rows = k12_block_rows(s);  // rows of the caller per kernel row
+    if (s.rows > block_rows && s.rows % block_rows != 0 && s.rows * width >= short_block_apart(mode, s.dtype, big)) {
+        const size_t isz = s.dtype == BQ_F32 ? 4 : 2;
+        Shape whole = s, rest = s;
+        rest.rows = s.rows % block_rows;
+        whole.rows = s.rows - rest.rows;
+        hipError_t e = launch_k12(mode, in, out, pv, whole, q, stream);
+        if (e != hipSuccess) return e;
+        QuantArgs qr = q ? *q : QuantArgs{};
+        if (mode == kFwdQuant) {
+            qr.codes += (size_t)whole.rows * (width * q->bits / 8);
+            qr.scales = (char *)q->scales + (size_t)whole.rows * (width / q->group) * (q->scale_f16 ? 2 : 4);
+        }
+        return launch_k12(mode, (const char *)in + (size_t)whole.rows * s.ld_x * isz, out ? (char *)out + (size_t)whole.rows * s.ld_y * isz : nullptr,
+                          pv, rest, q ? &qr : nullptr, stream);
+    }
     K12Args A{};
     A.in = in;
     A.out = out;
@@ -82,8 +114,6 @@ hipError_t launch_k12(Mode mode, const void *in, void *out, const PlanView &pv, 
     A.fd = mode == kInv ? pv.fd_inv : pv.fd_fwd;
     A.cs = pv.cs;
     A.plan = pv.ref;
-    const bool virt = s.n < kN, wide = s.n > kN;
-    const int block_rows = k12_block_rows(s);  // rows of the caller per kernel row
     A.rows = (s.rows + block_rows - 1) / block_rows;
     A.tail_rows = (int)(s.rows % block_rows);
     A.ld_in = s.ld_x * block_rows;
@@ -94,7 +124,6 @@ hipError_t launch_k12(Mode mode, const void *in, void *out, const PlanView &pv, 
     A.n_log = s.k;
     // beyond the 256 MB of the memory-side cache neither input nor output is found in a cache again
     A.streaming = (int64_t)s.rows * s.n * s.heads * (s.dtype == BQ_F32 ? 4 : 2) >= ((int64_t)256 << 20) ? 1 : 0;
-    const int64_t width = (int64_t)s.n * s.heads;
     A.heads = virt ? (width > kN ? (int)(width / kN) : 1) : s.heads;  // virt: 4096-element blocks per row
     A.row_log = virt ? (width >= kN ? kK : ilog2_exact((int)width)) : 0;
     int bits = 4;
@@ -123,7 +152,6 @@ hipError_t launch_k12(Mode mode, const void *in, void *out, const PlanView &pv, 
     int64_t per_head = target / A.heads > 0 ? target / A.heads : 1;
     if (per_head > A.rows) per_head = A.rows;
     const unsigned grid = split_rows(A, per_head);
-    const bool big = (mode == kFwdQuant || mode == kFwdFake) && q->group > 128;
     if (A.tail_rows) return launch_k12_tail_dtype(mode, A, bits, grid, s.dtype, big, stream);
     if (big)
         return launch_k12_big_dtype(mode, A, bits, grid, s.dtype, virt, wide, stream);

@@ -85,10 +85,10 @@ struct K12Args {
     // (row_log = log2 of the row width; ld_in / ld_out are the strides between blocks, sub_ld_* the caller's
     // strides, heads = 1).  Wider rows: block `head` of the heads = width / 4096 blocks of a row (row_log = 12).
     // tail_rows != 0: the last of the `rows` blocks has only so many of the caller's rows.  Its missing rows are read as
-    // copies of its first one and not stored.  (kTail variants: in the kernels for whole
-    // blocks the check cost 1 to 5 %, and 14 % in one.  As rows of their own they went through the kernel for any n, a launch of
-    // 10 to 95 us behind this one: 2001 rows of 2048, float32 inverse 34 -> 11 us, fp16 INT4
-    // 36 -> 14 us.)
+    // copies of its first one and not stored.  (kTail variants; large batches take them for the last block alone,
+    // short_block_apart().  The rows of a short block went through the kernel for any n, a launch of 10 to
+    // 95 us behind this one: 2001 rows of 2048, float32 inverse 34 -> 11 us, fp16 INT4 36 -> 14 us, one scale per row
+    // 112 -> 15 us.)
     int n, n_log, row_log, tail_rows;
     int64_t sub_ld_in, sub_ld_out;
 };

@@ -146,3 +146,68 @@ def test_transforms_of_flagged_plans(n, heads, rows, dtype):
         gu.check_rotated(gu.run_transform(x, th, n, heads, dtype, inverse=True, pad=pad), oracle.inverse(x64, th, n, heads), dtype, tag + " inv")
     codes, scales = gu.run_fwd_quant(x, th, n, heads, dtype, 4, min(n, 128), "f16")
     gu.check_fused_codes(codes, scales, oracle.forward(x64, th, n, heads), 4, min(n, 128), "f16", dtype, tag)
+
+
+@pytest.mark.parametrize("n,rows", [(256, 17), (1024, 5), (2048, 3)])
+@pytest.mark.parametrize("dtype", ["f16", "f32"])
+@pytest.mark.parametrize("bits,group,sd", [(4, 128, "f16"), (2, 64, "f32"), (4, 256, "f16")])
+def test_short_last_block_stored_without_counts(n, rows, dtype, bits, group, sd):
+    # fake-quantised rows alone (no bin counters): a variant of its own
+    x, th, _ = synth.small_case(n, rows, dtype, seed=800 + n)
+    codes, scales = gu.run_fwd_quant(x, th, n, 1, dtype, bits, group, sd)
+    want = synth.cast_storage(oracle.dequantize(oracle.unpack_codes(codes, bits), scales.astype(np.float32), group).astype(np.float64), dtype)
+    yq, _ = gu.run_fwd_fakequant(x, th, n, 1, dtype, bits, group, sd, want_hist=False)
+    u = np.uint16 if dtype != "f32" else np.uint32
+    np.testing.assert_array_equal(yq.view(u), want.view(u), err_msg=f"n={n} {dtype}")
+
+
+@pytest.mark.parametrize("n,heads,rows,dtype", [
+    (2048, 1, (1 << 16) + 1, "f16"), (256, 1, (1 << 19) + 5, "bf16"),  # 16-bit rows beyond the memory-side cache, one launch
+    (1024, 2, (1 << 17) + 1, "bf16"), (256, 1, (1 << 20) + 5, "f16"),  # ... and the short block as a launch of its own
+    (2048, 1, (1 << 15) + 1, "f32"), (512, 2, (1 << 16) + 3, "f32")])  # float32 rows: likewise for the codes
+def test_large_batches_with_a_short_last_block(n, heads, rows, dtype):
+    # rows at the front, in the middle and at the end (whole blocks and the short one) against the oracle; nothing behind the last
+    # row or beside the rows is written; a row has the same bits in a short block as in a whole one
+    import torch
+    from paper_2509_09679_amd import binding as B
+
+    dev, w = "cuda:0", n * heads
+    rng = np.random.default_rng(900 + n)
+    th = (rng.standard_normal((heads, n.bit_length() - 1, n // 2)) * 0.7).astype(np.float32)
+    plan = B.alloc_plan(torch.from_numpy(th).to(dev), n, heads)
+    gen = torch.Generator(device=dev).manual_seed(n)
+    t = synth.torch_dtype(dtype)
+    x = torch.empty((rows, w), dtype=t, device=dev)
+    for r in range(0, rows, 1 << 14):
+        x[r:r + (1 << 14)] = torch.randn(x[r:r + (1 << 14)].shape, generator=gen, device=dev).to(t)
+    block = 4096 // w
+    pick = torch.tensor([0, 1, block, rows // 2] + list(range(rows - 2 * block - 1, rows)), device=dev)
+    end = x[rows - 2 * block:].contiguous()  # the last rows as whole blocks
+    xs = synth.to_f64(synth.torch_to_storage(x[pick], dtype), dtype)
+    store = lambda a: synth.torch_to_storage(a, dtype)
+    tag = f"n={n} H={heads} T={rows} {dtype}"
+    for inverse, ref in ((False, oracle.forward(xs, th, n, heads)), (True, oracle.inverse(xs, th, n, heads))):
+        call = B.bq_butterfly_inv if inverse else B.bq_butterfly_fwd
+        out = torch.full((rows + 3, w + 8), 7.0, dtype=t, device=dev)
+        call(x, out, plan, B.make_rows(x, n, heads, out=out[:rows]))
+        whole = torch.empty_like(end)
+        call(end, whole, plan, B.make_rows(end, n, heads))
+        gu.check_rotated(store(out[pick, :w].contiguous()), ref, dtype, f"{tag} inverse={inverse}")
+        assert torch.equal(out[rows - 2 * block:rows, :w], whole)
+        assert (out[rows:] == 7.0).all() and (out[:, w:] == 7.0).all()
+        del out
+    back = x.clone()
+    B.bq_butterfly_fwd(back, back, plan, B.make_rows(back, n, heads))
+    y = back[pick]
+    B.bq_butterfly_inv(back, back, plan, B.make_rows(back, n, heads))
+    gu.check_rotated(store(back[pick]), oracle.inverse(synth.to_f64(store(y), dtype), th, n, heads), dtype, tag + " in place")
+    ref = oracle.forward(xs, th, n, heads)
+    for bits, group, sd in ((2, 128, "f16"), (4, 64, "f32"), (4, 256, "f16")):
+        q, spec = B.alloc_quant_outputs(rows + 1, n, heads, bits, group, sd, dev), B.make_quant(bits, group, sd)
+        q[0][rows:], q[1][rows:] = 77, 7.0
+        B.bq_butterfly_fwd_quant(x, plan, q[0], q[1], spec, B.make_rows(x, n, heads))
+        whole = B.alloc_quant_outputs(2 * block, n, heads, bits, group, sd, dev)
+        B.bq_butterfly_fwd_quant(end, plan, whole[0], whole[1], spec, B.make_rows(end, n, heads))
+        gu.check_fused_codes(q[0][pick].cpu().numpy(), q[1][pick].cpu().numpy(), ref, bits, group, sd, dtype, tag)
+        for a, b, guard in zip(q, whole, (77, 7.0)):
+            assert torch.equal(a[rows - 2 * block:rows], b) and (a[rows:] == guard).all()
