@@ -69,9 +69,9 @@ struct K12Args {
     PlanRef plan;  // not read by the fixed transform (its coefficients come from the element index)
     int64_t rows, ld_in, ld_out;
     int heads;
-    // The workgroups of a head take its rows in turn: row_step of them, each rows / row_step rows (< 2^31), the first
-    // rows % row_step one more.  Divided on the host: a 64-bit division takes the kernel a hundred instructions.
-    int row_step, rows_each, rows_extra;
+    // The gridDim.x / heads workgroups of a head take its rows in turn: each has rows_each of them (< 2^31), the first
+    // rows_extra one more.  Divided on the host: a 64-bit division takes the kernel a hundred instructions.
+    int rows_each, rows_extra;
     // quantiser
     uint8_t *codes;
     void *scales;
