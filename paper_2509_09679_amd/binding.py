@@ -133,8 +133,11 @@ def _stream_ptr(stream=None) -> int:
         import torch
 
         torch.cuda.init()
-        device, raw = torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream
-        _current_raw_stream = lambda: raw(device())  # noqa: E731
+        device, raw = getattr(torch._C, "_cuda_getDevice", None), getattr(torch._C, "_cuda_getCurrentRawStream", None)
+        if device is None or raw is None:  # (not part of torch's public interface)
+            _current_raw_stream = lambda: int(torch.cuda.current_stream().cuda_stream)  # noqa: E731
+        else:
+            _current_raw_stream = lambda: raw(device())  # noqa: E731
     return _current_raw_stream()
 
 

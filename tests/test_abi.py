@@ -275,3 +275,30 @@ def test_calibration_entries_validation():
     assert grad(v=None) == grad(vq=None) == grad(g=None) == grad(f=None) == 1
     assert grad(v=FAKE + 8) == grad(vq=FAKE + 8) == grad(g=FAKE + 8) == grad(f=FAKE + 2) == 4
     assert grad(r=_rows(rows=0, dtype=B.BQ_F16), v=None) == 0
+
+
+def test_stream_handle_without_the_private_torch_calls(monkeypatch):
+    import torch
+
+    class Stream:
+        cuda_stream = 0x1234
+
+    monkeypatch.setattr(B, "_current_raw_stream", None)
+    monkeypatch.setattr(torch.cuda, "init", lambda: None)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: Stream)
+    for name in ("_cuda_getDevice", "_cuda_getCurrentRawStream"):
+        monkeypatch.delattr(torch._C, name, raising=False)
+    assert B._stream_ptr() == 0x1234
+    Stream.cuda_stream = 0x5678  # asked anew on every call
+    assert B._stream_ptr() == 0x5678 and B._stream_ptr(type("S", (), {"cuda_stream": 7})) == 7
+
+
+@pytest.mark.gpu
+def test_default_stream_handle_is_the_current_streams():
+    import torch
+
+    assert B._stream_ptr() == torch.cuda.current_stream().cuda_stream
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        assert B._stream_ptr() == side.cuda_stream != 0
+    assert B._stream_ptr() == torch.cuda.current_stream().cuda_stream and B._stream_ptr(side) == side.cuda_stream
