@@ -141,6 +141,22 @@ def _stream_ptr(stream=None) -> int:
     return _current_raw_stream()
 
 
+def _require(ok: bool, status: int, text: str) -> None:
+    if not ok:
+        raise BqError(status, text)
+
+
+def _require_dense(who: str, name: str, t, code: int, count: int) -> None:
+    """What the library cannot see in a bare pointer: element type, extent, contiguity."""
+    import torch
+
+    if t is None:  # the library's own check
+        return
+    known = t.dtype in (torch.float32, torch.float16, torch.bfloat16) and _dtype_code(t) == code
+    _require(known, 3, f"{who}: {name} is {t.dtype}")
+    _require(t.is_contiguous() and t.numel() >= count, 2, f"{who}: {name} must be contiguous with at least {count} elements")
+
+
 def _ptr(t) -> Optional[int]:
     return None if t is None else int(t.data_ptr())
 
@@ -223,13 +239,19 @@ def bq_residual_split(e, pieces, result, scratch, stream=None) -> None:
     RESIDUAL_STEP ** p; result: float32 [2]; scratch: uint8."""
     rows, cols = e.shape
     assert e.is_contiguous() and pieces.is_contiguous() and pieces.shape[0] == (2 if _dtype_code(pieces) == BQ_F16 else 3)
-    assert pieces.shape[1] == rows and result.numel() >= 2 and scratch.numel() >= bq_residual_scratch_bytes()
+    assert pieces.shape[1] == rows and scratch.numel() * scratch.element_size() >= bq_residual_scratch_bytes()
+    _require_dense("bq_residual_split", "e", e, BQ_F32, 0)
+    _require_dense("bq_residual_split", "result", result, BQ_F32, 2)
     _check(lib().bq_residual_split(_ptr(e), rows, cols, _ptr(pieces), pieces.shape[2], _dtype_code(pieces), _ptr(result),
                                    _ptr(scratch), _stream_ptr(stream)))
 
 
 def bq_quantiser_grad(v, vq, g, factor, quant: bq_quant, rows: bq_rows, stream=None) -> None:
     """In place on g (float32); factor: float32 device tensor of one element."""
+    count = rows.rows * rows.n * rows.heads
+    for name, t, code, least in (("v", v, rows.dtype, count), ("vq", vq, rows.dtype, count), ("g", g, BQ_F32, count),
+                                 ("factor", factor, BQ_F32, 1)):
+        _require_dense("bq_quantiser_grad", name, t, code, least)
     _check(lib().bq_quantiser_grad(_ptr(v), _ptr(vq), _ptr(g), _ptr(factor), ctypes.byref(quant), ctypes.byref(rows),
                                    _stream_ptr(stream)))
 

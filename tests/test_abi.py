@@ -302,3 +302,26 @@ def test_default_stream_handle_is_the_current_streams():
     with torch.cuda.stream(side):
         assert B._stream_ptr() == side.cuda_stream != 0
     assert B._stream_ptr() == torch.cuda.current_stream().cuda_stream and B._stream_ptr(side) == side.cuda_stream
+
+
+def test_calibration_binding_rejects_what_a_pointer_does_not_show():
+    # element types, extents and contiguity, before anything reaches the library (CPU tensors: nothing could be launched)
+    import torch
+
+    f, h = torch.float32, torch.float16
+
+    def split(e=torch.zeros(3, 5), p=torch.zeros(2, 3, 8, dtype=h), res=torch.zeros(2)):
+        B.bq_residual_split(e, p, res, torch.zeros(B.bq_residual_scratch_bytes(), dtype=torch.uint8))
+
+    def grad(v=torch.zeros(4, 64, dtype=h), vq=torch.zeros(4, 64, dtype=h), g=torch.zeros(4, 64), factor=torch.zeros(1), rows=None):
+        B.bq_quantiser_grad(v, vq, g, factor, B.make_quant(4, 64, "f16"), rows or _rows(rows=4, n=64, dtype=B.BQ_F16))
+
+    for call, status in ((lambda: split(e=torch.zeros(3, 5, dtype=torch.float64)), 3), (lambda: split(res=torch.zeros(2, dtype=torch.float64)), 3),
+                         (lambda: split(res=torch.zeros(1)), 2), (lambda: split(e=torch.zeros(3, 5, dtype=h)), 3),
+                         (lambda: grad(g=torch.zeros(4, 64, dtype=torch.float64)), 3), (lambda: grad(factor=torch.zeros(1, dtype=torch.float64)), 3),
+                         (lambda: grad(v=torch.zeros(4, 64)), 3), (lambda: grad(vq=torch.zeros(4, 64, dtype=torch.bfloat16)), 3),
+                         (lambda: grad(g=torch.zeros(3, 64)), 2), (lambda: grad(vq=torch.zeros(64, 4, dtype=h).t()), 2),
+                         (lambda: grad(g=torch.zeros(4, 128)[:, :64]), 2), (lambda: grad(factor=torch.zeros(0)), 2)):
+        with pytest.raises(B.BqError) as e:
+            call()
+        assert e.value.status == status, str(e.value)
