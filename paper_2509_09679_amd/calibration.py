@@ -151,7 +151,10 @@ class ButterflyCalibrator:
         B.bq_butterfly_fwd(self.W, Wr, self.plan, rw)
         B.bq_butterfly_fwd_fakequant(self.W, self.plan, self.Wq, None, qw, rw)
         # the layer's dense products (float32 accumulate)
-        tracked = torch.is_grad_enabled() and (X.requires_grad or self.W.requires_grad)  # autograd through the loss
+        # autograd through the loss, reverse or forward: the 16-bit products have no derivative
+        tangent = torch.autograd.forward_ad.unpack_dual
+        tracked = (torch.is_grad_enabled() and (X.requires_grad or self.W.requires_grad)) or any(
+            tangent(t).tangent is not None for t in (X, self.W))
         if X.dtype != torch.float32 and X.dtype == self.W.dtype and X.shape[0] > 0 and self.m > 0 and not tracked:
             loss, dV, dWr = self._half_step(X, Xq, V, Wr)
         else:

@@ -283,3 +283,26 @@ def test_small_rows_beside_a_large_one_keep_their_gradient(tokens, channels):
         plain = cal._through_quantiser(R.float(), Q.float(), G32, QuantSpec(*spec))
         err = [float(np.linalg.norm((d(t) - want)[1:]) / np.linalg.norm(want[1:])) for t in (got, plain)]
         assert err[0] <= err[1], err
+
+
+@gpu
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+def test_forward_mode_derivative_of_the_loss(dtype):
+    # a dual X: the fake-quantised values are constants of the graph, so d loss = -2 sum(E * (dX W^T))
+    import torch
+    import torch.autograd.forward_ad as fwad
+    from paper_2509_09679_amd.calibration import ButterflyCalibrator, QuantSpec
+
+    dev, n, m, T = "cuda:0", 256, 48, 40
+    X = synth.storage_to_torch(synth.small_case(n, T, dtype, seed=91)[0], dtype, dev)
+    W = synth.storage_to_torch(synth.small_case(n, m, dtype, seed=92, outliers=0, dist="normal")[0], dtype, dev)
+    dX = torch.randn((T, n), generator=torch.Generator().manual_seed(3)).to(X.dtype).to(dev)
+    cal = ButterflyCalibrator(W, QuantSpec(4, 64, "f16"), QuantSpec(2, 64, "f16"))
+    with fwad.dual_level():
+        loss, _, _ = cal.loss_and_grad(fwad.make_dual(X, dX))
+        primal, tangent = fwad.unpack_dual(loss)
+    E = cal.Xq.double() @ cal.Wq.double().t() - X.double() @ W.double().t()
+    want = -2.0 * (E * (dX.double() @ W.double().t())).sum()
+    room = 2.0 * float(E.norm() * (dX.double().norm() * W.double().norm()))  # sums of float32 products
+    assert abs(float(tangent) - float(want)) <= 1e-5 * room, (float(tangent), float(want))
+    assert abs(float(primal) - float((E * E).sum())) <= 1e-4 * float((E * E).sum())
