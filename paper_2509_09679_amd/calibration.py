@@ -155,7 +155,9 @@ class ButterflyCalibrator:
         tangent = torch.autograd.forward_ad.unpack_dual
         tracked = (torch.is_grad_enabled() and (X.requires_grad or self.W.requires_grad)) or any(
             tangent(t).tangent is not None for t in (X, self.W))
-        if X.dtype != torch.float32 and X.dtype == self.W.dtype and X.shape[0] > 0 and self.m > 0 and not tracked:
+        # the float32 products work on copies; the 16-bit ones on X and W as they lie, which are left to them only 16-byte aligned
+        aligned = all(t.data_ptr() % 16 == 0 and t.stride(0) % 8 == 0 for t in (X, self.W))
+        if X.dtype != torch.float32 and X.dtype == self.W.dtype and X.shape[0] > 0 and self.m > 0 and aligned and not tracked:
             loss, dV, dWr = self._half_step(X, Xq, V, Wr)
         else:
             Xq32, Wq32 = Xq.float(), self.Wq.float()

@@ -306,3 +306,24 @@ def test_forward_mode_derivative_of_the_loss(dtype):
     room = 2.0 * float(E.norm() * (dX.double().norm() * W.double().norm()))  # sums of float32 products
     assert abs(float(tangent) - float(want)) <= 1e-5 * room, (float(tangent), float(want))
     assert abs(float(primal) - float((E * E).sum())) <= 1e-4 * float((E * E).sum())
+
+
+@gpu
+@pytest.mark.parametrize("which", ["X", "W"])
+def test_rows_that_are_not_16_byte_aligned_take_the_float32_products(which, monkeypatch):
+    import torch
+    from paper_2509_09679_amd.calibration import ButterflyCalibrator, QuantSpec
+
+    dev, n, m, T = "cuda:0", 256, 48, 40
+    X = synth.storage_to_torch(synth.small_case(n, T, "f16", seed=93)[0], "f16", dev)
+    W = synth.storage_to_torch(synth.small_case(n, m, "f16", seed=94, outliers=0, dist="normal")[0], "f16", dev)
+    specs = QuantSpec(4, 64, "f16"), QuantSpec(2, 64, "f16")
+    theta = 0.3 * torch.rand((1, 8, n // 2), generator=torch.Generator().manual_seed(4)).to(dev)
+    loss, grad, _ = ButterflyCalibrator(W, *specs, theta=theta).loss_and_grad(X)
+    apart = lambda t: torch.cat([t.new_zeros(1), t.flatten()])[1:].view(t.shape)  # one element behind an aligned address
+    X, W = (apart(X), W) if which == "X" else (X, apart(W))
+    cal = ButterflyCalibrator(W, *specs, theta=theta)
+    monkeypatch.setattr(cal, "_half_step", lambda *a: pytest.fail("16-bit products on rows that are not aligned"))
+    loss2, grad2, _ = cal.loss_and_grad(X)
+    # other kernels rotate rows that are not aligned: a few codes move by a step
+    assert abs(float(loss) - float(loss2)) <= 2e-2 * float(loss) and float((grad - grad2).norm()) <= 0.1 * float(grad.norm())
