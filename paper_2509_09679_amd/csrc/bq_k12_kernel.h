@@ -85,7 +85,9 @@ struct K12Args {
     // (row_log = log2 of the row width; ld_in / ld_out are the strides between blocks, sub_ld_* the caller's
     // strides, heads = 1).  Wider rows: block `head` of the heads = width / 4096 blocks of a row (row_log = 12).
     // tail_rows != 0: the last of the `rows` blocks has only so many of the caller's rows.  Its missing rows are read as
-    // copies of its first one and not stored.  (kTail variants; large batches take them for the last block alone,
+    // copies of its first one and not stored; the rows it has are rotated like those of whole blocks, so that a row's result does
+    // not depend on how many rows come with it (in the kernel for any n, which they went through before, plain rotations rounded
+    // them: a few codes in 10^6 of theirs differ from those).  (kTail variants; large batches take them for the last block alone,
     // short_block_apart().  The rows of a short block went through the kernel for any n, a launch of 10 to
     // 95 us behind this one: 2001 rows of 2048, float32 inverse 34 -> 11 us, fp16 INT4 36 -> 14 us, one scale per row
     // 112 -> 15 us.)
@@ -163,9 +165,9 @@ __device__ __forceinline__ void lds_read_p(const float *buf, int ap, float (&u)[
 
 // Two rows of a plan table in layout P.  They are read from memory in natural order (s0, s1: the thread's 8 consecutive
 // entries, its own place in layout N) and transposed through two row buffers in LDS.  Read straight from memory in layout P,
-// neighbouring lanes are 512 bytes apart and every lane becomes an access of its own: the 20 eight-byte loads of the five
-// rows took 13 000 cycles per workgroup, two thirds of a call with few rows and 5.5 us for every further workgroup of a
-// compute unit; this way all tables of a workgroup are there after 4 000.  Every thread of the workgroup must call it.
+// neighbouring lanes are 512 bytes apart and every lane becomes an access of its own, 20 eight-byte loads for the five rows:
+// a call with one fp16 row of 4096 took 8.0 us (forward), 10.8 (inverse) and 8.3 (INT4) that way and takes 5.0, 5.1 and 5.3
+// this way.  Every thread of the workgroup must call it.
 __device__ __forceinline__ void to_layout_p(float *b0, float *b1, int an, int ap, const float (&s0)[8], const float (&s1)[8],
                                             float (&c0)[8], float (&c1)[8])
 {

@@ -411,8 +411,8 @@ hipError_t launch_small(Mode mode, const void *in, void *out, const PlanView &pv
     if (per_slice > A.n_groups) per_slice = A.n_groups;
     const unsigned grid = (unsigned)(per_slice * A.slices);
     // The quantisers of widths that went to the LDS kernel before (all but divisors of 2048 and multiples of 512) keep its plain
-    // rotations, bit for bit: the deferred form's last bit would move a few codes in 10^6 across a rounding boundary, each of
-    // them by a whole step.  20011 fp16 rows of 12 x 64, INT4: 96 us there, 24 us here (14.5 in the
+    // rotations, bit for bit, in every row of a batch: the deferred form's last bit would move a few codes in 10^6 across a
+    // rounding boundary, each of them by a whole step.  20011 fp16 rows of 12 x 64, INT4: 96 us there, 24 us here (14.5 in the
     // deferred form: the plain one takes two operations per element and layer, five where a pair sits in two lanes).
     const bool plain = 2048 % A.width != 0 && A.width % 512 != 0;
     void (*kern)(SmallArgs) = s.dtype == BQ_F32   ? pick_small_k<float>(s.k, mode, bits, plain)
