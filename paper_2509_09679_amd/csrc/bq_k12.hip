@@ -75,13 +75,13 @@ int k12_block_rows(const Shape &s)
 // Elements of a batch from which its short last block is a launch of its own behind the whole blocks, which then run in the
 // kernels without the check: the second launch costs 5 to 6 us, the check a share of the batch.  Measured at n = 256, 1024 and
 // 2048, 2^18 to 2^30 elements, as one launch / as two:
-//   codes of float32 rows, groups of up to 128    2^25 43 / 43 us, 2^26 75 / 68, 2^28 285 / 238
+//   INT2 codes of float32 rows, groups up to 128  2^25 43 / 43 us, 2^26 74 / 67, 2^28 293 / 237  (INT4: 2^28 286 / 290)
 //   transforms of 16-bit rows                     2^26 52 / 56, 2^28 202 / 194 (forward), 191 / 190 (inverse), 2^30 789 / 752, 752 / 740
 //   quantisers of 16-bit rows, groups above 128   2^26 65 / 67, 2^28 242 / 220, 2^30 939 / 820
 //   everything else                               2^28 -2 to +6 %, 2^30 -4 to +1 %
-static int64_t short_block_apart(Mode mode, int dtype, bool big)
+static int64_t short_block_apart(Mode mode, int dtype, int bits, bool big)
 {
-    if (dtype == BQ_F32) return mode == kFwdQuant && !big ? (int64_t)1 << 26 : (int64_t)1 << 29;
+    if (dtype == BQ_F32) return mode == kFwdQuant && bits == 2 && !big ? (int64_t)1 << 26 : (int64_t)1 << 29;
     return mode == kFwd || mode == kInv || big ? (int64_t)1 << 28 : (int64_t)1 << 29;
 }
 
@@ -92,7 +92,7 @@ hipError_t launch_k12(Mode mode, const void *in, void *out, const PlanView &pv, 
     const bool big = (mode == kFwdQuant || mode == kFwdFake) && q->group > 128;
     const int64_t width = (int64_t)s.n * s.heads;
     const int block_rows = k12_block_rows(s);  // rows of the caller per kernel row
-    if (s.rows > block_rows && s.rows % block_rows != 0 && s.rows * width >= short_block_apart(mode, s.dtype, big)) {
+    if (s.rows > block_rows && s.rows % block_rows != 0 && s.rows * width >= short_block_apart(mode, s.dtype, q ? q->bits : 0, big)) {
         const size_t isz = s.dtype == BQ_F32 ? 4 : 2;
         Shape whole = s, rest = s;
         rest.rows = s.rows % block_rows;
