@@ -267,8 +267,7 @@ template <typename T>
 __global__ __launch_bounds__(kGenThreads) void generic_bwd_kernel(BwdArgs A)
 {
     extern __shared__ float lds[];
-    const PlanHead ph = plan_head(A.plan);
-    if (!ph.matches || (A.only_if_bad && (ph.bad_fwd | ph.bad_inv) == 0)) return;
+    if (!plan_matches(A.plan) || (A.only_if_bad && (A.plan.hdr->fast_bad_fwd | A.plan.hdr->fast_bad_inv) == 0)) return;
     const int n = A.n, k = A.k, heads = A.heads, U = A.rows_per_tile;
     float *xb = lds;
     float *gb = lds + (size_t)U * n;
