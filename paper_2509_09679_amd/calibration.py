@@ -123,7 +123,7 @@ class ButterflyCalibrator:
     def _bwd_f32(self, X, dV, dtheta):
         """dtheta from (X, dL/dV) with float32 rows: the gradient's entries span many orders of magnitude (the
         term through the scale sits on one element per group), which a 16-bit row type would flush to zero."""
-        X32 = X if X.dtype == self.torch.float32 else X.float()
+        X32 = X.float().contiguous()  # rows as far apart as dV's
         rows = B.make_rows(X32, self.n, 1)
         B.bq_butterfly_bwd(X32, dV.contiguous(), self.plan, None, dtheta, self._workspace(rows), rows)
         return dtheta
@@ -142,8 +142,8 @@ class ButterflyCalibrator:
         self.hist holds the activation code bins."""
         torch = self.torch
         B.bq_plan_build(self.theta, self.n, 1, self.plan)
-        rx, rw = B.make_rows(X, self.n, 1), B.make_rows(self.W, self.n, 1)
-        V, Xq, Wr = torch.empty_like(X), torch.empty_like(X), torch.empty_like(self.W)
+        V, Xq, Wr = torch.empty_like(X), torch.empty_like(X), torch.empty_like(self.W)  # dense also where X or W is not
+        rx, rw = B.make_rows(X, self.n, 1, out=V), B.make_rows(self.W, self.n, 1, out=Wr)
         qa = B.make_quant(self.act.bits, self.act.group, self.act.scale_dtype)
         qw = B.make_quant(self.wgt.bits, self.wgt.group, self.wgt.scale_dtype)
         B.bq_butterfly_fwd(X, V, self.plan, rx)

@@ -327,3 +327,26 @@ def test_rows_that_are_not_16_byte_aligned_take_the_float32_products(which, monk
     loss2, grad2, _ = cal.loss_and_grad(X)
     # other kernels rotate rows that are not aligned: a few codes move by a step
     assert abs(float(loss) - float(loss2)) <= 2e-2 * float(loss) and float((grad - grad2).norm()) <= 0.1 * float(grad.norm())
+
+
+@gpu
+@pytest.mark.parametrize("dtype", ["f16", "f32"])
+@pytest.mark.parametrize("which", ["X", "W"])
+def test_rows_inside_a_wider_matrix(dtype, which):
+    # X or W as columns of a wider matrix: every intermediate is dense and must not be written at the wider stride
+    import torch
+    from paper_2509_09679_amd.calibration import ButterflyCalibrator, QuantSpec
+
+    dev, n, m, T = "cuda:0", 256, 48, 40
+    X = synth.storage_to_torch(synth.small_case(n, T, dtype, seed=95)[0], dtype, dev)
+    W = synth.storage_to_torch(synth.small_case(n, m, dtype, seed=96, outliers=0, dist="normal")[0], dtype, dev)
+    specs = QuantSpec(4, 64, "f16"), QuantSpec(2, 64, "f16")
+    theta = 0.3 * torch.rand((1, 8, n // 2), generator=torch.Generator().manual_seed(4)).to(dev)
+    loss, grad, _ = ButterflyCalibrator(W, *specs, theta=theta).loss_and_grad(X)
+    wide = lambda t: torch.cat([t, torch.full_like(t[:, :16], 9.0)], dim=1)[:, :n]
+    X, W = (wide(X), W) if which == "X" else (X, wide(W))
+    cal = ButterflyCalibrator(W, *specs, theta=theta)
+    loss2, grad2, _ = cal.loss_and_grad(X)
+    assert cal.Xq.is_contiguous() and cal.Wq.is_contiguous()
+    # the same codes; float32 products that may be summed in another order
+    assert abs(float(loss) - float(loss2)) <= 1e-4 * float(loss) and float((grad - grad2).norm()) <= 1e-3 * float(grad.norm())
