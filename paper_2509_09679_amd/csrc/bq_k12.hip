@@ -135,20 +135,23 @@ hipError_t launch_k12(Mode mode, const void *in, void *out, const PlanView &pv, 
         A.scale_f16 = q->scale_f16;
         bits = q->bits;
     }
-    // Persistent workgroups, a multiple of the head count.  Two fit on a compute unit at a time.  Swept on
-    // large batches (same box, 512 .. 2304, after a long warm-up): the fused kernels (VALU-bound) do not care
-    // (768 .. 2048 within 1 %), the plain transforms (HBM-bound) are fastest with an odd multiple of 256
-    // (768, 1280, 1792, 2304 alike) and 6 .. 18 % slower with anything else tried (512, 640, 896, 1000, 1024,
-    // 1152, 1536, 2048).  The forward transform is faster still with ONE workgroup per compute unit (256: 0.84 ->
-    // 0.79 ms for 2^30 16-bit elements at every n from 256 to 4096, float32 rows 0.793 -> 0.776 ms, small
-    // batches too).  The three-phase inverse was not on 16-bit rows (0.88 against 0.855 ms), which now take the two-phase
-    // kernel; on float32 rows, which it still serves, it is.
-    // n = 8192: one workgroup (512 threads of up to 256 registers) per compute unit at a time.
-    // The two-phase inverse of 16-bit rows (bq_k12_inv.h) also runs best with one workgroup per compute unit (256: 0.78 ms,
-    // 512: 0.86, 768: 0.85, 1024: 0.99, 1280: 0.85, 2048: 0.95 ms for 2^30 fp16 elements).
+    // Persistent workgroups, a multiple of the head count: each pays for its tables (213 KB from L2 at n = 4096) once.
+    // Transforms: one per compute unit (2^30 16-bit elements at every n from 256 to 4096: forward 0.79 ms, 0.84 with three, five or
+    // seven per unit, 6 to 18 % more at other counts; two-phase inverse of 16-bit rows 0.78 ms, 512 workgroups 0.86, 768 0.85,
+    // 1024 0.99; float32 rows forward 0.776, inverse 0.779 ms; small batches too).  n = 8192: one fits.
+    // Quantisers: the two that fit, from the batch on that gives each a few rows; below, one, which reads half as many tables.
+    // One / two per unit / 1280 workgroups (as it was): 1777 fp16 rows of 4096, INT4 11.4 / 11.5 / 17.2 us, 700 rows 7.2 / 8.3 /
+    // 10.3, 4000 rows 19.8 / 18.2 / 22.5, 65536 rows 225 / 185 / 189; float32 rows 2000 13.5 / 13.9 / 19.5, 16000 64.6 / 61.0 / 68.2;
+    // 2000 blocks of n = 512 .. 2048 12.7 / 11.7 / 17.2.  The lines cross between 800 and 2000 rows.  A call that counts bins ends
+    // with one atomic per bin and workgroup, and its lines cross later: 2000 rows 25.8 / 28.1 / 43.5, 4000 33.7 / 33.9 / 50.9,
+    // 16000 80.0 / 69.8 / 89.5.  Batches of 1.5 GB and more run 1 to 5 % faster in 1280 workgroups, which drift out of step (two
+    // per unit / 1280: 262144 fp16 rows, INT2 674 / 664, fake-quantised 870 / 852; 131072 float32 rows 482 / 459; half as many rows
+    // -2 to +1.5 %), unless their groups are large (910 / 922).
     const bool inv_ring = mode == kInv && !wide && s.dtype != BQ_F32;
-    // (and so does the three-phase inverse on float32 rows: 0.798 -> 0.779 ms for 2^29 elements)
-    const int target = (mode == kFwdQuant || mode == kFwdFake) && !wide ? 1280 : 256;
+    const bool fused = mode == kFwdQuant || mode == kFwdFake;
+    const int64_t blocks = A.rows * A.heads;  // of 4096 elements
+    const int64_t few = mode == kFwdFake && A.hist ? 3072 : 1280, vast = ((int64_t)3 << 29) / (kN * (s.dtype == BQ_F32 ? 4 : 2));
+    const int target = !fused || wide || blocks <= few ? 256 : big || blocks < vast ? 512 : 1280;
     int64_t per_head = target / A.heads > 0 ? target / A.heads : 1;
     if (per_head > A.rows) per_head = A.rows;
     const unsigned grid = split_rows(A, per_head);

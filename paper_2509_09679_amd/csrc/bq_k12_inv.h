@@ -33,6 +33,7 @@ constexpr int kInvPiece = 1088;                     // bytes between the pieces 
 constexpr int kInvSlotBytes = 8 * kInvPiece;        // 8704
 constexpr int kInvRingBytes = kInvSlots * kInvSlotBytes;
 constexpr size_t kInvLdsBytes = kInvRingBytes + 2 * kLdsRow * sizeof(float);
+static_assert(8 * 2 * kPieceFloats <= 2 * kLdsRow, "two rows per wave in the row buffers");
 static_assert(kInvLdsBytes <= 80 * 1024, "two workgroups per compute unit");
 
 // byte offset inside a ring slot of element idx (even) of the 4096-point block
@@ -76,6 +77,7 @@ __global__ __launch_bounds__(kThreads, 4) void k12_inv_ring_kernel(K12Args A)
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     const int chunk = wave * 64 + lane_chunk(lane);
     const int idx_n = chunk * 8;
+    const int idx_p = base_p(wave, lane);
     const int head = blockIdx.x % A.heads;
     const int64_t row_first = blockIdx.x / A.heads;
     const int64_t row_step = gridDim.x / A.heads;
@@ -104,26 +106,26 @@ __global__ __launch_bounds__(kThreads, 4) void k12_inv_ring_kernel(K12Args A)
     }
 
     // coefficients: cn[j][r] for layer j+1 (layout N), cp[j][r'] for layer 8+j (layout P), d[r] (layout N)
-    const int idx_p = base_p(wave, lane);
     const int an = lds_addr(idx_n);
     const int ap = lds_addr(idx_p);
     float cn[7][8], cp[5][8], d[8];
     {
-        const size_t th = kVirt ? (size_t)virt_head(A, head, idx_n) : (size_t)head;
-        const float *fg = A.fg + th * nk * tn + (idx_n & tmask);
-        float st[5][8];
+        auto table_head = [&](int e) { return kVirt ? (size_t)virt_head(A, head, e) : (size_t)head; };
+        auto table = [&](int e) { return A.fg + table_head(e) * nk * tn + (e & tmask); };
+        const float *fg = table(idx_n), *pp[2] = {table(piece_idx(wave, lane, 0)), table(piece_idx(wave, lane, 1))};
+        float4 st[5][2];
 #pragma unroll
-        for (int j = 0; j < 5; ++j) {  // layers above log2 n do not exist: weight zero leaves the element as it is
+        for (int j = 0; j < 5; ++j)  // layers above log2 n do not exist: weight zero leaves the element as it is
 #pragma unroll
-            for (int r = 0; r < 8; ++r) st[j][r] = 0.0f;
-            if (!kVirt || 8 + j <= nk) load_coef8(fg + (size_t)(7 + j) * tn, st[j]);
-        }
+            for (int q = 0; q < 2; ++q)
+                st[j][q] = !kVirt || 8 + j <= nk ? *(const float4 *)(pp[q] + (size_t)(7 + j) * tn) : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
 #pragma unroll
         for (int j = 0; j < 7; ++j) load_coef8(fg + (size_t)j * tn, cn[j]);
-        load_coef8(A.fd + th * tn + (idx_n & tmask), d);
-        to_layout_p(bufs, bufs + kLdsRow, an, ap, st[0], st[1], cp[0], cp[1]);
-        to_layout_p(bufs, bufs + kLdsRow, an, ap, st[2], st[3], cp[2], cp[3]);
-        to_layout_p(bufs, an, ap, st[4], cp[4]);
+        load_coef8(A.fd + table_head(idx_n) * tn + (idx_n & tmask), d);
+        float *own = bufs + wave * (2 * kPieceFloats);  // the row buffers hold no rows yet; the barrier before the row loop follows
+        turn_own<2>(own, lane, idx_p, st, cp);
+        turn_own<2>(own, lane, idx_p, st + 2, cp + 2);
+        turn_own<1>(own, lane, idx_p, st + 4, cp + 4);
         // the empty statements consume the loaded values: their waits then sit here and not inside the row loop
 #pragma unroll
         for (int r = 0; r < 8; ++r) {

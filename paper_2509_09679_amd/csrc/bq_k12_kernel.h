@@ -163,26 +163,53 @@ __device__ __forceinline__ void lds_read_p(const float *buf, int ap, float (&u)[
     }
 }
 
-// Two rows of a plan table in layout P.  They are read from memory in natural order (s0, s1: the thread's 8 consecutive
-// entries, its own place in layout N) and transposed through two row buffers in LDS.  Read straight from memory in layout P,
-// neighbouring lanes are 512 bytes apart and every lane becomes an access of its own, 20 eight-byte loads for the five rows:
-// a call with one fp16 row of 4096 took 8.0 us (forward), 10.8 (inverse) and 8.3 (INT4) that way and takes 5.0, 5.1 and 5.3
-// this way.  Every thread of the workgroup must call it.
-__device__ __forceinline__ void to_layout_p(float *b0, float *b1, int an, int ap, const float (&s0)[8], const float (&s1)[8],
-                                            float (&c0)[8], float (&c1)[8])
+// Rows of a plan table in layout P.  They are read from memory in 16-byte pieces and turned around in LDS: read straight from
+// memory in layout P, neighbouring lanes are 512 bytes apart and every lane becomes an access of its own, 20 eight-byte loads for
+// the five rows (one fp16 row of 4096, INT4: 8.3 us).
+//
+// A wave's elements in layout P are the runs of 16 with idx bits 4..6 = wave, 32 of them 128 apart.  The wave loads its runs
+// with two loads per lane and row and turns them around in a piece of LDS of its own; a wave's LDS instructions complete in
+// order, so there is no barrier and no wait but those for the data.  One row, back to back inside a graph, against two barriers
+// per two rows through the whole workgroup's row buffers (turn_together): fp16 INT4 n = 4096 4.96 -> 4.68 us, inverse 4.81 -> 4.62,
+// float32 4.74 -> 4.44, n = 8192 forward 7.79 -> 7.45, inverse 7.73 -> 7.12.  Of the 4.68 us 1.7 are the launch and 0.8 the tables.
+constexpr int kPieceFloats = 512;  // a wave's part of a table row
+// first of the four elements that a lane loads, part 0 or 1
+__device__ __forceinline__ int piece_idx(int wave, int lane, int part) { return ((lane >> 2) + 16 * part) * 128 + wave * 16 + (lane & 3) * 4; }
+// place of element o of run `run`; every other pair of runs has its two halves swapped, so that the runs that lane bits 0..2 walk
+// over in layout P lie in different banks
+__device__ __forceinline__ int piece_addr(int run, int o) { return run * 16 + (o ^ ((run & 2) << 2)); }
+// kRows rows: v[j][part] -> c[j], through `own`, kRows * kPieceFloats floats of LDS that only this wave uses
+template <int kRows>
+__device__ __forceinline__ void turn_own(float *own, int lane, int idx_p, const float4 (*v)[2], float (*c)[8])
+{
+    const int at = piece_addr(lane >> 2, (lane & 3) * 4), from = piece_addr(idx_p >> 7, idx_p & 15);
+    asm volatile("" ::: "memory");
+#pragma unroll
+    for (int j = 0; j < kRows; ++j) {
+        *(float4 *)&own[j * kPieceFloats + at] = v[j][0];
+        *(float4 *)&own[j * kPieceFloats + at + 256] = v[j][1];  // 16 runs further on
+    }
+    asm volatile("" ::: "memory");  // (other lanes' pieces: the compiler must not move the reads up)
+#pragma unroll
+    for (int j = 0; j < kRows; ++j)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {  // idx bits 10 and 11: 8 and 16 runs
+            const float2 w = *(const float2 *)&own[j * kPieceFloats + from + (q & 1) * 128 + (q >> 1) * 256];
+            c[j][2 * q] = w.x;
+            c[j][2 * q + 1] = w.y;
+        }
+    asm volatile("" ::: "memory");
+}
+// The same through two row buffers of the workgroup, from the thread's 8 consecutive entries (its own place in layout N).
+// Every thread of the workgroup must call it.
+__device__ __forceinline__ void turn_together(float *b0, float *b1, int an, int ap, const float (&s0)[8], const float (&s1)[8],
+                                              float (&c0)[8], float (&c1)[8])
 {
     lds_write_n(b0, an, s0);
     lds_write_n(b1, an, s1);
     __syncthreads();
     lds_read_p(b0, ap, c0);
     lds_read_p(b1, ap, c1);
-    __syncthreads();
-}
-__device__ __forceinline__ void to_layout_p(float *b0, int an, int ap, const float (&s0)[8], float (&c0)[8])
-{
-    lds_write_n(b0, an, s0);
-    __syncthreads();
-    lds_read_p(b0, ap, c0);
     __syncthreads();
 }
 
@@ -398,7 +425,7 @@ __global__ __launch_bounds__(kThreads, kWide ? 2 : 4) void k12_kernel(K12Args A)
     // kFwdFake: per-thread counts -> workgroup counts -> the caller's counters (every thread gets here)
     auto flush_bins = [&]() {
         if (kMode == kFwdFake && kHist) {
-            ((BinCount<kBits> &)bins).drain(wg_bins);
+            ((BinCount<kBits> &)bins).drain_wave(wg_bins);
             __syncthreads();
             if (threadIdx.x < (1 << kBits) && wg_bins[threadIdx.x]) atomicAdd(&A.hist[threadIdx.x], wg_bins[threadIdx.x]);
         }
@@ -428,6 +455,13 @@ __global__ __launch_bounds__(kThreads, kWide ? 2 : 4) void k12_kernel(K12Args A)
     constexpr int kRingFloats = kSlots * kPoints * (int)sizeof(T) / 4;
     static_assert((kRingFloats + kSlots * kHalves * kLdsRow) * sizeof(float) + (kParkScales + (kParkFirst ? kHalves : 0)) * kParkQuadBytes <=
                       (kWide ? kLdsBytesWide : kLdsBytes), "dynamic LDS of the launch");
+    // How the tables get into layout P.  The variants that are shortest of registers come out of the compiler with more spilled
+    // ones in the row loop where the waves turn their own pieces (40001 float32 rows of 2048, fake-quantised INT4 with counts, 173
+    // -> 220 us; 32768 bf16 rows of 8192, INT4 with one group per row, 344 -> 355): they keep the turn through the row buffers.
+    constexpr bool kTurnOwn = kMode != kFwdFake && !(kWide && kBig);
+    // a wave's share of the row buffers, before they hold rows
+    constexpr int kOwnFloats = kSlots * kHalves * kLdsRow / 8 & ~3, kOwnRows = kOwnFloats / kPieceFloats;
+    static_assert(kOwnRows >= 2, "five rows in three turns");
     extern __shared__ float lds_raw[];
     float *lds = lds_raw + kRingFloats;
     constexpr bool kInverse = (kMode == kInv);
@@ -487,28 +521,55 @@ __global__ __launch_bounds__(kThreads, kWide ? 2 : 4) void k12_kernel(K12Args A)
             }
     } else {
         // tables are [head][layer][n]; kVirt: the head is the element's own (virt_head)
-        const float *fg0 = A.fg + (kVirt ? (size_t)virt_head(A, head, idx_n) * nk * tn : (size_t)head * kLayers * kPoints) + (idx_n & tmask);
+        auto table = [&](int e) {
+            return A.fg + (kVirt ? (size_t)virt_head(A, head, e) * nk * tn : (size_t)head * kLayers * kPoints) + (e & tmask);
+        };
+        const float *fg0 = table(idx_n);
+        auto load_n = [&](int h) {  // layers 1..7 and, where it is applied in layout N, layer 13
 #pragma unroll
-        for (int h = 0; h < kHalves; ++h) {
-            const float *fg = fg0 + h * kN;
-            float st[5][8], sw[8];
+            for (int j = 0; j < 7; ++j) load_coef8(fg0 + h * kN + (size_t)j * tn, cn[h][j]);
+            if (kWide && !kInverse) load_coef8(fg0 + h * kN + (size_t)kK * tn, cw[h]);
+        };
+        if constexpr (kTurnOwn) {
+            const float *pp[2] = {table(piece_idx(wave, lane, 0)), table(piece_idx(wave, lane, 1))};
+            float *own = lds + wave * kOwnFloats;
 #pragma unroll
-            for (int j = 0; j < 5; ++j) {  // layers above log2 n do not exist: weight zero leaves the element as it is
+            for (int h = 0; h < kHalves; ++h) {
+                // layers 8..12 and, where it is applied in layout P, layer 13 (the upper half's coefficients)
+                constexpr int kRowsP = kWide && kInverse ? 6 : 5;
+                float4 st[kRowsP][2];
 #pragma unroll
-                for (int r = 0; r < 8; ++r) st[j][r] = 0.0f;
-                if (!kVirt || 8 + j <= nk) load_coef8(fg + (size_t)(7 + j) * tn, st[j]);
+                for (int j = 0; j < kRowsP; ++j)  // layers above log2 n do not exist: weight zero leaves the element as it is
+#pragma unroll
+                    for (int q = 0; q < 2; ++q)
+                        st[j][q] = j < 5 + h && (!kVirt || 8 + j <= nk) ? *(const float4 *)(pp[q] + (size_t)(7 + j) * tn + h * kN)
+                                                                        : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+                load_n(h);
+                // as many rows at a time as the wave's piece holds
+                constexpr int kFirst = kOwnRows < 5 ? kOwnRows : 5, kSecond = 5 - kFirst < kFirst ? 5 - kFirst : kFirst;
+                turn_own<kFirst>(own, lane, idx_p, st, cp[h]);
+                turn_own<kSecond>(own, lane, idx_p, st + kFirst, cp[h] + kFirst);
+                turn_own<5 - kFirst - kSecond>(own, lane, idx_p, st + kFirst + kSecond, cp[h] + kFirst + kSecond);
+                if constexpr (kWide && kInverse)
+                    if (h == 1) turn_own<1>(own, lane, idx_p, st + 5, cw + 1);
             }
+            __syncthreads();  // the pieces are row buffers from here on
+        } else {
+            static_assert(!(kWide && kInverse), "layer 13 in layout P");
 #pragma unroll
-            for (int j = 0; j < 7; ++j) load_coef8(fg + (size_t)j * tn, cn[h][j]);
-            if (kWide && !kInverse) load_coef8(fg + (size_t)kK * tn, cw[h]);
-            float *b0 = lds + h * kLdsRow, *b1 = lds + (kHalves + h) * kLdsRow;
-            to_layout_p(b0, b1, an, ap, st[0], st[1], cp[h][0], cp[h][1]);
-            to_layout_p(b0, b1, an, ap, st[2], st[3], cp[h][2], cp[h][3]);
-            if (kWide && kInverse && h == 1) {
-                load_coef8(fg + (size_t)kK * tn, sw);
-                to_layout_p(b0, b1, an, ap, st[4], sw, cp[h][4], cw[1]);
-            } else {
-                to_layout_p(b0, an, ap, st[4], cp[h][4]);
+            for (int h = 0; h < kHalves; ++h) {
+                float st[5][8], unused[8];
+#pragma unroll
+                for (int j = 0; j < 5; ++j) {
+#pragma unroll
+                    for (int r = 0; r < 8; ++r) st[j][r] = 0.0f;
+                    if (!kVirt || 8 + j <= nk) load_coef8(fg0 + h * kN + (size_t)(7 + j) * tn, st[j]);
+                }
+                load_n(h);
+                float *b0 = lds + h * kLdsRow, *b1 = lds + (kHalves + h) * kLdsRow;
+                turn_together(b0, b1, an, ap, st[0], st[1], cp[h][0], cp[h][1]);
+                turn_together(b0, b1, an, ap, st[2], st[3], cp[h][2], cp[h][3]);
+                turn_together(b0, b1, an, ap, st[4], st[4], cp[h][4], unused);
             }
         }
     }

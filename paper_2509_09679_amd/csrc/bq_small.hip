@@ -137,7 +137,7 @@ __global__ __launch_bounds__(kSmallThreads) void small_kernel(SmallArgs A)
     }
     auto flush_bins = [&]() {  // every thread gets here
         if (kMode == kFwdFake && A.hist) {
-            bins.drain(wg_bins);
+            bins.drain_wave(wg_bins);
             __syncthreads();
             if (tid < (1 << kBits) && wg_bins[tid]) atomicAdd(&A.hist[tid], wg_bins[tid]);
         }
