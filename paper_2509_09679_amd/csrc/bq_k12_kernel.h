@@ -171,7 +171,8 @@ __device__ __forceinline__ void lds_read_p(const float *buf, int ap, float (&u)[
 // with two loads per lane and row and turns them around in a piece of LDS of its own; a wave's LDS instructions complete in
 // order, so there is no barrier and no wait but those for the data.  One row, back to back inside a graph, against two barriers
 // per two rows through the whole workgroup's row buffers (turn_together): fp16 INT4 n = 4096 4.96 -> 4.68 us, inverse 4.81 -> 4.62,
-// float32 4.74 -> 4.44, n = 8192 forward 7.79 -> 7.45, inverse 7.73 -> 7.12.  Of the 4.68 us 1.7 are the launch and 0.8 the tables.
+// float32 4.74 -> 4.44, n = 8192 forward 7.79 -> 7.45, inverse 7.73 -> 7.12.  Of these 1.7 us are the launch and 0.8 (n = 8192:
+// 2.1) the tables.
 constexpr int kPieceFloats = 512;  // a wave's part of a table row
 // first of the four elements that a lane loads, part 0 or 1
 __device__ __forceinline__ int piece_idx(int wave, int lane, int part) { return ((lane >> 2) + 16 * part) * 128 + wave * 16 + (lane & 3) * 4; }
@@ -554,6 +555,13 @@ __global__ __launch_bounds__(kThreads, kWide ? 2 : 4) void k12_kernel(K12Args A)
                     if (h == 1) turn_own<1>(own, lane, idx_p, st + 5, cw + 1);
             }
             __syncthreads();  // the pieces are row buffers from here on
+            // The empty statements keep the compiler from dropping the lower elements' coefficients of layer 1, which the forward
+            // cascade does without: it would read the others with four strided 4-byte loads instead of two of 16 bytes (one fp16
+            // row of 4096, INT4: 4.81 -> 4.50 us, 37 rows of 8192 8.13 -> 7.47, 1777 rows 11.6 -> 11.2).
+#pragma unroll
+            for (int h = 0; h < kHalves; ++h)
+#pragma unroll
+                for (int r = 0; r < 8; r += 2) asm volatile("" ::"v"(cn[h][0][r]));
         } else {
             static_assert(!(kWide && kInverse), "layer 13 in layout P");
 #pragma unroll
@@ -771,7 +779,11 @@ __global__ __launch_bounds__(kThreads, kWide ? 2 : 4) void k12_kernel(K12Args A)
         // share a buffer.  n = 4096: C, B, A measured 1-2 % faster than the other orders on all modes.
         if (it >= 2) phase_c();
         if (it >= 1 && it <= n_my) phase_b(lb);  // B(it-1)
+        // (ahead of the other waves' arithmetic: it is this phase that sends for the next row.  131072 fp16 rows, forward, 356 ->
+        // 348 us; the quantisers within 1 %; with a second barrier in the iteration 1 % slower)
+        if (!kBig) __builtin_amdgcn_s_setprio(1);
         if (it < n_my) phase_a();
+        if (!kBig) __builtin_amdgcn_s_setprio(0);
         __syncthreads();
     };
     typedef std::integral_constant<int, 0> I0;
