@@ -32,10 +32,11 @@
 // of rows add to it in stream order, and a last kernel sums the slices in double in a fixed order: no
 // atomics, the result does not depend on scheduling.
 //
-// The kernel exits at once when the plan flags the scale-deferred tables as unusable; the generic
-// backward kernel, launched behind it with the opposite condition, then does the work, and the last kernel adds that
-// kernel's partial sums.
+// When the plan flags the scale-deferred tables as unusable the kernel runs the backward pass for any n instead
+// (bq_generic_bwd.h), and the last kernel adds those partial sums.  As a launch of its own behind this one, empty on other
+// plans, that pass took 2 us of every call; in the 1024 threads of this kernel it is two to three times as fast.
 #include "bq_bwd_blocks.h"
+#include "bq_generic_bwd.h"
 
 namespace bq {
 
@@ -107,6 +108,8 @@ struct BwdFastArgs {
     int64_t ld_in, ld_out;
     int64_t slice_floats;
     int first_chunk;  // != 0: slices are overwritten, else added to
+    int slots;        // row slots; workgroups beyond them only help on flagged plans
+    int plain_parts;  // flagged plans: the workgroups that take part, each with a slice of its own
     // n = 2^n_log < 4096 (kVirt): a row of the kernels is a block of 4096 / n consecutive rows of the caller;
     // row0, rows, ld_in, ld_out then count and stride blocks, sub_ld_* are the caller's strides and total_rows
     // its row count (the last block may be short: its missing rows are given dy = 0 and are not stored)
@@ -139,7 +142,7 @@ struct Part {
     {
         half = kHalf ? (blockIdx.x >> 3) & 1 : 0;
         slot = kHalf ? (int)((blockIdx.x & 7) | ((blockIdx.x >> 4) << 3)) : (int)blockIdx.x;
-        nslots = kHalf ? (int)(gridDim.x >> 1) : (int)gridDim.x;
+        nslots = A.slots;
         c0 = half * G::n;
         ts = kVirt ? A.n : xs;
         tmask = ts - 1;
@@ -369,31 +372,20 @@ __device__ __forceinline__ void n_forward(float (&w)[8], const float (&cn)[6][8]
     }
 }
 
-// fw_inv entry (scale before transposed layer i) of block element e; rmask != 0: the tables of e's own head
-__device__ __forceinline__ float fw_at(const float *fw_inv, int stride, int tmask, int n_log, int rmask, int c0, int e, int i)
-{
-    const int hd = (e & rmask) >> n_log;
-    return fw_inv[((size_t)hd * n_log + (i - 1)) * stride + ((c0 + e) & tmask)];
-}
-
-// Deferred sums -> dtheta partials of this workgroup.  part: its slice, `pairs` sums per layer, indexed by the
-// pair's position in the whole kernel row (c0 + element); fw_inv: the plan table, rows `stride` apart, column
-// (c0 + element) & tmask.
+// Deferred sums of this workgroup -> its slice: `pairs` sums per layer, indexed by the pair's position in the whole kernel row
+// (c0 + element).  They stay in deferred units: the scales E_i[a] E_i[b] are the same for every slice and are applied to the sum
+// over the slices.  Applied here, each workgroup gathered 2 * 4 bytes of table for every 4 bytes of sums it stored: at 2048 fp16
+// rows of n = 4096 (8 rows per workgroup) the whole pass took 41.0 us that way, 37.1 this way.
 struct FinArgs {
     float *part;
-    const float *fw_inv;
-    int stride, tmask, pairs, c0, n_log, rmask, first;
-    __device__ __forceinline__ float scale(int a, int b, int i) const
-    {
-        return fw_at(fw_inv, stride, tmask, n_log, rmask, c0, a, i) * fw_at(fw_inv, stride, tmask, n_log, rmask, c0, b, i);
-    }
+    int pairs, c0, n_log, first;
     __device__ __forceinline__ float *at(int a, int i) const { return part + (size_t)(i - 1) * pairs + pair_index(c0 + a, i); }
 };
 
 // Prologue and epilogue go through LDS because layout Q has neighbouring lanes 128 elements apart: read or written from
-// there directly, every instruction touches one cache line per lane.  At 2048 fp16 rows of n = 4096 (8 rows per workgroup)
-// the pass took 58 us with 48 such table loads, 88 loads of the sums' scales and 44 stores per thread of group Q; in natural
-// order, with 16-byte table loads and one trip each through the row buffers, it takes 36 us.
+// there directly, every instruction touches one cache line per lane.  At 2048 fp16 rows of n = 4096 the kernel took 58 us with 48
+// such table loads, 88 loads of the sums' scales and 44 stores per thread of group Q; in natural order, with 16-byte table loads and
+// one trip each through the row buffers, 36 us.
 //
 // Tables of layers 7..12 (kHalf: 13 as well) in natural order: thread t of 1024 holds elements 4 t .. 4 t + 3 of each.
 template <int kTables>
@@ -426,7 +418,7 @@ __device__ __forceinline__ void spread_pairs(const float (&acc)[4], float (&o)[8
 #pragma unroll
     for (int r = 0; r < 8; ++r) o[r] = (r & (1 << J)) ? 0.0f : acc[q++];
 }
-// Row buffer j holds the sums of layer kFirst + j by element; all 1024 threads scale and store them in pair order.
+// Row buffer j holds the sums of layer kFirst + j by element; all 1024 threads store them in pair order.
 template <int kFirst>
 __device__ __forceinline__ void write_partials(const FinArgs &F, const float *lds)
 {
@@ -441,7 +433,7 @@ __device__ __forceinline__ void write_partials(const FinArgs &F, const float *ld
             const int a = ((p >> (i - 1)) << i) | (p & ((1 << (i - 1)) - 1)), b = a | (1 << (i - 1));
             float v = buf[lds_addr2(a)];
             if (i >= 4 && i <= 10) v -= buf[lds_addr2(b)];  // lane layers: each lane kept its own element's products
-            put_partial(F.at(a, i), v * F.scale(a, b, i), F.first);
+            put_partial(F.at(a, i), v, F.first);
         }
     }
 }
@@ -524,12 +516,18 @@ struct FusedLds {
 };
 
 template <typename T, bool kDx, bool kHalf, bool kVirt>
-__global__ __launch_bounds__(kFusedThreads) void bwd_fused_kernel(BwdFastArgs A)
+__global__ __launch_bounds__(kFusedThreads) void bwd_fused_kernel(BwdFastArgs A, BwdArgs P)
 {
     extern __shared__ float lds[];
-    if (!plan_fast_both(A.plan)) return;
+    const PlanUse use = plan_use(A.plan);
+    if (use == kPlanForeign) return;
+    if (use == kPlanPlain) {  // the whole batch in plain rotations, by the first chunk's launch
+        if (A.first_chunk && (int)blockIdx.x < A.plain_parts) generic_bwd_rows<T, kFusedThreads>(P, lds, (int)blockIdx.x, A.plain_parts);
+        return;
+    }
     using L = FusedLds<T, kHalf>;
     const Part<kHalf, kVirt> pt(A);
+    if (pt.slot >= pt.nslots) return;
     const int ts = pt.ts;
     constexpr int xs = Part<kHalf, kVirt>::xs;
     const int role = threadIdx.x >> 9;  // uniform per wave
@@ -541,13 +539,9 @@ __global__ __launch_bounds__(kFusedThreads) void bwd_fused_kernel(BwdFastArgs A)
     const float *fg = A.fg_inv;
     FinArgs F;
     F.part = A.partial + (size_t)pt.slot * A.slice_floats;
-    F.fw_inv = A.fw_inv;
-    F.stride = ts;
-    F.tmask = pt.tmask;
     F.pairs = xs / 2;
     F.c0 = pt.c0;
     F.n_log = pt.n_log;
-    F.rmask = kVirt ? pt.rmask : 0;
     F.first = A.first_chunk;
     TableStage<L::kTables> st;
     st.load(fg, pt, kVirt ? pt.n_log : K + 1);
@@ -630,6 +624,9 @@ __global__ __launch_bounds__(kFusedThreads) void bwd_fused_kernel(BwdFastArgs A)
                 raw = load_row(pt.slot);
             }
         }
+        // (the loop starts on a cache line of its own: where it lay otherwise, float32 rows took 8 % longer, 32768 rows of 4096 446 us
+        // instead of 408, and bf16 rows of 8192 1178 instead of 1150)
+        asm volatile(".p2align 6");
         for (int it = 0; it < iters; ++it) {
             float vx[8], vg[8];
             if (it >= 2) {
@@ -801,6 +798,7 @@ __global__ __launch_bounds__(kFusedThreads) void bwd_fused_kernel(BwdFastArgs A)
             for (int r = 0; r < 8; ++r) gap_mask |= pt.in_tail_gap(idx_q + p_reg_idx2<K>(r)) ? (1 << r) : 0;
         if (mine > 0)
             for (int j = 0; j < kLead; ++j) ring_load(j);
+        asm volatile(".p2align 6");  // (see group N)
         for (int it = 0; it < iters; ++it) {
             ring_load(it + kLead);
             float vx[8], vg[8];
@@ -866,26 +864,26 @@ __global__ __launch_bounds__(kFusedThreads) void bwd_fused_kernel(BwdFastArgs A)
     }
     write_partials<7>(F, lds);
     if (kHalf) {
-        // sum of layer 13 = (scale after the layer)^2 * deferred sum; the lower half's share goes to the
-        // layer's place in the slice, the upper half's, negated, behind the slice's regular part
+        // the lower half's share of layer 13's sum goes to the layer's place in the slice, the upper half's, negated, behind the
+        // slice's regular part
         float *dst = F.part + (size_t)(pt.half ? 13 : 12) * G::n;
 #pragma unroll
         for (int m = 0; m < 4; ++m) {
             const int e = (int)threadIdx.x + 1024 * m;
-            const float d = A.fw_inv[11 * ts + pt.col(e)];
-            const float v = lds[(L::kTables - 1) * G::kRowFloats + lds_addr2(e)] * (d * d);
+            const float v = lds[(L::kTables - 1) * G::kRowFloats + lds_addr2(e)];
             put_partial(dst + e, pt.half ? -v : v, A.first_chunk);
         }
     }
 }
 
 // out[q] = sum over slices of partial[s][q] (+ the upper-half share of the last layer where a slice has one), in
-// double, in a fixed order.  n_angles and last_layer_at are multiples of kReduceAngles.  Flagged plans: the sums of the
-// generic kernel's plain_parts slices (0: left to a later kernel).
+// double, in a fixed order, times the angle's scale (n_log; 0: left to a later kernel).  n_angles and last_layer_at are multiples
+// of kReduceAngles.  Flagged plans: the sums of plain_parts slices in true units (0: left to a later kernel).
 template <typename Out>
 __global__ __launch_bounds__(kReduceThreads) void bwd_reduce_kernel(const float *__restrict__ partial, Out *__restrict__ out,
                                                                     size_t n_angles, size_t slice_floats, size_t last_layer_at,
-                                                                    int n_parts, PlanRef plan, int plain_parts)
+                                                                    int n_parts, PlanRef plan, int plain_parts,
+                                                                    const float *__restrict__ fw_inv, int n_log)
 {
     __shared__ double lds[kReduceThreads * 4];
     const PlanUse use = plan_use(plan);
@@ -897,14 +895,19 @@ __global__ __launch_bounds__(kReduceThreads) void bwd_reduce_kernel(const float 
     }
     const size_t first = (size_t)blockIdx.x * kReduceAngles;
     const size_t extra = first >= last_layer_at ? slice_floats - n_angles : 0;  // 0, or the number of angles of the last layer
+    double scale = 1.0;
+    if (use == kPlanFast && n_log > 0 && threadIdx.x < kReduceAngles) {
+        const int q = (int)first + (int)threadIdx.x, half = 1 << (n_log - 1);
+        scale = sum_scale(fw_inv, n_log, 0, q / half + 1, q & (half - 1), extra != 0);
+    }
     const double t = sum_slices(partial, first, slice_floats, extra, n_parts, lds);
-    if (threadIdx.x < kReduceAngles) out[first + threadIdx.x] = (Out)t;
+    if (threadIdx.x < kReduceAngles) out[first + threadIdx.x] = (Out)(t * scale);
 }
 
 // n < 4096: the sums of a 4096-point block hold, per layer, the block's rows side by side, each with its `heads`
-// transforms; dtheta[h][i][p] = sum over the rows, in row order (flagged plans: over the generic kernel's slices)
+// transforms; dtheta[h][i][p] = sum over the rows, in row order, times the angle's scale (flagged plans: sum over plain_parts slices)
 __global__ void bwd_fold_kernel(const double *__restrict__ sums, float *__restrict__ dtheta, int n_log, int heads,
-                                PlanRef plan, const float *__restrict__ plain, int plain_parts)
+                                PlanRef plan, const float *__restrict__ plain, int plain_parts, const float *__restrict__ fw_inv)
 {
     const PlanUse use = plan_use(plan);
     if (use == kPlanForeign) return;
@@ -921,12 +924,21 @@ __global__ void bwd_fold_kernel(const double *__restrict__ sums, float *__restri
         return;
     }
     for (int row = 0; row < block_rows; ++row) acc += sums[layer * (G::n / 2) + (row * heads + h) * half + p];
-    dtheta[q] = (float)acc;
+    dtheta[q] = (float)(acc * sum_scale(fw_inv, n_log, h, layer + 1, p, false));
 }
 
 // ---- host side -----------------------------------------------------------------------------------
-// Slices = row slots of the kernel, which runs one workgroup per compute unit (n = 8192: two per slot).
+// Slices = row slots of the kernel, which runs at most one workgroup per compute unit (n = 8192: two per slot).
 static int bwd_fast_slices(int k) { return k == 13 ? 128 : 256; }
+// The slots a batch of so many kernel rows fills evenly: every slot writes its 98 KB of sums (n = 8192: 213 KB) and the last kernel
+// reads them, rows or not.  One row of 4096 took 23.0 us with
+// 256 of them, 13.3 with one; 64 rows 23.9 and 16.4; 300 rows 23.5 with 150.
+static int bwd_fast_slots(int k, int64_t kernel_rows)
+{
+    const int64_t most = bwd_fast_slices(k), each = (kernel_rows + most - 1) / most;
+    const int64_t slots = (kernel_rows + each - 1) / each;
+    return (int)(k == 13 ? (slots + 7) & ~(int64_t)7 : slots);  // n = 8192: whole rounds of the eight dies (Part)
+}
 // Kernel rows (of 4096 or 8192 elements) per launch: row counters inside the kernel are 32-bit.
 static int64_t bwd_fast_chunk_rows(int) { return (int64_t)1 << 22; }
 static size_t bwd_fast_slice_floats(int k) { return k == 13 ? (size_t)13 * 4096 + 4096 : (size_t)K * (G::n / 2); }
@@ -984,8 +996,8 @@ template <typename T, bool kHalf, bool kVirt>
 static hipError_t launch_bwd_fast_t(BwdFastArgs A, const PlanView &pv, const Shape &s, float *dtheta, char *ws,
                                     hipStream_t stream)
 {
-    const int slices = bwd_fast_slices(s.k);
     const int64_t kernel_rows = bwd_fast_kernel_rows(s);
+    const int slices = bwd_fast_slots(s.k, kernel_rows);
     const int64_t chunk_rows = kernel_rows < bwd_fast_chunk_rows(s.k) ? kernel_rows : bwd_fast_chunk_rows(s.k);
     A.slice_floats = (int64_t)bwd_fast_slice_floats(s.k);
     A.partial = (float *)ws;
@@ -993,32 +1005,41 @@ static hipError_t launch_bwd_fast_t(BwdFastArgs A, const PlanView &pv, const Sha
     const size_t lds_bytes = FusedLds<T, kHalf>::kBytes;
     hipError_t e = A.dx ? fused_kernel_ready<T, true, kHalf, kVirt>() : fused_kernel_ready<T, false, kHalf, kVirt>();
     if (e != hipSuccess) return e;
-    const int grid = kHalf ? 2 * slices : slices;  // kHalf: a multiple of 16 (see Part)
+    A.slots = slices;
+    // Flagged plans: the tiles grow to 4096 elements where the batch has more of them than workgroups, so that 1024 threads find
+    // work between two barriers (20000 fp16 rows of 512: 359 -> 226 us, as a launch of its own 334), and take workgroups without a slot.
+    BwdArgs P = generic_bwd_args(A.x, A.dy, pv, A.dx, ws, s, &A.plain_parts);
+    static_assert(2 * G::n * sizeof(float) * (kHalf ? 2 : 1) <= FusedLds<T, kHalf>::kBytes, "4096 elements, or one row, and the gradient");
+    while (P.rows_per_tile * s.n < G::n && P.n_tiles > 256) {
+        P.rows_per_tile *= 2;
+        P.n_tiles = (s.rows + P.rows_per_tile - 1) / P.rows_per_tile * s.heads;
+    }
+    const int most = P.n_tiles < 256 ? (int)P.n_tiles : 256;
+    if (A.plain_parts > most) A.plain_parts = most;
+    const int with_slot = kHalf ? 2 * slices : slices;  // kHalf: a multiple of 16 (see Part)
+    const int grid = with_slot > A.plain_parts ? with_slot : A.plain_parts;
     for (int64_t r0 = 0; r0 < kernel_rows; r0 += chunk_rows) {
         A.row0 = r0;
         A.rows = kernel_rows - r0 < chunk_rows ? kernel_rows - r0 : chunk_rows;
         A.first_chunk = (r0 == 0);
-        // every slice must be written by the first chunk, so the grid does not shrink with the row count
+        // every slice must be written by the first chunk, so the grid is the whole batch's
         if (A.dx)
-            hipLaunchKernelGGL((bwd_fused_kernel<T, true, kHalf, kVirt>), dim3(grid), dim3(kFusedThreads), lds_bytes, stream, A);
+            hipLaunchKernelGGL((bwd_fused_kernel<T, true, kHalf, kVirt>), dim3(grid), dim3(kFusedThreads), lds_bytes, stream, A, P);
         else
-            hipLaunchKernelGGL((bwd_fused_kernel<T, false, kHalf, kVirt>), dim3(grid), dim3(kFusedThreads), lds_bytes, stream, A);
+            hipLaunchKernelGGL((bwd_fused_kernel<T, false, kHalf, kVirt>), dim3(grid), dim3(kFusedThreads), lds_bytes, stream, A, P);
     }
-    int plain_parts;
-    e = launch_generic_bwd_if_bad(A.x, A.dy, pv, A.dx, ws, s, stream, &plain_parts);
-    if (e != hipSuccess) return e;
     if (kVirt) {
         const size_t sums = (size_t)s.k * (G::n / 2);  // the layers the transform has
         hipLaunchKernelGGL(bwd_reduce_kernel<double>, dim3((unsigned)(sums / kReduceAngles)), dim3(kReduceThreads), 0, stream,
-                           (const float *)ws, fold, sums, (size_t)A.slice_floats, sums, slices, A.plan, 0);
+                           (const float *)ws, fold, sums, (size_t)A.slice_floats, sums, slices, A.plan, 0, A.fw_inv, 0);
         const unsigned angles = (unsigned)(s.heads * s.k * (s.n / 2));
         hipLaunchKernelGGL(bwd_fold_kernel, dim3((angles + 255) / 256), dim3(256), 0, stream, (const double *)fold, dtheta, s.k,
-                           s.heads, A.plan, (const float *)ws, plain_parts);
+                           s.heads, A.plan, (const float *)ws, A.plain_parts, A.fw_inv);
     } else {
         const size_t angles = (size_t)s.k * (s.n / 2);
         hipLaunchKernelGGL(bwd_reduce_kernel<float>, dim3((unsigned)(angles / kReduceAngles)), dim3(kReduceThreads), 0, stream,
                            (const float *)ws, dtheta, angles, (size_t)A.slice_floats, (size_t)(s.k - 1) * (s.n / 2), slices,
-                           A.plan, plain_parts);
+                           A.plan, A.plain_parts, A.fw_inv, s.k);
     }
     return hipGetLastError();
 }

@@ -64,6 +64,15 @@ __device__ __forceinline__ void put_partial(float *p, float v, int first)
         *p += v;
 }
 
+// What turns angle p of layer i of head `head` from deferred units into dtheta: E_i[a] E_i[b].  after_last: the sums of the last layer
+// were formed behind it (n = 8192), on the layer's inputs, where both elements have the scale before the next layer down.
+__device__ __forceinline__ double sum_scale(const float *__restrict__ fw_inv, int n_log, int head, int i, int p, bool after_last)
+{
+    const float *fw = fw_inv + ((size_t)head * n_log + (after_last ? i - 2 : i - 1) << n_log);
+    const int a = ((p >> (i - 1)) << i) | (p & ((1 << (i - 1)) - 1));
+    return (double)fw[a] * (double)fw[a | (1 << (i - 1))];
+}
+
 // ---- second pass: sums over slices ----------------------------------------------------------------------------
 // A workgroup of 256 threads sums kReduceAngles consecutive entries of every slice: eight lanes cover the 128 bytes
 // of a slice's entries with 16-byte loads, the 32 groups of eight lanes take every 32nd slice each (up to eight

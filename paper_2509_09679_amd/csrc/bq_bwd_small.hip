@@ -128,17 +128,15 @@ __global__ __launch_bounds__(kSbThreads) void small_bwd_kernel(SmallBwdArgs A)
     // deferred sums -> this slot's entries (workgroups without rows write zeros)
     if (idle) return;  // (whole transforms are idle, so no partner is missing below)
     float *part = A.partial + slot * A.n_angles + (size_t)head * K * (n / 2);
-    const float *fw_head = A.fw_inv + (size_t)head * K * n;
 #pragma unroll
     for (int J = 0; J < 3; ++J) {  // layers 1..3: pairs of registers
         const int i = J + 1;
-        const float *fw = fw_head + (size_t)(i - 1) * n;
         int q = 0;
 #pragma unroll
         for (int r = 0; r < 8; ++r) {
             if (!(r & (1 << J))) {
-                const int a = idx + r, b = idx + (r | (1 << J));
-                part[(i - 1) * (n / 2) + pair_index(a, i)] = acc.r[J][q] * (fw[a] * fw[b]);
+                const int a = idx + r;
+                part[(i - 1) * (n / 2) + pair_index(a, i)] = acc.r[J][q];
                 ++q;
             }
         }
@@ -147,28 +145,27 @@ __global__ __launch_bounds__(kSbThreads) void small_bwd_kernel(SmallBwdArgs A)
     for (int j = 0; j < 4; ++j) {  // layers 4..7: pairs of lanes (masks 1, 2, 7, 8)
         const int i = 4 + j;
         if (i > K) continue;
-        const float *fw = fw_head + (size_t)(i - 1) * n;
 #pragma unroll
         for (int r = 0; r < 8; ++r) {
             const float mine = acc.d[j][r];
             const float other = lane_partner(mine, j);
             const int e = idx + r;
             if (!(e & (1 << (i - 1)))) {  // the lane holding the lower element writes
-                const int b = e | (1 << (i - 1));
-                part[(i - 1) * (n / 2) + pair_index(e, i)] = (mine - other) * (fw[e] * fw[b]);
+                part[(i - 1) * (n / 2) + pair_index(e, i)] = mine - other;
             }
         }
     }
 }
 
-// dtheta[q] = sum over slots of partial[slot][q], in double: a workgroup takes 16 angles (64 bytes of a slot), its 64 groups
+// dtheta[q] = sum over slots of partial[slot][q], in double, times the angle's scale: a workgroup takes 16 angles (64 bytes of a slot), its 64 groups
 // of 16 threads take every 64th slot each and their sums are added in group order.  A serial chain of loads per thread: with
 // 32 angles and 8 groups of 256 threads, 4096 slots of n = 128 ran 14 workgroups of 512
 // loads each (whole backward pass of 8192 fp16 rows of 128: 156 -> 26 us).  Flagged
 // plans: the same over the generic kernel's plain_slots slices.
 constexpr int kSbReduceAngles = 16, kSbReduceGroups = 64;
 __global__ __launch_bounds__(kSbReduceAngles * kSbReduceGroups) void small_bwd_reduce_kernel(
-    const float *__restrict__ partial, float *__restrict__ dtheta, int64_t n_angles, int64_t slots, PlanRef plan, int64_t plain_slots)
+    const float *__restrict__ partial, float *__restrict__ dtheta, int64_t n_angles, int64_t slots, PlanRef plan, int64_t plain_slots,
+    const float *__restrict__ fw_inv, int k)
 {
     const PlanUse use = plan_use(plan);
     if (use == kPlanForeign) return;
@@ -176,7 +173,11 @@ __global__ __launch_bounds__(kSbReduceAngles * kSbReduceGroups) void small_bwd_r
     __shared__ double sums[kSbReduceGroups][kSbReduceAngles];
     const int lane = threadIdx.x % kSbReduceAngles, grp = threadIdx.x / kSbReduceAngles;
     const int64_t q = (int64_t)blockIdx.x * kSbReduceAngles + lane;
-    double acc = 0.0;
+    double acc = 0.0, scale = 1.0;
+    if (grp == 0 && q < n_angles && use == kPlanFast) {
+        const int layer = (int)(q >> (k - 1));  // counted through the heads
+        scale = sum_scale(fw_inv, k, layer / k, layer % k + 1, (int)q & ((1 << (k - 1)) - 1), false);
+    }
     if (q < n_angles) {
 #pragma unroll 8
         for (int64_t s = grp; s < slots; s += kSbReduceGroups) acc += (double)partial[s * n_angles + q];
@@ -186,7 +187,7 @@ __global__ __launch_bounds__(kSbReduceAngles * kSbReduceGroups) void small_bwd_r
     if (grp == 0 && q < n_angles) {
         double t = sums[0][lane];
         for (int g = 1; g < kSbReduceGroups; ++g) t += sums[g][lane];
-        dtheta[q] = (float)t;
+        dtheta[q] = (float)(t * scale);
     }
 }
 
@@ -286,7 +287,7 @@ hipError_t launch_small_bwd(const void *x, const void *dy, const PlanView &pv, v
     if (e != hipSuccess) return e;
     const unsigned blocks = (unsigned)((A.n_angles + kSbReduceAngles - 1) / kSbReduceAngles);
     hipLaunchKernelGGL(small_bwd_reduce_kernel, dim3(blocks), dim3(kSbReduceAngles * kSbReduceGroups), 0, stream, (const float *)ws,
-                       dtheta, A.n_angles, g.slots, A.plan, (int64_t)plain_parts);
+                       dtheta, A.n_angles, g.slots, A.plan, (int64_t)plain_parts, A.fw_inv, s.k);
     return hipGetLastError();
 }
 
