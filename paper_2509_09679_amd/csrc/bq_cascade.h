@@ -270,12 +270,29 @@ __device__ __forceinline__ void scaled8(const float (&y)[8], int lanes, bool sca
             inv = (s == 0.0f) ? 0.0f : rcp_f16_valued(s);
         }
     } else {
-        s = (BITS == 2) ? m : m / qmax;
-        inv = 1.0f / s;
-        ordinary = s >= 0x1p-100f;
-        if (__builtin_expect(!ordinary, 0)) {
+        // The correctly rounded quotient m / 7 as above and the correctly rounded reciprocal by hardware estimate (1 ulp) and one
+        // Newton step, which is exact for every float32 significand but the one of all ones (checked on the CPU for every
+        // significand and every estimate within 1 ulp; tests/test_scale_arithmetic.py).  That one, scales near the ends of
+        // the exponent range, zero, infinity and NaN take the divisions.  These two divisions were 20 of the 165 vector instructions
+        // of a thread-row at n = 128.
+        if (BITS == 2) {
+            s = m;
+        } else {
+            constexpr float kRcp = 1.0f / qmax;
+            const float q0 = m * kRcp;
+            s = __builtin_fmaf(__builtin_fmaf(-qmax, q0, m), kRcp, q0);
+        }
+        const bool quick = __float_as_uint(m) - 0x12800000u < 0x71800000u - 0x12800000u &&  // 2^-90 <= m < 2^100
+                           (__float_as_uint(s) & 0x7FFFFFu) != 0x7FFFFFu;
+        const float r = __builtin_amdgcn_rcpf(s);
+        inv = __builtin_fmaf(__builtin_fmaf(-s, r, 1.0f), r, r);
+        ordinary = true;
+        if (__builtin_expect(!quick, 0)) {
             asm volatile("");
-            inv = (s == 0.0f) ? 0.0f : inv;
+            s = (BITS == 2) ? m : m / qmax;
+            inv = 1.0f / s;
+            ordinary = s >= 0x1p-100f;
+            if (!ordinary) inv = (s == 0.0f) ? 0.0f : inv;
         }
     }
 #pragma unroll

@@ -74,6 +74,7 @@ __global__ __launch_bounds__(kThreads, 4) void k12_inv_ring_kernel(K12Args A)
     unsigned long long *const wg_bins = nullptr;  // (the quantiser's workgroup scratch: not used by a plain transform)
     float *const wg_max = nullptr;
     NoCount bins;
+    const PlanHead ph = plan_head(A.plan);  // (looked at below)
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     const int chunk = wave * 64 + lane_chunk(lane);
     const int idx_n = chunk * 8;
@@ -87,7 +88,6 @@ __global__ __launch_bounds__(kThreads, 4) void k12_inv_ring_kernel(K12Args A)
     const int tmask = tn - 1;
     const T *in = (const T *)A.in;
     if (n_my == 0) return;
-    const PlanHead ph = plan_head(A.plan);
     if (!ph.matches) return;
 
     if (ph.bad_inv != 0) {  // rare: plain rotations through LDS

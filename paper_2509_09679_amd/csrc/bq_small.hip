@@ -9,8 +9,7 @@
 // over the batch with the same coefficients.  Two independent row groups are processed per iteration and the next two are
 // prefetched meanwhile, so that four 16-byte loads per lane are in flight.
 //
-// If the plan flags the scale-deferred tables as unusable, rows go through plain (cos, sin) rotations (rare): the transforms
-// hold them in registers, the quantisers, which are short of those, re-read them from the plan for every row.
+// If the plan flags the scale-deferred tables as unusable, rows go through plain (cos, sin) rotations (rare).
 #include "bq_cascade.h"
 
 namespace bq {
@@ -23,10 +22,12 @@ struct SmallArgs {
     const float *fg, *fd;
     const float2 *cs;
     PlanRef plan;
-    int64_t rows, ld_in, ld_out;
+    int64_t group_in, group_out;  // bytes from one row group to the next
+    uint32_t row_in, row_out;     // ... and from row to row of a group
     int heads, width;    // width = heads * n
     int span, rows_per_block, slices;  // SmallTiling
-    int64_t n_groups;    // row groups = ceil(rows / rows_per_block)
+    int n_groups;        // row groups = ceil(rows / rows_per_block); < 2^31: each is about a kilobyte or more
+    int last_rows;       // rows of the last group
     uint8_t *codes;
     void *scales;
     unsigned long long *hist;  // kFwdFake: 2^bits counters or NULL
@@ -34,7 +35,7 @@ struct SmallArgs {
 };
 
 // The cascade in plain (cos, sin) rotations held in registers.
-// kOwn: rounded as slow_small() rounds them, an element's own product inside the fused operation:
+// kOwn: an element's own product inside the fused operation:
 //   y_a = fma(c, x_a, -(s x_b)),  y_b = fma(c, x_b, s x_a)   (transposed: the signs of s swap)
 // i.e. fma(w1, own, w2 partner) in either lane of a pair.  Else (forward only) as the kernel for any n rounds them:
 //   y_a = fma(c, x_a, -(s x_b)),  y_b = fma(s, x_a, c x_b)
@@ -120,13 +121,14 @@ struct PlainCascade {
     }
 };
 
-template <typename T, int K, int kMode, int kBits, bool kPlain = false>
-__global__ __launch_bounds__(kSmallThreads) void small_kernel(SmallArgs A)
+// kWhole: quantiser groups of n channels (else any that divide n)
+template <typename T, int K, int kMode, int kBits, bool kPlain = false, bool kWhole = false>
+// (four waves per SIMD: the quantisers fill them; without the bound some end up a few registers above 128)
+__global__ __launch_bounds__(kSmallThreads, kMode == kFwd || kMode == kInv || (kPlain && kMode == kFwdFake && sizeof(T) == 4) ? 1 : 4) void small_kernel(SmallArgs A)
 {
     constexpr int n = 1 << K;
     constexpr bool kInverse = (kMode == kInv);
-    const PlanHead ph = plan_head(A.plan);
-    if (!ph.matches) return;
+    const PlanHead ph = plan_head(A.plan);  // (looked at below: the scalar arithmetic up to there passes in its latency)
     const int tid = threadIdx.x;
     __shared__ unsigned long long wg_bins[16];  // kFwdFake: this workgroup's bin counts
     BinCount<kBits> bins;
@@ -144,46 +146,56 @@ __global__ __launch_bounds__(kSmallThreads) void small_kernel(SmallArgs A)
     };
     const int chunk = (tid & ~15) | lane_chunk(tid & 15);  // chunk of 8 elements inside the workgroup's span
     const int e0 = chunk * 8;
-    int col;
-    int64_t row_in_block, grp_first, grp_step;
+    // Everything about a row but the lane's place in its group is uniform: rows are addressed as a scalar base per group, which moves
+    // on by a constant, and a 32-bit offset per lane.  (With a 64-bit row number per lane, the four 64-bit products and comparisons
+    // of a row were a tenth of its vector cycles; with a product per group, transforms of 2^22 elements took 4 to 9 % longer.)
+    int col, row_in_group = 0, grp_first, grp_step;
     if (A.slices > 1) {
-        row_in_block = 0;
         col = (int)(blockIdx.x % A.slices) * A.span + e0;
-        grp_first = blockIdx.x / A.slices;
-        grp_step = gridDim.x / A.slices;
+        grp_first = (int)blockIdx.x / A.slices;
+        grp_step = (int)gridDim.x / A.slices;
     } else {
-        row_in_block = e0 / A.width;
-        col = e0 - (int)row_in_block * A.width;
-        grp_first = blockIdx.x;
-        grp_step = gridDim.x;
+        row_in_group = e0 / A.width;
+        col = e0 - row_in_group * A.width;
+        grp_first = (int)blockIdx.x;
+        grp_step = (int)gridDim.x;
     }
-    if (e0 >= A.span || col >= A.width) {  // idle lane (whole transforms are): no row of the batch is its own
-        row_in_block = (int64_t)1 << 60;
-        col = 0;
-    }
+    const bool idle = e0 >= A.span || col >= A.width;  // idle lane (whole transforms are): no row of the batch is its own
+    if (idle) row_in_group = col = 0;
+    const bool in_last = !idle && row_in_group < A.last_rows;  // its row exists in the last group, too
+    const int last = A.n_groups - 1;
+    const uint32_t col_bytes = (uint32_t)col * (uint32_t)sizeof(T);
+    const uint32_t off_in = (uint32_t)row_in_group * A.row_in + col_bytes, off_out = (uint32_t)row_in_group * A.row_out + col_bytes;
+
+    const int groups = kMode == kFwdQuant ? A.width / A.group : 0;  // quantiser groups of a row
+    const uint32_t off_code = (uint32_t)(row_in_group * (A.width * kBits / 8) + col * kBits / 8);
+    const uint32_t off_scale = kMode == kFwdQuant ? (uint32_t)(row_in_group * groups + col / A.group) : 0u;
+    struct Place {  // of a row group: byte offsets of its rows and outputs
+        int64_t in, out, code, scale;
+    };
+    const int64_t code_bytes = (int64_t)A.rows_per_block * (A.width * kBits / 8), scale_bytes = (int64_t)A.rows_per_block * groups * (A.scale_f16 ? 2 : 4);
+    Place at = {grp_first * A.group_in, grp_first * A.group_out, grp_first * code_bytes, grp_first * scale_bytes};
+    const Place step = {grp_step * A.group_in, grp_step * A.group_out, grp_step * code_bytes, grp_step * scale_bytes};
+    auto load_row = [&](int g, int64_t in) {
+        uint32_t off = off_in;
+        if (g == last && !in_last) off = col_bytes;  // no such row: the group's first (the value is not used)
+        if (g > last) in = off = 0;                  // past the end: one cache line (not used either)
+        asm volatile("" : "+v"(off));
+        return load8((const T *)((const char *)A.in + in + off));
+    };
+    if (grp_first >= A.n_groups || !ph.matches) return;
     const int head = col >> K;
     const int idx = col & (n - 1);
     const bool fast = (kInverse ? ph.bad_inv : ph.bad_fwd) == 0;
 
     const float2 *cs_head = A.cs + (size_t)head * K * (n >> 1);
-    const T *in = (const T *)A.in;
-    const uint32_t col_bytes = (uint32_t)col * (uint32_t)sizeof(T);
-
-    auto row_of = [&](int64_t g) { return g * A.rows_per_block + row_in_block; };
-    auto load_row = [&](int64_t g) {
-        int64_t row = row_of(g);
-        if (row >= A.rows) row = A.rows - 1;  // clamp: the value is not used
-        uint32_t off = col_bytes;
-        asm volatile("" : "+v"(off));
-        return load8((const T *)((const char *)(in + row * A.ld_in) + off));
-    };
-    auto finish = [&](const float (&y)[8], int64_t g) {
-        const int64_t row = row_of(g);
+    auto finish = [&](const float (&y)[8], int g, const Place &p) {
+        const bool live = g == last ? in_last : !idle;  // lanes of a wave may hold different rows
+        const int lanes = kWhole ? n / 8 : A.group >> 3;
         if (kMode == kFwdFake) {
-            const bool live = row < A.rows;  // lanes of a wave may hold different rows
             float f[8], s;
             bool ordinary;
-            rounded8<kBits>(y, A.group >> 3, A.scale_f16 != 0, f, &s, &ordinary);
+            rounded8<kBits>(y, lanes, A.scale_f16 != 0, f, &s, &ordinary);
             if (A.hist) {
                 if (live)
                     count8<kBits>(bins, f, ordinary);
@@ -194,48 +206,57 @@ __global__ __launch_bounds__(kSmallThreads) void small_kernel(SmallArgs A)
             if (A.out && live) {
                 float yq[8];
                 dequant8(f, s, yq);
-                uint32_t off = col_bytes;
+                uint32_t off = off_out;
                 asm volatile("" : "+v"(off));
-                store8((T *)((char *)((T *)A.out + row * A.ld_out) + off), yq);
+                store8((T *)((char *)A.out + p.out + off), yq);
             }
             return;
         }
-        if (row >= A.rows) return;
+        if (!live) return;
         if (kMode != kFwdQuant) {
-            uint32_t off = col_bytes;
+            uint32_t off = off_out;
             asm volatile("" : "+v"(off));
-            store8((T *)((char *)((T *)A.out + row * A.ld_out) + off), y);
+            store8((T *)((char *)A.out + p.out + off), y);
         } else {
-            const int lanes = A.group >> 3;
             float s;
             const uint32_t packed = quant8<kBits>(y, lanes, A.scale_f16 != 0, &s);
-            uint8_t *codes_row = A.codes + row * (int64_t)(A.width * kBits / 8);
-            const uint32_t coff = (uint32_t)col * kBits / 8;
+            uint32_t coff = off_code;
+            asm volatile("" : "+v"(coff));
+            uint8_t *codes = A.codes + p.code + coff;
             if (kBits == 2)
-                *(uint16_t *)(codes_row + coff) = (uint16_t)packed;
+                *(uint16_t *)codes = (uint16_t)packed;
             else
-                *(uint32_t *)(codes_row + coff) = packed;
-            const int64_t sidx = row * (int64_t)(A.width / A.group) + (uint32_t)col / (uint32_t)A.group;
+                *(uint32_t *)codes = packed;
+            uint32_t soff = off_scale;
+            asm volatile("" : "+v"(soff));
+            char *scales = (char *)A.scales + p.scale;
             if (A.scale_f16)
-                ((__half *)A.scales)[sidx] = __float2half_rn(s);
+                *((__half *)scales + soff) = __float2half_rn(s);
             else
-                ((float *)A.scales)[sidx] = s;
+                *((float *)scales + soff) = s;
+        }
+    };
+    auto advance = [&](int64_t groups_on) {
+        at.in += groups_on * step.in;
+        if (kMode != kFwdQuant) at.out += groups_on * step.out;
+        if (kMode == kFwdQuant) {
+            at.code += groups_on * step.code;
+            at.scale += groups_on * step.scale;
         }
     };
 
-    if (grp_first >= A.n_groups) return;
-    constexpr bool kTransform = kMode == kFwd || kMode == kInv;
     auto plain_rows = [&](auto cascade) {
         cascade.load(cs_head, idx);
-        Raw8 raw0 = load_row(grp_first);
-        Raw8 raw1 = load_row(grp_first + grp_step);
-        for (int64_t g = grp_first; g < A.n_groups; g += grp_step) {
+        Raw8 raw0 = load_row(grp_first, at.in);
+        Raw8 raw1 = load_row(grp_first + grp_step, at.in + step.in);
+        for (int g = grp_first; g < A.n_groups; g += grp_step) {
             float u[8];
             unpack8(raw0, u, (const T *)nullptr);
             raw0 = raw1;
-            raw1 = load_row(g + 2 * grp_step);
+            raw1 = load_row(g + 2 * grp_step, at.in + 2 * step.in);
             cascade.run(u);
-            finish(u, g);
+            finish(u, g, at);
+            advance(1);
         }
     };
     if constexpr (kPlain) {
@@ -243,17 +264,10 @@ __global__ __launch_bounds__(kSmallThreads) void small_kernel(SmallArgs A)
         flush_bins();
         return;
     }
-    if constexpr (kTransform) {
-        // (re-read for every row, 20011 rows of 12 x 64 took 213 us, 2.5 times as long as in the LDS kernel these widths had)
-        if (!fast) return plain_rows(PlainCascade<K, kInverse, true>());
-    }
-    if (!kTransform && !fast) {  // rare
-        for (int64_t g = grp_first; g < A.n_groups; g += grp_step) {
-            float u[8];
-            unpack8(load_row(g), u, (const T *)nullptr);
-            slow_small<K, kInverse>(u, cs_head, idx);
-            finish(u, g);
-        }
+    // rare: a flagged plan.  (Re-read for every row, 20011 rows of 12 x 64, forward, took 213 us, 8192 rows of 32 x 128, fp16 INT4, 402;
+    // held in registers 18 and 30.5.)
+    if (!fast) {
+        plain_rows(PlainCascade<K, kInverse, true>());
         flush_bins();
         return;
     }
@@ -267,44 +281,48 @@ __global__ __launch_bounds__(kSmallThreads) void small_kernel(SmallArgs A)
 #pragma unroll
         for (int r = 0; r < 8; ++r) d[r] = A.fd[(size_t)head * n + idx + r];
     }
-    Raw8 raw0 = load_row(grp_first);
-    Raw8 raw1 = load_row(grp_first + grp_step);
-    for (int64_t g = grp_first; g < A.n_groups; g += 2 * grp_step) {
+    Raw8 raw0 = load_row(grp_first, at.in);
+    Raw8 raw1 = load_row(grp_first + grp_step, at.in + step.in);
+    for (int g = grp_first; g < A.n_groups; g += 2 * grp_step) {
         float u0[8], u1[8];
         unpack8(raw0, u0, (const T *)nullptr);
         unpack8(raw1, u1, (const T *)nullptr);
-        raw0 = load_row(g + 2 * grp_step);
-        raw1 = load_row(g + 3 * grp_step);
+        raw0 = load_row(g + 2 * grp_step, at.in + 2 * step.in);
+        raw1 = load_row(g + 3 * grp_step, at.in + 3 * step.in);
         fast_small<K, kInverse>(u0, c, d);
         fast_small<K, kInverse>(u1, c, d);
-        finish(u0, g);
-        if (g + grp_step < A.n_groups) finish(u1, g + grp_step);
+        finish(u0, g, at);
+        advance(1);
+        if (g + grp_step < A.n_groups) finish(u1, g + grp_step, at);
+        advance(1);
     }
     flush_bins();
 }
 
 template <typename T, int K>
-static void (*pick_small(Mode mode, int bits, bool plain))(SmallArgs)
+static void (*pick_small(Mode mode, int bits, bool plain, bool whole))(SmallArgs)
 {
     if (mode == kFwd) return small_kernel<T, K, kFwd, 4>;
     if (mode == kInv) return small_kernel<T, K, kInv, 4>;
     if (plain) {
         if (mode == kFwdFake) return bits == 2 ? small_kernel<T, K, kFwdFake, 2, true> : small_kernel<T, K, kFwdFake, 4, true>;
+        if (whole) return bits == 2 ? small_kernel<T, K, kFwdQuant, 2, true, true> : small_kernel<T, K, kFwdQuant, 4, true, true>;
         return bits == 2 ? small_kernel<T, K, kFwdQuant, 2, true> : small_kernel<T, K, kFwdQuant, 4, true>;
     }
     if (mode == kFwdFake) return bits == 2 ? small_kernel<T, K, kFwdFake, 2> : small_kernel<T, K, kFwdFake, 4>;
+    if (whole) return bits == 2 ? small_kernel<T, K, kFwdQuant, 2, false, true> : small_kernel<T, K, kFwdQuant, 4, false, true>;
     return bits == 2 ? small_kernel<T, K, kFwdQuant, 2> : small_kernel<T, K, kFwdQuant, 4>;
 }
 
 template <typename T>
-static void (*pick_small_k(int k, Mode mode, int bits, bool plain))(SmallArgs)
+static void (*pick_small_k(int k, Mode mode, int bits, bool plain, bool whole))(SmallArgs)
 {
     switch (k) {
-        case 3: return pick_small<T, 3>(mode, bits, plain);
-        case 4: return pick_small<T, 4>(mode, bits, plain);
-        case 5: return pick_small<T, 5>(mode, bits, plain);
-        case 6: return pick_small<T, 6>(mode, bits, plain);
-        default: return pick_small<T, 7>(mode, bits, plain);
+        case 3: return pick_small<T, 3>(mode, bits, plain, whole);
+        case 4: return pick_small<T, 4>(mode, bits, plain, whole);
+        case 5: return pick_small<T, 5>(mode, bits, plain, whole);
+        case 6: return pick_small<T, 6>(mode, bits, plain, whole);
+        default: return pick_small<T, 7>(mode, bits, plain, whole);
     }
 }
 
@@ -377,9 +395,6 @@ hipError_t launch_small(Mode mode, const void *in, void *out, const PlanView &pv
     A.fd = mode == kInv ? pv.fd_inv : pv.fd_fwd;
     A.cs = pv.cs;
     A.plan = pv.ref;
-    A.rows = s.rows;
-    A.ld_in = s.ld_x;
-    A.ld_out = s.ld_y;
     A.heads = s.heads;
     A.width = s.n * s.heads;
     const bool counts = mode == kFwdFake && q->hist != nullptr;
@@ -388,10 +403,21 @@ hipError_t launch_small(Mode mode, const void *in, void *out, const PlanView &pv
     // four-wave ones at the same number of waves; float32 rows and the quantisers prefer the wider ones)
     if ((mode == kFwd || mode == kInv) && s.dtype != BQ_F32 && (A.width % 512 == 0 || 512 % A.width == 0))
         t = SmallTiling{64, 512, A.width < 512 ? 512 / A.width : 1, A.width < 512 ? 1 : A.width / 512};
+    // a lane's offset inside a row group has 32 bits: rows further apart than that are groups of their own
+    const int64_t isz = s.dtype == BQ_F32 ? 4 : 2;
+    if (t.slices == 1 && t.rows_per_block * (s.ld_x > s.ld_y ? s.ld_x : s.ld_y) * isz >= (int64_t)1 << 32) {
+        t.rows_per_block = 1;
+        t.span = A.width;
+    }
     A.span = t.span;
     A.rows_per_block = t.rows_per_block;
     A.slices = t.slices;
-    A.n_groups = (s.rows + A.rows_per_block - 1) / A.rows_per_block;
+    A.n_groups = (int)((s.rows + A.rows_per_block - 1) / A.rows_per_block);
+    A.last_rows = (int)(s.rows - (int64_t)(A.n_groups - 1) * A.rows_per_block);
+    A.row_in = (uint32_t)(s.ld_x * isz);
+    A.row_out = (uint32_t)(s.ld_y * isz);
+    A.group_in = A.rows_per_block * s.ld_x * isz;
+    A.group_out = A.rows_per_block * s.ld_y * isz;
     int bits = 4;
     if (q) {
         A.codes = q->codes;
@@ -401,23 +427,41 @@ hipError_t launch_small(Mode mode, const void *in, void *out, const PlanView &pv
         A.scale_f16 = q->scale_f16;
         bits = q->bits;
     }
-    // Persistent workgroups, a multiple of the slice count.  How many waves stream best was measured per mode
-    // (262144 rows of 32 x 128): the plain transforms and everything on float32 rows with 2048 waves (8 per
-    // compute unit: 5.5 TB/s against 4.4 TB/s with four times as many), the 16-bit quantisers, which need the
-    // occupancy to hide their arithmetic, with 8192.
-    const bool few = mode == kFwd || mode == kInv || s.dtype == BQ_F32;
-    const int64_t wgs = (few ? 2048 : 8192) / (t.threads / 64);
-    int64_t per_slice = wgs / A.slices > 0 ? wgs / A.slices : 1;
-    if (per_slice > A.n_groups) per_slice = A.n_groups;
-    const unsigned grid = (unsigned)(per_slice * A.slices);
     // The quantisers of widths that went to the LDS kernel before (all but divisors of 2048 and multiples of 512) keep its plain
     // rotations, bit for bit, in every row of a batch: the deferred form's last bit would move a few codes in 10^6 across a
     // rounding boundary, each of them by a whole step.  20011 fp16 rows of 12 x 64, INT4: 96 us there, 24 us here (14.5 in the
     // deferred form: the plain one takes two operations per element and layer, five where a pair sits in two lanes).
     const bool plain = 2048 % A.width != 0 && A.width % 512 != 0;
-    void (*kern)(SmallArgs) = s.dtype == BQ_F32   ? pick_small_k<float>(s.k, mode, bits, plain)
-                              : s.dtype == BQ_F16 ? pick_small_k<__half>(s.k, mode, bits, plain)
-                                                  : pick_small_k<bf16_t>(s.k, mode, bits, plain);
+    // Persistent workgroups, a multiple of the slice count.  How many waves run best was measured, in us at 2^22, 2^24, 2^25 and 2^27
+    // elements of 32 x 128 (plain rotations: 12 x 64):
+    //   transforms      2048 (8 per compute unit: 5.5 TB/s, 4.4 with four times as many)
+    //   bf16 INT4       8192 8.7 14.4 21.2 74.2 | 4096 6.1 13.2 20.5 75.0 | 3072 5.7 12.8 20.6 78.4 | 2048 5.6 13.4 22.3 93.5
+    //   plain rotations 8192 13.6 21.8 32.5 115 | 4096 9.8 21.1 35.2 128 | 3072 8.6 19.0 31.3 118 | 2048 9.1 24.0 42.5 161
+    //   float32 INT4    4096 7.8 16.2 32.9 126 | 3072 7.4 16.0 32.3 118 | 2048 7.4 16.2 31.1 115 | 1024 7.8 19.7 40.0 135
+    //   plain rotations 4096 10.6 21.7 44.9 180 | 3072 9.0 19.5 35.4 129 | 2048 9.8 24.0 45.1 164
+    //   bf16 values     8192 10.1 17.6 33.6 115 | 4096 7.5 16.7 32.0 115 | 3072 7.1 15.3 30.4 109 | 2048 7.1 16.2 32.0 111
+    //   ... and counts  8192 35.0 38.7 47.1 124 | 4096 21.2 28.8 37.8 121 | 3072 19.1 25.2 36.8 115 | 2048 16.2 24.5 41.4 132
+    //   float32 values  3072 9.6 31.3 56.9 213 | 2048 10.0 29.8 55.3 211 | 1024 9.8 28.1 50.9 187
+    const int64_t elements = s.rows * A.width;
+    int waves = 2048;
+    if (mode == kFwdQuant || mode == kFwdFake) {
+        if (s.dtype == BQ_F32)
+            waves = plain ? (elements < (int64_t)1 << (counts ? 25 : 22) ? 2048 : 3072) : mode == kFwdFake && !counts ? 1024 : 2048;
+        else if (elements >= (int64_t)1 << 23)
+            waves = mode == kFwdFake || elements < (int64_t)3 << 23 ? 3072 : !plain ? 4096 : elements < (int64_t)1 << 26 ? 3072 : 8192;
+    }
+    int64_t per_slice = waves / (t.threads / 64) / A.slices;
+    // A workgroup takes two row groups at a time (in plain rotations one, but counts make it want fewer): as many workgroups as groups leave it half empty (2^20 elements, forward 3.8 us, with
+    // half as many 3.2; INT4 4.2 and 3.7), which they may where there are compute units to spare.
+    if (per_slice * 2 > A.n_groups && (counts || !plain || mode == kFwd || mode == kInv)) per_slice = (A.n_groups + 1) / 2;
+    if (per_slice < 256 / A.slices) per_slice = 256 / A.slices;
+    if (per_slice < 1) per_slice = 1;
+    if (per_slice > A.n_groups) per_slice = A.n_groups;
+    const unsigned grid = (unsigned)(per_slice * A.slices);
+    const bool whole = q && q->group == s.n;
+    void (*kern)(SmallArgs) = s.dtype == BQ_F32   ? pick_small_k<float>(s.k, mode, bits, plain, whole)
+                              : s.dtype == BQ_F16 ? pick_small_k<__half>(s.k, mode, bits, plain, whole)
+                                                  : pick_small_k<bf16_t>(s.k, mode, bits, plain, whole);
     hipLaunchKernelGGL(kern, dim3(grid), dim3(t.threads), 0, stream, A);
     return hipGetLastError();
 }

@@ -211,3 +211,73 @@ def test_large_batches_with_a_short_last_block(n, heads, rows, dtype):
         gu.check_fused_codes(q[0][pick].cpu().numpy(), q[1][pick].cpu().numpy(), ref, bits, group, sd, dtype, tag)
         for a, b, guard in zip(q, whole, (77, 7.0)):
             assert torch.equal(a[rows - 2 * block:rows], b) and (a[rows:] == guard).all()
+
+
+@pytest.mark.parametrize("n,heads,rows", [(4096, 1, 255), (4096, 1, 257), (4096, 1, 515), (8192, 1, 1), (8192, 1, 9), (8192, 1, 130),
+                                          (2048, 2, 300), (512, 1, 70)])
+def test_backward_at_the_slot_counts(n, heads, rows):
+    # batches that fill no, some and several rows per slot; n = 8192 rounds the slots up to whole rounds of the dies, so some
+    # of them have no rows and must still write their zeros
+    x, th, dy = synth.small_case(n, rows, "f16", heads=heads, seed=700 + n + rows, with_dy=True, outliers=0)
+    rdx, rdth, ab = oracle.backward(synth.to_f64(x, "f16"), synth.to_f64(dy, "f16"), th, n, heads)
+    dx, dth = gu.run_bwd(x, dy, th, n, heads, "f16")
+    gu.check_rotated(dx, rdx, "f16", f"dx n={n} T={rows}")
+    floor = np.median(ab, axis=2, keepdims=True) if rows < 32 else ab  # (few rows: as in the seeded sweep)
+    gu.check_dtheta(dth, rdth, np.maximum(ab, floor), what=f"dtheta n={n} T={rows}")
+
+
+@pytest.mark.parametrize("n,heads,rows", [(512, 1, 3000), (512, 8, 300), (256, 1, 10), (2048, 1, 600), (8192, 1, 300)])
+def test_backward_of_flagged_plans_with_grown_tiles(n, heads, rows):
+    # more tiles than workgroups: they grow, and their last one is ragged; fewer: workgroups without a slot take them
+    x, th, dy = synth.small_case(n, rows, "f32", heads=heads, seed=800 + n + rows, with_dy=True, outliers=0)
+    th = th.copy()
+    th[:, :3] = np.float32(np.pi / 2)
+    rdx, rdth, ab = oracle.backward(synth.to_f64(x, "f32"), synth.to_f64(dy, "f32"), th, n, heads)
+    dx, dth = gu.run_bwd(x, dy, th, n, heads, "f32")
+    gu.check_rotated(dx, rdx, "f32", f"dx n={n} T={rows}")
+    floor = np.median(ab, axis=2, keepdims=True) if rows < 32 else ab
+    gu.check_dtheta(dth, rdth, np.maximum(ab, floor), what=f"dtheta n={n} T={rows}")
+
+
+@pytest.mark.parametrize("n,heads,rows", [(128, 1, 5), (128, 32, 3), (128, 32, 700), (64, 24, 40), (32, 3, 77), (8, 1, 600), (16, 4, 1)])
+@pytest.mark.parametrize("dtype", ["f16", "f32"])
+def test_small_quantisers_on_flagged_plans(n, heads, rows, dtype):
+    # plain rotations held in registers; quantiser groups of the whole transform (their own instantiation) and smaller
+    x, th, _ = synth.small_case(n, rows, dtype, heads=heads, seed=900 + n + rows)
+    th = th.copy()
+    th[:, :3] = np.float32(np.pi / 2)
+    ref = oracle.forward(synth.to_f64(x, dtype), th, n, heads)
+    for bits, group, sd in ((4, n, "f16"), (2, n, "f32"), (4, 8, "f32")):
+        tag = f"n={n} H={heads} T={rows} {dtype} INT{bits} g{group} {sd}"
+        codes, scales = gu.run_fwd_quant(x, th, n, heads, dtype, bits, group, sd)
+        gu.check_fused_codes(codes, scales, ref, bits, group, sd, dtype, tag)
+        c = oracle.unpack_codes(codes, bits)
+        yq, hist = gu.run_fwd_fakequant(x, th, n, heads, dtype, bits, group, sd)
+        want = synth.cast_storage(oracle.dequantize(c, scales.astype(np.float32), group).astype(np.float64), dtype)
+        u = np.uint16 if dtype != "f32" else np.uint32
+        np.testing.assert_array_equal(yq.view(u), want.view(u), err_msg=tag)
+        np.testing.assert_array_equal(hist, oracle.bin_histogram(c, bits), err_msg=tag)
+
+
+def test_small_transforms_of_rows_far_apart():
+    # rows_per_block rows of 2^24 bytes and more apart do not fit a lane's 32-bit offset: every row is a group of its own
+    import torch
+    from paper_2509_09679_amd import binding as B
+
+    n, rows, ld = 8, 5, (1 << 23) + 8
+    x, th, _ = synth.small_case(n, rows, "f16", seed=11)
+    plan = B.alloc_plan(torch.from_numpy(th).cuda(), n, 1)
+    buf, out = torch.zeros(rows * ld, dtype=torch.float16, device="cuda"), torch.zeros(rows * ld, dtype=torch.float16, device="cuda")
+    xs, ys = buf.as_strided((rows, n), (ld, 1)), out.as_strided((rows, n), (ld, 1))
+    dense = torch.from_numpy(np.ascontiguousarray(x).view(np.float16)).cuda()
+    xs.copy_(dense)
+    B.bq_butterfly_fwd(xs, ys, plan, B.make_rows(xs, n, 1, out=ys))
+    y = torch.empty_like(dense)
+    B.bq_butterfly_fwd(dense, y, plan, B.make_rows(dense, n, 1))
+    assert torch.equal(ys, y) and int((out != 0).sum()) == int((y != 0).sum())
+    codes, scales = B.alloc_quant_outputs(rows, n, 1, 4, 8, "f32", "cuda")
+    codes2, scales2 = torch.empty_like(codes), torch.empty_like(scales)
+    q = B.make_quant(4, 8, "f32")
+    B.bq_butterfly_fwd_quant(xs, plan, codes, scales, q, B.make_rows(xs, n, 1))
+    B.bq_butterfly_fwd_quant(dense, plan, codes2, scales2, q, B.make_rows(dense, n, 1))
+    assert torch.equal(codes, codes2) and torch.equal(scales, scales2)
