@@ -305,16 +305,16 @@ __device__ __forceinline__ void split8_bf16(const float (&v)[8], v8b *hi, v8b *l
 }
 
 // KS: steps of four input sub-rows (d1 <= 4 KS; inputs past d1 carry zero weights and re-read the last
-// sub-row), IT = ceil(KS / 4) blocks of 16 output sub-rows.  kSlow: the variant for plans whose scale-deferred tables
-// are flagged unusable (plain rotations); both variants are launched and the one that does not apply exits at
-// once, which keeps the out-of-line rotation code, and the stack traffic it brings, out of the fast variant.
-template <typename T, bool kInverse, int KS, bool kSlow>
+// sub-row), IT = ceil(KS / 4) blocks of 16 output sub-rows.  Plans that flag their scale-deferred tables as unusable take plain
+// rotations held in registers (as a kernel of its own, launched behind this one and empty on all other plans, they took 2 us of every
+// call).
+template <typename T, bool kInverse, int KS>
 __global__ __launch_bounds__(kFusedMaxThreads) void kron128_kernel(FusedArgs A)
 {
     constexpr int IT = (KS + 3) / 4;
     extern __shared__ __align__(16) float tile[];  // 3 kStepRows x [d1][kTileRow]
     const PlanHead ph = plan_head(A.plan);
-    if (!ph.matches || ((kInverse ? ph.bad_inv : ph.bad_fwd) != 0) != kSlow) return;
+    if (!ph.matches) return;
     const int d1 = A.d1;
     const int tile_floats = d1 * kTileRow;
     const int tid = threadIdx.x, lane = tid & 63;
@@ -326,48 +326,38 @@ __global__ __launch_bounds__(kFusedMaxThreads) void kron128_kernel(FusedArgs A)
     auto tile_of = [&](int64_t step, int r) { return tile + ((int)(step % 3) * kStepRows + r) * tile_floats; };
     if (tid < A.bfly_threads) {
         // ---- butterfly group ---------------------------------------------------------------------------------
+        // Few sub-rows: this group's loads and arithmetic are the longer part and go first (70000 fp16 rows of 7 x 128 113 -> 110 us, 170000
+        // bf16 rows of 3 x 128 235 -> 224; at d1 = 40 no difference).
+        if (KS == 4) __builtin_amdgcn_s_setprio(2);
         const int sub = tid >> 4, l16 = tid & 15;
         const int idx = lane_chunk(l16) * 8;  // first column of the thread's 8 elements
         const bool live = sub < d1;
-        float c[7][8], d[8];
-#pragma unroll
-        for (int j = 0; j < 7; ++j)
-#pragma unroll
-            for (int r = 0; r < 8; ++r) c[j][r] = A.fg[j * kFusedD2 + idx + r];
-#pragma unroll
-        for (int r = 0; r < 8; ++r) d[r] = A.fd[idx + r];
         const T *in = (const T *)A.in + (size_t)sub * kFusedD2 + idx;
-        // kAhead rows are in flight from memory: a compute unit runs one workgroup, and a row is only 256 bytes
-        // per sub-row, so it takes several to cover the latency (four instead of two: d1 = 8 and 16 run 20 % and
-        // 16 % faster; d1 = 40, which is bound by arithmetic, is unchanged; six measured slower again).
+        // Four rows (plain rotations, short of registers: two) are in flight from memory: a compute unit runs one workgroup, and a
+        // row is only 256 bytes per sub-row, so it takes several to cover the latency (four instead of two: d1 = 8 and 16 run 20 %
+        // and 16 % faster; d1 = 40, which is bound by arithmetic, is unchanged; six measured slower again).
         // This group only loads; the rows are stored by the store group: memory operations of a wave retire
         // in order, so a wave that both stores and prefetches ends up waiting for its stores to be
         // acknowledged before it may use a prefetched row.
-        constexpr int kAhead = 4;
-        Raw8 raw[kAhead] = {};
-#pragma unroll
-        for (int a = 0; a < kAhead; ++a)
-            if (live && mine > a) raw[a] = load8(in + ((int64_t)blockIdx.x + a * (int64_t)gridDim.x) * width);
-        // one step: row `it` out of `slot`, which is then refilled with row it + kAhead (the loop below is unrolled
+        //
+        // one step: row `it` out of `slot`, which is then refilled with row it + ahead (the loop below is unrolled
         // over the slots, so that no row moves between registers)
-        auto row_step = [&](int64_t it, Raw8 &slot, float *z_tile) {
+        auto row_step = [&](int64_t it, Raw8 &slot, float *z_tile, auto &transform, int ahead) {
             if (live && it < mine) {  // transform row it
                 float u[8];
                 unpack8(slot, u, (const T *)nullptr);
-                if (it + kAhead < mine) slot = load8(in + (blockIdx.x + (it + kAhead) * gridDim.x) * width);
-                if (!kSlow)
-                    fast_small<7, kInverse>(u, c, d);
-                else
-                    slow_small<7, kInverse>(u, A.cs, idx);
+                if (it + ahead < mine) slot = load8(in + (blockIdx.x + (it + ahead) * gridDim.x) * width);
+                transform(u);
                 if (kSplitMix<T>) {
                     // binary16 rows: the tile takes each value as its two-way bfloat16 split, hi (rounded) in the upper
                     // half of the word and lo (truncated: |v - hi - lo| < 2^-16 |v| either way) in the lower, ready
                     // to be packed into matrix operands by the mix group
 #pragma unroll
-                    for (int r = 0; r < 8; ++r) {
-                        const uint32_t h = bf16_bits_of(u[r]);
-                        const float rest = u[r] - __uint_as_float(h);
-                        u[r] = __uint_as_float(__builtin_amdgcn_perm(h, __float_as_uint(rest), 0x07060302u));
+                    for (int r = 0; r < 8; r += 2) {
+                        const uint32_t h = f32x2_to_bf16x2_bits(u[r], u[r + 1]);
+                        const float rest0 = u[r] - __uint_as_float(h << 16), rest1 = u[r + 1] - __uint_as_float(h & 0xFFFF0000u);
+                        u[r] = __uint_as_float(__builtin_amdgcn_perm(h, __float_as_uint(rest0), 0x05040302u));
+                        u[r + 1] = __uint_as_float(__builtin_amdgcn_perm(h, __float_as_uint(rest1), 0x07060302u));
                     }
                 }
                 float4 *dst = (float4 *)&z_tile[sub * kTileRow + idx];
@@ -375,16 +365,34 @@ __global__ __launch_bounds__(kFusedMaxThreads) void kron128_kernel(FusedArgs A)
                 dst[1] = make_float4(u[4], u[5], u[6], u[7]);
             }
         };
-        static_assert(kAhead % kStepRows == 0, "whole steps per turn of the prefetch slots");
-        for (int64_t st = 0; st < steps; st += kAhead / kStepRows) {
+        auto rows = [&](auto transform, auto ahead) {
+            constexpr int kAhead = decltype(ahead)::value;
+            static_assert(kAhead % kStepRows == 0, "whole steps per turn of the prefetch slots");
+            Raw8 raw[kAhead] = {};
 #pragma unroll
-            for (int h = 0; h < kAhead / kStepRows; ++h)
-                if (st + h < steps) {
+            for (int a = 0; a < kAhead; ++a)
+                if (live && mine > a) raw[a] = load8(in + ((int64_t)blockIdx.x + a * (int64_t)gridDim.x) * width);
+            for (int64_t st = 0; st < steps; st += kAhead / kStepRows) {
 #pragma unroll
-                    for (int r = 0; r < kStepRows; ++r)
-                        row_step((st + h) * kStepRows + r, raw[h * kStepRows + r], tile_of(st + h, r));
-                    __syncthreads();
-                }
+                for (int h = 0; h < kAhead / kStepRows; ++h)
+                    if (st + h < steps) {
+#pragma unroll
+                        for (int r = 0; r < kStepRows; ++r)
+                            row_step((st + h) * kStepRows + r, raw[h * kStepRows + r], tile_of(st + h, r), transform, kAhead);
+                        __syncthreads();
+                    }
+            }
+        };
+        if ((kInverse ? ph.bad_inv : ph.bad_fwd) == 0) {
+            float c[7][8], d[8];
+#pragma unroll
+            for (int j = 0; j < 7; ++j) load_coef8(A.fg + j * kFusedD2 + idx, c[j]);
+            load_coef8(A.fd + idx, d);
+            rows([&](float (&u)[8]) { fast_small<7, kInverse>(u, c, d); }, std::integral_constant<int, 4>());
+        } else {
+            PlainCascade<7, kInverse, true> p;
+            p.load(A.cs, idx);
+            rows([&](float (&u)[8]) { p.run(u); }, std::integral_constant<int, 2>());
         }
     } else if (tid >= A.bfly_threads + kMixWaves * 64) {
         // ---- store group: row it-2, 16-byte pieces of 8 consecutive elements, one rounding to the row type ------
@@ -421,6 +429,9 @@ __global__ __launch_bounds__(kFusedMaxThreads) void kron128_kernel(FusedArgs A)
         }
     } else {
         // ---- mix group ---------------------------------------------------------------------------------------
+        // d1 = 40, bfloat16 rows: the float32 matrix instructions are the longer part (10007 rows 78 -> 72 us; float32 rows, whose loads
+        // are twice as long, 50 -> 53, binary16 rows 60 -> 59 and inverse 56 -> 56.5: not there; few sub-rows 2 to 6 % slower).
+        if (KS == 10 && std::is_same<T, bf16_t>::value) __builtin_amdgcn_s_setprio(2);
         const int mw = (tid - A.bfly_threads) >> 6;  // 0 .. kMixWaves-1: column blocks 2 mw and 2 mw + 1
         if constexpr (kSplitMix<T>) {
             // binary16 rows: the product runs on the bfloat16 matrix instruction with two-way splits of both
@@ -566,27 +577,14 @@ static hipError_t launch_kron_fused_t(FusedArgs &A, hipStream_t stream)
     A.bfly_threads = ((A.d1 * 16 + 63) / 64) * 64;  // 16 lanes per sub-row, whole waves
     const int threads = A.bfly_threads + (kMixWaves + kStoreWaves) * 64;
     const size_t lds = 3 * kStepRows * (size_t)A.d1 * kTileRow * sizeof(float);
-    void (*kern)(FusedArgs), (*kern_slow)(FusedArgs);
-    if (A.d1 <= 16) {
-        kern = kron128_kernel<T, kInverse, 4, false>;
-        kern_slow = kron128_kernel<T, kInverse, 4, true>;
-    } else if (A.d1 <= 32) {
-        kern = kron128_kernel<T, kInverse, 8, false>;
-        kern_slow = kron128_kernel<T, kInverse, 8, true>;
-    } else {
-        kern = kron128_kernel<T, kInverse, 10, false>;
-        kern_slow = kron128_kernel<T, kInverse, 10, true>;
-    }
+    void (*kern)(FusedArgs) = A.d1 <= 16 ? kron128_kernel<T, kInverse, 4> : A.d1 <= 32 ? kron128_kernel<T, kInverse, 8> : kron128_kernel<T, kInverse, 10>;
     hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
-    e = hipFuncSetAttribute((const void *)kern_slow, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
     // one workgroup per compute unit; two for d1 <= 8 (8 waves each), which a single one leaves latency-bound
     // (d1 = 8: 0.81 -> 0.54 ms for 327680 rows; at d1 = 16 two fit as well but measured no faster)
     int64_t grid = A.d1 <= 8 ? 512 : 256;
     if (grid > A.rows) grid = A.rows;
     hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(threads), lds, stream, A);
-    hipLaunchKernelGGL(kern_slow, dim3((unsigned)grid), dim3(threads), lds, stream, A);
     return hipGetLastError();
 }
 

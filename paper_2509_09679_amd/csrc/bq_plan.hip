@@ -27,14 +27,14 @@ __global__ void plan_header_kernel(PlanHeader *hdr, int n, int heads, int k)
 // pair) and the cosines of the other layers (one per element), then runs both directions over the own layers, the
 // forward cascade in threads 0 .. 127 and the transposed one in threads 128 .. 255, partners' scales exchanged through
 // LDS.  At n = 4096 that is 128 workgroups of 576 evaluations each (1.5 times the angles there are).  Bound by the
-// latency of the double-precision sine and cosine, three rounds of them.  One workgroup per head and direction walking
+// latency of the double-precision sine and cosine.  One workgroup per head and direction walking
 // all layers with a barrier each, which this replaces, evaluated every angle four times on two compute units.
 // A high group's elements are 2^kl apart, so neighbouring groups share the cache lines they read and write: workgroups
 // (dealt to the eight dies in turn) are numbered so that neighbouring groups are on the same die, whose L2 then puts the lines
 // together.  In launch order many heads were slower than the kernel this replaces: 512 heads of 4096 396 us before, 606
 // in launch order, 319 this way; 512 heads of 8192 897, 1209, 669.  One head, both launches, back to back: n = 4096
 // 80 -> 7.1 us, n = 8192 163 -> 8.9, n = 16384 342 -> 10.9.
-constexpr int kPlanThreads = 256;
+constexpr int kPlanThreads = 256, kPlanMaxThreads = 1024;  // of a workgroup (launch_plan_build)
 constexpr int kPlanMaxGroup = 128;  // elements of a group: k <= 7 has one group per head, k <= 14 groups of <= 2^7
 
 struct PlanTableArgs {
@@ -47,7 +47,7 @@ struct PlanTableArgs {
     int *bad[2];
 };
 
-__global__ __launch_bounds__(kPlanThreads) void plan_table_kernel(PlanTableArgs A)
+__global__ __launch_bounds__(kPlanMaxThreads) void plan_table_kernel(PlanTableArgs A)
 {
     __shared__ double own_c[7][kPlanMaxGroup / 2], own_t[7][kPlanMaxGroup / 2];  // own layers, per pair
     __shared__ double other_c[7][kPlanMaxGroup];                                // the other layers, per element
@@ -68,7 +68,7 @@ __global__ __launch_bounds__(kPlanThreads) void plan_table_kernel(PlanTableArgs 
     const float *th = A.theta + (size_t)head * k * (n / 2);
     const int tid = threadIdx.x;
 
-    for (int q = tid; q < own * pairs + others * size; q += kPlanThreads) {
+    for (int q = tid; q < own * pairs + others * size; q += blockDim.x) {
         const bool mine = q < own * pairs;
         const int r = mine ? q : q - own * pairs;
         const int j = mine ? r >> (own - 1) : r >> own;       // layer inside its set
@@ -79,19 +79,19 @@ __global__ __launch_bounds__(kPlanThreads) void plan_table_kernel(PlanTableArgs 
         const int p = ((e >> i) << (i - 1)) | (e & ((1 << (i - 1)) - 1));
         const size_t at = (size_t)(i - 1) * (n / 2) + p;
         const double t = (double)th[at];
-        const double c = cos(t);
         if (mine) {
-            const double s = sin(t);
+            double s, c;
+            sincos(t, &s, &c);
             own_c[j][r & (pairs - 1)] = c;
             own_t[j][r & (pairs - 1)] = s / c;
             A.cs[(size_t)head * k * (n / 2) + at] = make_float2((float)c, (float)s);
         } else {
-            other_c[j][l] = c;
+            other_c[j][l] = cos(t);
         }
     }
     __syncthreads();
     const int inverse = tid >= kPlanMaxGroup, l = tid & (kPlanMaxGroup - 1);
-    const bool live = l < size;
+    const bool live = l < size && tid < 2 * kPlanMaxGroup;
     const int e = base | (l << shift);
     float *fgh = A.fg[inverse] + (size_t)head * k * n;
     // scale in front of the group's own layers: the other layers' cosines in cascade order, if they come first
@@ -156,7 +156,19 @@ hipError_t launch_plan_build(const float *theta, int n, int heads, int k, void *
     F.fm = (float *)(p + L.fm_fwd);
     F.bad[0] = &hdr->fast_bad_fwd;
     F.bad[1] = &hdr->fast_bad_inv;
-    hipLaunchKernelGGL(plan_table_kernel, dim3((unsigned)(heads * (F.low_groups + F.high_groups))), dim3(kPlanThreads), 0, stream, F);
+    // A plan that leaves compute units free: as many threads as evaluations, up to the workgroup's limit, because the rounds are one
+    // behind the other (one head of 4096, both launches, 7.14 -> 6.82 us, 16384 10.5 -> 9.7).  Many heads: 256, so that the units
+    // are not held by waves that wait (512 heads of 4096 325 us, with 576 threads 522).
+    const int64_t workgroups = (int64_t)heads * (F.low_groups + F.high_groups);
+    int threads = kPlanThreads;
+    if (workgroups <= 256) {
+        const int kh = k - F.kl;
+        const int low = (F.kl << (F.kl - 1)) + (kh << F.kl), high = kh > 0 ? (kh << (kh - 1)) + (F.kl << kh) : 0;
+        const int evals = low > high ? low : high, rounds = (evals + kPlanMaxThreads - 1) / kPlanMaxThreads;
+        threads = ((evals + rounds - 1) / rounds + 63) & ~63;
+        if (threads < kPlanThreads) threads = kPlanThreads;
+    }
+    hipLaunchKernelGGL(plan_table_kernel, dim3((unsigned)workgroups), dim3((unsigned)threads), 0, stream, F);
     return hipGetLastError();
 }
 

@@ -34,93 +34,6 @@ struct SmallArgs {
     int group, scale_f16;
 };
 
-// The cascade in plain (cos, sin) rotations held in registers.
-// kOwn: an element's own product inside the fused operation:
-//   y_a = fma(c, x_a, -(s x_b)),  y_b = fma(c, x_b, s x_a)   (transposed: the signs of s swap)
-// i.e. fma(w1, own, w2 partner) in either lane of a pair.  Else (forward only) as the kernel for any n rounds them:
-//   y_a = fma(c, x_a, -(s x_b)),  y_b = fma(s, x_a, c x_b)
-// i.e. fma(w1, x_a, w2 x_b), with the lane's own (w1, w2).
-template <int K, bool kInverse, bool kOwn>
-struct PlainCascade {
-    static_assert(kOwn || !kInverse, "");
-    float rc[3][4], rs[3][4];        // layers 1..3: cos and (transposed: minus) sin of the thread's four pairs
-    float w1[4][8], w2[4][8];        // layers 4..K
-    bool upper[4];                   // this lane holds the upper elements of the layer's pairs
-    __device__ __forceinline__ void load(const float2 *cs_head, int idx)
-    {
-        constexpr int half = 1 << (K - 1);
-        auto entry = [&](int e, int i) {  // of the pair that element e belongs to in layer i
-            const int h = 1 << (i - 1);
-            return cs_head[(size_t)(i - 1) * half + (((e >> i) << (i - 1)) | (e & (h - 1)))];
-        };
-#pragma unroll
-        for (int j = 0; j < 3; ++j) {
-            int q = 0;
-#pragma unroll
-            for (int r = 0; r < 8; ++r)
-                if (!(r & (1 << j))) {
-                    const float2 w = entry(idx + r, j + 1);
-                    rc[j][q] = w.x;
-                    rs[j][q] = kInverse ? -w.y : w.y;
-                    ++q;
-                }
-        }
-#pragma unroll
-        for (int j = 0; j < K - 3; ++j) {
-            upper[j] = ((idx >> (3 + j)) & 1) != 0;
-#pragma unroll
-            for (int r = 0; r < 8; ++r) {
-                const float2 w = entry(idx + r, 4 + j);
-                w1[j][r] = !kOwn && upper[j] ? w.y : w.x;
-                w2[j][r] = kOwn ? (upper[j] != kInverse ? w.y : -w.y) : (upper[j] ? w.x : -w.y);
-            }
-        }
-    }
-    template <int J>
-    __device__ __forceinline__ void pairs(float (&u)[8]) const
-    {
-        int q = 0;
-#pragma unroll
-        for (int r = 0; r < 8; ++r)
-            if (!(r & (1 << J))) {
-                const float xa = u[r], xb = u[r | (1 << J)];
-                u[r] = __builtin_fmaf(rc[J][q], xa, -(rs[J][q] * xb));
-                u[r | (1 << J)] = kOwn ? __builtin_fmaf(rc[J][q], xb, rs[J][q] * xa) : __builtin_fmaf(rs[J][q], xa, rc[J][q] * xb);
-                ++q;
-            }
-    }
-    template <int J, int CTRL>
-    __device__ __forceinline__ void lanes(float (&u)[8]) const
-    {
-#pragma unroll
-        for (int r = 0; r < 8; ++r) {
-            const float p = dpp_read<CTRL>(u[r]);
-            const float xa = !kOwn && upper[J] ? p : u[r], xb = !kOwn && upper[J] ? u[r] : p;
-            u[r] = __builtin_fmaf(w1[J][r], xa, w2[J][r] * xb);
-        }
-    }
-    __device__ __forceinline__ void run(float (&u)[8]) const
-    {
-        if (!kInverse) {
-            pairs<0>(u);
-            pairs<1>(u);
-            pairs<2>(u);
-            if (K >= 4) lanes<0, 0xB1>(u);   // quad_perm [1,0,3,2]
-            if (K >= 5) lanes<1, 0x4E>(u);   // quad_perm [2,3,0,1]
-            if (K >= 6) lanes<2, 0x141>(u);  // row_half_mirror
-            if (K >= 7) lanes<3, 0x128>(u);  // row_ror:8
-        } else {
-            if (K >= 7) lanes<3, 0x128>(u);
-            if (K >= 6) lanes<2, 0x141>(u);
-            if (K >= 5) lanes<1, 0x4E>(u);
-            if (K >= 4) lanes<0, 0xB1>(u);
-            pairs<2>(u);
-            pairs<1>(u);
-            pairs<0>(u);
-        }
-    }
-};
-
 // kWhole: quantiser groups of n channels (else any that divide n)
 template <typename T, int K, int kMode, int kBits, bool kPlain = false, bool kWhole = false>
 // (four waves per SIMD: the quantisers fill them; without the bound some end up a few registers above 128)
