@@ -1,4 +1,5 @@
-"""ctypes binding of libbq.so: the same entry points as include/bq.h, taking torch tensors.
+"""Binding of libbq.so: the same entry points as include/bq.h, taking torch tensors.  The calls of the path go through
+bqcall.so (csrc/bqcall.c), the others through ctypes.
 
 Argument marshalling only — every step of the path runs in the library's HIP kernels.  torch is used
 for device memory and the current stream, nothing else.  There is no CPU or eager fallback: if the
@@ -12,6 +13,7 @@ from typing import Optional
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(HERE, "libbq.so")
+CALL_PATH = os.path.join(HERE, "bqcall.so")
 
 BQ_OK = 0
 BQ_F32, BQ_F16, BQ_BF16 = 0, 1, 2
@@ -109,6 +111,38 @@ def lib() -> ctypes.CDLL:
     return _LIB
 
 
+_CALLS = None
+
+# the entry points a program calls per batch, and what their arguments are (csrc/bqcall.c)
+_KINDS = {"bq_plan_build": "piipus", "bq_butterfly_fwd": "ppprs", "bq_butterfly_inv": "ppprs", "bq_butterfly_fwd_quant": "ppppqrs",
+          "bq_butterfly_fwd_fakequant": "ppppqrs", "bq_kron_fwd": "pppiprs", "bq_kron_inv": "pppiprs", "bq_butterfly_bwd": "ppppppurs"}
+
+
+class _Calls:
+    """One Caller per entry point of _KINDS, without the "bq_" in front."""
+
+    def __init__(self):
+        import importlib.machinery
+        import importlib.util
+
+        L = lib()
+        if not os.path.exists(CALL_PATH):
+            raise FileNotFoundError(f"{CALL_PATH} not built: run `python -m paper_2509_09679_amd.build`")
+        loader = importlib.machinery.ExtensionFileLoader("bqcall", CALL_PATH)
+        module = importlib.util.module_from_spec(importlib.util.spec_from_loader("bqcall", loader))
+        loader.exec_module(module)
+        for name, kinds in _KINDS.items():
+            address = ctypes.cast(getattr(L, name), ctypes.c_void_p).value
+            setattr(self, name[3:], module.Caller(address, kinds, bq_rows, bq_quant))
+
+
+def _calls() -> _Calls:
+    global _CALLS
+    if _CALLS is None:
+        _CALLS = _Calls()
+    return _CALLS
+
+
 def _check(status: int):
     if status != BQ_OK:
         raise BqError(status, lib().bq_last_error().decode())
@@ -191,16 +225,15 @@ def bq_plan_bytes(n: int, heads: int = 1) -> int:
 
 def bq_plan_build(theta, n: int, heads: int, plan, stream=None) -> None:
     """theta: float32 device tensor [heads, log2 n, n/2]; plan: uint8 device tensor of bq_plan_bytes."""
-    _check(lib().bq_plan_build(_ptr(theta), n, heads, _ptr(plan), plan.numel() * plan.element_size(),
-                               _stream_ptr(stream)))
+    _check((_CALLS or _calls()).plan_build(theta, n, heads, plan, plan.numel() * plan.element_size(), _stream_ptr(stream)))
 
 
 def bq_butterfly_fwd(x, y, plan, rows: bq_rows, stream=None) -> None:
-    _check(lib().bq_butterfly_fwd(_ptr(x), _ptr(y), _ptr(plan), ctypes.byref(rows), _stream_ptr(stream)))
+    _check((_CALLS or _calls()).butterfly_fwd(x, y, plan, rows, _stream_ptr(stream)))
 
 
 def bq_butterfly_inv(y, x, plan, rows: bq_rows, stream=None) -> None:
-    _check(lib().bq_butterfly_inv(_ptr(y), _ptr(x), _ptr(plan), ctypes.byref(rows), _stream_ptr(stream)))
+    _check((_CALLS or _calls()).butterfly_inv(y, x, plan, rows, _stream_ptr(stream)))
 
 
 def bq_hadamard_fwd(x, y, rows: bq_rows, stream=None) -> None:
@@ -208,14 +241,12 @@ def bq_hadamard_fwd(x, y, rows: bq_rows, stream=None) -> None:
 
 
 def bq_butterfly_fwd_quant(x, plan, codes, scales, quant: bq_quant, rows: bq_rows, stream=None) -> None:
-    _check(lib().bq_butterfly_fwd_quant(_ptr(x), _ptr(plan), _ptr(codes), _ptr(scales), ctypes.byref(quant),
-                                        ctypes.byref(rows), _stream_ptr(stream)))
+    _check((_CALLS or _calls()).butterfly_fwd_quant(x, plan, codes, scales, quant, rows, _stream_ptr(stream)))
 
 
 def bq_butterfly_fwd_fakequant(x, plan, yq, hist, quant: bq_quant, rows: bq_rows, stream=None) -> None:
     """yq (rows' dtype, or None) and hist (uint64/int64 tensor of 2^bits counters, or None)."""
-    _check(lib().bq_butterfly_fwd_fakequant(_ptr(x), _ptr(plan), _ptr(yq), _ptr(hist), ctypes.byref(quant),
-                                            ctypes.byref(rows), _stream_ptr(stream)))
+    _check((_CALLS or _calls()).butterfly_fwd_fakequant(x, plan, yq, hist, quant, rows, _stream_ptr(stream)))
 
 
 def bq_cayley_build(params, d1: int, q1, stream=None) -> None:
@@ -223,11 +254,11 @@ def bq_cayley_build(params, d1: int, q1, stream=None) -> None:
 
 
 def bq_kron_fwd(x, y, q1, d1: int, plan, rows: bq_rows, stream=None) -> None:
-    _check(lib().bq_kron_fwd(_ptr(x), _ptr(y), _ptr(q1), d1, _ptr(plan), ctypes.byref(rows), _stream_ptr(stream)))
+    _check((_CALLS or _calls()).kron_fwd(x, y, q1, d1, plan, rows, _stream_ptr(stream)))
 
 
 def bq_kron_inv(y, x, q1, d1: int, plan, rows: bq_rows, stream=None) -> None:
-    _check(lib().bq_kron_inv(_ptr(y), _ptr(x), _ptr(q1), d1, _ptr(plan), ctypes.byref(rows), _stream_ptr(stream)))
+    _check((_CALLS or _calls()).kron_inv(y, x, q1, d1, plan, rows, _stream_ptr(stream)))
 
 
 def bq_residual_scratch_bytes() -> int:
@@ -261,9 +292,8 @@ def bq_butterfly_bwd_workspace_bytes(rows: bq_rows) -> int:
 
 
 def bq_butterfly_bwd(x, dy, plan, dx, dtheta, workspace, rows: bq_rows, stream=None) -> None:
-    _check(lib().bq_butterfly_bwd(_ptr(x), _ptr(dy), _ptr(plan), _ptr(dx), _ptr(dtheta), _ptr(workspace),
-                                  workspace.numel() * workspace.element_size(), ctypes.byref(rows),
-                                  _stream_ptr(stream)))
+    _check((_CALLS or _calls()).butterfly_bwd(x, dy, plan, dx, dtheta, workspace, workspace.numel() * workspace.element_size(), rows,
+                                              _stream_ptr(stream)))
 
 
 def bq_butterfly_bwd_static(x, dy, plan, dx, dtheta, rows: bq_rows, stream=None) -> None:

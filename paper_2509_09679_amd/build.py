@@ -1,9 +1,11 @@
-"""Compile the HIP sources in csrc/ into paper_2509_09679_amd/libbq.so for gfx950 (in-tree)."""
+"""Compile the HIP sources in csrc/ into paper_2509_09679_amd/libbq.so for gfx950 and the binding's caller, csrc/bqcall.c, into
+bqcall.so (in-tree)."""
 from __future__ import annotations
 
 import glob
 import os
 import subprocess
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -11,6 +13,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 OBJ_DIR = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libbq.so")
+CALL = os.path.join(HERE, "bqcall.so")
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 # Packed-fp32 VALU instructions are switched off for every device translation unit.
@@ -39,6 +42,8 @@ def build(verbose: bool = False, save_temps: bool = False) -> str:
         objs = list(ex.map(lambda s: _compile(s, extra), srcs))
     cmd = [HIPCC, "-shared", "-fPIC", "--offload-arch=gfx950", "-o", LIB] + objs
     subprocess.run(cmd, check=True)
+    subprocess.run(["gcc", "-O2", "-Wall", "-shared", "-fPIC", "-I" + sysconfig.get_paths()["include"], os.path.join(CSRC, "bqcall.c"), "-o", CALL],
+                   check=True)
     if verbose:
         print("built", LIB)
     return LIB

@@ -68,7 +68,7 @@ __device__ __forceinline__ void put_partial(float *p, float v, int first)
 // were formed behind it (n = 8192), on the layer's inputs, where both elements have the scale before the next layer down.
 __device__ __forceinline__ double sum_scale(const float *__restrict__ fw_inv, int n_log, int head, int i, int p, bool after_last)
 {
-    const float *fw = fw_inv + ((size_t)head * n_log + (after_last ? i - 2 : i - 1) << n_log);
+    const float *fw = fw_inv + (((size_t)head * n_log + (after_last ? i - 2 : i - 1)) << n_log);
     const int a = ((p >> (i - 1)) << i) | (p & ((1 << (i - 1)) - 1));
     return (double)fw[a] * (double)fw[a | (1 << (i - 1))];
 }

@@ -1,0 +1,74 @@
+"""The caller behind the binding's hot entry points: argument kinds, refusals, agreement with the ctypes prototypes."""
+import ctypes
+
+import pytest
+
+from paper_2509_09679_amd import binding as B
+
+
+class Fake:  # a tensor as far as the binding looks at one
+    def data_ptr(self):
+        return 0x7F0000001000
+
+    def numel(self):
+        return 64
+
+    def element_size(self):
+        return 1
+
+
+def _rows(**kw):
+    r = B.bq_rows()
+    r.rows, r.n, r.heads, r.ld_x, r.ld_y, r.dtype = 4, 64, 1, 64, 64, B.BQ_F16
+    for k, v in kw.items():
+        setattr(r, k, v)
+    return r
+
+
+def test_kinds_match_the_ctypes_prototypes():
+    L = B.lib()
+    kind = {ctypes.c_void_p: "ps", ctypes.c_int32: "i", ctypes.c_size_t: "u", ctypes.POINTER(B.bq_rows): "r", ctypes.POINTER(B.bq_quant): "q"}
+    for name, kinds in B._KINDS.items():
+        types = getattr(L, name).argtypes
+        assert len(types) == len(kinds) and all(k in kind[t] for k, t in zip(kinds, types)), name
+
+
+def test_arguments_arrive_and_errors_come_back():
+    # every call ends in the library's own checks: nothing is launched
+    x, s = Fake(), 0
+    with pytest.raises(B.BqError, match="power of two") as e:
+        B.bq_butterfly_fwd(x, x, x, _rows(n=12, ld_x=12, ld_y=12), stream=type("S", (), {"cuda_stream": s}))
+    assert e.value.status == 2
+    for args in ((None, x, x), (x, None, x), (x, x, None)):
+        with pytest.raises(B.BqError) as e:
+            B.bq_butterfly_inv(*args, _rows(), stream=type("S", (), {"cuda_stream": s}))
+        assert e.value.status == 1
+    with pytest.raises(B.BqError) as e:  # a workspace of 64 bytes: size_t and the ninth argument
+        B.bq_butterfly_bwd(x, x, x, x, x, x, _rows(), stream=type("S", (), {"cuda_stream": s}))
+    assert e.value.status == 5
+    q = B.make_quant(3, 32, "f16")
+    with pytest.raises(B.BqError):
+        B.bq_butterfly_fwd_quant(x, x, x, x, q, _rows(), stream=type("S", (), {"cuda_stream": s}))
+    with pytest.raises(B.BqError):
+        B.bq_plan_build(x, 64, -1, x, stream=type("S", (), {"cuda_stream": s}))
+
+
+def test_what_is_not_an_argument_is_refused():
+    c, x = B._calls(), Fake()
+    for bad in ((x, x, x, None, 0), (x, x, x, B.bq_quant(), 0), (x, x, x, _rows()), (x, x, x, _rows(), 0, 0), (x, x, x, _rows(), 0.0),
+                (x, x, x, _rows(), None)):
+        with pytest.raises(TypeError):
+            c.butterfly_fwd(*bad)
+    with pytest.raises(AttributeError):
+        c.butterfly_fwd(x, 3, x, _rows(), 0)
+    with pytest.raises(TypeError):
+        c.plan_build(x, 64.0, 1, x, 64, 0)
+    with pytest.raises(TypeError):
+        c.butterfly_fwd(x, x, x, rows=_rows(), stream=0)
+
+    class Raises(Fake):
+        def data_ptr(self):
+            raise RuntimeError("no storage")
+
+    with pytest.raises(RuntimeError, match="no storage"):
+        c.butterfly_fwd(x, Raises(), x, _rows(), 0)
