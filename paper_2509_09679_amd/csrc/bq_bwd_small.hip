@@ -12,9 +12,11 @@
 // angles; an entry is written by exactly one thread.  A second kernel adds the slots in double in a fixed
 // order: no atomics, the result does not depend on scheduling.
 //
-// The kernels exit at once when the plan flags the scale-deferred tables as unusable; the generic backward
-// kernel, launched between the two with the opposite condition, then does the work, and the second kernel adds its sums.
+// When the plan flags the scale-deferred tables as unusable, workgroups of 256 threads run the backward pass for any n instead
+// (bq_generic_bwd.h); narrower ones exit and leave it to a launch of its own (2 us of every call on other plans; in 64 threads that
+// pass would take longer).  The second kernel adds those sums.
 #include "bq_bwd_blocks.h"
+#include "bq_generic_bwd.h"
 #include "bq_internal.h"
 
 namespace bq {
@@ -37,13 +39,23 @@ struct SmallBwdArgs {
     int span, rows_per_block, slices;  // SmallTiling
     int64_t n_groups;    // row groups = ceil(rows / rows_per_block)
     int64_t n_angles;    // heads * k * n / 2
+    int grid;            // workgroups; a launch may have more, which only help on flagged plans
+    int plain_parts;     // flagged plans: the workgroups that take part, each with a slice of its own; 0: a launch of its own does
 };
+constexpr int kSbPlainTile = 1024;  // elements of a tile of that pass at n <= 128
 
 template <typename T, int K, bool kDx>
-__global__ __launch_bounds__(kSbThreads) void small_bwd_kernel(SmallBwdArgs A)
+__global__ __launch_bounds__(kSbThreads) void small_bwd_kernel(SmallBwdArgs A, BwdArgs P)
 {
     constexpr int n = 1 << K;
-    if (!plan_fast_both(A.plan)) return;
+    __shared__ float plain_tile[2 * kSbPlainTile];
+    const PlanUse use = plan_use(A.plan);
+    if (use == kPlanForeign) return;
+    if (use == kPlanPlain) {
+        if ((int)blockIdx.x < A.plain_parts) generic_bwd_rows<T, kSbThreads>(P, plain_tile, (int)blockIdx.x, A.plain_parts);
+        return;
+    }
+    if ((int)blockIdx.x >= A.grid) return;
     const int tid = threadIdx.x;
     const int chunk = (tid & ~15) | lane_chunk(tid & 15);  // chunk of 8 elements inside the workgroup's span
     const int e0 = chunk * 8;
@@ -53,13 +65,13 @@ __global__ __launch_bounds__(kSbThreads) void small_bwd_kernel(SmallBwdArgs A)
         row_in_block = 0;
         col = (int)(blockIdx.x % A.slices) * A.span + e0;
         grp_first = blockIdx.x / A.slices;
-        grp_step = gridDim.x / A.slices;
+        grp_step = A.grid / A.slices;
         slot = grp_first;
     } else {
         row_in_block = e0 / A.width;
         col = e0 - (int)row_in_block * A.width;
         grp_first = blockIdx.x;
-        grp_step = gridDim.x;
+        grp_step = A.grid;
         slot = (int64_t)blockIdx.x * A.rows_per_block + row_in_block;
     }
     const bool idle = e0 >= A.span || col >= A.width;  // no row of the batch and no slot is this lane's own
@@ -232,23 +244,23 @@ size_t small_bwd_workspace_bytes(const Shape &s)
 }
 
 template <typename T, int K>
-static void launch_small_bwd_k(const SmallBwdArgs &A, const SmallBwdGrid &g, hipStream_t stream)
+static void launch_small_bwd_k(const SmallBwdArgs &A, const BwdArgs &P, unsigned grid, int threads, hipStream_t stream)
 {
     if (A.dx)
-        hipLaunchKernelGGL((small_bwd_kernel<T, K, true>), dim3(g.grid), dim3(g.t.threads), 0, stream, A);
+        hipLaunchKernelGGL((small_bwd_kernel<T, K, true>), dim3(grid), dim3(threads), 0, stream, A, P);
     else
-        hipLaunchKernelGGL((small_bwd_kernel<T, K, false>), dim3(g.grid), dim3(g.t.threads), 0, stream, A);
+        hipLaunchKernelGGL((small_bwd_kernel<T, K, false>), dim3(grid), dim3(threads), 0, stream, A, P);
 }
 
 template <typename T>
-static void launch_small_bwd_t(const SmallBwdArgs &A, int k, const SmallBwdGrid &g, hipStream_t stream)
+static void launch_small_bwd_t(const SmallBwdArgs &A, const BwdArgs &P, int k, unsigned grid, int threads, hipStream_t stream)
 {
     switch (k) {
-        case 3: return launch_small_bwd_k<T, 3>(A, g, stream);
-        case 4: return launch_small_bwd_k<T, 4>(A, g, stream);
-        case 5: return launch_small_bwd_k<T, 5>(A, g, stream);
-        case 6: return launch_small_bwd_k<T, 6>(A, g, stream);
-        default: return launch_small_bwd_k<T, 7>(A, g, stream);
+        case 3: return launch_small_bwd_k<T, 3>(A, P, grid, threads, stream);
+        case 4: return launch_small_bwd_k<T, 4>(A, P, grid, threads, stream);
+        case 5: return launch_small_bwd_k<T, 5>(A, P, grid, threads, stream);
+        case 6: return launch_small_bwd_k<T, 6>(A, P, grid, threads, stream);
+        default: return launch_small_bwd_k<T, 7>(A, P, grid, threads, stream);
     }
 }
 
@@ -277,14 +289,21 @@ hipError_t launch_small_bwd(const void *x, const void *dy, const PlanView &pv, v
     A.slices = g.t.slices;
     A.n_groups = g.n_groups;
     A.n_angles = (int64_t)s.heads * s.k * (s.n / 2);
-    switch (s.dtype) {
-        case BQ_F32: launch_small_bwd_t<float>(A, s.k, g, stream); break;
-        case BQ_F16: launch_small_bwd_t<__half>(A, s.k, g, stream); break;
-        default: launch_small_bwd_t<bf16_t>(A, s.k, g, stream); break;
-    }
     int plain_parts;
-    const hipError_t e = launch_generic_bwd_if_bad(x, dy, pv, dx, ws, s, stream, &plain_parts);
-    if (e != hipSuccess) return e;
+    const BwdArgs P = generic_bwd_args(x, dy, pv, dx, ws, s, &plain_parts);
+    const bool inside = g.t.threads == kSbThreads && P.rows_per_tile * s.n <= kSbPlainTile;
+    A.grid = (int)g.grid;
+    const unsigned grid = inside && plain_parts > A.grid ? (unsigned)plain_parts : g.grid;
+    if (inside) A.plain_parts = plain_parts;
+    switch (s.dtype) {
+        case BQ_F32: launch_small_bwd_t<float>(A, P, s.k, grid, g.t.threads, stream); break;
+        case BQ_F16: launch_small_bwd_t<__half>(A, P, s.k, grid, g.t.threads, stream); break;
+        default: launch_small_bwd_t<bf16_t>(A, P, s.k, grid, g.t.threads, stream); break;
+    }
+    if (!inside) {
+        const hipError_t e = launch_generic_bwd_if_bad(x, dy, pv, dx, ws, s, stream, &plain_parts);
+        if (e != hipSuccess) return e;
+    }
     const unsigned blocks = (unsigned)((A.n_angles + kSbReduceAngles - 1) / kSbReduceAngles);
     hipLaunchKernelGGL(small_bwd_reduce_kernel, dim3(blocks), dim3(kSbReduceAngles * kSbReduceGroups), 0, stream, (const float *)ws,
                        dtheta, A.n_angles, g.slots, A.plan, (int64_t)plain_parts, A.fw_inv, s.k);
