@@ -179,8 +179,8 @@ size_t bwd_workspace_bytes_generic(const Shape &s);
 hipError_t launch_generic_bwd(const void *x, const void *dy, const PlanView &pv, void *dx, float *dtheta,
                               void *ws, const Shape &s, hipStream_t stream);
 // The same pass without its last kernel, for plans that flag their scale-deferred tables as unusable (else it does nothing):
-// the specialised backward passes, whose kernels exit at once on such a plan, launch it behind them, and their own last
-// kernel then adds its *parts partial sums ([part][head][layer][pair], from ws on) instead of theirs.
+// the backward pass of n = 8 .. 128 launches it behind its own kernel where that has workgroups too narrow to do the work itself; its
+// last kernel then adds the *parts partial sums ([part][head][layer][pair], from ws on) instead of its own.
 hipError_t launch_generic_bwd_if_bad(const void *x, const void *dy, const PlanView &pv, void *dx, void *ws, const Shape &s,
                                      hipStream_t stream, int *parts);
 
