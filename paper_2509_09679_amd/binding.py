@@ -118,6 +118,19 @@ _KINDS = {"bq_plan_build": "piipus", "bq_butterfly_fwd": "ppprs", "bq_butterfly_
           "bq_butterfly_fwd_fakequant": "ppppqrs", "bq_kron_fwd": "pppiprs", "bq_kron_inv": "pppiprs", "bq_butterfly_bwd": "ppppppurs"}
 
 
+def _general_call(name: str, kinds: str):
+    """An entry point through its ctypes prototype, with the arguments a Caller takes."""
+    fn = getattr(lib(), name)
+
+    def call(*args):
+        try:
+            return fn(*[_ptr(a) if k == "p" else ctypes.byref(a) if k in "rq" else a for k, a in zip(kinds, args)])
+        except ctypes.ArgumentError as e:
+            raise TypeError(str(e)) from None
+
+    return call
+
+
 class _Calls:
     """One Caller per entry point of _KINDS, without the "bq_" in front."""
 
@@ -133,7 +146,7 @@ class _Calls:
         loader.exec_module(module)
         for name, kinds in _KINDS.items():
             address = ctypes.cast(getattr(L, name), ctypes.c_void_p).value
-            setattr(self, name[3:], module.Caller(address, kinds, bq_rows, bq_quant))
+            setattr(self, name[3:], module.Caller(address, kinds, bq_rows, bq_quant, _general_call(name, kinds)))
 
 
 def _calls() -> _Calls:

@@ -3,7 +3,9 @@
  * calls on 1024 float32 rows of 128 took 12.5 us where the GPU needs 8.6.
  *
  *   p  device pointer: None, or an object with data_ptr() (a tensor)
- *   i  int32, u  size_t, s  stream handle: Python integers
+ *   i  int32, u  size_t: Python integers; a call with anything else there goes to `general`, which takes what a ctypes prototype takes
+ *      (numpy's integers, objects with __index__) and refuses the rest
+ *   s  stream handle: a Python integer
  *   r, q  host descriptors: instances of the two ctypes structures the module is given, passed by address
  *
  * All of these travel in 64-bit integer registers and stack slots in the x86-64 calling convention, so one prototype per argument
@@ -27,6 +29,7 @@ typedef struct {
     int count;
     char kinds[kMaxArgs + 1];
     PyObject *types[2]; /* of 'r' and 'q' */
+    PyObject *general;
     vectorcallfunc vectorcall;
 } Caller;
 
@@ -51,7 +54,7 @@ static PyObject *caller_call(PyObject *self, PyObject *const *args, size_t nargs
     }
     W a[kMaxArgs];
     Py_buffer views[2];
-    int held = 0, ok = 1;
+    int held = 0, ok = 1, general = 0;
     for (int i = 0; i < c->count && ok; ++i) {
         PyObject *o = args[i];
         switch (c->kinds[i]) {
@@ -61,9 +64,9 @@ static PyObject *caller_call(PyObject *self, PyObject *const *args, size_t nargs
                 } else {
                     PyObject *p = PyObject_CallMethodNoArgs(o, name_data_ptr);
                     if (p && !PyLong_Check(p)) {
+                        PyObject *q = PyNumber_Long(p);
                         Py_DECREF(p);
-                        p = NULL;
-                        PyErr_SetString(PyExc_TypeError, "data_ptr() must return an integer");
+                        p = q;
                     }
                     ok = p != NULL;
                     if (ok) {
@@ -84,7 +87,9 @@ static PyObject *caller_call(PyObject *self, PyObject *const *args, size_t nargs
                 }
                 break;
             default:
-                if (!PyLong_Check(o)) {
+                if (c->kinds[i] != 's' && !PyLong_Check(o)) {
+                    general = 1;
+                } else if (!PyLong_Check(o)) {
                     PyErr_Format(PyExc_TypeError, "argument %d must be an integer", i + 1);
                     ok = 0;
                 } else {
@@ -93,12 +98,13 @@ static PyObject *caller_call(PyObject *self, PyObject *const *args, size_t nargs
         }
     }
     int status = 0;
-    if (ok) {
+    if (ok && !general) {
         Py_BEGIN_ALLOW_THREADS
         status = invoke(c->fn, c->count, a);
         Py_END_ALLOW_THREADS
     }
     while (held) PyBuffer_Release(&views[--held]);
+    if (ok && general) return PyObject_Vectorcall(c->general, args, c->count, NULL);
     return ok ? PyLong_FromLong(status) : NULL;
 }
 
@@ -106,14 +112,15 @@ static PyObject *caller_new(PyTypeObject *type, PyObject *args, PyObject *kw)
 {
     unsigned long long fn;
     const char *kinds;
-    PyObject *rows, *quant;
+    PyObject *rows, *quant, *general;
     (void)kw;
-    if (!PyArg_ParseTuple(args, "KsOO", &fn, &kinds, &rows, &quant)) return NULL;
+    if (!PyArg_ParseTuple(args, "KsOOO", &fn, &kinds, &rows, &quant, &general)) return NULL;
     const size_t n = strlen(kinds);
     size_t structs = 0;
     for (const char *k = kinds; *k; ++k) structs += *k == 'r' || *k == 'q';
-    if (!fn || !(n == 5 || n == 6 || n == 7 || n == 9) || strspn(kinds, "piusrq") != n || structs > 2 || !PyType_Check(rows) || !PyType_Check(quant)) {
-        PyErr_SetString(PyExc_ValueError, "Caller(address, kinds, rows type, quant type)");
+    if (!fn || !(n == 5 || n == 6 || n == 7 || n == 9) || strspn(kinds, "piusrq") != n || structs > 2 || !PyType_Check(rows) || !PyType_Check(quant) ||
+        !PyCallable_Check(general)) {
+        PyErr_SetString(PyExc_ValueError, "Caller(address, kinds, rows type, quant type, general)");
         return NULL;
     }
     Caller *c = (Caller *)type->tp_alloc(type, 0);
@@ -123,6 +130,8 @@ static PyObject *caller_new(PyTypeObject *type, PyObject *args, PyObject *kw)
     memcpy(c->kinds, kinds, n + 1);
     Py_INCREF(rows);
     Py_INCREF(quant);
+    Py_INCREF(general);
+    c->general = general;
     c->types[0] = rows;
     c->types[1] = quant;
     c->vectorcall = caller_call;
@@ -133,6 +142,7 @@ static void caller_dealloc(PyObject *self)
 {
     Py_XDECREF(((Caller *)self)->types[0]);
     Py_XDECREF(((Caller *)self)->types[1]);
+    Py_XDECREF(((Caller *)self)->general);
     Py_TYPE(self)->tp_free(self);
 }
 

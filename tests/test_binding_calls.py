@@ -1,7 +1,9 @@
 """The caller behind the binding's hot entry points: argument kinds, refusals, agreement with the ctypes prototypes."""
 import ctypes
 
+import numpy as np
 import pytest
+import torch
 
 from paper_2509_09679_amd import binding as B
 
@@ -72,3 +74,43 @@ def test_what_is_not_an_argument_is_refused():
 
     with pytest.raises(RuntimeError, match="no storage"):
         c.butterfly_fwd(x, Raises(), x, _rows(), 0)
+
+
+class Index:
+    def __index__(self):
+        return 64
+
+
+class Parameter:
+    _as_parameter_ = 64
+
+
+@pytest.mark.parametrize("n", [64, np.int64(64), np.int32(64), np.array(64), torch.tensor(64), ctypes.c_int32(64), Index(), Parameter(),
+                               (1 << 32) + 64])
+def test_integers_that_are_not_python_s(n):
+    # whatever a ctypes prototype takes for an int32 and a size_t; the calls end in the library's checks, whose texts show the values
+    stream, x = type("S", (), {"cuda_stream": 0}), Fake()
+    with pytest.raises(B.BqError, match=f"64 bytes, {B.bq_plan_bytes(64)} needed"):
+        B.bq_plan_build(x, n, 1, x, stream=stream)
+    with pytest.raises(B.BqError, match="n=64 heads=-3"):
+        B.bq_plan_build(x, n, np.int64(-3), x, stream=stream)
+    for f in (B.bq_kron_fwd, B.bq_kron_inv):
+        with pytest.raises(B.BqError, match=f.__name__ + ": d1=65 outside"):
+            f(x, x, x, np.int64(65), x, _rows(), stream=stream)
+
+    class Sizes(Fake):
+        def numel(self):
+            return np.int64(32)
+
+        def data_ptr(self):
+            return np.uint64(0x7F0000001000)
+
+    with pytest.raises(B.BqError, match="plan buffer has 32 bytes"):
+        B.bq_plan_build(Sizes(), n, 1, Sizes(), stream=stream)
+
+
+def test_numbers_that_are_no_integers_stay_refused():
+    stream, x = type("S", (), {"cuda_stream": 0}), Fake()
+    for n in (64.0, np.float32(64), "64", None, ctypes.c_long(64)):
+        with pytest.raises(TypeError):
+            B.bq_plan_build(x, n, 1, x, stream=stream)
