@@ -1,5 +1,5 @@
-"""Binding of libbq.so: the same entry points as include/bq.h, taking torch tensors.  The calls of the path go through
-bqcall.so (csrc/bqcall.c), the others through ctypes.
+"""Binding of libbq.so: the same entry points as include/bq.h, taking torch tensors.  The calls of the path go through the
+module bqcall (csrc/bqcall.c) where it is built for this Python, else, as the others do, through ctypes.
 
 Argument marshalling only — every step of the path runs in the library's HIP kernels.  torch is used
 for device memory and the current stream, nothing else.  There is no CPU or eager fallback: if the
@@ -8,12 +8,14 @@ library is missing or a call fails, an exception is raised.
 from __future__ import annotations
 
 import ctypes
+import importlib.machinery
+import importlib.util
 import os
 from typing import Optional
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(HERE, "libbq.so")
-CALL_PATH = os.path.join(HERE, "bqcall.so")
+CALL_PATH = os.path.join(HERE, "bqcall" + importlib.machinery.EXTENSION_SUFFIXES[0])  # (the suffix names the Python it is built for)
 
 BQ_OK = 0
 BQ_F32, BQ_F16, BQ_BF16 = 0, 1, 2
@@ -132,21 +134,20 @@ def _general_call(name: str, kinds: str):
 
 
 class _Calls:
-    """One Caller per entry point of _KINDS, without the "bq_" in front."""
+    """One callable per entry point of _KINDS, without the "bq_" in front: a Caller, or its ctypes prototype where `path` does not exist."""
 
-    def __init__(self):
-        import importlib.machinery
-        import importlib.util
-
+    def __init__(self, path: str = CALL_PATH):
         L = lib()
-        if not os.path.exists(CALL_PATH):
-            raise FileNotFoundError(f"{CALL_PATH} not built: run `python -m paper_2509_09679_amd.build`")
-        loader = importlib.machinery.ExtensionFileLoader("bqcall", CALL_PATH)
-        module = importlib.util.module_from_spec(importlib.util.spec_from_loader("bqcall", loader))
-        loader.exec_module(module)
+        module = None
+        if os.path.exists(path):
+            loader = importlib.machinery.ExtensionFileLoader("bqcall", path)
+            module = importlib.util.module_from_spec(importlib.util.spec_from_loader("bqcall", loader))
+            loader.exec_module(module)
         for name, kinds in _KINDS.items():
-            address = ctypes.cast(getattr(L, name), ctypes.c_void_p).value
-            setattr(self, name[3:], module.Caller(address, kinds, bq_rows, bq_quant, _general_call(name, kinds)))
+            call = _general_call(name, kinds)
+            if module:
+                call = module.Caller(ctypes.cast(getattr(L, name), ctypes.c_void_p).value, kinds, bq_rows, bq_quant, call)
+            setattr(self, name[3:], call)
 
 
 def _calls() -> _Calls:

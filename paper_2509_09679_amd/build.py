@@ -1,9 +1,11 @@
 """Compile the HIP sources in csrc/ into paper_2509_09679_amd/libbq.so for gfx950 and the binding's caller, csrc/bqcall.c, into
-bqcall.so (in-tree)."""
+the module bqcall of the Python that runs this (in-tree)."""
 from __future__ import annotations
 
 import glob
+import importlib.machinery
 import os
+import shutil
 import subprocess
 import sysconfig
 from concurrent.futures import ThreadPoolExecutor
@@ -13,7 +15,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 OBJ_DIR = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libbq.so")
-CALL = os.path.join(HERE, "bqcall.so")
+CALL = os.path.join(HERE, "bqcall" + importlib.machinery.EXTENSION_SUFFIXES[0])
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 # Packed-fp32 VALU instructions are switched off for every device translation unit.
@@ -34,6 +36,20 @@ def _compile(src: str, extra=()) -> str:
     return obj
 
 
+def build_caller() -> bool:
+    """The binding calls through ctypes without it, so a machine that has no Python headers or no C compiler does without."""
+    include = sysconfig.get_paths()["include"]
+    cc = shutil.which("gcc") or shutil.which("cc")
+    if cc is None or not os.path.exists(os.path.join(include, "Python.h")):
+        print("bqcall is not built (no C compiler or no Python.h): the binding's calls go through ctypes")
+        if os.path.exists(CALL):
+            os.remove(CALL)
+        return False
+    subprocess.run([cc, "-O2", "-Wall", "-shared", "-fPIC", "-I" + include, "-I" + os.path.join(ROOT, "include"),
+                    os.path.join(CSRC, "bqcall.c"), "-o", CALL], check=True)
+    return True
+
+
 def build(verbose: bool = False, save_temps: bool = False) -> str:
     os.makedirs(OBJ_DIR, exist_ok=True)
     extra = ["-save-temps=obj"] if save_temps else []
@@ -42,8 +58,7 @@ def build(verbose: bool = False, save_temps: bool = False) -> str:
         objs = list(ex.map(lambda s: _compile(s, extra), srcs))
     cmd = [HIPCC, "-shared", "-fPIC", "--offload-arch=gfx950", "-o", LIB] + objs
     subprocess.run(cmd, check=True)
-    subprocess.run(["gcc", "-O2", "-Wall", "-shared", "-fPIC", "-I" + sysconfig.get_paths()["include"], os.path.join(CSRC, "bqcall.c"), "-o", CALL],
-                   check=True)
+    build_caller()
     if verbose:
         print("built", LIB)
     return LIB

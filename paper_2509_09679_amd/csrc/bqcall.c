@@ -7,25 +7,29 @@
  *      (numpy's integers, objects with __index__) and refuses the rest
  *   s  stream handle: a Python integer
  *   r, q  host descriptors: instances of the two ctypes structures the module is given, passed by address
- *
- * All of these travel in 64-bit integer registers and stack slots in the x86-64 calling convention, so one prototype per argument
- * count serves every entry point. */
+ */
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
 #include <stddef.h>
 #include <stdint.h>
 #include <string.h>
 
-#if !defined(__x86_64__) || defined(_WIN32)
-#error "argument passing is that of the System V x86-64 ABI"
-#endif
+#include "bq.h"
 
 enum { kMaxArgs = 9 };
-typedef uint64_t W;
+typedef union {
+    void *p;
+    uint64_t u;
+} Arg;
+
+/* kinds of the entry points' arguments, one per prototype */
+static const char *const kKinds[] = {"piipus", "ppprs", "ppppqrs", "pppiprs", "ppppppurs"};
+enum { kPrototypes = 5 };
 
 typedef struct {
     PyObject_HEAD
     void *fn;
+    int prototype; /* of kKinds */
     int count;
     char kinds[kMaxArgs + 1];
     PyObject *types[2]; /* of 'r' and 'q' */
@@ -35,13 +39,14 @@ typedef struct {
 
 static PyObject *name_data_ptr;
 
-static int invoke(void *f, int n, const W *a)
+static bq_status invoke(void *f, int prototype, const Arg *a)
 {
-    switch (n) {
-        case 5: return ((int (*)(W, W, W, W, W))f)(a[0], a[1], a[2], a[3], a[4]);
-        case 6: return ((int (*)(W, W, W, W, W, W))f)(a[0], a[1], a[2], a[3], a[4], a[5]);
-        case 7: return ((int (*)(W, W, W, W, W, W, W))f)(a[0], a[1], a[2], a[3], a[4], a[5], a[6]);
-        default: return ((int (*)(W, W, W, W, W, W, W, W, W))f)(a[0], a[1], a[2], a[3], a[4], a[5], a[6], a[7], a[8]);
+    switch (prototype) {
+        case 0: return ((__typeof__(&bq_plan_build))f)(a[0].p, (int32_t)a[1].u, (int32_t)a[2].u, a[3].p, (size_t)a[4].u, a[5].p);
+        case 1: return ((__typeof__(&bq_butterfly_fwd))f)(a[0].p, a[1].p, a[2].p, a[3].p, a[4].p);
+        case 2: return ((__typeof__(&bq_butterfly_fwd_quant))f)(a[0].p, a[1].p, a[2].p, a[3].p, a[4].p, a[5].p, a[6].p);
+        case 3: return ((__typeof__(&bq_kron_fwd))f)(a[0].p, a[1].p, a[2].p, (int32_t)a[3].u, a[4].p, a[5].p, a[6].p);
+        default: return ((__typeof__(&bq_butterfly_bwd))f)(a[0].p, a[1].p, a[2].p, a[3].p, a[4].p, a[5].p, (size_t)a[6].u, a[7].p, a[8].p);
     }
 }
 
@@ -52,7 +57,7 @@ static PyObject *caller_call(PyObject *self, PyObject *const *args, size_t nargs
         PyErr_Format(PyExc_TypeError, "%d positional arguments expected", c->count);
         return NULL;
     }
-    W a[kMaxArgs];
+    Arg a[kMaxArgs];
     Py_buffer views[2];
     int held = 0, ok = 1, general = 0;
     for (int i = 0; i < c->count && ok; ++i) {
@@ -60,7 +65,7 @@ static PyObject *caller_call(PyObject *self, PyObject *const *args, size_t nargs
         switch (c->kinds[i]) {
             case 'p':
                 if (o == Py_None) {
-                    a[i] = 0;
+                    a[i].p = NULL;
                 } else {
                     PyObject *p = PyObject_CallMethodNoArgs(o, name_data_ptr);
                     if (p && !PyLong_Check(p)) {
@@ -70,7 +75,7 @@ static PyObject *caller_call(PyObject *self, PyObject *const *args, size_t nargs
                     }
                     ok = p != NULL;
                     if (ok) {
-                        a[i] = PyLong_AsUnsignedLongLongMask(p);
+                        a[i].p = (void *)(uintptr_t)PyLong_AsUnsignedLongLongMask(p);
                         Py_DECREF(p);
                     }
                 }
@@ -83,7 +88,7 @@ static PyObject *caller_call(PyObject *self, PyObject *const *args, size_t nargs
                 } else if (PyObject_GetBuffer(o, &views[held], PyBUF_SIMPLE) != 0) {
                     ok = 0;
                 } else {
-                    a[i] = (W)(uintptr_t)views[held++].buf;
+                    a[i].p = views[held++].buf;
                 }
                 break;
             default:
@@ -92,20 +97,22 @@ static PyObject *caller_call(PyObject *self, PyObject *const *args, size_t nargs
                 } else if (!PyLong_Check(o)) {
                     PyErr_Format(PyExc_TypeError, "argument %d must be an integer", i + 1);
                     ok = 0;
+                } else if (c->kinds[i] == 's') {
+                    a[i].p = (void *)(uintptr_t)PyLong_AsUnsignedLongLongMask(o);
                 } else {
-                    a[i] = PyLong_AsUnsignedLongLongMask(o);
+                    a[i].u = PyLong_AsUnsignedLongLongMask(o);
                 }
         }
     }
-    int status = 0;
+    bq_status status = BQ_OK;
     if (ok && !general) {
         Py_BEGIN_ALLOW_THREADS
-        status = invoke(c->fn, c->count, a);
+        status = invoke(c->fn, c->prototype, a);
         Py_END_ALLOW_THREADS
     }
     while (held) PyBuffer_Release(&views[--held]);
     if (ok && general) return PyObject_Vectorcall(c->general, args, c->count, NULL);
-    return ok ? PyLong_FromLong(status) : NULL;
+    return ok ? PyLong_FromLong((long)status) : NULL;
 }
 
 static PyObject *caller_new(PyTypeObject *type, PyObject *args, PyObject *kw)
@@ -115,19 +122,18 @@ static PyObject *caller_new(PyTypeObject *type, PyObject *args, PyObject *kw)
     PyObject *rows, *quant, *general;
     (void)kw;
     if (!PyArg_ParseTuple(args, "KsOOO", &fn, &kinds, &rows, &quant, &general)) return NULL;
-    const size_t n = strlen(kinds);
-    size_t structs = 0;
-    for (const char *k = kinds; *k; ++k) structs += *k == 'r' || *k == 'q';
-    if (!fn || !(n == 5 || n == 6 || n == 7 || n == 9) || strspn(kinds, "piusrq") != n || structs > 2 || !PyType_Check(rows) || !PyType_Check(quant) ||
-        !PyCallable_Check(general)) {
+    int prototype = 0;
+    while (prototype < kPrototypes && strcmp(kinds, kKinds[prototype]) != 0) ++prototype;
+    if (!fn || prototype == kPrototypes || !PyType_Check(rows) || !PyType_Check(quant) || !PyCallable_Check(general)) {
         PyErr_SetString(PyExc_ValueError, "Caller(address, kinds, rows type, quant type, general)");
         return NULL;
     }
     Caller *c = (Caller *)type->tp_alloc(type, 0);
     if (!c) return NULL;
     c->fn = (void *)(uintptr_t)fn;
-    c->count = (int)n;
-    memcpy(c->kinds, kinds, n + 1);
+    c->prototype = prototype;
+    c->count = (int)strlen(kinds);
+    memcpy(c->kinds, kinds, (size_t)c->count + 1);
     Py_INCREF(rows);
     Py_INCREF(quant);
     Py_INCREF(general);

@@ -114,3 +114,29 @@ def test_numbers_that_are_no_integers_stay_refused():
     for n in (64.0, np.float32(64), "64", None, ctypes.c_long(64)):
         with pytest.raises(TypeError):
             B.bq_plan_build(x, n, 1, x, stream=stream)
+
+
+def test_the_caller_is_the_one_built_for_this_python():
+    import sysconfig
+
+    assert B.CALL_PATH.endswith(sysconfig.get_config_var("EXT_SUFFIX"))
+    assert all(type(getattr(B._calls(), name[3:])).__name__ == "Caller" for name in B._KINDS)
+
+
+def test_calls_without_the_caller(monkeypatch):
+    # another Python, a host without a compiler: the same calls through ctypes
+    monkeypatch.setattr(B, "_CALLS", B._Calls("/nonexistent/bqcall.so"))
+    assert all(type(getattr(B._calls(), name[3:])).__name__ == "function" for name in B._KINDS)
+    test_arguments_arrive_and_errors_come_back()
+    test_integers_that_are_not_python_s(np.int64(64))
+    test_numbers_that_are_no_integers_stay_refused()
+
+
+def test_build_without_python_headers(monkeypatch, tmp_path):
+    from paper_2509_09679_amd import build
+
+    stale = tmp_path / "bqcall.so"
+    stale.write_bytes(b"")
+    monkeypatch.setattr(build, "CALL", str(stale))
+    monkeypatch.setattr(build.sysconfig, "get_paths", lambda: {"include": str(tmp_path)})
+    assert build.build_caller() is False and not stale.exists()
