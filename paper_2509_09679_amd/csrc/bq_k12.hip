@@ -1,4 +1,5 @@
 // n = 256 .. 4096 instantiations of the specialised transform kernels, and the choice between them.
+#include "bq_k12_grid.h"
 #include "bq_k12_kernel.h"
 #include "bq_k12_inv.h"
 
@@ -139,20 +140,11 @@ hipError_t launch_k12(Mode mode, const void *in, void *out, const PlanView &pv, 
     // Transforms: one per compute unit (2^30 16-bit elements at every n from 256 to 4096: forward 0.79 ms, 0.84 with three, five or
     // seven per unit, 6 to 18 % more at other counts; two-phase inverse of 16-bit rows 0.78 ms, 512 workgroups 0.86, 768 0.85,
     // 1024 0.99; float32 rows forward 0.776, inverse 0.779 ms; small batches too).  n = 8192: one fits.
-    // Quantisers: the two that fit, from the batch on that gives each a few rows; below, one, which reads half as many tables.
-    // One / two per unit / 1280 workgroups (as it was): 1777 fp16 rows of 4096, INT4 11.4 / 11.5 / 17.2 us, 700 rows 7.2 / 8.3 /
-    // 10.3, 4000 rows 19.8 / 18.2 / 22.5, 65536 rows 225 / 185 / 189; float32 rows 2000 13.5 / 13.9 / 19.5, 16000 64.6 / 61.0 / 68.2;
-    // 2000 blocks of n = 512 .. 2048 12.7 / 11.7 / 17.2.  The lines cross between 800 and 2000 rows.  A call that counts bins ends
-    // with one atomic per bin and workgroup, and its lines cross later: 2000 rows 25.8 / 28.1 / 43.5, 4000 33.7 / 33.9 / 50.9,
-    // 16000 80.0 / 69.8 / 89.5.  Batches of 1.5 GB and more run 1 to 5 % faster in 1280 workgroups, which drift out of step (two
-    // per unit / 1280: 262144 fp16 rows, INT2 674 / 664, fake-quantised 870 / 852; 131072 float32 rows 482 / 459; half as many rows
-    // -2 to +1.5 %), unless their groups are large (910 / 922).
     const bool inv_ring = mode == kInv && !wide && s.dtype != BQ_F32;
-    const bool fused = mode == kFwdQuant || mode == kFwdFake;
-    const int64_t blocks = A.rows * A.heads;  // of 4096 elements
-    const int64_t few = mode == kFwdFake && A.hist ? 3072 : 1280, vast = ((int64_t)3 << 29) / (kN * (s.dtype == BQ_F32 ? 4 : 2));
-    const int target = !fused || wide || blocks <= few ? 256 : big || blocks < vast ? 512 : 1280;
-    int64_t per_head = target / A.heads > 0 ? target / A.heads : 1;
+    int64_t per_head = 256 / A.heads > 0 ? 256 / A.heads : 1;
+    if ((mode == kFwdQuant || mode == kFwdFake) && !wide)
+        per_head = quantiser_workgroups_per_head(A.rows, A.heads,
+                                                 {mode == kFwdFake && out != nullptr, mode == kFwdFake && A.hist != nullptr, big, s.dtype == BQ_F32});
     if (per_head > A.rows) per_head = A.rows;
     const unsigned grid = split_rows(A, per_head);
     if (A.tail_rows) return launch_k12_tail_dtype(mode, A, bits, grid, s.dtype, big, stream);
