@@ -382,17 +382,19 @@ struct BinCount<2> {
     }
     // The end of a kernel: every lane of the wave calls this together, the wave adds up and one lane updates the counters.  Lane
     // by lane, 512 threads' additions to the same four LDS words came one after the other (513 fp16 rows of 32 x 128: 28.7 us that
-    // way, 19.1 this way).
+    // way, 19.1 this way).  Sum: 32 bits hold a wave's sums, too (64 lanes of kDrainEvery rows: |q| <= 2, so squares < 2^30 and
+    // squares - sum < 2^31); which of the two costs a kernel fewer spilled registers is the compiler's whim.
+    template <typename Sum>
     __device__ __forceinline__ void drain_wave(unsigned long long *wg)
     {
-        long long v[4] = {sum, squares, m2, rows};
+        Sum v[4] = {sum, squares, m2, rows};
 #pragma unroll
         for (int m = 1; m < 64; m <<= 1)
 #pragma unroll
             for (int j = 0; j < 4; ++j) v[j] += __shfl_xor(v[j], m, 64);
         if ((threadIdx.x & 63) == 0) {
-            const long long pos = (v[0] + v[1] - 2 * v[2]) / 2, neg = (v[1] - v[0] - 6 * v[2]) / 2;
-            const long long counts[4] = {v[2], neg, 8 * v[3] - pos - neg - v[2], pos};
+            const Sum pos = (v[0] + v[1] - 2 * v[2]) / 2, neg = (v[1] - v[0] - 6 * v[2]) / 2;
+            const Sum counts[4] = {v[2], neg, 8 * v[3] - pos - neg - v[2], pos};
 #pragma unroll
             for (int c = 0; c < 4; ++c)
                 if (counts[c]) atomicAdd(&wg[c], (unsigned long long)counts[c]);
@@ -400,7 +402,7 @@ struct BinCount<2> {
         clear();
     }
     __device__ __forceinline__ void skip() {}
-    static constexpr int kDrainEvery = 1 << 24;  // rows; int range
+    static constexpr int kDrainEvery = 1 << 19;  // rows (drain_wave)
     __device__ __forceinline__ bool full() const { return rows >= kDrainEvery; }
 };
 
@@ -430,7 +432,11 @@ struct BinCount<4> {
         rows += 1;
     }
     __device__ __forceinline__ void skip() { rows += 1; }  // keeps `rows` uniform over the wave
-    __device__ __forceinline__ void drain_wave(unsigned long long *wg) { drain(wg); }
+    template <typename Sum>
+    __device__ __forceinline__ void drain_wave(unsigned long long *wg)
+    {
+        drain(wg);
+    }
     __device__ __forceinline__ bool full() const { return rows >= 31; }
     // every lane of the wave must call this together
     __device__ __forceinline__ void drain(unsigned long long *wg)

@@ -52,7 +52,7 @@ __global__ __launch_bounds__(kSmallThreads, kMode == kFwd || kMode == kInv || (k
     }
     auto flush_bins = [&]() {  // every thread gets here
         if (kMode == kFwdFake && A.hist) {
-            bins.drain_wave(wg_bins);
+            bins.template drain_wave<long long>(wg_bins);
             __syncthreads();
             if (tid < (1 << kBits) && wg_bins[tid]) atomicAdd(&A.hist[tid], wg_bins[tid]);
         }
