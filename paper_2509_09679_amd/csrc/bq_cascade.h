@@ -233,7 +233,7 @@ __device__ __forceinline__ float amax8(const float (&y)[8])
 // finite binary16 number (one range test on its bit pattern); then no clip can act (|y * inv| <= qmax (1 + 2^-10)),
 // the scale is not zero and did not saturate.  Everything else -- a zero or subnormal scale, a scale beyond
 // 65504 (which saturates), the clip -- is redone on a cold path from the same inputs.
-template <int BITS, bool kMaxGiven = false>
+template <int BITS, bool kMaxGiven = false, bool kDivide = false>
 __device__ __forceinline__ void scaled8(const float (&y)[8], int lanes, bool scale_f16, float (&t)[8], float *scale_out,
                                         bool *ordinary_out, float group_max = -1.0f)
 {
@@ -274,19 +274,22 @@ __device__ __forceinline__ void scaled8(const float (&y)[8], int lanes, bool sca
         // Newton step, which is exact for every float32 significand but the one of all ones (checked on the CPU for every
         // significand and every estimate within 1 ulp; tests/test_scale_arithmetic.py).  That one, scales near the ends of
         // the exponent range, zero, infinity and NaN take the divisions.  These two divisions were 20 of the 165 vector instructions
-        // of a thread-row at n = 128.
-        if (BITS == 2) {
-            s = m;
-        } else {
-            constexpr float kRcp = 1.0f / qmax;
-            const float q0 = m * kRcp;
-            s = __builtin_fmaf(__builtin_fmaf(-qmax, q0, m), kRcp, q0);
+        // of a thread-row at n = 128.  kDivide: the divisions always, where a kernel is short of registers.
+        bool quick = false;
+        if (!kDivide) {
+            if (BITS == 2) {
+                s = m;
+            } else {
+                constexpr float kRcp = 1.0f / qmax;
+                const float q0 = m * kRcp;
+                s = __builtin_fmaf(__builtin_fmaf(-qmax, q0, m), kRcp, q0);
+            }
+            quick = __float_as_uint(m) - 0x12800000u < 0x71800000u - 0x12800000u &&  // 2^-90 <= m < 2^100
+                    (__float_as_uint(s) & 0x7FFFFFu) != 0x7FFFFFu;
+            const float r = __builtin_amdgcn_rcpf(s);
+            inv = __builtin_fmaf(__builtin_fmaf(-s, r, 1.0f), r, r);
+            ordinary = true;
         }
-        const bool quick = __float_as_uint(m) - 0x12800000u < 0x71800000u - 0x12800000u &&  // 2^-90 <= m < 2^100
-                           (__float_as_uint(s) & 0x7FFFFFu) != 0x7FFFFFu;
-        const float r = __builtin_amdgcn_rcpf(s);
-        inv = __builtin_fmaf(__builtin_fmaf(-s, r, 1.0f), r, r);
-        ordinary = true;
         if (__builtin_expect(!quick, 0)) {
             asm volatile("");
             s = (BITS == 2) ? m : m / qmax;
@@ -322,13 +325,13 @@ __device__ __forceinline__ uint32_t shl_add(uint32_t acc, uint32_t v)
 // gathered with one shift-add each (no borrows between fields); the upper bits of the patterns do not reach
 // the low 16 bits (INT2) or are subtracted as one constant (INT4); the final XOR turns every field
 // q + 2^(BITS-1) into q in two's complement.
-template <int BITS, bool kMaxGiven = false>
+template <int BITS, bool kMaxGiven = false, bool kDivide = false>
 __device__ __forceinline__ uint32_t quant8(const float (&y)[8], int lanes, bool scale_f16, float *scale_out,
                                            float group_max = -1.0f)
 {
     float t[8];
     bool ordinary;
-    scaled8<BITS, kMaxGiven>(y, lanes, scale_f16, t, scale_out, &ordinary, group_max);
+    scaled8<BITS, kMaxGiven, kDivide>(y, lanes, scale_f16, t, scale_out, &ordinary, group_max);
     constexpr float kBiasedMagic = kRoundMagic + (float)(1 << (BITS - 1));
     uint32_t acc = __float_as_uint(t[7] + kBiasedMagic);
 #pragma unroll
@@ -471,12 +474,12 @@ struct BinCount<4> {
 // the output (fewer values alive at once): rounded8 gives f = t + 1.5 * 2^23 (the code q is f - 1.5 * 2^23,
 // and the low bits of f's pattern hold q in two's complement); Dequant is s * q, one float32 rounding, with
 // the same scale and codes as quant8.
-template <int BITS, bool kMaxGiven = false>
+template <int BITS, bool kMaxGiven = false, bool kDivide = false>
 __device__ __forceinline__ void rounded8(const float (&y)[8], int lanes, bool scale_f16, float (&f)[8], float *s,
                                          bool *ordinary, float group_max = -1.0f)
 {
     float t[8];
-    scaled8<BITS, kMaxGiven>(y, lanes, scale_f16, t, s, ordinary, group_max);
+    scaled8<BITS, kMaxGiven, kDivide>(y, lanes, scale_f16, t, s, ordinary, group_max);
 #pragma unroll
     for (int r = 0; r < 8; ++r) f[r] = t[r] + kRoundMagic;
 }

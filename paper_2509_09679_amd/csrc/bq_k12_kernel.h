@@ -318,6 +318,12 @@ __device__ __forceinline__ void big_group_max(const float (&y)[kHalves][8], int 
 // kLanes > 0 fixes the group size (8 * kLanes) and kScale fixes the scale type (0 = float32,
 // 1 = binary16) at compile time; kLanes == 0 reads both from the arguments.
 // Addresses are a uniform row base plus a 32-bit per-thread offset.
+constexpr int kScaleF16 = 2, kScaleF32 = 3;
+template <int kLanes, int kScale>
+__device__ __forceinline__ bool scale_is_f16(const K12Args &A)
+{
+    return kLanes > 0 ? kScale != 0 : kScale == kScaleF16 || (kScale != kScaleF32 && A.scale_f16 != 0);
+}
 struct NoCount {};
 template <int kMode, int kBits>
 struct CountOf {
@@ -348,7 +354,8 @@ __device__ __forceinline__ void finish_row(const K12Args &A, const float (&y)[kH
             const int lanes = A.group >> 3;  // lanes per group
             float f[8], s;
             bool ordinary;
-            rounded8<kBits, kBig>(y[h], lanes, A.scale_f16 != 0, f, &s, &ordinary, group_max[h]);
+            // (rows with float32 scales apart: three registers spilled with the short quotient and reciprocal, none with the divisions)
+            rounded8<kBits, kBig, kScale == kScaleF32>(y[h], lanes, scale_is_f16<kLanes, kScale>(A), f, &s, &ordinary, group_max[h]);
             if (kHist) {
                 auto &bc = (BinCount<kBits> &)bins;
                 if (!kVirt || live)
@@ -376,7 +383,7 @@ __device__ __forceinline__ void finish_row(const K12Args &A, const float (&y)[kH
                 store8((T *)((char *)out_row + off), y[h]);
         } else {
             const int lanes = kLanes > 0 ? kLanes : (A.group >> 3);  // lanes per group
-            const bool f16 = kLanes > 0 ? (kScale != 0) : (A.scale_f16 != 0);
+            const bool f16 = scale_is_f16<kLanes, kScale>(A);
             float s;
             const uint32_t packed = quant8<kBits, kBig>(y[h], lanes, f16, &s, group_max[h]);
             if (kVirt && !live) continue;
@@ -826,16 +833,27 @@ template <typename T, bool kVirt, bool kWide, bool kBig, bool kTail>
 static hipError_t launch_k12_t(Mode mode, const K12Args &A, int bits, unsigned grid, hipStream_t stream)
 {
     constexpr bool V = kVirt, W = kWide, G = kBig;
+    // Where the row loop is slower for the code of the other scale type beside it, the types are apart (us together / apart): 40001 and
+    // 131072 fp16 rows of 4096, INT2 rows with groups of 4096, binary16 scales 174 / 154 and 534 / 471, float32 scales 172 / 153 and
+    // 533 / 478, bf16 173 / 152 and 536 / 479; 32768 bf16 rows of 8192, INT4 codes, groups of 8192 351 / 335 and 349 / 337, of 256 249 /
+    // 230 and 245 / 232.
+    constexpr int kFakeF16 = kBig && !kVirt && !kWide && sizeof(T) == 2 ? kScaleF16 : 0, kFakeF32 = kFakeF16 ? kScaleF32 : 0;
+    constexpr int kCodesF16 = kBig && kWide ? kScaleF16 : 0, kCodesF32 = kCodesF16 ? kScaleF32 : 0;
     void (*kern)(K12Args) = nullptr;
     if (mode == kFwdFake) {
         if (A.out && A.hist)
             kern = bits == 2 ? k12_kernel<T, kFwdFake, 2, 0, 0, true, true, V, W, G, false, kTail> : k12_kernel<T, kFwdFake, 4, 0, 0, true, true, V, W, G, false, kTail>;
         else if (A.out)
-            kern = bits == 2 ? k12_kernel<T, kFwdFake, 2, 0, 0, true, false, V, W, G, false, kTail> : k12_kernel<T, kFwdFake, 4, 0, 0, true, false, V, W, G, false, kTail>;
+            kern = bits == 2 ? (A.scale_f16 ? k12_kernel<T, kFwdFake, 2, 0, kFakeF16, true, false, V, W, G, false, kTail>
+                                            : k12_kernel<T, kFwdFake, 2, 0, kFakeF32, true, false, V, W, G, false, kTail>)
+                             : k12_kernel<T, kFwdFake, 4, 0, 0, true, false, V, W, G, false, kTail>;
         else
             kern = bits == 2 ? k12_kernel<T, kFwdFake, 2, 0, 0, false, true, V, W, G, false, kTail> : k12_kernel<T, kFwdFake, 4, 0, 0, false, true, V, W, G, false, kTail>;
     } else if (mode == kFwdQuant && (kBig || kVirt || A.group != 128 || !A.scale_f16)) {
-        kern = bits == 2 ? k12_kernel<T, kFwdQuant, 2, 0, 0, true, false, V, W, G, false, kTail> : k12_kernel<T, kFwdQuant, 4, 0, 0, true, false, V, W, G, false, kTail>;
+        if (A.scale_f16)
+            kern = bits == 2 ? k12_kernel<T, kFwdQuant, 2, 0, kCodesF16, true, false, V, W, G, false, kTail> : k12_kernel<T, kFwdQuant, 4, 0, kCodesF16, true, false, V, W, G, false, kTail>;
+        else
+            kern = bits == 2 ? k12_kernel<T, kFwdQuant, 2, 0, kCodesF32, true, false, V, W, G, false, kTail> : k12_kernel<T, kFwdQuant, 4, 0, kCodesF32, true, false, V, W, G, false, kTail>;
     } else if constexpr (!kBig) {
         if constexpr (!kVirt) {
             if (mode == kHadamard)
@@ -857,11 +875,13 @@ static hipError_t launch_k12_t(Mode mode, const K12Args &A, int bits, unsigned g
     }
     if (!kern) return hipErrorInvalidValue;
     constexpr size_t lds_bytes = kWide ? kLdsBytesWide : kLdsBytes;
-    // one record per kernel of this instantiation of the launcher (the modes, bit widths and output choices)
+    // one record per kernel of this instantiation of the launcher (the modes, bit widths, output choices, scale types)
     static LdsLimitOnce once[5][2][3][2];
     const int variant = mode != kFwdFake ? 0 : (A.out && A.hist) ? 0 : A.out ? 1 : 2;
     const int general = (mode == kFwdQuant && (kBig || kVirt || A.group != 128 || !A.scale_f16)) ? 1 : 0;
-    hipError_t e = once[mode][bits == 2 ? 0 : 1][mode == kFwdQuant ? general : variant][(A.streaming && sizeof(T) == 2 && (mode == kFwd || mode == kHadamard)) ? 1 : 0].set((const void *)kern, lds_bytes);
+    const bool quantises = mode == kFwdQuant || mode == kFwdFake;
+    const int last = quantises ? A.scale_f16 != 0 : A.streaming && sizeof(T) == 2 && (mode == kFwd || mode == kHadamard);
+    hipError_t e = once[mode][bits == 2 ? 0 : 1][mode == kFwdQuant ? general : variant][last].set((const void *)kern, lds_bytes);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(kern, dim3(grid), dim3(kThreads), lds_bytes, stream, A);
     return hipGetLastError();

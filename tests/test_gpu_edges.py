@@ -285,21 +285,24 @@ def test_small_transforms_of_rows_far_apart():
 
 @pytest.mark.parametrize("n,heads,rows", [(4096, 1, 3), (4096, 1, 1303), (4096, 3, 171), (1024, 1, 1301), (8192, 1, 130)])
 @pytest.mark.parametrize("dtype", ["f32", "f16", "bf16"])
-def test_bin_counts_of_large_groups(n, heads, rows, dtype):
-    # how a workgroup's counts are added up at its end differs by what is stored, row type and size; every sixteenth row is so small that
-    # its binary16 scale is subnormal and the clip acts (code -2)
+def test_large_groups_with_either_scale_type(n, heads, rows, dtype):
+    # kernels with the scale types apart and together; how a workgroup's bin counts are added up at its end differs by what is stored, row
+    # type and size; every sixteenth row is so small that its binary16 scale is subnormal and the clip acts
     x, th, _ = synth.small_case(n, rows, "f32", heads=heads, seed=950 + n + rows)
     x[::16] *= np.float32(1e-6 / np.abs(x[::16]).max())
     x = synth.cast_storage(x.astype(np.float64), dtype)
+    ref = oracle.forward(synth.to_f64(x, dtype), th, n, heads)
+    ordinary = np.arange(rows) % 16 != 0
     u = np.uint16 if dtype != "f32" else np.uint32
-    for group, sd in ((256, "f16"), (n, "f32")):
-        tag = f"n={n} H={heads} T={rows} {dtype} g{group} {sd}"
-        codes, scales = gu.run_fwd_quant(x, th, n, heads, dtype, 2, group, sd)
-        c = oracle.unpack_codes(codes, 2)
+    for bits, group, sd in ((2, 256, "f16"), (2, n, "f32"), (4, n, "f16"), (4, 256, "f32")):
+        tag = f"n={n} H={heads} T={rows} {dtype} INT{bits} g{group} {sd}"
+        codes, scales = gu.run_fwd_quant(x, th, n, heads, dtype, bits, group, sd)
+        gu.check_fused_codes(codes[ordinary], scales[ordinary], ref[ordinary], bits, group, sd, dtype, tag)
+        c = oracle.unpack_codes(codes, bits)
         want = synth.cast_storage(oracle.dequantize(c, scales.astype(np.float32), group).astype(np.float64), dtype)
         for want_y, want_hist in ((True, True), (True, False), (False, True)):
-            yq, hist = gu.run_fwd_fakequant(x, th, n, heads, dtype, 2, group, sd, want_y=want_y, want_hist=want_hist)
+            yq, hist = gu.run_fwd_fakequant(x, th, n, heads, dtype, bits, group, sd, want_y=want_y, want_hist=want_hist)
             if want_y:
                 np.testing.assert_array_equal(yq.view(u), want.view(u), err_msg=tag)
             if want_hist:
-                np.testing.assert_array_equal(hist, oracle.bin_histogram(c, 2), err_msg=tag)
+                np.testing.assert_array_equal(hist, oracle.bin_histogram(c, bits), err_msg=tag)
