@@ -34,9 +34,11 @@
 //
 // When the plan flags the scale-deferred tables as unusable the kernel runs the backward pass for any n instead
 // (bq_generic_bwd.h), and the last kernel adds those partial sums.  As a launch of its own behind this one, empty on other
-// plans, that pass took 2 us of every call; in the 1024 threads of this kernel it is two to three times as fast.
+// plans, that pass took 2 us of every call; in the 1024 threads of this kernel it is faster as well (float32 rows, flagged: 20000 of 4096
+// 4342 -> 1439 us, 8000 of 8192 7723 -> 2387, 20000 of 2048 1516 -> 644; fp16: 20000 of 512 332 -> 235).
 #include "bq_bwd_blocks.h"
 #include "bq_generic_bwd.h"
+#include "bq_plain_split.h"
 
 namespace bq {
 
@@ -522,7 +524,8 @@ __global__ __launch_bounds__(kFusedThreads) void bwd_fused_kernel(BwdFastArgs A,
     const PlanUse use = plan_use(A.plan);
     if (use == kPlanForeign) return;
     if (use == kPlanPlain) {  // the whole batch in plain rotations, by the first chunk's launch
-        if (A.first_chunk && (int)blockIdx.x < A.plain_parts) generic_bwd_rows<T, kFusedThreads>(P, lds, (int)blockIdx.x, A.plain_parts);
+        typedef typename std::conditional<kHalf, float, double>::type Acc;  // (n = 8192: one row per tile, nothing to add up)
+        if (A.first_chunk && (int)blockIdx.x < A.plain_parts) generic_bwd_rows<T, kFusedThreads, Acc>(P, lds, (int)blockIdx.x, A.plain_parts);
         return;
     }
     using L = FusedLds<T, kHalf>;
@@ -1006,16 +1009,12 @@ static hipError_t launch_bwd_fast_t(BwdFastArgs A, const PlanView &pv, const Sha
     hipError_t e = A.dx ? fused_kernel_ready<T, true, kHalf, kVirt>() : fused_kernel_ready<T, false, kHalf, kVirt>();
     if (e != hipSuccess) return e;
     A.slots = slices;
-    // Flagged plans: the tiles grow to 4096 elements where the batch has more of them than workgroups, so that 1024 threads find
-    // work between two barriers (20000 fp16 rows of 512: 359 -> 226 us, as a launch of its own 334), and take workgroups without a slot.
     BwdArgs P = generic_bwd_args(A.x, A.dy, pv, A.dx, ws, s, &A.plain_parts);
-    static_assert(2 * G::n * sizeof(float) * (kHalf ? 2 : 1) <= FusedLds<T, kHalf>::kBytes, "4096 elements, or one row, and the gradient");
-    while (P.rows_per_tile * s.n < G::n && P.n_tiles > 256) {
-        P.rows_per_tile *= 2;
-        P.n_tiles = (s.rows + P.rows_per_tile - 1) / P.rows_per_tile * s.heads;
-    }
-    const int most = P.n_tiles < 256 ? (int)P.n_tiles : 256;
-    if (A.plain_parts > most) A.plain_parts = most;
+    const PlainSplit split = grown_split({P.rows_per_tile, P.n_tiles, A.plain_parts}, s.rows, s.n, s.heads);
+    static_assert(2 * 2 * G::n * sizeof(float) <= FusedLds<T, kHalf>::kBytes, "8192 elements and the gradient");
+    P.rows_per_tile = split.rows_per_tile;
+    P.n_tiles = split.tiles;
+    A.plain_parts = split.parts;
     const int with_slot = kHalf ? 2 * slices : slices;  // kHalf: a multiple of 16 (see Part)
     const int grid = with_slot > A.plain_parts ? with_slot : A.plain_parts;
     for (int64_t r0 = 0; r0 < kernel_rows; r0 += chunk_rows) {

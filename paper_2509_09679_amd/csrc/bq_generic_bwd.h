@@ -39,8 +39,9 @@ struct BwdArgs {
     int only_if_bad;  // != 0: run only when one of the plan's table sets is flagged unusable
 };
 
-// The share of workgroup `part` of `parts`; kThreads threads.  lds: 2 * rows_per_tile * n floats.
-template <typename T, int kThreads>
+// The share of workgroup `part` of `parts`; kThreads threads.  lds: 2 * rows_per_tile * n floats.  Acc: what a tile's rows are
+// added up in, and its sum to the slice's.
+template <typename T, int kThreads, typename Acc = float>
 __device__ __forceinline__ void generic_bwd_rows(const BwdArgs &A, float *lds, int my_part, int parts)
 {
     const int n = A.n, k = A.k, heads = A.heads, U = A.rows_per_tile;
@@ -85,11 +86,11 @@ __device__ __forceinline__ void generic_bwd_rows(const BwdArgs &A, float *lds, i
             for (int p = threadIdx.x; p < (n >> 1); p += kThreads) {
                 const float2 w = csh[(size_t)(i - 1) * (n >> 1) + p];
                 const int a0 = ((p >> (i - 1)) << i) | (p & (h - 1));
-                float acc = 0.0f;
+                Acc acc = 0;
                 for (int ul = 0; ul < U; ++ul) {
                     const int a = (ul << k) + a0;
                     float xa = xb[a], xv = xb[a + h], ga = gb[a], gv = gb[a + h];
-                    acc += gv * xa - ga * xv;
+                    acc += (Acc)(gv * xa - ga * xv);
                     rotate_pair<true>(xa, xv, w.x, w.y);
                     rotate_pair<true>(ga, gv, w.x, w.y);
                     xb[a] = xa;
@@ -97,7 +98,8 @@ __device__ __forceinline__ void generic_bwd_rows(const BwdArgs &A, float *lds, i
                     gb[a] = ga;
                     gb[a + h] = gv;
                 }
-                part[((size_t)head * k + (i - 1)) * (size_t)(n >> 1) + p] += acc;
+                float &sum = part[((size_t)head * k + (i - 1)) * (size_t)(n >> 1) + p];
+                sum = (float)((Acc)sum + acc);
             }
             __syncthreads();
         }

@@ -226,7 +226,8 @@ def test_backward_at_the_slot_counts(n, heads, rows):
     gu.check_dtheta(dth, rdth, np.maximum(ab, floor), what=f"dtheta n={n} T={rows}")
 
 
-@pytest.mark.parametrize("n,heads,rows", [(512, 1, 3000), (512, 8, 300), (256, 1, 10), (2048, 1, 600), (8192, 1, 300)])
+@pytest.mark.parametrize("n,heads,rows", [(512, 1, 3000), (512, 8, 300), (256, 1, 10), (2048, 1, 600), (8192, 1, 300), (4096, 1, 1501),
+                                          (2048, 1, 2103), (1024, 2, 1101)])
 def test_backward_of_flagged_plans_with_grown_tiles(n, heads, rows):
     # more tiles than workgroups: they grow, and their last one is ragged; fewer: workgroups without a slot take them
     x, th, dy = synth.small_case(n, rows, "f32", heads=heads, seed=800 + n + rows, with_dy=True, outliers=0)
