@@ -260,27 +260,54 @@ def test_small_quantisers_on_flagged_plans(n, heads, rows, dtype):
         np.testing.assert_array_equal(hist, oracle.bin_histogram(c, bits), err_msg=tag)
 
 
-def test_small_transforms_of_rows_far_apart():
-    # rows_per_block rows of 2^24 bytes and more apart do not fit a lane's 32-bit offset: every row is a group of its own
+@pytest.mark.parametrize("op", ["fwd", "inv", "quant", "fake"])
+def test_small_transforms_of_rows_far_apart(op):
+    # A workgroup takes four rows of 128 or more at a time and a lane's offset among them has 32 bits; rows 1.5 GB apart must be groups
+    # of their own.  Row 3 lies 4.5 GB behind row 0: an offset of 32 bits would come out 0.5 GB behind it, where nothing is a row's
+    # (all wrapped places hold 7, so a load from one shows in the result and a store to one in what it holds).
     import torch
     from paper_2509_09679_amd import binding as B
 
-    n, rows, ld = 8, 5, (1 << 23) + 8
+    n, ld = 128, (3 << 28) + 256
+    rows = 4 if op in ("fwd", "inv") else 16
+    starts = [r * ld for r in range(rows)]
+    wrapped = [s % (1 << 31) for s in starts if 2 * s >= 1 << 32]  # in elements of two bytes
+    assert wrapped and not set(wrapped) & set(starts)
     x, th, _ = synth.small_case(n, rows, "f16", seed=11)
     plan = B.alloc_plan(torch.from_numpy(th).cuda(), n, 1)
-    buf, out = torch.zeros(rows * ld, dtype=torch.float16, device="cuda"), torch.zeros(rows * ld, dtype=torch.float16, device="cuda")
-    xs, ys = buf.as_strided((rows, n), (ld, 1)), out.as_strided((rows, n), (ld, 1))
     dense = torch.from_numpy(np.ascontiguousarray(x).view(np.float16)).cuda()
-    xs.copy_(dense)
-    B.bq_butterfly_fwd(xs, ys, plan, B.make_rows(xs, n, 1, out=ys))
-    y = torch.empty_like(dense)
-    B.bq_butterfly_fwd(dense, y, plan, B.make_rows(dense, n, 1))
-    assert torch.equal(ys, y) and int((out != 0).sum()) == int((y != 0).sum())
-    codes, scales = B.alloc_quant_outputs(rows, n, 1, 4, 8, "f32", "cuda")
-    codes2, scales2 = torch.empty_like(codes), torch.empty_like(scales)
-    q = B.make_quant(4, 8, "f32")
-    B.bq_butterfly_fwd_quant(xs, plan, codes, scales, q, B.make_rows(xs, n, 1))
-    B.bq_butterfly_fwd_quant(dense, plan, codes2, scales2, q, B.make_rows(dense, n, 1))
+
+    def far(fill):
+        buf = torch.empty((rows - 1) * ld + n, dtype=torch.float16, device="cuda")
+        for w in wrapped:
+            buf[w:w + n] = 7.0
+        view = buf.as_strided((rows, n), (ld, 1))
+        view.copy_(fill)
+        return buf, view
+
+    if op in ("fwd", "inv"):
+        f = B.bq_butterfly_fwd if op == "fwd" else B.bq_butterfly_inv
+        call = lambda a, b: f(a, b, plan, B.make_rows(a, n, 1, out=b))  # noqa: E731
+    elif op == "fake":
+        q = B.make_quant(4, 32, "f16")
+        call = lambda a, b: B.bq_butterfly_fwd_fakequant(a, plan, b, None, q, B.make_rows(a, n, 1, out=b))  # noqa: E731
+    if op != "quant":
+        want = torch.empty_like(dense)
+        call(dense, want)
+        xs, got = far(dense)[1], torch.empty_like(dense)
+        call(xs, got)  # loads far apart
+        assert torch.equal(got, want)
+        del xs
+        buf, ys = far(torch.zeros_like(dense))
+        call(dense, ys)  # stores far apart
+        assert torch.equal(ys, want) and all(bool((buf[w:w + n] == 7.0).all()) for w in wrapped)
+        return
+    codes, scales = B.alloc_quant_outputs(rows, n, 1, 4, 32, "f32", "cuda")
+    codes2, scales2 = torch.zeros_like(codes), torch.zeros_like(scales)
+    q = B.make_quant(4, 32, "f32")
+    B.bq_butterfly_fwd_quant(dense, plan, codes, scales, q, B.make_rows(dense, n, 1))
+    xs = far(dense)[1]
+    B.bq_butterfly_fwd_quant(xs, plan, codes2, scales2, q, B.make_rows(xs, n, 1))
     assert torch.equal(codes, codes2) and torch.equal(scales, scales2)
 
 

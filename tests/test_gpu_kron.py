@@ -149,8 +149,12 @@ def test_kron_5120_with_device_built_cayley_roundtrip():
     _check(synth.torch_to_storage(y[:64], dtype), ref, dtype, "5120 forward", True, (d1, d2))
 
 
-@pytest.mark.parametrize("d1,d2,dtype", [(40, 128, "f16"), (6, 64, "f32")])
-def test_kron_with_a_plan_flagged_singular(d1, d2, dtype):
+# rows: with 256 workgroups (512 for d1 <= 8) several per workgroup, prefetch slots refilled and tiles reused, the last turn ragged
+@pytest.mark.parametrize("d1,d2,rows,dtype", [(40, 128, 13, "f16"), (6, 64, 13, "f32"), (40, 128, 5 * 256 + 3, "f16"),
+                                              (40, 128, 2 * 256 + 1, "bf16"), (37, 128, 4 * 256 + 7, "f32"), (7, 128, 5 * 512 + 1, "f32"),
+                                              (8, 128, 3 * 512 - 1, "bf16"), (12, 128, 6 * 256 + 5, "f16"), (20, 128, 5 * 256 + 130, "bf16"),
+                                              (32, 128, 3 * 256 + 2, "f32"), (20, 128, 4 * 256, "f16")])
+def test_kron_with_a_plan_flagged_singular(d1, d2, rows, dtype):
     # cos(theta) = 0 somewhere: the scale-deferred tables are unusable, the kernels fall back to plain rotations
     rng = np.random.default_rng(11)
     k = int(math.log2(d2))
@@ -158,8 +162,8 @@ def test_kron_with_a_plan_flagged_singular(d1, d2, dtype):
     theta[0, 1, :] = np.float32(math.pi / 2)
     theta[0, k - 1, ::3] = np.float32(-math.pi / 2)
     q1 = kron.cayley((0.4 * rng.standard_normal(d1 * (d1 - 1) // 2)).astype(np.float32), d1).astype(np.float32)
-    x, _, _ = synth.small_case(d2, 13 * d1, dtype, seed=5)
-    x = x.reshape(13, d1 * d2)
+    x, _, _ = synth.small_case(d2, rows * d1, dtype, seed=5)
+    x = x.reshape(rows, d1 * d2)
     x64 = synth.to_f64(x, dtype)
     _check(_run(x, q1, theta, d1, d2, dtype), kron.kron_forward(x64, q1.astype(np.float64), theta, d2), dtype, "flagged fwd", True, (d1, d2))
     _check(_run(x, q1, theta, d1, d2, dtype, inverse=True), kron.kron_inverse(x64, q1.astype(np.float64), theta, d2), dtype,
