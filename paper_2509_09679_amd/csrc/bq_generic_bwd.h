@@ -1,5 +1,5 @@
 // The backward pass for any n in plain (cos, sin) rotations, as device code: the kernel for any n (bq_generic.hip) and, on plans
-// that flag their scale-deferred tables, the specialised kernels of bq_bwd.hip run it.
+// that flag their scale-deferred tables, the specialised kernels of bq_bwd.hip and bq_bwd_small.hip run it.
 #pragma once
 
 #include "bq_device.h"

@@ -120,13 +120,6 @@ __device__ __forceinline__ bool plan_matches(const PlanRef &p)
     return p.hdr->magic == kPlanMagic && p.hdr->n == p.n && p.hdr->heads == p.heads;
 }
 
-// the plan is of this shape and both of its scale-deferred table sets (forward, transposed) are usable
-__device__ __forceinline__ bool plan_fast_both(const PlanRef &p)
-{
-    const PlanHead h = plan_head(p);
-    return h.matches && (h.bad_fwd | h.bad_inv) == 0;
-}
-
 struct PlanView {  // device pointers into a plan
     const PlanHeader *hdr;
     PlanRef ref;
