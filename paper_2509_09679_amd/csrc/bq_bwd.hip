@@ -7,7 +7,7 @@
 // start it with scale 1, so they share the scale-deferred coefficients c_i and, before layer i, the scales
 // E_i[e] (plan table fw_inv).  Sums are accumulated in deferred units,
 //   acc += v_g[b] v_x[a] - v_g[a] v_x[b],   dtheta = E_i[a] E_i[b] acc,
-// the factor being applied once per workgroup at the end.  For a layer that pairs lanes each lane keeps
+// the factor being applied once, to the sum over the workgroups.  For a layer that pairs lanes each lane keeps
 // the partial sum of its own element (one v_fmac_f32 with a DPP operand per element); the two lanes'
 // sums are combined at the end.
 //
@@ -933,7 +933,7 @@ __global__ void bwd_fold_kernel(const double *__restrict__ sums, float *__restri
 // ---- host side -----------------------------------------------------------------------------------
 // Slices = row slots of the kernel, which runs at most one workgroup per compute unit (n = 8192: two per slot).
 static int bwd_fast_slices(int k) { return k == 13 ? 128 : 256; }
-// The slots a batch of so many kernel rows fills evenly: every slot writes its 98 KB of sums (n = 8192: 213 KB) and the last kernel
+// The slots a batch of so many kernel rows fills evenly: every slot writes its 98 KB of sums (n = 8192: 229 KB) and the last kernel
 // reads them, rows or not.  One row of 4096 took 23.0 us with
 // 256 of them, 13.3 with one; 64 rows 23.9 and 16.4; 300 rows 23.5 with 150.
 static int bwd_fast_slots(int k, int64_t kernel_rows)

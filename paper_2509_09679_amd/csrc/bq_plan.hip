@@ -32,8 +32,8 @@ __global__ void plan_header_kernel(PlanHeader *hdr, int n, int heads, int k)
 // A high group's elements are 2^kl apart, so neighbouring groups share the cache lines they read and write: workgroups
 // (dealt to the eight dies in turn) are numbered so that neighbouring groups are on the same die, whose L2 then puts the lines
 // together.  In launch order many heads were slower than the kernel this replaces: 512 heads of 4096 396 us before, 606
-// in launch order, 319 this way; 512 heads of 8192 897, 1209, 669.  One head, both launches, back to back: n = 4096
-// 80 -> 7.1 us, n = 8192 163 -> 8.9, n = 16384 342 -> 10.9.
+// in launch order, 321 this way; 512 heads of 8192 897, 1209, 672.  One head, both launches, back to back: n = 4096
+// 80 -> 7.2 us, n = 8192 163 -> 8.1, n = 16384 342 -> 9.4.
 constexpr int kPlanThreads = 256, kPlanMaxThreads = 1024;  // of a workgroup (launch_plan_build)
 constexpr int kPlanMaxGroup = 128;  // elements of a group: k <= 7 has one group per head, k <= 14 groups of <= 2^7
 
@@ -157,8 +157,8 @@ hipError_t launch_plan_build(const float *theta, int n, int heads, int k, void *
     F.bad[0] = &hdr->fast_bad_fwd;
     F.bad[1] = &hdr->fast_bad_inv;
     // A plan that leaves compute units free: as many threads as evaluations, up to the workgroup's limit, because the rounds are one
-    // behind the other (one head of 4096, both launches, 7.14 -> 6.82 us, 16384 10.5 -> 9.7).  Many heads: 256, so that the units
-    // are not held by waves that wait (512 heads of 4096 325 us, with 576 threads 522).
+    // behind the other (one head, both launches, 256 threads, sine and cosine apart / as it is: 4096 7.45 / 7.2 us, 8192 8.6 / 8.1, 16384 10.2 / 9.4).  Many
+    // heads: 256, so that the units are not held by waves that wait (512 heads of 4096 321 us, with 576 threads 522).
     const int64_t workgroups = (int64_t)heads * (F.low_groups + F.high_groups);
     int threads = kPlanThreads;
     if (workgroups <= 256) {
